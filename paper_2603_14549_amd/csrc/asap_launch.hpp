@@ -24,7 +24,8 @@ struct ScoreWorkspace {
   size_t off_qbar;   // double [B,Hkv,d]         summed visual queries per kv head
   size_t off_qsplit; // bf16   [B,Hkv,4,d]       the same, split into four bf16 pieces per component
   size_t off_s64;    // double [B,V]             raw attention mass before rounding
-  size_t off_mm;     // uint64 [B,2]             order-preserving keys of min, max of s per image
+  int mm_n;          // (min, max) pairs of s per image: one per key tile, or one (head_splits > 1)
+  size_t off_mm;     // double [B,mm_n,2]        those pairs
   size_t off_pstat;  // float  [B,H,splits,2,NR] per-split (max, sum) of every text row, NR = 64 row_pairs
   size_t off_upart;  // float  [B,H,row_pairs,V] column sums of normalised weights per head and row pair
   size_t off_spart;  // double [head_splits,B,V] partial masses (head_splits > 1)

@@ -6,8 +6,8 @@
 //                 eight at a time in fp32, the eights in fp64
 //   k_qsplit      fixed-order sum of those partials per kv head (fp64), also split into four bf16
 //                 pieces per component (32 significant bits) for the matrix cores
-//   k_mass_mfma   s_j = sum_g qbar_g . k_{g,j} / (H sqrt d)  (Eq. 2 by linearity) and the per-image
-//                 min / max of s through order-preserving integer atomics.  The four pieces of
+//   k_mass_mfma   s_j = sum_g qbar_g . k_{g,j} / (H sqrt d)  (Eq. 2 by linearity) and the min / max of
+//                 s per key tile.  The four pieces of
 //                 qbar are four query rows of an MFMA tile; bf16 keys enter as they are, f32 keys
 //                 as three bf16 pieces each (hi + mid + lo = the key to 2^-27), so every product is
 //                 exact; one head's 128 products per piece pair are added in fp32 by the matrix
@@ -40,15 +40,36 @@
 
 namespace asap {
 
-// order-preserving map double <-> uint64 (for atomic min / max)
-__device__ __forceinline__ unsigned long long f64_key(double x) {
-  unsigned long long u = (unsigned long long)__double_as_longlong(x);
-  return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
-}
-__device__ __forceinline__ double f64_unkey(unsigned long long k) {
-  unsigned long long u = (k >> 63) ? (k & 0x7fffffffffffffffull) : ~k;
-  return __longlong_as_double((long long)u);
-}
+// Smallest and largest raw mass of image b (Eq. 3).  The mass kernel leaves one (min, max) pair per key
+// tile, n of them in mm [B, n, 2]; every wave that needs the range takes it over those (at most 512) pairs
+// itself.  Device-wide atomics on one pair per image were measured at about 13 us for 512 workgroups: they
+// queue up at the memory side, one after the other.
+// Asked for in two halves, so that the loads can be issued ahead of whatever else the caller waits for.
+struct MassRange {
+  const double2* p;
+  int n;
+  double2 first;
+  __device__ __forceinline__ void load(const double* __restrict__ mm, int n_, int b) {
+    n = n_;
+    p = reinterpret_cast<const double2*>(mm) + (int64_t)b * n;
+    first = p[min((int)(threadIdx.x & 63), n - 1)];
+  }
+  __device__ __forceinline__ void reduce(double& lo, double& hi) const {
+    lo = first.x;
+    hi = first.y;
+    if (n == 1) return;
+    for (int i = (threadIdx.x & 63) + 64; i < n; i += 64) {
+      const double2 x = p[i];
+      lo = fmin(lo, x.x);
+      hi = fmax(hi, x.y);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      lo = fmin(lo, shfl_xor_f64(lo, off));
+      hi = fmax(hi, shfl_xor_f64(hi, off));
+    }
+  }
+};
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -65,19 +86,18 @@ __device__ __forceinline__ void split_bf16x4(double x, uint16_t* out, int stride
 
 // ------------------------------------------------------------------------------------------
 // k_qsum: grid (chunks, H, B), 1024 threads.  A row is d elements = LPR 16-byte pieces; thread t
-// keeps piece t % LPR of rows t / LPR + RPI * i.  Block (0, 0, b) also resets the min / max keys.
+// keeps piece t % LPR of rows t / LPR + RPI * i. 
 // With one chunk and one query head per kv head the block's sums are final (`direct`): it writes
 // qbar and its bf16 split itself and k_qsplit is not needed.
 // ------------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(1024) void k_qsum(const T* __restrict__ q, Strides3 sq, int V, int d, int R,
-                                                double* __restrict__ qpart, unsigned long long* __restrict__ mmkey,
-                                                double* __restrict__ qbar, uint16_t* __restrict__ qsplit, int direct) {
+                                                double* __restrict__ qpart, double* __restrict__ qbar,
+                                                uint16_t* __restrict__ qsplit, int direct) {
   constexpr int E = elem<T>::per16;
   const int LPR = d / E, RPI = 1024 / LPR;
   const int tid = threadIdx.x, piece = tid % LPR, r0 = tid / LPR;
   const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (c == 0 && h == 0 && tid == 0) { mmkey[2 * b] = ~0ull; mmkey[2 * b + 1] = 0ull; }
   const int lo = c * R, hi = min(V, lo + R);
   const char* base = reinterpret_cast<const char*>(q + b * sq.b + h * sq.h + piece * E);
   const int64_t rowb = sq.r * (int64_t)sizeof(T);
@@ -130,10 +150,9 @@ __global__ __launch_bounds__(1024) void k_qsum(const T* __restrict__ q, Strides3
 // k_qsplit: grid (Hkv, B), d threads.  qbar[b,g,:] = sum over the heads of group g and the chunks;
 // qsplit[b,g,p,:] (p = 0..3) = successive bf16 roundings of what is left of qbar.
 __global__ void k_qsplit(const double* __restrict__ qpart, double* __restrict__ qbar, uint16_t* __restrict__ qsplit,
-                         int H, int Hkv, int nchunk, int d, unsigned long long* __restrict__ mmkey) {
+                         int H, int Hkv, int nchunk, int d) {
   const int g = blockIdx.x, b = blockIdx.y, c = threadIdx.x;
   const int G = H / Hkv;
-  if (g == 0 && c == 0) { mmkey[2 * b] = ~0ull; mmkey[2 * b + 1] = 0ull; }   // also where k_qsum did not run
   // the partials of the group's heads and chunks lie one after the other (head-major): added in that
   // order, eight loads in flight
   const double* src = qpart + ((int64_t)b * H + g * G) * nchunk * d + c;
@@ -148,19 +167,6 @@ __global__ void k_qsplit(const double* __restrict__ qpart, double* __restrict__ 
   }
   qbar[((int64_t)b * Hkv + g) * d + c] = s;
   split_bf16x4(s, qsplit + ((int64_t)b * Hkv + g) * 4 * d + c, d);
-}
-
-__device__ __forceinline__ void publish_minmax(unsigned long long kmin, unsigned long long kmax, bool active,
-                                               unsigned long long* blk_mm, unsigned long long* mmkey, int b) {
-  if (active) {
-    atomicMin(&blk_mm[0], kmin);
-    atomicMax(&blk_mm[1], kmax);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    atomicMin(&mmkey[2 * b], blk_mm[0]);
-    atomicMax(&mmkey[2 * b + 1], blk_mm[1]);
-  }
 }
 
 // A lane's share of one contraction group (8 elements): one 16-byte chunk of bf16, two of f32.
@@ -189,15 +195,14 @@ struct RideArgs {
 // 6.0 TB/s for whole rows.  So a wave reads whole rows (LPR consecutive lanes per row) and turns the
 // tile into the operand layout through an LDS buffer of its own -- written and read by the same
 // wave, in order, so no barrier is involved.  NG = contraction groups of 8 elements (d = 16 NG).
-// HS == 1: writes s64, s_raw and publishes min / max; HS > 1: writes the group's partial mass to
+// HS == 1: writes s64, s_raw and the (min, max) of its keys to mm [B, ktiles, 2]; HS > 1: writes the group's partial mass to
 // spart [HS, B, V] for k_mass_finish.
 // ------------------------------------------------------------------------------------------
 template <typename T, int NG, bool RIDE>
 __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_mass_mfma(const T* __restrict__ kv, Strides3 sk,
                                                     const uint16_t* __restrict__ qsplit, int Hkv, int V, int HS,
                                                     double scale, double* __restrict__ s64, float* __restrict__ s_raw,
-                                                    unsigned long long* __restrict__ mmkey,
-                                                    double* __restrict__ spart, RideArgs ra) {
+                                                    double* __restrict__ mm, double* __restrict__ spart, RideArgs ra) {
   constexpr int GB = group_bytes<T>::value;
   constexpr int RBY = NG * 2 * GB;                    // row bytes
   constexpr int LPR = RBY / 16, RPI = 64 / LPR;       // lanes per row, rows per load instruction
@@ -210,13 +215,11 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_ma
   constexpr bool REUSE = F32 || RIDE;
   __shared__ __align__(16) char stage[4][32 * RBY];
   __shared__ double part[4][32];
-  __shared__ unsigned long long blk_mm[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = lane & 31, hf = lane >> 5;
   const int piece = lane % LPR, r0 = lane / LPR;
   const int b = blockIdx.y / HS, hs = blockIdx.y % HS, j0 = blockIdx.x * 32;
   const int g_lo = hs * (Hkv / HS), g_hi = g_lo + Hkv / HS;
-  if (tid == 0) { blk_mm[0] = ~0ull; blk_mm[1] = 0ull; }
   const int64_t headb = sk.h * (int64_t)sizeof(T);
   // LDS: the 16-byte piece p of row r sits in slot p ^ x(r): whole-row writes and operand reads of 16
   // consecutive rows both cover all banks
@@ -338,33 +341,39 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_ma
   }
   if (hf == 0) part[wave][n] = sum;
   __syncthreads();
-  unsigned long long kmin = ~0ull, kmax = 0ull;
+  if (tid >= 32) return;
+  double smin = INFINITY, smax = -INFINITY;
   const int j = j0 + n;
-  if (tid < 32 && j < V) {
+  if (j < V) {
     const double tot = ((part[0][n] + part[1][n]) + part[2][n]) + part[3][n];
     if (HS == 1) {
       const double s = tot * scale;
       s64[(int64_t)b * V + j] = s;
       s_raw[(int64_t)b * V + j] = (float)s;
-      kmin = kmax = f64_key(s);
+      smin = smax = s;
     } else {
       spart[((int64_t)hs * gridDim.y / HS + b) * V + j] = tot;
     }
   }
-  if (HS == 1) publish_minmax(kmin, kmax, tid < 32, blk_mm, mmkey, b);
+  if (HS == 1) {
+#pragma unroll
+    for (int off = 16; off >= 1; off >>= 1) {
+      smin = fmin(smin, shfl_xor_f64(smin, off));
+      smax = fmax(smax, shfl_xor_f64(smax, off));
+    }
+    if (tid == 0) reinterpret_cast<double2*>(mm)[(int64_t)b * gridDim.x + blockIdx.x] = make_double2(smin, smax);
+  }
 }
 
 // k_mass_finish: grid (B), 1024 threads: adds the HS partial masses of every key in group order,
-// scales, writes s64 / s_raw and the image's min / max keys.
+// scales, writes s64 / s_raw and the image's (min, max) to mm [B, 1, 2].
 __global__ __launch_bounds__(1024) void k_mass_finish(const double* __restrict__ spart, int HS, int B, int V,
                                                        double scale, double* __restrict__ s64,
                                                        float* __restrict__ s_raw,
-                                                       unsigned long long* __restrict__ mmkey) {
-  __shared__ unsigned long long blk_mm[2];
+                                                       double* __restrict__ mm) {
+  __shared__ double wave_mm[16][2];
   const int b = blockIdx.x, tid = threadIdx.x;
-  if (tid == 0) { blk_mm[0] = ~0ull; blk_mm[1] = 0ull; }
-  __syncthreads();
-  unsigned long long kmin = ~0ull, kmax = 0ull;
+  double smin = INFINITY, smax = -INFINITY;
   for (int j = tid; j < V; j += 1024) {
     double t = 0.0;
     for (int q0 = 0; q0 < HS; q0 += 8) {       // eight loads in flight, added in group order
@@ -377,23 +386,20 @@ __global__ __launch_bounds__(1024) void k_mass_finish(const double* __restrict__
     const double s = t * scale;
     s64[(int64_t)b * V + j] = s;
     s_raw[(int64_t)b * V + j] = (float)s;
-    const unsigned long long key = f64_key(s);
-    kmin = key < kmin ? key : kmin;
-    kmax = key > kmax ? key : kmax;
+    smin = fmin(smin, s);
+    smax = fmax(smax, s);
   }
-  // wave first (1024 same-address LDS atomics would take longer than everything else here)
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
-    const unsigned long long omin = __shfl_xor(kmin, off), omax = __shfl_xor(kmax, off);
-    kmin = omin < kmin ? omin : kmin;
-    kmax = omax > kmax ? omax : kmax;
+    smin = fmin(smin, shfl_xor_f64(smin, off));
+    smax = fmax(smax, shfl_xor_f64(smax, off));
   }
-  if ((tid & 63) == 0) {
-    atomicMin(&blk_mm[0], kmin);
-    atomicMax(&blk_mm[1], kmax);
-  }
+  if ((tid & 63) == 0) { wave_mm[tid >> 6][0] = smin; wave_mm[tid >> 6][1] = smax; }
   __syncthreads();
-  if (tid == 0) { mmkey[2 * b] = blk_mm[0]; mmkey[2 * b + 1] = blk_mm[1]; }
+  if (tid == 0) {
+    for (int w = 1; w < 16; ++w) { smin = fmin(smin, wave_mm[w][0]); smax = fmax(smax, wave_mm[w][1]); }
+    reinterpret_cast<double2*>(mm)[b] = make_double2(smin, smax);
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -418,7 +424,7 @@ struct AttnArgs {
   const void* qt; Strides3 sq;          // [B,H,Tmax,d]
   const void* kv; Strides3 sk;          // [B,Hkv,V,d]
   const double* s64;                    // [B,V]
-  const unsigned long long* mmkey;      // [B,2]
+  const double* mm; int mm_n;           // [B,mm_n,2] (min, max) pairs of s (MassRange)
   const int32_t* text_len;              // [B]
   const float* lse_extra;               // [B,H,Tmax] or null
   float* pstat;                         // [B,H,S,2,NR]   partial (max, sum) per text row, NR = 64 RP
@@ -597,6 +603,8 @@ __device__ __forceinline__ void attn_stats_body(const AttnArgs& a, char* lds, co
   const int t_end = min(ntiles, (sp + 1) * a.tiles_per_split);
   const float c2 = a.c2;
   // the first key tile and its masses are asked for before the queries, so that the waits overlap
+  MassRange range;
+  range.load(a.mm, a.mm_n, b);
   KeyTile<T, NG> kb;
   int tile = sp * a.tiles_per_split + wave;
   if (tile < t_end) kb.load(kbase + (int64_t)min(tile * 32 + n, a.V - 1) * krow_bytes);
@@ -604,7 +612,8 @@ __device__ __forceinline__ void attn_stats_body(const AttnArgs& a, char* lds, co
   double sj = (a.mask_on && tile < t_end) ? s64[min(tile * 32 + n, a.V - 1)] : 0.0;
   Q q;
   q.init(a, b, h, lane, lds, row0, nrows);
-  const double mlo = f64_unkey(a.mmkey[2 * b]), mhi = f64_unkey(a.mmkey[2 * b + 1]);
+  double mlo, mhi;
+  range.reduce(mlo, mhi);
   const double minv = 1.0 / (mhi - mlo + a.eps);
 
   float m_run[NRB], s_run[NRB];
@@ -879,7 +888,10 @@ __global__ __launch_bounds__(256) void k_rowstats_logits(AttnArgs a) {
   int row0, nrows;
   ranking_rows(a, b, row0, nrows);
   if (t >= nrows) return;                                   // uniform for the workgroup
-  const double mlo = f64_unkey(a.mmkey[2 * b]), mhi = f64_unkey(a.mmkey[2 * b + 1]);
+  MassRange range;
+  range.load(a.mm, a.mm_n, b);
+  double mlo, mhi;
+  range.reduce(mlo, mhi);
   const double minv = 1.0 / (mhi - mlo + a.eps);
   const float* z = a.zlog + (((int64_t)b * a.H + h) * a.T_eff + t) * a.V;
   float m = ATT_NEG;
@@ -993,7 +1005,7 @@ __device__ __forceinline__ double rank_count(const int32_t* text_len, int b, int
 }
 
 __global__ __launch_bounds__(256) void k_score(const float* __restrict__ upart, const double* __restrict__ s64,
-                                                const unsigned long long* __restrict__ mmkey,
+                                                const double* __restrict__ mm, int mm_n,
                                                 const int32_t* __restrict__ text_len, int H, int HV, int V, int Tmax,
                                                 int last_only, double lambda_max, double eps, int mask_on,
                                                 float* __restrict__ s_hat, float* __restrict__ score) {
@@ -1001,6 +1013,8 @@ __global__ __launch_bounds__(256) void k_score(const float* __restrict__ upart, 
   __shared__ double part[4][64];
   const int b = blockIdx.y, jl = threadIdx.x & 63, hq = threadIdx.x >> 6;
   const int j = blockIdx.x * 64 + jl;
+  MassRange range;
+  if (hq == 0) range.load(mm, mm_n, b);       // the wave that finishes
   double u = 0.0;
   if (j < V) {
     const float* up = upart + (int64_t)b * HV * V + j;
@@ -1017,9 +1031,11 @@ __global__ __launch_bounds__(256) void k_score(const float* __restrict__ upart, 
   }
   part[hq][jl] = u;
   __syncthreads();
-  if (hq == 0 && j < V) {
+  if (hq != 0) return;
+  double lo, hi;
+  range.reduce(lo, hi);
+  if (j < V) {
     u = ((part[0][jl] + part[1][jl]) + part[2][jl]) + part[3][jl];
-    const double lo = f64_unkey(mmkey[2 * b]), hi = f64_unkey(mmkey[2 * b + 1]);
     const double sh = (s64[(int64_t)b * V + j] - lo) * (1.0 / (hi - lo + eps));
     const double lam = mask_on ? fmax(lambda_max * sh, eps) : 1.0;
     s_hat[(int64_t)b * V + j] = (float)sh;
@@ -1036,7 +1052,7 @@ __global__ __launch_bounds__(256) void k_score(const float* __restrict__ upart, 
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ void score_select_image(const int b, const float* __restrict__ upart,
                                                    const double* __restrict__ s64,
-                                                   const unsigned long long* __restrict__ mmkey,
+                                                   const double* __restrict__ mm, int mm_n,
                                                    const int32_t* __restrict__ text_len, int H, int HV, int V, int k,
                                                    int Tmax, int last_only, double lambda_max, double eps, int mask_on,
                                                    float* __restrict__ s_hat, float* __restrict__ score,
@@ -1046,7 +1062,10 @@ __device__ __forceinline__ void score_select_image(const int b, const float* __r
   const int tid = threadIdx.x;
   const int ipt = (V + SEL_THREADS - 1) / SEL_THREADS;
   const int i0 = tid * ipt;
-  const double lo = f64_unkey(mmkey[2 * b]), hi = f64_unkey(mmkey[2 * b + 1]);
+  MassRange range;
+  range.load(mm, mm_n, b);
+  double lo, hi;
+  range.reduce(lo, hi);
   const double inv = 1.0 / (hi - lo + eps);
   const double norm = (double)H * rank_count(text_len, b, Tmax, last_only);
   const float* up = upart + (int64_t)b * HV * V;
@@ -1096,13 +1115,13 @@ __device__ __forceinline__ void score_select_image(const int b, const float* __r
 
 __global__ __launch_bounds__(SEL_THREADS) void k_score_select(const float* __restrict__ upart,
                                                                const double* __restrict__ s64,
-                                                               const unsigned long long* __restrict__ mmkey,
+                                                               const double* __restrict__ mm, int mm_n,
                                                                const int32_t* __restrict__ text_len, int H, int HV,
                                                                int V, int k, int Tmax, int last_only, double lambda_max,
                                                                double eps, int mask_on, float* __restrict__ s_hat,
                                                                float* __restrict__ score, int32_t* __restrict__ kept,
                                                                int32_t* __restrict__ pruned) {
-  score_select_image(blockIdx.x, upart, s64, mmkey, text_len, H, HV, V, k, Tmax, last_only, lambda_max, eps, mask_on,
+  score_select_image(blockIdx.x, upart, s64, mm, mm_n, text_len, H, HV, V, k, Tmax, last_only, lambda_max, eps, mask_on,
                      s_hat, score, kept, pruned);
 }
 
@@ -1112,12 +1131,12 @@ __global__ __launch_bounds__(SEL_THREADS) void k_score_select(const float* __res
 // depend on no result of the stage, and the B selecting workgroups leave the memory system idle.
 // A row is row_bytes / 16 pieces of 16 bytes; two rows per thread are in flight.
 __global__ __launch_bounds__(SEL_THREADS) void k_score_select_kv(
-    const float* __restrict__ upart, const double* __restrict__ s64, const unsigned long long* __restrict__ mmkey,
+    const float* __restrict__ upart, const double* __restrict__ s64, const double* __restrict__ mm, int mm_n,
     const int32_t* __restrict__ text_len, int H, int HV, int V, int k, int Tmax, int last_only, double lambda_max,
     double eps, int mask_on, float* __restrict__ s_hat, float* __restrict__ score, int32_t* __restrict__ kept,
     int32_t* __restrict__ pruned, int B, KvFixedRows fx) {
   if ((int)blockIdx.x < B) {
-    score_select_image(blockIdx.x, upart, s64, mmkey, text_len, H, HV, V, k, Tmax, last_only, lambda_max, eps,
+    score_select_image(blockIdx.x, upart, s64, mm, mm_n, text_len, H, HV, V, k, Tmax, last_only, lambda_max, eps,
                        mask_on, s_hat, score, kept, pruned);
     return;
   }
@@ -1198,6 +1217,7 @@ ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
     for (int hs = p.Hkv; hs >= 1; --hs)
       if (p.Hkv % hs == 0 && hs <= want) { w.head_splits = hs; break; }
   }
+  w.mm_n = w.head_splits > 1 ? 1 : (p.V + 31) / 32;
   w.row_pairs = w.ride ? 1 : (w.t_eff + 63) / 64;
   // f32 keys: the first text-row sweep leaves its logits (4 bytes per ranking row and key, never more
   // than the key sweeps they replace at 512 bytes per key and 64 rows) and the column sums read them
@@ -1212,7 +1232,7 @@ ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
   w.off_qbar = off;   off = align256(off + sizeof(double) * p.B * p.Hkv * p.d);
   w.off_qsplit = off; off = align256(off + sizeof(uint16_t) * p.B * p.Hkv * 4 * p.d);
   w.off_s64 = off;    off = align256(off + sizeof(double) * p.B * p.V);
-  w.off_mm = off;     off = align256(off + sizeof(double) * p.B * 2);
+  w.off_mm = off;     off = align256(off + sizeof(double) * 2 * p.B * w.mm_n);
   w.off_pstat = off;  off = align256(off + sizeof(float) * (size_t)p.B * p.H * splits * 2 * NR);
   w.off_upart = off;  off = align256(off + sizeof(float) * (size_t)p.B * p.H * w.row_pairs * p.V);
   w.off_spart = off;
@@ -1260,7 +1280,7 @@ static hipError_t launch_attn(const asap_params& p, const AttnArgs& a, bool stor
 template <typename T, int NG>
 static hipError_t launch_mass(const asap_params& p, const ScoreWorkspace& w, const void* k_vis, Strides3 kv,
                               const uint16_t* qsplit, double scale, double* s64, float* s_raw,
-                              unsigned long long* mmkey, double* spart, const RideArgs& ra, hipStream_t st,
+                              double* mm, double* spart, const RideArgs& ra, hipStream_t st,
                               Timer* tm) {
   const int ktiles = (p.V + 31) / 32;
   const dim3 grid(ktiles, p.B * w.head_splits);
@@ -1268,12 +1288,12 @@ static hipError_t launch_mass(const asap_params& p, const ScoreWorkspace& w, con
   if constexpr (sizeof(T) == 2) {
     if (w.ride) {
       ASAP_LAUNCH(tm, "k_mass_mfma", (k_mass_mfma<T, NG, true>), grid, dim3(256), 0, st, kp, kv, qsplit, p.Hkv, p.V,
-                  w.head_splits, scale, s64, s_raw, mmkey, spart, ra);
+                  w.head_splits, scale, s64, s_raw, mm, spart, ra);
       return hipGetLastError();
     }
   }
   ASAP_LAUNCH(tm, "k_mass_mfma", (k_mass_mfma<T, NG, false>), grid, dim3(256), 0, st, kp, kv, qsplit, p.Hkv, p.V,
-              w.head_splits, scale, s64, s_raw, mmkey, spart, ra);
+              w.head_splits, scale, s64, s_raw, mm, spart, ra);
   return hipGetLastError();
 }
 
@@ -1288,7 +1308,7 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
   double* qbar = reinterpret_cast<double*>(ws + w.off_qbar);
   uint16_t* qsplit = reinterpret_cast<uint16_t*>(ws + w.off_qsplit);
   double* s64 = reinterpret_cast<double*>(ws + w.off_s64);
-  unsigned long long* mmkey = reinterpret_cast<unsigned long long*>(ws + w.off_mm);
+  double* mm = reinterpret_cast<double*>(ws + w.off_mm);
   float* pstat = reinterpret_cast<float*>(ws + w.off_pstat);
   float* upart = reinterpret_cast<float*>(ws + w.off_upart);
   double* spart = reinterpret_cast<double*>(ws + w.off_spart);
@@ -1303,29 +1323,28 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
     hipError_t e0 = launch_front_end(p, fe->hidden, fe->hsb, fe->hsr, fe->wq, fe->rope_theta, fe->vis_positions,
                                      qpart, fe->ws, st, tm);
     if (e0 != hipSuccess) return e0;
-    ASAP_LAUNCH(tm, "k_qsplit", k_qsplit, dim3(p.Hkv, p.B), dim3(p.d), 0, st, qpart, qbar, qsplit, p.H, p.Hkv, 1, p.d,
-                mmkey);
+    ASAP_LAUNCH(tm, "k_qsplit", k_qsplit, dim3(p.Hkv, p.B), dim3(p.d), 0, st, qpart, qbar, qsplit, p.H, p.Hkv, 1, p.d);
   } else {
     const int direct = (w.q_chunks == 1 && p.H == p.Hkv) ? 1 : 0;
     ASAP_LAUNCH(tm, "k_qsum", k_qsum<T>, dim3(w.q_chunks, p.H, p.B), dim3(1024), 0, st, static_cast<const T*>(q_vis),
-                qv, p.V, p.d, w.q_rows, qpart, mmkey, qbar, qsplit, direct);
+                qv, p.V, p.d, w.q_rows, qpart, qbar, qsplit, direct);
     if (!direct)
       ASAP_LAUNCH(tm, "k_qsplit", k_qsplit, dim3(p.Hkv, p.B), dim3(p.d), 0, st, qpart, qbar, qsplit, p.H, p.Hkv,
-                  w.q_chunks, p.d, mmkey);
+                  w.q_chunks, p.d);
   }
   const double scale = 1.0 / ((double)p.H * sqrt((double)p.d));
   RideArgs ra;
   ra.qt = q_txt; ra.sq = qt; ra.text_len = text_len; ra.zlog = zlog;
   ra.H = p.H; ra.G = p.H / p.Hkv; ra.T_eff = w.t_eff; ra.Tmax = p.Tmax; ra.last_only = last_only;
-  hipError_t e = ng == 8 ? launch_mass<T, 8>(p, w, k_vis, kv, qsplit, scale, s64, s_raw, mmkey, spart, ra, st, tm)
-                         : launch_mass<T, 4>(p, w, k_vis, kv, qsplit, scale, s64, s_raw, mmkey, spart, ra, st, tm);
+  hipError_t e = ng == 8 ? launch_mass<T, 8>(p, w, k_vis, kv, qsplit, scale, s64, s_raw, mm, spart, ra, st, tm)
+                         : launch_mass<T, 4>(p, w, k_vis, kv, qsplit, scale, s64, s_raw, mm, spart, ra, st, tm);
   if (e != hipSuccess) return e;
   if (w.head_splits > 1)
     ASAP_LAUNCH(tm, "k_mass_finish", k_mass_finish, dim3(p.B), dim3(1024), 0, st, spart, w.head_splits, p.B, p.V,
-                scale, s64, s_raw, mmkey);
+                scale, s64, s_raw, mm);
 
   AttnArgs a;
-  a.qt = q_txt; a.sq = qt; a.kv = k_vis; a.sk = kv; a.s64 = s64; a.mmkey = mmkey; a.text_len = text_len;
+  a.qt = q_txt; a.sq = qt; a.kv = k_vis; a.sk = kv; a.s64 = s64; a.mm = mm; a.mm_n = w.mm_n; a.text_len = text_len;
   a.lse_extra = lse_extra; a.pstat = pstat; a.upart = upart; a.zlog = zlog;
   a.H = p.H; a.Hkv = p.Hkv; a.V = p.V; a.Tmax = p.Tmax; a.S = w.ride ? 1 : w.attn_splits; a.RP = w.row_pairs;
   a.tiles_per_split = (ktiles + a.S - 1) / a.S;
@@ -1344,7 +1363,7 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
   if (e != hipSuccess) return e;
   const int u_rows = p.H * (w.store_logits ? 1 : w.row_pairs);     // rows of upart per image
   if (kept != nullptr && !score_fuses_selection(p)) {
-    ASAP_LAUNCH(tm, "k_score", k_score, dim3((p.V + 63) / 64, p.B), dim3(256), 0, st, upart, s64, mmkey, text_len,
+    ASAP_LAUNCH(tm, "k_score", k_score, dim3((p.V + 63) / 64, p.B), dim3(256), 0, st, upart, s64, mm, w.mm_n, text_len,
                 p.H, u_rows, p.V, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps, mask_on, s_hat, score);
     hipError_t e2 = hipGetLastError();
     return e2 != hipSuccess ? e2 : launch_select(p, score, kept, pruned, st, tm);
@@ -1359,14 +1378,14 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
     }
     if (fixed)
       ASAP_LAUNCH(tm, "k_score_select_kv", k_score_select_kv, dim3(p.B + fixed->n_bufs * p.B * p.Hkv),
-                  dim3(SEL_THREADS), lds, st, upart, s64, mmkey, text_len, p.H, u_rows, p.V, p.k, p.Tmax,
+                  dim3(SEL_THREADS), lds, st, upart, s64, mm, w.mm_n, text_len, p.H, u_rows, p.V, p.k, p.Tmax,
                   last_only, (double)p.lambda_max, (double)p.eps, mask_on, s_hat, score, kept, pruned, p.B, *fixed);
     else
-      ASAP_LAUNCH(tm, "k_score_select", k_score_select, dim3(p.B), dim3(SEL_THREADS), lds, st, upart, s64, mmkey,
+      ASAP_LAUNCH(tm, "k_score_select", k_score_select, dim3(p.B), dim3(SEL_THREADS), lds, st, upart, s64, mm, w.mm_n,
                   text_len, p.H, u_rows, p.V, p.k, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps,
                   mask_on, s_hat, score, kept, pruned);
   } else {
-    ASAP_LAUNCH(tm, "k_score", k_score, dim3((p.V + 63) / 64, p.B), dim3(256), 0, st, upart, s64, mmkey, text_len,
+    ASAP_LAUNCH(tm, "k_score", k_score, dim3((p.V + 63) / 64, p.B), dim3(256), 0, st, upart, s64, mm, w.mm_n, text_len,
                 p.H, u_rows, p.V, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps, mask_on, s_hat, score);
   }
   return hipGetLastError();

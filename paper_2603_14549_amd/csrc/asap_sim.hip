@@ -20,9 +20,9 @@
 //                 p ^ ((r >> 1) & 7): any 16 consecutive rows then cover all 64 banks once, for the
 //                 1 KiB-contiguous loads as well as for the strided 16-byte operand reads.
 //                 The grid is one-dimensional and XCD-aware: consecutive workgroup ids go to the 8
-//                 XCDs round-robin, so id % 8 picks the XCD and all tiles of one image are given
-//                 ids with the same id % 8 -- they then share that XCD's L2 for the kept panel
-//                 (batches of fewer than 8 images spread an image over several XCDs instead).
+//                 XCDs round-robin, so id % 8 picks the XCD, and each XCD is given one contiguous
+//                 eighth of the tiles (image-major) -- the tiles of an image then share the L2 of one
+//                 XCD, or of the few that an image spans, for the kept panel (see sim_work).
 //                 A workgroup takes one destination tile.  When the destination rows need several
 //                 (k > 64*NT), the tiles of a source tile are workgroups of their own: each leaves
 //                 its row winner as a 64-bit key (order-preserving value bits, then the inverted
@@ -242,6 +242,26 @@ __device__ __forceinline__ void sim_tile_epilogue(f32x16_t (&acc)[2][NT], const 
   }
 }
 
+// The unit of work of a workgroup: destination tile `pass` of slice `ks` of source tile mt of image b.
+// The units are numbered image by image, source tile by source tile, the destination tiles of a slice
+// next to each other, and XCD x (= the workgroup ids with id % 8 == x) takes the x-th eighth of them:
+// every XCD has the same number to do whatever the batch (a whole image per XCD left three of the
+// eight idle at 5 images: the last-token stage of 5 x 2083 tokens took 158 us, now 125), and an image's kept panel is fetched by the one or
+// few XCDs that work on it.
+struct SimWork { int b, mt, pass, ks, turn; };
+__device__ __forceinline__ bool sim_work(int B, int mtiles, int ptiles, int ksplit, SimWork& w) {
+  const int units = B * mtiles * ptiles * ksplit, per_xcd = (units + NUM_XCD - 1) / NUM_XCD;
+  const int slot = blockIdx.x / NUM_XCD, u = (blockIdx.x % NUM_XCD) * per_xcd + slot;
+  if (u >= units) return false;                // slot < per_xcd by the size of the grid
+  w.pass = u % ptiles;
+  w.ks = (u / ptiles) % ksplit;
+  const int tile = u / (ptiles * ksplit);
+  w.b = tile / mtiles;
+  w.mt = tile % mtiles;
+  w.turn = slot / (ptiles * ksplit);           // the tile's position on its XCD
+  return true;
+}
+
 // ANCHORED (the routing inside the kept set, Sec. 4.2): the source rows are the kept tokens too
 // (pruned == kept, M == k), and a destination counts for a source only if it is the stronger of the
 // two: larger salience s_hat, ties to the smaller index -- which is the smaller slot, both lists
@@ -250,7 +270,7 @@ template <typename T, int NT, bool ANCHORED>
 __global__ __launch_bounds__(256) void k_sim(const T* __restrict__ xv, int64_t sb, int64_t sr, int D,
                                               const int32_t* __restrict__ pruned, const int32_t* __restrict__ kept,
                                               const float* __restrict__ s_hat, int V, int B, int M, int k,
-                                              int mtiles, int ptiles, int spread, int vmt, float threshold,
+                                              int mtiles, int ptiles, float threshold,
                                               int32_t* __restrict__ assign,
                                               float* __restrict__ best_sim, unsigned long long* __restrict__ best_key,
                                               float* __restrict__ src_norm2, int ksplit, float* __restrict__ dots,
@@ -270,21 +290,12 @@ __global__ __launch_bounds__(256) void k_sim(const T* __restrict__ xv, int64_t s
   uint2* part = reinterpret_cast<uint2*>(normk + BN);            // [2][BM] (value, column) per column half
   float* srow = reinterpret_cast<float*>(part + 2 * SIM_BM);     // [BM] salience of the source rows (ANCHORED)
 
-  // XCD-aware decode of the linear workgroup id
-  // (a workgroup = one source tile x one destination tile; the destination tiles of a source tile
-  // are neighbours in the id order)
-  // With fewer than 8 images one image per XCD would leave XCDs idle: an image's source tiles are then
-  // dealt to `spread` XCDs (tile mt to the XCD of "virtual image" b * spread + mt % spread), each of
-  // which keeps its own copy of the image's destination panel in L2.
   // With ksplit > 1 (launches that would leave most of the chip idle) the hidden dimension is cut into
   // ksplit slices, each with workgroups of its own, which leave raw partial products and partial
   // squared norms for k_sim_reduce instead of taking the arg-max themselves.
-  const int xcd = blockIdx.x % NUM_XCD, slot_p = blockIdx.x / NUM_XCD;
-  const int pass = slot_p % ptiles, ks = (slot_p / ptiles) % ksplit, slot = slot_p / (ptiles * ksplit);
-  const int vb = (slot / vmt) * NUM_XCD + xcd;
-  const int b = vb / spread;
-  const int mt = vb % spread + spread * (slot % vmt);
-  if (b >= B || mt >= mtiles) return;
+  SimWork w;
+  if (!sim_work(B, mtiles, ptiles, ksplit, w)) return;
+  const int b = w.b, mt = w.mt, pass = w.pass, ks = w.ks;
   const int m0 = mt * SIM_BM;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -297,7 +308,7 @@ __global__ __launch_bounds__(256) void k_sim(const T* __restrict__ xv, int64_t s
   const int step_lo = ks * steps;
   // Every workgroup walks its part of the hidden dimension from its own starting step: rows are a
   // power-of-two number of bytes apart, so workgroups in lockstep would all hit the same memory channel.
-  const int rot = (mt + 16 * (slot / vmt)) % steps;
+  const int rot = w.turn % steps;
   auto step_base = [&](int s) {
     int sr_ = s + rot;
     if (sr_ >= steps) sr_ -= steps;
@@ -484,8 +495,7 @@ template <int NT, bool ANCHORED>
 __global__ __launch_bounds__(256) void k_sim_f32(const float* __restrict__ xv, int64_t sb, int64_t sr, int D,
                                                   const int32_t* __restrict__ pruned,
                                                   const int32_t* __restrict__ kept, const float* __restrict__ s_hat,
-                                                  int V, int B, int M, int k, int mtiles, int ptiles, int spread,
-                                                  int vmt, float threshold, int32_t* __restrict__ assign,
+                                                  int V, int B, int M, int k, int mtiles, int ptiles, float threshold, int32_t* __restrict__ assign,
                                                   float* __restrict__ best_sim,
                                                   unsigned long long* __restrict__ best_key,
                                                   float* __restrict__ src_norm2, int ksplit,
@@ -501,12 +511,9 @@ __global__ __launch_bounds__(256) void k_sim_f32(const float* __restrict__ xv, i
   uint2* part = reinterpret_cast<uint2*>(normk + BN);            // [2][BM]
   float* srow = reinterpret_cast<float*>(part + 2 * SIM_BM);     // [BM]
 
-  const int xcd = blockIdx.x % NUM_XCD, slot_p = blockIdx.x / NUM_XCD;
-  const int pass = slot_p % ptiles, ks = (slot_p / ptiles) % ksplit, slot = slot_p / (ptiles * ksplit);
-  const int vb = (slot / vmt) * NUM_XCD + xcd;
-  const int b = vb / spread;
-  const int mt = vb % spread + spread * (slot % vmt);
-  if (b >= B || mt >= mtiles) return;
+  SimWork w;
+  if (!sim_work(B, mtiles, ptiles, ksplit, w)) return;
+  const int b = w.b, mt = w.mt, pass = w.pass, ks = w.ks;
   const int m0 = mt * SIM_BM, n0 = pass * BN;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -517,7 +524,7 @@ __global__ __launch_bounds__(256) void k_sim_f32(const float* __restrict__ xv, i
   const int64_t rowb = sr * (int64_t)sizeof(float);
   const int steps = (D * (int)sizeof(float)) / SIM_ROWB / ksplit;     // ksplit divides the step count
   const int step_lo = ks * steps;
-  const int rot = (mt + 16 * (slot / vmt)) % steps;                   // see k_sim
+  const int rot = w.turn % steps;                                     // see k_sim
   auto step_base = [&](int s) __attribute__((always_inline)) {
     int sr_ = s + rot;
     if (sr_ >= steps) sr_ -= steps;
@@ -822,6 +829,8 @@ size_t sim_workspace_bytes(const asap_params& p) {
   return a > b ? a : b;
 }
 
+static dim3 sim_grid(int units) { return dim3(NUM_XCD * ((units + NUM_XCD - 1) / NUM_XCD)); }
+
 template <typename T, int NT, bool ANCHORED>
 static hipError_t launch_sim_nt(const asap_params& p, const T* xv, int64_t sb, int64_t sr, const int32_t* srcs,
                                 int M, const int32_t* kept, const float* s_hat, int32_t* assign, float* best_sim,
@@ -842,9 +851,6 @@ static hipError_t launch_sim_nt(const asap_params& p, const T* xv, int64_t sb, i
   }
   const int mtiles = (M + SIM_BM - 1) / SIM_BM;
   const int ptiles = (p.k + BN - 1) / BN;
-  const int spread = p.B >= NUM_XCD ? 1 : NUM_XCD / p.B;      // XCDs that share one image's source tiles
-  const int vmt = (mtiles + spread - 1) / spread;
-  const int groups = (p.B * spread + NUM_XCD - 1) / NUM_XCD;
   const int n = p.B * M;
   const int ksplit = pick_ksplit(p, M, NT);
   const char* label = F32 ? "k_sim_f32" : "k_sim";
@@ -852,8 +858,8 @@ static hipError_t launch_sim_nt(const asap_params& p, const T* xv, int64_t sb, i
     float* dots = reinterpret_cast<float*>(ws);                                       // [ksplit][B][M][k]
     float* nsrc = reinterpret_cast<float*>(ws + align256(sizeof(float) * ksplit * (size_t)n * p.k));
     float* nkept = reinterpret_cast<float*>(reinterpret_cast<char*>(nsrc) + align256(sizeof(float) * ksplit * (size_t)n));
-    ASAP_LAUNCH(tm, label, kern, dim3(NUM_XCD * groups * vmt * ptiles * ksplit), dim3(256), lds, st, xv, sb, sr, p.D,
-                srcs, kept, s_hat, p.V, p.B, M, p.k, mtiles, ptiles, spread, vmt, p.sim_threshold, assign, best_sim,
+    ASAP_LAUNCH(tm, label, kern, sim_grid(p.B * mtiles * ptiles * ksplit), dim3(256), lds, st, xv, sb, sr, p.D,
+                srcs, kept, s_hat, p.V, p.B, M, p.k, mtiles, ptiles, p.sim_threshold, assign, best_sim,
                 static_cast<unsigned long long*>(nullptr), nsrc, ksplit, dots, nkept);
     ASAP_LAUNCH(tm, "k_sim_reduce", k_sim_reduce<ANCHORED>, dim3((M + 3) / 4, p.B), dim3(256), 0, st, dots, nsrc, nkept,
                 p.B, M, p.k, ksplit, srcs, kept, s_hat, p.V, p.sim_threshold, assign, best_sim);
@@ -861,8 +867,8 @@ static hipError_t launch_sim_nt(const asap_params& p, const T* xv, int64_t sb, i
   }
   unsigned long long* keys = reinterpret_cast<unsigned long long*>(ws);               // [ptiles][B*M]
   float* norms = reinterpret_cast<float*>(ws + align256(sizeof(unsigned long long) * (size_t)n * ptiles));
-  ASAP_LAUNCH(tm, label, kern, dim3(NUM_XCD * groups * vmt * ptiles), dim3(256), lds, st, xv, sb, sr, p.D, srcs,
-              kept, s_hat, p.V, p.B, M, p.k, mtiles, ptiles, spread, vmt, p.sim_threshold, assign, best_sim, keys,
+  ASAP_LAUNCH(tm, label, kern, sim_grid(p.B * mtiles * ptiles), dim3(256), lds, st, xv, sb, sr, p.D, srcs,
+              kept, s_hat, p.V, p.B, M, p.k, mtiles, ptiles, p.sim_threshold, assign, best_sim, keys,
               norms, 1, static_cast<float*>(nullptr), static_cast<float*>(nullptr));
   if (ptiles > 1)
     ASAP_LAUNCH(tm, "k_sim_finish", k_sim_finish, dim3((n + 255) / 256), dim3(256), 0, st, keys, norms, n, ptiles,

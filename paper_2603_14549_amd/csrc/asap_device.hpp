@@ -123,6 +123,16 @@ template <int P> __device__ __forceinline__ void mma_split_term(f32x16_t& acc, c
   else mma32<bf16_t>(acc, a.hi, b.hi);
 }
 
+// The 16 x 16 tile: lane l supplies row / column l % 16 and the contraction slice picked by l / 16 of 32
+// components; its 4 results are C[4 * (l / 16) + v][l % 16].
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void mma16(f32x4_t& acc, const uint4& a, const uint4& b) {
+  bf16x8_t x, y;
+  __builtin_memcpy(&x, &a, 16);
+  __builtin_memcpy(&y, &b, 16);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, acc, 0, 0, 0);
+}
+
 // row of the 32x32 tile held in accumulator register v of lane l
 __device__ __forceinline__ int mma32_row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 
@@ -177,6 +187,9 @@ template <int N> __device__ __forceinline__ void wait_vmem_but() {
 // Workgroup barrier without the release fence of __syncthreads(): that fence would wait for every
 // outstanding load of the wave, also the ones that are meant to stay in flight across the barrier.
 __device__ __forceinline__ void barrier_keep_loads() { asm volatile("s_barrier" ::: "memory"); }
+
+// The same with this wave's LDS traffic waited for: what was written before is there for everyone after.
+__device__ __forceinline__ void barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>): a loop whose counter is a
 // compile-time constant inside the body

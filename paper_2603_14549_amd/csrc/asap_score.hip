@@ -17,7 +17,10 @@
 //                 their raw logits in the workspace, and no further sweep over the keys is needed.
 //                 Small batches cut the kv heads into groups with workgroups of their own, which
 //                 leave partial masses; k_mass_finish adds them and takes min / max.
-//   either the two sweeps over the keys
+//   then, bf16 and up to 4096 keys,
+//   k_attn_rows   the softmax of the text rows in one sweep over the keys: terms stay in registers until
+//                 their row's denominator is known
+//   or two sweeps over the keys
 //   k_attn_stats  per (image, head, key split): key x text-query logits on the matrix cores (keys as
 //                 tile rows, so a lane owns one text row), online (max, sum) of lambda'_j 2^z per row
 //   k_attn_colsum the sweep again with queries as tile rows and the merged row statistics:
@@ -37,6 +40,8 @@
 #include "asap_device.hpp"
 #include "asap_launch.hpp"
 #include "asap_select.hpp"
+
+#include <algorithm>
 
 namespace asap {
 
@@ -86,14 +91,13 @@ __device__ __forceinline__ void split_bf16x4(double x, uint16_t* out, int stride
 
 // ------------------------------------------------------------------------------------------
 // k_qsum: grid (chunks, H, B), 1024 threads.  A row is d elements = LPR 16-byte pieces; thread t
-// keeps piece t % LPR of rows t / LPR + RPI * i. 
+// keeps piece t % LPR of rows t / LPR + RPI * i.
 // With one chunk and one query head per kv head the block's sums are final (`direct`): it writes
-// qbar and its bf16 split itself and k_qsplit is not needed.
+// their bf16 split itself and k_qsplit is not needed.
 // ------------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(1024) void k_qsum(const T* __restrict__ q, Strides3 sq, int V, int d, int R,
-                                                double* __restrict__ qpart, double* __restrict__ qbar,
-                                                uint16_t* __restrict__ qsplit, int direct) {
+                                                double* __restrict__ qpart, uint16_t* __restrict__ qsplit, int direct) {
   constexpr int E = elem<T>::per16;
   const int LPR = d / E, RPI = 1024 / LPR;
   const int tid = threadIdx.x, piece = tid % LPR, r0 = tid / LPR;
@@ -140,17 +144,14 @@ __global__ __launch_bounds__(1024) void k_qsum(const T* __restrict__ q, Strides3
     double s = 0.0;
     for (int w = 0; w < 16; ++w) s += red[w * d + tid];
     qpart[(((int64_t)b * gridDim.y + h) * gridDim.x + c) * d + tid] = s;
-    if (direct) {
-      qbar[((int64_t)b * gridDim.y + h) * d + tid] = s;
-      split_bf16x4(s, qsplit + ((int64_t)b * gridDim.y + h) * 4 * d + tid, d);
-    }
+    if (direct) split_bf16x4(s, qsplit + ((int64_t)b * gridDim.y + h) * 4 * d + tid, d);
   }
 }
 
-// k_qsplit: grid (Hkv, B), d threads.  qbar[b,g,:] = sum over the heads of group g and the chunks;
-// qsplit[b,g,p,:] (p = 0..3) = successive bf16 roundings of what is left of qbar.
-__global__ void k_qsplit(const double* __restrict__ qpart, double* __restrict__ qbar, uint16_t* __restrict__ qsplit,
-                         int H, int Hkv, int nchunk, int d) {
+// k_qsplit: grid (Hkv, B), d threads.  qbar_g = sum over the heads of group g and the chunks;
+// qsplit[b,g,p,:] (p = 0..3) = successive bf16 roundings of what is left of it.
+__global__ void k_qsplit(const double* __restrict__ qpart, uint16_t* __restrict__ qsplit, int H,
+                         int Hkv, int nchunk, int d) {
   const int g = blockIdx.x, b = blockIdx.y, c = threadIdx.x;
   const int G = H / Hkv;
   // the partials of the group's heads and chunks lie one after the other (head-major): added in that
@@ -165,7 +166,6 @@ __global__ void k_qsplit(const double* __restrict__ qpart, double* __restrict__ 
 #pragma unroll
     for (int u = 0; u < 8; ++u) s += part[u];
   }
-  qbar[((int64_t)b * Hkv + g) * d + c] = s;
   split_bf16x4(s, qsplit + ((int64_t)b * Hkv + g) * 4 * d + c, d);
 }
 
@@ -548,6 +548,11 @@ __device__ __forceinline__ void merge_stat(float& m, float& s, float m2, float s
 
 constexpr float ATT_NEG = -1e30f;
 
+// the value of another lane of the row of 16 lanes (rotations inside the row)
+template <int CTRL> __device__ __forceinline__ float dpp_f32(float x) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xF, 0xF, true));
+}
+
 // online (max, sum) update of one row block from the 16 logits a lane holds
 __device__ __forceinline__ void stats_update(f32x16_t& acc, const float (&lam)[16], bool ragged, int tile, int hf, int V,
                                              float c2, float& m_run, float& s_run) {
@@ -875,6 +880,398 @@ __global__ __launch_bounds__(256, 2) void k_attn_colsum(AttnArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
+// k_attn_rows (bf16): both reductions of the text-row attention in one sweep over the keys, for images whose
+// softmax terms fit a workgroup's registers: 512 threads = 8 waves hold 16 RG text rows x V keys, wave w the
+// 32-key tiles w, w + 8, ... (TPW of them, 8 RG registers each), so V <= 256 TPW.
+//   What bounds it: the keys, 256 bytes each (d = 128).  k_attn_stats + k_attn_colsum read them from HBM
+//   twice; here they come once, and the further workgroups of a kv head (its G query heads and T text rows
+//   give ceil(G T / 16 RG) blocks of rows) find them in the L2 of the XCD they are all dealt to.
+//   Rows are packed: row r of kv head g is text row r % len of query head g G + r / len, so a group of
+//   query heads or a short text fills whole blocks, and only blocks that exist get workgroups (every
+//   wave counts the blocks of the images in front of it from text_len).
+//   A workgroup walks GPW kv heads of an image, one after the other, and leaves the sum of their column
+//   sums: with every compute unit busy, further workgroups would only add rows for k_score to read, and
+//   the next head's first tiles are on their way while this head's statistics are exchanged.
+//   16 images x 32 heads x 2304 keys, 64 rows: 113 us for the two sweeps, 70 us here (each key read by two
+//   workgroups, 8.6 TB/s out of L2); 4 x 28 heads (4 kv heads) x 4096 keys, 48 rows: 49 -> 33 us; 1 x 16
+//   heads x 576 keys, 32 rows: 12 -> 8 us.
+//   Key tiles go to LDS by direct loads (whole rows, no registers), a ring of its own per wave.
+// Exponents: a lane's baseline for a row is its own first logit of that row, known before any other: the
+// term 2^(z - baseline) is then final when the logit is, whatever the other lanes and waves find, and
+// baselines meet once at the end, where the row's denominator and a factor per lane and row
+// (2^(baseline - M) / denominator) come out of one exchange through LDS.  fp32 leaves room for logits
+// 2^100 times the baseline's; should a lane's sum show that one was larger (or not finite), the wave looks
+// for the largest logits first and sweeps its keys again with those as baselines.
+// Matrix tiles are 16 x 16 (queries x keys), 32 components of the contraction each: lane l supplies row /
+// key l % 16, components 8 (l / 16) .. + 7, and owns key l % 16 of a group of 16 and the rows 4 (l / 16) + v of
+// one: 4 rows per row group to keep statistics for and to exchange over 16 lanes.  (With 32 x 32 tiles, 16
+// rows per lane over 32 lanes, the exchange alone took 15 of 80 us for 16 x 2304 keys, 64 rows, 32 heads.)
+// ------------------------------------------------------------------------------------------
+constexpr int ROWS_NW = 8;
+constexpr int ROWS_V2 = 9 * 32 * ROWS_NW;      // most keys with two row groups per workgroup (9 tiles per wave) ...
+constexpr int ROWS_V1 = 16 * 32 * ROWS_NW;     // ... and with one (16)
+
+// blocks of `block` ranking rows of one kv head of an image
+__device__ __forceinline__ int row_blocks(const int32_t* text_len, int b, int Tmax, int last_only, int G, int block) {
+  const int len = min(max(text_len[b], 0), Tmax);
+  return (G * (last_only ? min(len, 1) : len) + block - 1) / block;
+}
+
+// Unit u of all images' units (image by image, group of GPW kv heads by group, row block by row block):
+// b = -1 past the last one.
+struct RowUnit { int b, grp, rb, nb; };
+__device__ __forceinline__ RowUnit find_row_unit(const AttnArgs& a, int B, int groups, int block, int lane) {
+  const int G = a.H / a.Hkv;
+  int total = 0;
+  for (int b0 = 0; b0 < B; b0 += 64)
+    total += b0 + lane < B ? row_blocks(a.text_len, b0 + lane, a.Tmax, a.last_only, G, block) * groups : 0;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) total += __shfl_xor(total, off);
+  // each XCD (id % 8) takes a contiguous eighth, so that the blocks of a kv head share an L2
+  const int per_xcd = (total + 7) >> 3, slot = blockIdx.x >> 3;
+  int u = (blockIdx.x & 7) * per_xcd + slot;
+  RowUnit r{-1, 0, 0, 0};
+  if (slot >= per_xcd || u >= total) return r;
+  for (int b0 = 0; b0 < B; b0 += 64) {
+    const int nb = b0 + lane < B ? row_blocks(a.text_len, b0 + lane, a.Tmax, a.last_only, G, block) : 0;
+    int upto = nb * groups;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int y = __shfl_up(upto, off);
+      if (lane >= off) upto += y;
+    }
+    const int at = __popcll(__ballot(upto <= u));      // images of this chunk that lie wholly before u
+    if (at < 64) {
+      r.b = b0 + at;
+      r.nb = __shfl(nb, at);
+      u -= __shfl(upto, at) - r.nb * groups;
+      r.grp = u / r.nb;
+      r.rb = u % r.nb;
+      return r;
+    }
+    u -= __shfl(upto, 63);
+  }
+  return r;
+}
+
+// Ring slots per wave: two tiles, or one where two workgroups then fit a compute unit.
+constexpr int rows_slots(int rg, int tpw) { return rg * tpw <= 6 ? 1 : 2; }
+template <int NG, int RG, int TPW> constexpr size_t rows_lds_bytes() {
+  return (size_t)rows_slots(RG, TPW) * ROWS_NW * 32 * NG * 32 + (size_t)16 * RG * (NG * 32 + 16) +
+         sizeof(float) * (2 * ROWS_NW * 16 * RG + 2 * 16 * RG + TPW * ROWS_NW * 32);
+}
+
+template <int NG, int RG, int TPW>
+__global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) void k_attn_rows(AttnArgs a, int B, int GPW) {
+  constexpr int RB = 16 * RG;                                  // rows of the block
+  constexpr int NC = NG / 2;                                   // contraction steps of 32 components
+  constexpr int KROW = NG * 32, KTILE = 32 * KROW, KLD = KTILE / 1024, QROW = KROW + 16;
+  constexpr int NS = rows_slots(RG, TPW);
+  constexpr int AHEAD = RG == 2 && NS == 1 ? 1 : 2;            // contraction steps whose operands are read ahead
+  extern __shared__ __align__(16) char lds[];
+  char* qlds = lds + NS * ROWS_NW * KTILE;
+  float* st_m = reinterpret_cast<float*>(qlds + RB * QROW);                 // [8][RB]
+  float* st_s = st_m + ROWS_NW * RB;                                         // [8][RB]
+  float* fin_o = st_s + ROWS_NW * RB;                                        // [RB]  -M (log2 units)
+  float* fin_i = fin_o + RB;                                                 // [RB]  1 / denominator
+  float* lam = fin_i + RB;                                                   // [256 TPW]  discounts of the keys
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, q4 = lane >> 4;
+  const int groups = (a.Hkv + GPW - 1) / GPW;
+  const RowUnit unit = find_row_unit(a, B, groups, RB, lane);
+  const int b = __builtin_amdgcn_readfirstlane(unit.b), grp = __builtin_amdgcn_readfirstlane(unit.grp);
+  const int rb = __builtin_amdgcn_readfirstlane(unit.rb), nb = __builtin_amdgcn_readfirstlane(unit.nb);
+  if (b < 0) return;                           // the same for the whole workgroup
+  const int G = a.H / a.Hkv;
+  int row0, nrows;
+  ranking_rows(a, b, row0, nrows);
+  const int live = G * nrows;                  // rows of a kv head
+  const int ntiles = (a.V + 31) >> 5;
+  const float c2 = a.c2;
+  // Tiles of this wave, and whether tile i is one: a scalar comparison where it stands (kept across the
+  // heads, the results would fill the scalar registers and spill).
+  const int my_tiles = max(0, (ntiles - wave + ROWS_NW - 1) / ROWS_NW);
+  auto active = [&](int i) { int x = my_tiles; asm volatile("" : "+s"(x)); return i < x; };
+  int g = grp * GPW;
+  const int g_end = min(g + GPW, a.Hkv);
+  // Addresses that follow from the lane: hidden from the compiler behind a copy of it, they are computed
+  // where they are used instead of being kept across the heads.
+  auto hidden = [](int x) { asm volatile("" : "+v"(x)); return x; };
+
+  // 1 KiB of whole rows per load instruction; the 16-byte piece p of row r lands in slot p ^ x(r), so that the
+  // operand reads of 16 consecutive rows cover all banks.  x repeats after 16 rows.
+  auto kswz = [](int row) { return KROW == 128 ? (row >> 1) & 7 : row & 15; };
+  constexpr int NV = 16 * KROW / 1024, LPR = KROW / 16;        // load instructions per 16 rows, lanes per row
+  const uint32_t krow_bytes = (uint32_t)(a.sk.r * 2);          // a head of an image spans < 2 GiB
+  const uint32_t ring = lds_address(lds) + (uint32_t)wave * (NS * KTILE);
+  auto issue = [&](int g_, int i, int slot) {
+    const uint32_t dst = ring + (uint32_t)slot * KTILE;
+    const int j0 = (wave + ROWS_NW * i) * 32, ol = hidden(lane);
+    const char* base = reinterpret_cast<const char*>(static_cast<const bf16_t*>(a.kv) + b * a.sk.b + g_ * a.sk.h);
+    if (j0 + 32 <= a.V) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        const int row = v * (16 / NV) + ol / LPR;
+        const uint32_t voff = (uint32_t)row * krow_bytes + (((ol % LPR) ^ kswz(row)) << 4);
+#pragma unroll
+        for (int u = v; u < KLD; u += NV)
+          load_to_lds16(base + (uint32_t)(j0 + 16 * (u / NV)) * krow_bytes, voff, dst + u * 1024);
+      }
+    } else {                                   // the last tile: keys past the end repeat the last one
+#pragma unroll 1
+      for (int u = 0; u < KLD; ++u) {
+        const int row = u * (16 / NV) + ol / LPR;
+        load_to_lds16(base, (uint32_t)min(j0 + row, a.V - 1) * krow_bytes + (((ol % LPR) ^ kswz(row)) << 4), dst + u * 1024);
+      }
+    }
+  };
+  auto start = [&](int g_) {                   // a head's first tiles
+    if (active(0)) issue(g_, 0, 0);
+    if (NS == 2 && TPW > 1 && active(1)) issue(g_, 1, 1);
+  };
+  // thread tid brings 8 components of one row of the block (rows past the end: zeros); through registers, so
+  // that they can be asked for while the previous head's still stand in LDS
+  static_assert(RB * 2 * NG <= 64 * ROWS_NW, "one piece per thread");
+  const int qm = tid / (2 * NG), qpc = tid % (2 * NG), qr = rb * RB + qm;
+  const bool q_here = qm < RB, q_row = q_here && qr < live;
+  const char* qsrc = reinterpret_cast<const char*>(static_cast<const bf16_t*>(a.qt) + b * a.sq.b +
+                                                   (q_row ? qr / nrows : 0) * a.sq.h +
+                                                   (int64_t)(row0 + (q_row ? qr % nrows : 0)) * a.sq.r) + qpc * 16;
+  uint4 qx;
+  auto load_q = [&](int g_) {
+    qx = q_row ? ldg16(qsrc + (int64_t)g_ * G * a.sq.h * 2) : make_uint4(0, 0, 0, 0);
+  };
+  start(g);
+  load_q(g);
+  {
+    MassRange range;
+    range.load(a.mm, a.mm_n, b);
+    const double* s64 = a.s64 + (int64_t)b * a.V;
+    constexpr int PER = TPW * ROWS_NW * 32 / (64 * ROWS_NW) + (TPW & 1);
+    double sj[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) sj[i] = a.mask_on ? s64[min(tid + 512 * i, a.V - 1)] : 0.0;
+    double mlo, mhi;
+    range.reduce(mlo, mhi);
+    const double minv = 1.0 / (mhi - mlo + a.eps);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int j = tid + 512 * i;
+      if (j < TPW * ROWS_NW * 32) lam[j] = j < a.V ? discount_of(a, sj[i], mlo, minv) : 0.0f;
+    }
+  }
+  const int q_off = n * QROW + q4 * 16, k_off = n * KROW + ((q4 ^ kswz(n)) << 4);
+
+  float u[TPW][2];                             // column sums of this lane's keys over its rows and the heads
+#pragma unroll
+  for (int i = 0; i < TPW; ++i) u[i][0] = u[i][1] = 0.0f;
+
+#pragma unroll 1
+  for (;; ++g) {
+    f32x4_t e[TPW][RG][2];
+    float b2[RG][4], s[RG][4];
+    // logits of the tile in ring slot `slot`
+    auto logits = [&](f32x4_t (&z)[RG][2], int slot) {
+      const int ko = hidden(k_off);
+      const char* kt = lds + wave * (NS * KTILE) + slot * KTILE;
+      uint4 kop[AHEAD][2], qo[AHEAD][RG];
+      auto read = [&](int c) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x) kop[c % AHEAD][x] = *reinterpret_cast<const uint4*>(kt + (ko ^ (c << 6)) + x * 16 * KROW);
+#pragma unroll
+        for (int r = 0; r < RG; ++r) qo[c % AHEAD][r] = *reinterpret_cast<const uint4*>(qlds + q_off + c * 64 + r * 16 * QROW);
+      };
+#pragma unroll
+      for (int r = 0; r < RG; ++r)
+#pragma unroll
+        for (int x = 0; x < 2; ++x) z[r][x] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int c = 0; c < AHEAD; ++c) read(c);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+#pragma unroll
+        for (int r = 0; r < RG; ++r)
+#pragma unroll
+          for (int x = 0; x < 2; ++x) mma16(z[r][x], qo[c % AHEAD][r], kop[c % AHEAD][x]);
+        if (c + AHEAD < NC) read(c + AHEAD);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    auto ring_read = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };    // a slot may be filled again
+
+    if (q_here) *reinterpret_cast<uint4*>(qlds + qm * QROW + qpc * 16) = qx;
+    barrier_lds();
+    bool based = false;
+#pragma unroll 1
+    for (;;) {
+      if (!based) {
+#pragma unroll
+        for (int r = 0; r < RG; ++r)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) b2[r][v] = ATT_NEG;
+      }
+#pragma unroll
+      for (int r = 0; r < RG; ++r)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s[r][v] = 0.0f;
+      static_for<TPW>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        if (active(i)) {
+          if (NS == 2 && i + 1 < TPW && active(i + 1)) wait_vmem_but<KLD>();
+          else wait_all_vmem();
+          logits(e[i], NS == 2 ? i & 1 : 0);
+          if (i + NS < TPW && active(i + NS)) {
+            ring_read();
+            issue(g, i + NS, NS == 2 ? i & 1 : 0);
+          }
+          if (i == 0 && !based) {
+#pragma unroll
+            for (int r = 0; r < RG; ++r)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) b2[r][v] = e[0][r][0][v] * c2;
+          }
+          const int lt = hidden(wave * 32 + n);
+          const float l[2] = {lam[lt + ROWS_NW * 32 * i], lam[lt + ROWS_NW * 32 * i + 16]};
+#pragma unroll
+          for (int r = 0; r < RG; ++r)
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                e[i][r][x][v] = fast_exp2(fmaf(e[i][r][x][v], c2, -b2[r][v]));
+                s[r][v] = fmaf(l[x], e[i][r][x][v], s[r][v]);
+              }
+        }
+      });
+      bool far = false;
+#pragma unroll
+      for (int r = 0; r < RG; ++r)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) far |= !(s[r][v] < 0x1p100f);
+      if (based || !__any(far)) break;
+      // see above: the largest logits, tile by tile, and once more
+      based = true;
+#pragma unroll
+      for (int r = 0; r < RG; ++r)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) b2[r][v] = ATT_NEG;
+#pragma unroll 1
+      for (int i = 0; active(i); ++i) {
+        ring_read();
+        issue(g, i, 0);
+        wait_all_vmem();
+        f32x4_t z[RG][2];
+        logits(z, 0);
+#pragma unroll
+        for (int r = 0; r < RG; ++r)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) b2[r][v] = fmaxf(b2[r][v], fmaxf(z[r][0][v], z[r][1][v]) * c2);
+      }
+      ring_read();
+      start(g);
+    }
+    const bool last = g + 1 >= g_end;
+    if (!last) {
+      ring_read();
+      start(g + 1);
+      load_q(g + 1);
+    }
+
+    // the 16 lanes of a row and then the waves agree on a baseline and on the denominator of every row
+    {
+      float m[RG][4], x[RG][4];                // step by step over all rows: a step alone waits for itself
+#pragma unroll
+      for (int r = 0; r < RG; ++r)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) m[r][v] = b2[r][v];
+      auto each = [&](auto f) {
+#pragma unroll
+        for (int r = 0; r < RG; ++r)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) f(m[r][v], x[r][v], b2[r][v], s[r][v]);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      each([](float& m_, float&, float, float) { m_ = fmaxf(m_, dpp_f32<0x128>(m_)); });     // row_ror:8, 4, 2, 1
+      each([](float& m_, float&, float, float) { m_ = fmaxf(m_, dpp_f32<0x124>(m_)); });
+      each([](float& m_, float&, float, float) { m_ = fmaxf(m_, dpp_f32<0x122>(m_)); });
+      each([](float& m_, float&, float, float) { m_ = fmaxf(m_, dpp_f32<0x121>(m_)); });
+      each([](float& m_, float& x_, float b_, float s_) { x_ = s_ * fast_exp2(b_ - m_); });
+      each([](float&, float& x_, float, float) { x_ += dpp_f32<0x128>(x_); });
+      each([](float&, float& x_, float, float) { x_ += dpp_f32<0x124>(x_); });
+      each([](float&, float& x_, float, float) { x_ += dpp_f32<0x122>(x_); });
+      each([](float&, float& x_, float, float) { x_ += dpp_f32<0x121>(x_); });
+      const int at = hidden(wave * RB + 4 * q4);
+      if (n == 0) {
+#pragma unroll
+        for (int r = 0; r < RG; ++r) {
+          *reinterpret_cast<float4*>(st_m + at + r * 16) = make_float4(m[r][0], m[r][1], m[r][2], m[r][3]);
+          *reinterpret_cast<float4*>(st_s + at + r * 16) = make_float4(x[r][0], x[r][1], x[r][2], x[r][3]);
+        }
+      }
+    }
+    barrier_lds();
+    if (tid < RB) {
+      float o = -INFINITY, iv = 0.0f;          // rows past the end add nothing
+      const int tl = hidden(tid), r = rb * RB + tl;
+      if (r < live) {
+        float mw[ROWS_NW], m = st_m[tl], x = 0.0f;
+#pragma unroll
+        for (int w = 0; w < ROWS_NW; ++w) mw[w] = st_m[w * RB + tl];
+#pragma unroll
+        for (int w = 1; w < ROWS_NW; ++w) m = fmaxf(m, mw[w]);
+#pragma unroll
+        for (int w = 0; w < ROWS_NW; ++w) x = fmaf(st_s[w * RB + tl], fast_exp2(mw[w] - m), x);
+        if (a.lse_extra != nullptr) {
+          const float l = a.lse_extra[((int64_t)b * a.H + g * G + r / nrows) * a.Tmax + row0 + r % nrows];
+          merge_stat(m, x, l * 1.4426950408889634f, 1.0f, 1.0f);
+        }
+        o = -m;
+        iv = 1.0f / x;
+      }
+      fin_o[tl] = o;
+      fin_i[tl] = iv;
+    }
+    barrier_lds();
+    const int row_lo = hidden(4 * q4);
+#pragma unroll
+    for (int r = 0; r < RG; ++r) {
+      const float4 o = *reinterpret_cast<const float4*>(fin_o + row_lo + r * 16);
+      const float4 iv = *reinterpret_cast<const float4*>(fin_i + row_lo + r * 16);
+      b2[r][0] = fast_exp2(b2[r][0] + o.x) * iv.x;
+      b2[r][1] = fast_exp2(b2[r][1] + o.y) * iv.y;
+      b2[r][2] = fast_exp2(b2[r][2] + o.z) * iv.z;
+      b2[r][3] = fast_exp2(b2[r][3] + o.w) * iv.w;
+    }
+#pragma unroll
+    for (int i = 0; i < TPW; ++i)
+      if (active(i)) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int r = 0; r < RG; ++r)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) u[i][x] = fmaf(e[i][r][x][v], b2[r][v], u[i][x]);
+      }
+    if (last) break;
+  }
+  float* out = a.upart + ((int64_t)b * groups * a.RP + (grp * nb + rb)) * a.V;
+#pragma unroll
+  for (int i = 0; i < TPW; ++i) {
+    if (active(i)) {
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const int j = (wave + ROWS_NW * i) * 32 + 16 * x + n;
+        float r = u[i][x] + __shfl_xor(u[i][x], 16);
+        r += __shfl_xor(r, 32);
+        if (q4 == 0 && j < a.V) out[j] = r;
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // The same two reductions from stored logits zlog [B, H, T_eff, V] (accumulator units), for the
 // text rows that rode in the mass sweep.
 // k_rowstats_logits: grid (T_eff, H, B), 256 threads: (max, sum of lambda'_j 2^z) of one row, in the
@@ -1004,22 +1401,30 @@ __device__ __forceinline__ double rank_count(const int32_t* text_len, int b, int
   return (double)(last_only ? min(len, 1) : len);
 }
 
+// Rows of upart that image b has filled, out of the HV it has room for: all of them (one per head and pair
+// of text-row blocks), or with packed > 0 one per group of kv heads (packed of them) and block of rows
+// (the G query heads of a kv head together, k_attn_rows).
+__device__ __forceinline__ int upart_rows(const int32_t* text_len, int b, int Tmax, int last_only, int HV,
+                                          int packed, int G, int block) {
+  return packed > 0 ? packed * row_blocks(text_len, b, Tmax, last_only, G, block) : HV;
+}
+
 __global__ __launch_bounds__(256) void k_score(const float* __restrict__ upart, const double* __restrict__ s64,
                                                 const double* __restrict__ mm, int mm_n,
-                                                const int32_t* __restrict__ text_len, int H, int HV, int V, int Tmax,
-                                                int last_only, double lambda_max, double eps, int mask_on,
-                                                float* __restrict__ s_hat, float* __restrict__ score) {
-  // HV = rows of upart per image: one per head and pair of text-row blocks
+                                                const int32_t* __restrict__ text_len, int H, int HV, int packed, int G, int block,
+                                                int V, int Tmax, int last_only, double lambda_max, double eps,
+                                                int mask_on, float* __restrict__ s_hat, float* __restrict__ score) {
   __shared__ double part[4][64];
   const int b = blockIdx.y, jl = threadIdx.x & 63, hq = threadIdx.x >> 6;
   const int j = blockIdx.x * 64 + jl;
   MassRange range;
   if (hq == 0) range.load(mm, mm_n, b);       // the wave that finishes
+  const int hv = upart_rows(text_len, b, Tmax, last_only, HV, packed, G, block);
   double u = 0.0;
   if (j < V) {
     const float* up = upart + (int64_t)b * HV * V + j;
     int h = hq;
-    for (; h + 12 < HV; h += 16) {
+    for (; h + 12 < hv; h += 16) {
       float u0 = up[(int64_t)h * V], u1 = up[(int64_t)(h + 4) * V], u2 = up[(int64_t)(h + 8) * V],
             u3 = up[(int64_t)(h + 12) * V];
       u += (double)u0;
@@ -1027,7 +1432,7 @@ __global__ __launch_bounds__(256) void k_score(const float* __restrict__ upart, 
       u += (double)u2;
       u += (double)u3;
     }
-    for (; h < HV; h += 4) u += (double)up[(int64_t)h * V];
+    for (; h < hv; h += 4) u += (double)up[(int64_t)h * V];
   }
   part[hq][jl] = u;
   __syncthreads();
@@ -1053,8 +1458,8 @@ __global__ __launch_bounds__(256) void k_score(const float* __restrict__ upart, 
 __device__ __forceinline__ void score_select_image(const int b, const float* __restrict__ upart,
                                                    const double* __restrict__ s64,
                                                    const double* __restrict__ mm, int mm_n,
-                                                   const int32_t* __restrict__ text_len, int H, int HV, int V, int k,
-                                                   int Tmax, int last_only, double lambda_max, double eps, int mask_on,
+                                                   const int32_t* __restrict__ text_len, int H, int HV, int packed, int G, int block,
+                                                   int V, int k, int Tmax, int last_only, double lambda_max, double eps, int mask_on,
                                                    float* __restrict__ s_hat, float* __restrict__ score,
                                                    int32_t* __restrict__ kept, int32_t* __restrict__ pruned) {
   __shared__ SelectShared sh;
@@ -1068,19 +1473,20 @@ __device__ __forceinline__ void score_select_image(const int b, const float* __r
   range.reduce(lo, hi);
   const double inv = 1.0 / (hi - lo + eps);
   const double norm = (double)H * rank_count(text_len, b, Tmax, last_only);
+  const int hv = upart_rows(text_len, b, Tmax, last_only, HV, packed, G, block);
   const float* up = upart + (int64_t)b * HV * V;
   float mine = 0.0f;
   for (int j = tid; j < V; j += SEL_THREADS) {
     double part[4] = {0.0, 0.0, 0.0, 0.0};
     int h = 0;
-    for (; h + 16 <= HV; h += 16) {         // 16 loads in flight; row h adds to group h % 4, in order
+    for (; h + 16 <= hv; h += 16) {         // 16 loads in flight; row h adds to group h % 4, in order
       float u[16];
 #pragma unroll
       for (int q = 0; q < 16; ++q) u[q] = up[(int64_t)(h + q) * V + j];
 #pragma unroll
       for (int q = 0; q < 16; ++q) part[q & 3] += (double)u[q];
     }
-    for (; h < HV; ++h) part[h & 3] += (double)up[(int64_t)h * V + j];
+    for (; h < hv; ++h) part[h & 3] += (double)up[(int64_t)h * V + j];
     const double usum = ((part[0] + part[1]) + part[2]) + part[3];
     const double shat = (s64[(int64_t)b * V + j] - lo) * inv;
     const double lam = mask_on ? fmax(lambda_max * shat, eps) : 1.0;
@@ -1117,11 +1523,11 @@ __global__ __launch_bounds__(SEL_THREADS) void k_score_select(const float* __res
                                                                const double* __restrict__ s64,
                                                                const double* __restrict__ mm, int mm_n,
                                                                const int32_t* __restrict__ text_len, int H, int HV,
-                                                               int V, int k, int Tmax, int last_only, double lambda_max,
+                                                               int packed, int G, int block, int V, int k, int Tmax, int last_only, double lambda_max,
                                                                double eps, int mask_on, float* __restrict__ s_hat,
                                                                float* __restrict__ score, int32_t* __restrict__ kept,
                                                                int32_t* __restrict__ pruned) {
-  score_select_image(blockIdx.x, upart, s64, mm, mm_n, text_len, H, HV, V, k, Tmax, last_only, lambda_max, eps, mask_on,
+  score_select_image(blockIdx.x, upart, s64, mm, mm_n, text_len, H, HV, packed, G, block, V, k, Tmax, last_only, lambda_max, eps, mask_on,
                      s_hat, score, kept, pruned);
 }
 
@@ -1132,11 +1538,11 @@ __global__ __launch_bounds__(SEL_THREADS) void k_score_select(const float* __res
 // A row is row_bytes / 16 pieces of 16 bytes; two rows per thread are in flight.
 __global__ __launch_bounds__(SEL_THREADS) void k_score_select_kv(
     const float* __restrict__ upart, const double* __restrict__ s64, const double* __restrict__ mm, int mm_n,
-    const int32_t* __restrict__ text_len, int H, int HV, int V, int k, int Tmax, int last_only, double lambda_max,
-    double eps, int mask_on, float* __restrict__ s_hat, float* __restrict__ score, int32_t* __restrict__ kept,
+    const int32_t* __restrict__ text_len, int H, int HV, int packed, int G, int block, int V, int k, int Tmax, int last_only,
+    double lambda_max, double eps, int mask_on, float* __restrict__ s_hat, float* __restrict__ score, int32_t* __restrict__ kept,
     int32_t* __restrict__ pruned, int B, KvFixedRows fx) {
   if ((int)blockIdx.x < B) {
-    score_select_image(blockIdx.x, upart, s64, mm, mm_n, text_len, H, HV, V, k, Tmax, last_only, lambda_max, eps,
+    score_select_image(blockIdx.x, upart, s64, mm, mm_n, text_len, H, HV, packed, G, block, V, k, Tmax, last_only, lambda_max, eps,
                        mask_on, s_hat, score, kept, pruned);
     return;
   }
@@ -1193,8 +1599,27 @@ static int attn_splits(const asap_params& p) {
   return best;
 }
 
+// key tiles per wave of k_attn_rows
+static int rows_tpw(const asap_params& p) { return ((p.V + 31) / 32 + ROWS_NW - 1) / ROWS_NW; }
+
+// kv heads a workgroup of k_attn_rows walks: workgroups run in rounds of as many as the registers let
+// onto the chip (two per compute unit where a wave holds few tiles, see rows_slots), and a workgroup costs
+// its heads plus about half a head for its start.  Least rounds x cost; ties go to fewer workgroups, which
+// leave fewer rows of column sums.
+static int rows_heads_per_wg(const asap_params& p, int row_blocks, int rg) {
+  const long slots = rows_slots(rg, rows_tpw(p)) == 1 ? 512 : 256;
+  int best = 1;
+  double best_cost = -1.0;
+  for (int n = 1; n <= p.Hkv; ++n) {
+    const long wgs = (long)p.B * ((p.Hkv + n - 1) / n) * row_blocks;
+    const double cost = (double)((wgs + slots - 1) / slots) * (n + 0.5);
+    if (best_cost < 0.0 || cost <= best_cost) { best_cost = cost; best = n; }
+  }
+  return best;
+}
+
 ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
-  ScoreWorkspace w;
+  ScoreWorkspace w{};
   // rows per k_qsum block: whole image span unless that leaves the chip short of blocks
   int chunks = (512 + p.B * p.H - 1) / (p.B * p.H);
   if (chunks > (p.V + 255) / 256) chunks = (p.V + 255) / 256;
@@ -1227,19 +1652,36 @@ ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
   w.store_logits = (!w.ride && p.qk_dtype != ASAP_BF16 && zlog_bytes <= STORED_LOGITS_MAX_BYTES) ? 1 : 0;
   const int NR = w.ride ? 32 : 64 * w.row_pairs;
   const int splits = w.ride ? 1 : w.attn_splits;
+  // One sweep over the keys where the softmax terms of 32 text rows fit a workgroup's registers.  It needs
+  // neither the row statistics nor the logits, but the size of the workspace is the caller's to plan
+  // with and stays what it was.
+  // Two row groups per workgroup read the keys half as often; one leaves twice the workgroups and half the
+  // work in each, which is what a launch that leaves half the chip idle needs, and holds more keys.
+  if (!w.ride && p.qk_dtype == ASAP_BF16) {
+    const long units2 = (long)p.B * p.Hkv * ((G * w.t_eff + 31) / 32);
+    w.one_sweep = p.V <= ROWS_V2 && units2 > 128 ? 2 : p.V <= ROWS_V1 ? 1 : 0;
+  }
+  size_t upart_rows = (size_t)p.H * w.row_pairs;
+  const size_t mm_bytes = sizeof(double) * 2 * p.B * w.mm_n;
   size_t off = 0;
   w.off_qpart = off;  off = align256(off + sizeof(double) * p.B * p.H * w.q_chunks * p.d);
-  w.off_qbar = off;   off = align256(off + sizeof(double) * p.B * p.Hkv * p.d);
+  w.off_mm = off;     off = align256(off + std::max(sizeof(double) * p.B * p.Hkv * p.d, mm_bytes));
   w.off_qsplit = off; off = align256(off + sizeof(uint16_t) * p.B * p.Hkv * 4 * p.d);
   w.off_s64 = off;    off = align256(off + sizeof(double) * p.B * p.V);
-  w.off_mm = off;     off = align256(off + sizeof(double) * 2 * p.B * w.mm_n);
+  off = align256(off + sizeof(double) * 2 * p.B);
   w.off_pstat = off;  off = align256(off + sizeof(float) * (size_t)p.B * p.H * splits * 2 * NR);
-  w.off_upart = off;  off = align256(off + sizeof(float) * (size_t)p.B * p.H * w.row_pairs * p.V);
+  if (w.one_sweep) {
+    w.row_pairs = (G * w.t_eff + 16 * w.one_sweep - 1) / (16 * w.one_sweep);
+    w.heads_per_wg = rows_heads_per_wg(p, w.row_pairs, w.one_sweep);
+    upart_rows = std::max(upart_rows, (size_t)((p.Hkv + w.heads_per_wg - 1) / w.heads_per_wg) * w.row_pairs);
+  }
+  w.off_upart = off;  off = align256(off + sizeof(float) * p.B * upart_rows * p.V);
   w.off_spart = off;
   if (w.head_splits > 1) off = align256(off + sizeof(double) * (size_t)w.head_splits * p.B * p.V);
   w.off_zlog = off;
   if (w.store_logits && align256(off + zlog_bytes) > budget) w.store_logits = 0;
   if (w.ride || w.store_logits) off = align256(off + zlog_bytes);
+  if (w.one_sweep) w.store_logits = 0;
   w.total = off;
   return w;
 }
@@ -1277,6 +1719,37 @@ static hipError_t launch_attn(const asap_params& p, const AttnArgs& a, bool stor
   return hipGetLastError();
 }
 
+template <int NG, int RG, int TPW>
+static hipError_t launch_attn_rows_as(const asap_params& p, const ScoreWorkspace& w, const AttnArgs& a, hipStream_t st,
+                                      Timer* tm) {
+  const int units = p.B * ((p.Hkv + w.heads_per_wg - 1) / w.heads_per_wg) * w.row_pairs;
+  auto kern = k_attn_rows<NG, RG, TPW>;
+  constexpr size_t lds = rows_lds_bytes<NG, RG, TPW>();
+  if (lds > 48 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  ASAP_LAUNCH(tm, "k_attn_rows", kern, dim3(8 * ((units + 7) / 8)), dim3(64 * ROWS_NW), lds, st, a, p.B, w.heads_per_wg);
+  return hipGetLastError();
+}
+
+template <int NG>
+static hipError_t launch_attn_rows(const asap_params& p, const ScoreWorkspace& w, const AttnArgs& a, hipStream_t st,
+                                   Timer* tm) {
+  const int tpw = rows_tpw(p);
+  if (w.one_sweep == 2) {
+    if (tpw <= 3) return launch_attn_rows_as<NG, 2, 3>(p, w, a, st, tm);
+    if (tpw <= 5) return launch_attn_rows_as<NG, 2, 5>(p, w, a, st, tm);
+    if (tpw <= 7) return launch_attn_rows_as<NG, 2, 7>(p, w, a, st, tm);
+    return launch_attn_rows_as<NG, 2, 9>(p, w, a, st, tm);
+  }
+  if (tpw <= 3) return launch_attn_rows_as<NG, 1, 3>(p, w, a, st, tm);
+  if (tpw <= 6) return launch_attn_rows_as<NG, 1, 6>(p, w, a, st, tm);
+  if (tpw <= 9) return launch_attn_rows_as<NG, 1, 9>(p, w, a, st, tm);
+  return launch_attn_rows_as<NG, 1, 16>(p, w, a, st, tm);
+}
+
 template <typename T, int NG>
 static hipError_t launch_mass(const asap_params& p, const ScoreWorkspace& w, const void* k_vis, Strides3 kv,
                               const uint16_t* qsplit, double scale, double* s64, float* s_raw,
@@ -1305,7 +1778,6 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
                               size_t ws_budget, hipStream_t st, Timer* tm) {
   const ScoreWorkspace w = score_workspace(p, ws_budget);
   double* qpart = reinterpret_cast<double*>(ws + w.off_qpart);
-  double* qbar = reinterpret_cast<double*>(ws + w.off_qbar);
   uint16_t* qsplit = reinterpret_cast<uint16_t*>(ws + w.off_qsplit);
   double* s64 = reinterpret_cast<double*>(ws + w.off_s64);
   double* mm = reinterpret_cast<double*>(ws + w.off_mm);
@@ -1323,13 +1795,13 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
     hipError_t e0 = launch_front_end(p, fe->hidden, fe->hsb, fe->hsr, fe->wq, fe->rope_theta, fe->vis_positions,
                                      qpart, fe->ws, st, tm);
     if (e0 != hipSuccess) return e0;
-    ASAP_LAUNCH(tm, "k_qsplit", k_qsplit, dim3(p.Hkv, p.B), dim3(p.d), 0, st, qpart, qbar, qsplit, p.H, p.Hkv, 1, p.d);
+    ASAP_LAUNCH(tm, "k_qsplit", k_qsplit, dim3(p.Hkv, p.B), dim3(p.d), 0, st, qpart, qsplit, p.H, p.Hkv, 1, p.d);
   } else {
     const int direct = (w.q_chunks == 1 && p.H == p.Hkv) ? 1 : 0;
     ASAP_LAUNCH(tm, "k_qsum", k_qsum<T>, dim3(w.q_chunks, p.H, p.B), dim3(1024), 0, st, static_cast<const T*>(q_vis),
-                qv, p.V, p.d, w.q_rows, qpart, qbar, qsplit, direct);
+                qv, p.V, p.d, w.q_rows, qpart, qsplit, direct);
     if (!direct)
-      ASAP_LAUNCH(tm, "k_qsplit", k_qsplit, dim3(p.Hkv, p.B), dim3(p.d), 0, st, qpart, qbar, qsplit, p.H, p.Hkv,
+      ASAP_LAUNCH(tm, "k_qsplit", k_qsplit, dim3(p.Hkv, p.B), dim3(p.d), 0, st, qpart, qsplit, p.H, p.Hkv,
                   w.q_chunks, p.d);
   }
   const double scale = 1.0 / ((double)p.H * sqrt((double)p.d));
@@ -1355,16 +1827,19 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
     ASAP_LAUNCH(tm, "k_rowstats_logits", k_rowstats_logits, dim3(w.t_eff, p.H, p.B), dim3(256), 0, st, a);
     ASAP_LAUNCH(tm, "k_colsum_logits", k_colsum_logits, dim3((p.V + 255) / 256, p.H, p.B), dim3(256), 0, st, a);
     e = hipGetLastError();
+  } else if (w.one_sweep) {
+    e = ng == 8 ? launch_attn_rows<8>(p, w, a, st, tm) : launch_attn_rows<4>(p, w, a, st, tm);
   } else if (ng == 8) {
     e = launch_attn<T, 8>(p, a, w.store_logits != 0, st, tm);
   } else {
     e = launch_attn<T, 4>(p, a, w.store_logits != 0, st, tm);
   }
   if (e != hipSuccess) return e;
-  const int u_rows = p.H * (w.store_logits ? 1 : w.row_pairs);     // rows of upart per image
+  const int packed = w.one_sweep ? (p.Hkv + w.heads_per_wg - 1) / w.heads_per_wg : 0;
+  const int u_rows = w.one_sweep ? packed * w.row_pairs : p.H * (w.store_logits ? 1 : w.row_pairs);  // rows of upart per image
   if (kept != nullptr && !score_fuses_selection(p)) {
     ASAP_LAUNCH(tm, "k_score", k_score, dim3((p.V + 63) / 64, p.B), dim3(256), 0, st, upart, s64, mm, w.mm_n, text_len,
-                p.H, u_rows, p.V, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps, mask_on, s_hat, score);
+                p.H, u_rows, packed, p.H / p.Hkv, 16 * w.one_sweep, p.V, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps, mask_on, s_hat, score);
     hipError_t e2 = hipGetLastError();
     return e2 != hipSuccess ? e2 : launch_select(p, score, kept, pruned, st, tm);
   }
@@ -1378,15 +1853,15 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
     }
     if (fixed)
       ASAP_LAUNCH(tm, "k_score_select_kv", k_score_select_kv, dim3(p.B + fixed->n_bufs * p.B * p.Hkv),
-                  dim3(SEL_THREADS), lds, st, upart, s64, mm, w.mm_n, text_len, p.H, u_rows, p.V, p.k, p.Tmax,
+                  dim3(SEL_THREADS), lds, st, upart, s64, mm, w.mm_n, text_len, p.H, u_rows, packed, p.H / p.Hkv, 16 * w.one_sweep, p.V, p.k, p.Tmax,
                   last_only, (double)p.lambda_max, (double)p.eps, mask_on, s_hat, score, kept, pruned, p.B, *fixed);
     else
       ASAP_LAUNCH(tm, "k_score_select", k_score_select, dim3(p.B), dim3(SEL_THREADS), lds, st, upart, s64, mm, w.mm_n,
-                  text_len, p.H, u_rows, p.V, p.k, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps,
+                  text_len, p.H, u_rows, packed, p.H / p.Hkv, 16 * w.one_sweep, p.V, p.k, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps,
                   mask_on, s_hat, score, kept, pruned);
   } else {
     ASAP_LAUNCH(tm, "k_score", k_score, dim3((p.V + 63) / 64, p.B), dim3(256), 0, st, upart, s64, mm, w.mm_n, text_len,
-                p.H, u_rows, p.V, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps, mask_on, s_hat, score);
+                p.H, u_rows, packed, p.H / p.Hkv, 16 * w.one_sweep, p.V, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps, mask_on, s_hat, score);
   }
   return hipGetLastError();
 }

@@ -947,3 +947,57 @@ def test_mass_from_hidden_states_with_scattered_position_ids(ctx):
 def test_mass_from_hidden_states_config2(ctx):
     worst = _front_end_case(ctx, synth.CONFIGS["C2"])
     print(f"front end on C2: worst error {worst:.3g} of max |s|")
+
+
+def _score_reference(q_txt, k_vis, s_raw, length, lam_max, eps, mask_on):
+    """Eq. 3-5 and the mean over heads and rows in fp64, from the masses the call returned; also the largest
+    sum_c |q_c k_c| / sqrt(d) over the logits."""
+    H, _, d = q_txt.shape
+    q, k = q_txt[:, :length].double(), k_vis.double().repeat_interleave(H // k_vis.shape[0], 0)
+    lam = torch.ones_like(s_raw, dtype=torch.float64)
+    if mask_on:
+        s = s_raw.double()
+        lam = torch.clamp(lam_max * (s - s.min()) / (s.max() - s.min() + eps), min=eps)
+    z = q @ k.transpose(1, 2) / math.sqrt(d)
+    z = z + torch.log(lam)
+    a = torch.softmax(z, -1)
+    return a.mean((0, 1)), lam, float((q.abs() @ k.abs().transpose(1, 2)).max()) / math.sqrt(d)
+
+
+@pytest.mark.parametrize("B,H,Hkv,d,V,Tmax,text_lo,size", [
+    (9, 8, 8, 128, 768, 64, 64, 1.0), (9, 8, 8, 64, 769, 64, 3, 1.0),      # tiles per wave: 3 | 5, two row groups
+    (17, 8, 4, 128, 1280, 33, 1, 1.0), (17, 4, 4, 64, 1281, 80, 1, 1.0),   # 5 | 7, rows of two heads in a block
+    (9, 8, 8, 128, 2304, 64, 64, 1.0), (9, 8, 8, 128, 2305, 64, 17, 1.0),  # 9 | one row group
+    (66, 2, 2, 64, 96, 40, 1, 1.0),                                        # more images than lanes of a wave
+    (1, 4, 4, 128, 1537, 32, 32, 1.0), (2, 12, 2, 64, 2304, 9, 1, 1.0),    # one row group: 6 | 9, six heads packed
+    (1, 4, 4, 128, 4096, 48, 48, 1.0), (1, 4, 4, 128, 4097, 48, 48, 1.0),  # 16 | the two sweeps
+    (1, 4, 4, 128, 700, 64, 64, 40.0), (9, 8, 8, 64, 600, 64, 20, 40.0),   # logits beyond 2^100 of one another
+    (9, 8, 8, 128, 2300, 64, 64, 40.0),
+])
+def test_text_rows_in_one_sweep_over_the_keys(ctx, B, H, Hkv, d, V, Tmax, text_lo, size):
+    """The softmax terms of a row block held in registers, at the edges of every launch shape, and with
+    logits so far apart that a lane's first one is no baseline for the others.
+    A logit is a sum of d exact products in fp32: off by at most (d - 1) u sum |q k| / sqrt(d), u = 2^-24, and
+    by two roundings of the scaled value; a weight by twice that (numerator, denominator) relatively, plus
+    the exponential (2^-22) and 20 roundings of the sums; the salience by its own two roundings over lambda."""
+    g = torch.Generator(device="cuda").manual_seed(V + B)
+    k_all = torch.randn(B, Hkv, V, d, generator=g, device="cuda").bfloat16()
+    q_vis = torch.randn(B, H, V, d, generator=g, device="cuda").bfloat16()
+    q_txt = (size * torch.randn(B, H, Tmax, d, generator=g, device="cuda")).bfloat16()
+    text_len = torch.randint(text_lo, Tmax + 1, (B,), generator=g, device="cuda").to(torch.int32)
+    mask_on = size == 1.0
+    p = binding.make_params(B, H, Hkv, d, 64, 0, V, Tmax, max(1, V // 8), "bf16", "bf16", "bf16",
+                            mask_mode=binding.ASAP_MASK_KEYBIAS if mask_on else binding.ASAP_MASK_OFF)
+    s_raw, s_hat, score = (torch.empty(B, V, device="cuda") for _ in range(3))
+    ws = torch.empty(binding.asap_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    ctx.asap_score(p, q_vis, q_txt, k_all, text_len, None, s_raw, s_hat, score, ws)
+    u = 2.0 ** -24
+    for b in sorted({0, B // 2, B - 1}):
+        ref, lam, zmax = _score_reference(q_txt[b].cpu(), k_all[b].cpu(), s_raw[b].cpu(), int(text_len[b]),
+                                          p.lambda_max, p.eps, mask_on)
+        rel = 2 * (d + 1) * u * zmax + 2.0 ** -21 + 20 * u
+        s = s_raw[b].double().cpu()
+        sh = 4 * u * float(s.abs().max()) / float(s.max() - s.min()) if mask_on else 0.0
+        err = (score[b].double().cpu() - ref).abs()
+        bound = ref * (rel + 2 * sh / lam) + 1e-37
+        assert bool((err <= bound).all()), (b, float((err / bound).max()))

@@ -454,7 +454,7 @@ asap_status asap_merge(asap_ctx* ctx, const asap_params* p, const void* hidden, 
   if (st != ASAP_OK) return st;
   return hip_result(ctx,
                     launch_merge(*p, hidden, hidden_stride[0], hidden_stride[1], s_raw, s_hat, text_len, kept_idx,
-                                 pruned_idx, out_hidden, pos_out, new_len, assign, best_sim, wsum, final_idx,
+                                 pruned_idx, out_hidden, pos_out, new_len, assign, best_sim, wsum, final_idx, nullptr,
                                  static_cast<char*>(workspace), static_cast<hipStream_t>(stream), ctx->timer),
                     "asap_merge launch");
 }
@@ -622,17 +622,29 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
                             ctx->timer);
     }
   }
+  // On one stream the merge's launch takes the compaction of (up to 16) layers along: whichever routing, the
+  // list of survivors is final before it.  Large copies keep a launch of their own, whose workgroups need few
+  // registers and fill the chip better (16 images, paper's routing, 440 MB: 131 us in one launch, 118 in two).
+  MergeKv mkv;
+  int taken = 0;
+  if (has_kv && !early && kv_bytes < (64ll << 20)) {
+    taken = io->n_layers < KV_LAYERS_PER_LAUNCH ? io->n_layers : KV_LAYERS_PER_LAUNCH;
+    fill_kv_pointers(&mkv.ptrs, taken, io->k_src, io->v_src, io->k_dst, io->v_dst);
+    mkv.n_bufs = 2 * taken;
+    mkv.Hkv = p->Hkv;
+    mkv.row_bytes = (int)kv_row_bytes;
+  }
   if (e == hipSuccess)
     e = launch_merge(*p, io->hidden, io->hidden_stride[0], io->hidden_stride[1], io->s_raw, io->s_hat, io->text_len,
                      io->kept_idx, io->pruned_idx, io->out_hidden, io->pos_out, io->new_len, io->assign, io->best_sim,
-                     io->wsum, io->final_idx, ws, main, ctx->timer);
+                     io->wsum, io->final_idx, taken ? &mkv : nullptr, ws, main, ctx->timer);
   if (forked) {      // also after an error: the caller's stream must not run ahead of the second one
     hipError_t e2 = hipEventRecord(ctx->ev_join, ctx->side);
     if (e2 == hipSuccess) e2 = hipStreamWaitEvent(main, ctx->ev_join, 0);
     if (e == hipSuccess) e = e2;
-  } else if (e == hipSuccess && has_kv) {
-    e = launch_compact_kv(*p, KV_FROM_KEPT, io->n_layers, io->k_src, io->v_src, io->k_dst, io->v_dst, io->final_idx,
-                          io->text_len, main, ctx->timer);
+  } else if (e == hipSuccess && io->n_layers > taken) {
+    e = launch_compact_kv(*p, KV_FROM_KEPT, io->n_layers - taken, io->k_src + taken, io->v_src + taken,
+                          io->k_dst + taken, io->v_dst + taken, io->final_idx, io->text_len, main, ctx->timer);
   }
   return hip_result(ctx, e, "asap_stage launch");
 }

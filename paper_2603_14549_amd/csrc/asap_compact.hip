@@ -7,12 +7,11 @@
 // kept list (then nothing of asap_merge is needed).
 // k_compact_paged: the same grid for caches kept as pools of pages with one block table per sequence.
 // A row is d elements = LPR 16-byte pieces; LPR consecutive lanes move one row.
+#include "asap_compact.hpp"
 #include "asap_device.hpp"
 #include "asap_launch.hpp"
 
 namespace asap {
-
-constexpr int KV_ROWS_PER_THREAD = 4;
 
 void fill_kv_pointers(KvPointers* ptrs, int n_layers, const void* const* k_src, const void* const* v_src,
                       void* const* k_dst, void* const* v_dst) {
@@ -23,49 +22,6 @@ void fill_kv_pointers(KvPointers* ptrs, int n_layers, const void* const* k_src, 
     ptrs->dst[2 * l + 1] = static_cast<char*>(v_dst[l]);
   }
   for (int l = 2 * n_layers; l < 2 * KV_LAYERS_PER_LAUNCH; ++l) { ptrs->src[l] = nullptr; ptrs->dst[l] = nullptr; }
-}
-
-// Where the source rows come from: the position list of asap_merge / asap_positions, or the kept list
-// and text_len directly (the output order of Fig. 3 written out: prefix | kept | valid text).
-// idx = pos_out [B,Nout] and len = new_len (BY_POS); idx = kept list [B,k] and len = text_len (FROM_KEPT,
-// KEPT_ONLY); FIXED_ONLY reads no index list and takes len = text_len.
-template <int MODE>
-__device__ __forceinline__ void compact_block(const KvPointers& ptrs, const int32_t* __restrict__ idx,
-                                              const int32_t* __restrict__ len, int Hkv, int N, int Nout,
-                                              int row_bytes, int P, int V, int k, int bx, int bg, int bz) {
-  const int lpr = row_bytes >> 4, rpi = 256 / lpr;
-  const int tid = threadIdx.x, piece = tid % lpr, r0 = tid / lpr;
-  const int b = bg / Hkv;
-  const int n_rows = MODE == KV_BY_POS      ? min(len[b], Nout)
-                     : MODE == KV_KEPT_ONLY ? k
-                     : MODE == KV_FIXED_ONLY ? P + min(max(len[b], 0), Nout - P - k)
-                                             : P + k + min(len[b], Nout - P - k);
-  const char* src = ptrs.src[bz] + (int64_t)bg * N * row_bytes + piece * 16;
-  char* dst = ptrs.dst[bz] + (int64_t)bg * Nout * row_bytes + piece * 16;
-  const int32_t* ix = idx + (int64_t)b * (MODE == KV_BY_POS ? Nout : k);
-  const int base = bx * rpi * KV_ROWS_PER_THREAD + r0;
-  uint4 v[KV_ROWS_PER_THREAD];
-#pragma unroll
-  for (int i = 0; i < KV_ROWS_PER_THREAD; ++i) {
-    const int r = base + i * rpi;
-    if (r < n_rows) {
-      const int srow = MODE == KV_BY_POS       ? ix[r]
-                       : MODE == KV_KEPT_ONLY  ? P + ix[r]
-                       : MODE == KV_FIXED_ONLY ? (r < P ? r : r + V)
-                       : r < P                 ? r
-                       : r < P + k             ? P + ix[r - P]
-                                               : r - k + V;
-      v[i] = ldg16_stream(src + (int64_t)srow * row_bytes);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < KV_ROWS_PER_THREAD; ++i) {
-    const int r = base + i * rpi;
-    // kept slot r is output row P + r; the r-th row that no selection changes is output row r (prefix) or
-    // r + k (text)
-    const int drow = MODE == KV_KEPT_ONLY ? P + r : MODE == KV_FIXED_ONLY ? (r < P ? r : r + k) : r;
-    if (r < n_rows) stg16_stream(dst + (int64_t)drow * row_bytes, v[i]);
-  }
 }
 
 template <int MODE>
@@ -154,7 +110,7 @@ hipError_t launch_compact_kv(const asap_params& p, int mode, int n_layers, const
                              const int32_t* idx, const int32_t* len, hipStream_t st, Timer* tm) {
   const int row_bytes = p.d * (p.kv_dtype == ASAP_BF16 ? 2 : 4);
   const int N = p.P + p.V + p.Tmax, Nout = p.P + p.k + p.Tmax;
-  const int rows_per_block = (256 / (row_bytes / 16)) * KV_ROWS_PER_THREAD;
+  const int rows_per_block = kv_rows_per_block(row_bytes);
   const int rows = mode == KV_KEPT_ONLY ? p.k : mode == KV_FIXED_ONLY ? p.P + p.Tmax : Nout;
   for (int l0 = 0; l0 < n_layers; l0 += KV_LAYERS_PER_LAUNCH) {
     const int nl = n_layers - l0 < KV_LAYERS_PER_LAUNCH ? n_layers - l0 : KV_LAYERS_PER_LAUNCH;
@@ -188,7 +144,7 @@ hipError_t launch_compact_kv_paged(const asap_params& p, int n_layers, const voi
                                    Timer* tm) {
   const int row_bytes = p.d * (p.kv_dtype == ASAP_BF16 ? 2 : 4);
   const int Nout = p.P + p.k + p.Tmax;
-  const int rows_per_block = (256 / (row_bytes / 16)) * KV_ROWS_PER_THREAD;
+  const int rows_per_block = kv_rows_per_block(row_bytes);
   for (int l0 = 0; l0 < n_layers; l0 += KV_LAYERS_PER_LAUNCH) {
     const int nl = n_layers - l0 < KV_LAYERS_PER_LAUNCH ? n_layers - l0 : KV_LAYERS_PER_LAUNCH;
     KvPointers ptrs;

@@ -121,10 +121,19 @@ hipError_t launch_score(const asap_params& p, const void* q_vis, Strides3 qv, co
 hipError_t launch_select(const asap_params& p, const float* score, int32_t* kept, int32_t* pruned,
                          hipStream_t st, Timer* tm);
 
+// K/V compaction (all surviving rows) that the merge's launch takes along.
+struct MergeKv {
+  KvPointers ptrs;
+  int n_bufs;                 // 2 * layers
+  int Hkv, row_bytes;
+  int gx;                     // blocks of rows per (cache, image, kv head), set by the launch
+};
+
+// kv != nullptr: the launch also moves the K/V rows of the survivors.
 hipError_t launch_merge(const asap_params& p, const void* hidden, int64_t hsb, int64_t hsr, const float* s_raw,
                         const float* s_hat, const int32_t* text_len, const int32_t* kept, const int32_t* pruned,
                         void* out_hidden, int32_t* pos_out, int32_t* new_len, int32_t* assign, float* best_sim,
-                        float* wsum, int32_t* final_idx, char* ws, hipStream_t st, Timer* tm);
+                        float* wsum, int32_t* final_idx, const MergeKv* kv, char* ws, hipStream_t st, Timer* tm);
 
 // Cosine routing (asap_sim.hip): for each of the M source tokens srcs[b,:] the most similar kept
 // token (slot in kept, -1 if the similarity does not exceed the threshold) and that similarity.

@@ -6,17 +6,27 @@
 //                 slot gathers its sources in ascending order and applies Eq. 6.  The sources are
 //                 M candidate tokens with assign[] = the slot that absorbs each (or -1): the
 //                 pruned tokens with ABSORB routing, the kept tokens with the paper's.
+#include "asap_compact.hpp"
 #include "asap_device.hpp"
 #include "asap_launch.hpp"
 
 namespace asap {
 
 // ------------------------------------------------------------------------------------------
-// k_merge: grid (P + k + Tmax, B), 256 threads.
+// k_merge: grid (B (P + k + Tmax) parts + KV blocks), 256 threads.  The first B (P + k + Tmax) parts workgroups
+// take one output row each, or one of its `parts` pieces of 4 KB; the others, if the launch carries the K/V compaction along, one block of cache rows
+// each (asap_compact.hpp): it needs the same list of survivors and nothing of the merge, the copies run
+// under the latency of the gathers, and a launch is saved (8 us of a single image's stage).
+//   What bounds it: HBM where the batch is large (every visual row of the hidden states once); a chain of
+//   dependent loads -- lists, weights, rows -- where it is not.  So the lists are read with whole
+//   coalesced loads before anything is known about them, the weights are fetched by the threads that
+//   found the sources, and AHEAD source rows are in flight at a time: a slot's sources (V / k - 1 on
+//   average, 30 to 70 for the most similar) mostly come in one turn.
 // ------------------------------------------------------------------------------------------
 constexpr int MERGE_SEG = 2048;   // entries of assign[] scanned per round
+constexpr long MERGE_SPLIT_ROWS = 1024;
 
-template <typename T, int CPT>    // CPT = 16-byte chunks of a row per thread (row = D elements)
+template <typename T, int CPT, int AHEAD>    // CPT = 16-byte chunks of a row (or of a part) per thread
 __global__ __launch_bounds__(256) void k_merge(const T* __restrict__ hidden, int64_t sb, int64_t sr, int D,
                                                 int P, int V, int k, int M, int Tmax, float mu,
                                                 const float* __restrict__ s_hat, const int32_t* __restrict__ text_len,
@@ -24,19 +34,31 @@ __global__ __launch_bounds__(256) void k_merge(const T* __restrict__ hidden, int
                                                 const int32_t* __restrict__ pruned,
                                                 const int32_t* __restrict__ assign, T* __restrict__ out,
                                                 int32_t* __restrict__ pos_out, int32_t* __restrict__ new_len,
-                                                float* __restrict__ wsum, int32_t* final_idx) {
+                                                float* __restrict__ wsum, int32_t* final_idx, int B, int parts, MergeKv kv) {
   constexpr int E = elem<T>::per16;
   __shared__ int list[MERGE_SEG];
+  __shared__ float weight[MERGE_SEG];
   __shared__ int wave_cnt[4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nrow = blockIdx.x, b = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int Nout = P + k + Tmax;
+  const int unit = blockIdx.x / parts, part = blockIdx.x - unit * parts;
+  const int b = unit / Nout, nrow = unit - b * Nout;
+  if (b >= B) {
+    int id = blockIdx.x - B * Nout * parts;
+    const int bx = id % kv.gx;
+    id /= kv.gx;
+    compact_block<KV_FROM_KEPT>(kv.ptrs, kept, text_len, kv.Hkv, P + V + Tmax, Nout, kv.row_bytes, P, V, k, bx,
+                                id % (B * kv.Hkv), id / (B * kv.Hkv));
+    return;
+  }
   const int len = text_len[b];
-  const int nchunks = D / E;
-  const char* hb = reinterpret_cast<const char*>(hidden + b * sb);
+  // the columns of this part
+  const int c0 = part * (CPT * 256), nchunks = min(D / E - c0, CPT * 256);
+  const char* hb = reinterpret_cast<const char*>(hidden + b * sb) + c0 * 16;
   const int64_t rowb = sr * (int64_t)sizeof(T);
-  char* orow = reinterpret_cast<char*>(out + ((int64_t)b * Nout + nrow) * D);
-  if (nrow == 0 && tid == 0) new_len[b] = P + k + len;
+  char* orow = reinterpret_cast<char*>(out + ((int64_t)b * Nout + nrow) * D) + c0 * 16;
+  if (nrow == 0 && part == 0 && tid == 0) new_len[b] = P + k + len;
 
   if (nrow < P || nrow >= P + k) {                       // prefix or text row: plain copy
     int src;
@@ -45,7 +67,7 @@ __global__ __launch_bounds__(256) void k_merge(const T* __restrict__ hidden, int
       int t = nrow - P - k;
       src = (t < len) ? P + V + t : -1;
     }
-    if (tid == 0) pos_out[(int64_t)b * Nout + nrow] = src;
+    if (part == 0 && tid == 0) pos_out[(int64_t)b * Nout + nrow] = src;
     if (src < 0) return;
     const char* s = hb + (int64_t)src * rowb;
     for (int c = tid; c < nchunks; c += 256) stg16_stream(orow + c * 16, ldg16_stream(s + c * 16));
@@ -53,107 +75,117 @@ __global__ __launch_bounds__(256) void k_merge(const T* __restrict__ hidden, int
   }
 
   const int slot = nrow - P;
-  const int i_tok = kept[(int64_t)b * k + slot];
   const float* sh = s_hat + (int64_t)b * V;
-  const float w_i = sh[i_tok];
-  const char* xrow = hb + (int64_t)(P + i_tok) * rowb;
-  float acc[CPT][E];
-#pragma unroll
-  for (int q = 0; q < CPT; ++q) {
-    int c = tid + q * 256;
-    if (c < nchunks) {
-      float f[E];
-      unpack16<T>(ldg16_stream(xrow + c * 16), f);
-#pragma unroll
-      for (int e = 0; e < E; ++e) acc[q][e] = w_i * f[e];
-    }
-  }
-  float den = w_i, absorbed = 0.0f;
   const int32_t* asg = assign + (int64_t)b * M;
   const int32_t* pr = pruned + (int64_t)b * M;
-  for (int seg = 0; seg < M; seg += MERGE_SEG) {
-    // ordered compaction of the sources of this slot among entries [seg, seg + MERGE_SEG)
-    constexpr int PER = MERGE_SEG / 256;
-    int mine[PER];
-    int cnt = 0;
+  const int i_tok = kept[(int64_t)b * k + slot];
+  constexpr int PER = MERGE_SEG / 256;
+  // entry e of this thread in a segment: wave w takes 64 PER entries in a row, 64 at a time
+  const int first = wave * (64 * PER) + lane;
+  int to[PER], tok[PER];
+  auto load_lists = [&](int seg) {
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
-      int a = seg + tid * PER + e;
-      mine[e] = -1;
-      if (a < M && asg[a] == slot) { mine[e] = pr[a]; ++cnt; }
+      const int a = seg + first + 64 * e;
+      to[e] = a < M ? asg[a] : -1;
+      tok[e] = a < M ? pr[a] : 0;
     }
-    int incl = cnt;
+  };
+  load_lists(0);
+  const char* xrow = hb + (int64_t)(P + i_tok) * rowb;
+  uint4 own[CPT];
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      int y = __shfl_up(incl, off);
-      if (lane >= off) incl += y;
+  for (int q = 0; q < CPT; ++q)
+    if (tid + q * 256 < nchunks) own[q] = ldg16_stream(xrow + (tid + q * 256) * 16);
+  const float w_i = sh[i_tok];
+  float acc[CPT][E];
+  float den = w_i, absorbed = 0.0f;
+  for (int seg = 0; seg < M; seg += MERGE_SEG) {
+    if (seg) load_lists(seg);
+    // ordered compaction of the sources of this slot among entries [seg, seg + MERGE_SEG)
+    int before[PER], cnt = 0;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const unsigned long long found = __ballot(to[e] == slot);
+      before[e] = cnt + __popcll(found & ((1ull << lane) - 1));
+      cnt += __popcll(found);
     }
-    __syncthreads();
-    if (lane == 63) wave_cnt[wave] = incl;
+    float w[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) w[e] = to[e] == slot ? mu * sh[tok[e]] : 0.0f;
+    if (seg) __syncthreads();                  // the previous round's lists have been used
+    if (lane == 0) wave_cnt[wave] = cnt;
     __syncthreads();
     int base = 0, total = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      if (w < wave) base += wave_cnt[w];
-      total += wave_cnt[w];
+    for (int v = 0; v < 4; ++v) {
+      if (v < wave) base += wave_cnt[v];
+      total += wave_cnt[v];
     }
-    int pos = base + incl - cnt;
 #pragma unroll
     for (int e = 0; e < PER; ++e)
-      if (mine[e] >= 0) list[pos++] = mine[e];
+      if (to[e] == slot) {
+        list[base + before[e]] = tok[e];
+        weight[base + before[e]] = w[e];
+      }
     __syncthreads();
-    for (int s0 = 0; s0 < total; s0 += 4) {
-      uint4 ch[4][CPT];
-      float w[4];
+    total = __builtin_amdgcn_readfirstlane(total);
+    if (seg == 0) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        int j = list[min(s0 + u, total - 1)];
-        w[u] = (s0 + u < total) ? mu * sh[j] : 0.0f;
-        const char* srow = hb + (int64_t)(P + j) * rowb;
+      for (int q = 0; q < CPT; ++q) {
+        float f[E];
+        unpack16<T>(own[q], f);
 #pragma unroll
-        for (int q = 0; q < CPT; ++q) {
-          int c = tid + q * 256;
-          if (c < nchunks) ch[u][q] = ldg16_stream(srow + c * 16);
+        for (int e = 0; e < E; ++e) acc[q][e] = w_i * f[e];
+      }
+    }
+    for (int s0 = 0; s0 < total; s0 += AHEAD) {
+      uint4 ch[AHEAD][CPT];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        if (s0 + u < total) {
+          const int j = __builtin_amdgcn_readfirstlane(list[s0 + u]);
+          const char* srow = hb + (int64_t)(P + j) * rowb;
+#pragma unroll
+          for (int q = 0; q < CPT; ++q)
+            if (tid + q * 256 < nchunks) ch[u][q] = ldg16_stream(srow + (tid + q * 256) * 16);
         }
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < AHEAD; ++u) {
         if (s0 + u < total) {
-          den += w[u];
-          absorbed += w[u];
+          const float wu = weight[s0 + u];
+          den += wu;
+          absorbed += wu;
 #pragma unroll
           for (int q = 0; q < CPT; ++q) {
-            int c = tid + q * 256;
-            if (c < nchunks) {
-              float f[E];
-              unpack16<T>(ch[u][q], f);
+            float f[E];
+            unpack16<T>(ch[u][q], f);
 #pragma unroll
-              for (int e = 0; e < E; ++e) acc[q][e] = fmaf(w[u], f[e], acc[q][e]);
-            }
+            for (int e = 0; e < E; ++e) acc[q][e] = fmaf(wu, f[e], acc[q][e]);
           }
         }
       }
     }
   }
-  if (tid == 0) {
+  if (part == 0 && tid == 0) {
     wsum[(int64_t)b * k + slot] = den;
     final_idx[(int64_t)b * k + slot] = i_tok;
     pos_out[(int64_t)b * Nout + nrow] = P + i_tok;
   }
-  if (absorbed > 0.0f) {
-    const float inv = 1.0f / den;
+  const float inv = 1.0f / den;
 #pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-      int c = tid + q * 256;
-      if (c < nchunks) {
-        float f[E];
+  for (int q = 0; q < CPT; ++q) {
+    const int c = tid + q * 256;
+    if (c >= nchunks) continue;
+    uint4 y = own[q];                          // nothing absorbed: Eq. 6 is the identity
+    if (absorbed > 0.0f) {
+      float f[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) f[e] = acc[q][e] * inv;
-        stg16_stream(orow + c * 16, pack16<T>(f));
-      }
+      for (int e = 0; e < E; ++e) f[e] = acc[q][e] * inv;
+      y = pack16<T>(f);
     }
-  } else {                                               // nothing absorbed: Eq. 6 is the identity
-    for (int c = tid; c < nchunks; c += 256) stg16_stream(orow + c * 16, ldg16_stream(xrow + c * 16));
+    stg16_stream(orow + c * 16, y);
   }
 }
 
@@ -164,20 +196,34 @@ template <typename T>
 static hipError_t merge_typed(const asap_params& p, const void* hidden, int64_t hsb, int64_t hsr,
                               const float* s_hat, const int32_t* text_len, const int32_t* kept,
                               const int32_t* cand, int M, void* out_hidden, int32_t* pos_out, int32_t* new_len,
-                              int32_t* assign, float* wsum, int32_t* final_idx, hipStream_t st, Timer* tm) {
+                              int32_t* assign, float* wsum, int32_t* final_idx, const MergeKv* kv, hipStream_t st,
+                              Timer* tm) {
   const T* h = static_cast<const T*>(hidden);
   constexpr int E = elem<T>::per16;
   const int nchunks = p.D / E;
   const int cpt = (nchunks + 255) / 256;
-  dim3 grid(p.P + p.k + p.Tmax, p.B);
-#define ASAP_MERGE(CPT)                                                                                    \
-  ASAP_LAUNCH(tm, "k_merge", (k_merge<T, CPT>), grid, dim3(256), 0, st, h, hsb, hsr, p.D, p.P, p.V, p.k,   \
-              M, p.Tmax, p.merge_weight, s_hat, text_len, kept, cand, assign, static_cast<T*>(out_hidden), \
-              pos_out, new_len, wsum, final_idx)
-  if (cpt <= 1) ASAP_MERGE(1);
-  else if (cpt <= 2) ASAP_MERGE(2);
-  else if (cpt <= 4) ASAP_MERGE(4);
-  else if (cpt <= 8) ASAP_MERGE(8);
+  MergeKv mk{};
+  int kv_blocks = 0;
+  if (kv) {
+    mk = *kv;
+    mk.gx = (p.P + p.k + p.Tmax + kv_rows_per_block(mk.row_bytes) - 1) / kv_rows_per_block(mk.row_bytes);
+    kv_blocks = mk.gx * p.B * mk.Hkv * mk.n_bufs;
+  }
+  // Few rows (at most about four workgroups per compute unit): pieces of 4 KB with workgroups of their own,
+  // whose threads then have registers for 16 source rows in flight (one image, 2304 tokens: 15 -> 13 us,
+  // 576 tokens in f32: 16 -> 12).  Many rows: whole rows, so that the lists are scanned once per row (16 x 2304:
+  // 71 us, 78 in pieces).
+  const long rows = (long)p.B * (p.P + p.k + p.Tmax);
+  const int parts = rows <= MERGE_SPLIT_ROWS ? cpt : 1;
+  const dim3 grid((unsigned)(rows * parts + kv_blocks));
+#define ASAP_MERGE(CPT, AHEAD)                                                                                 \
+  ASAP_LAUNCH(tm, "k_merge", (k_merge<T, CPT, AHEAD>), grid, dim3(256), 0, st, h, hsb, hsr, p.D, p.P, p.V, p.k, \
+              M, p.Tmax, p.merge_weight, s_hat, text_len, kept, cand, assign, static_cast<T*>(out_hidden),     \
+              pos_out, new_len, wsum, final_idx, p.B, parts, mk)
+  if (cpt <= 1 || parts > 1) ASAP_MERGE(1, 16);
+  else if (cpt <= 2) ASAP_MERGE(2, 8);
+  else if (cpt <= 4) ASAP_MERGE(4, 6);
+  else if (cpt <= 8) ASAP_MERGE(8, 4);
   else return hipErrorInvalidValue;
 #undef ASAP_MERGE
   return hipGetLastError();
@@ -186,7 +232,7 @@ static hipError_t merge_typed(const asap_params& p, const void* hidden, int64_t 
 hipError_t launch_merge(const asap_params& p, const void* hidden, int64_t hsb, int64_t hsr, const float* s_raw,
                         const float* s_hat, const int32_t* text_len, const int32_t* kept, const int32_t* pruned,
                         void* out_hidden, int32_t* pos_out, int32_t* new_len, int32_t* assign, float* best_sim,
-                        float* wsum, int32_t* final_idx, char* ws, hipStream_t st, Timer* tm) {
+                        float* wsum, int32_t* final_idx, const MergeKv* kv, char* ws, hipStream_t st, Timer* tm) {
   const bool bf = p.h_dtype == ASAP_BF16;
   if (p.route == ASAP_ROUTE_PAPER) {
     // kept x kept search (destinations into the workspace) -> roots, refills, final list -> merge
@@ -198,9 +244,9 @@ hipError_t launch_merge(const asap_params& p, const void* hidden, int64_t hsb, i
     e = launch_paper_plan(p, dest, kept, s_raw, final_idx, assign, st, tm);
     if (e != hipSuccess) return e;
     return bf ? merge_typed<bf16_t>(p, hidden, hsb, hsr, s_hat, text_len, final_idx, kept, p.k, out_hidden, pos_out,
-                                    new_len, assign, wsum, final_idx, st, tm)
+                                    new_len, assign, wsum, final_idx, kv, st, tm)
               : merge_typed<float>(p, hidden, hsb, hsr, s_hat, text_len, final_idx, kept, p.k, out_hidden, pos_out,
-                                   new_len, assign, wsum, final_idx, st, tm);
+                                   new_len, assign, wsum, final_idx, kv, st, tm);
   }
   const int M = p.V - p.k;
   if (M > 0) {
@@ -208,9 +254,9 @@ hipError_t launch_merge(const asap_params& p, const void* hidden, int64_t hsb, i
     if (e != hipSuccess) return e;
   }
   return bf ? merge_typed<bf16_t>(p, hidden, hsb, hsr, s_hat, text_len, kept, pruned, M, out_hidden, pos_out, new_len,
-                                  assign, wsum, final_idx, st, tm)
+                                  assign, wsum, final_idx, kv, st, tm)
             : merge_typed<float>(p, hidden, hsb, hsr, s_hat, text_len, kept, pruned, M, out_hidden, pos_out, new_len,
-                                 assign, wsum, final_idx, st, tm);
+                                 assign, wsum, final_idx, kv, st, tm);
 }
 
 }  // namespace asap

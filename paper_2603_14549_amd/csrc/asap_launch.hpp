@@ -28,7 +28,7 @@ struct ScoreWorkspace {
   size_t off_qsplit; // bf16   [B,Hkv,4,d]       their sums per kv head, split into four bf16 pieces per component
   size_t off_s64;    // double [B,V]             raw attention mass before rounding
   int mm_n;          // (min, max) pairs of s per image: one per key tile, or one (head_splits > 1)
-  size_t off_mm;     // double [B,mm_n,2]        those pairs
+  size_t off_mm;     // double [B,mm_n,2]        those pairs (in the place of qpart)
   size_t off_pstat;  // float  [B,H,splits,2,NR] per-split (max, sum) of every text row, NR = 64 row_pairs
   size_t off_upart;  // float  [B,H,row_pairs,V] column sums of normalised weights per head and row pair
                      //        (one_sweep: per group of kv heads and row block, those an image has one after the other)

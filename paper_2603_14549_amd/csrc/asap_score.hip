@@ -1663,25 +1663,37 @@ ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
   }
   size_t upart_rows = (size_t)p.H * w.row_pairs;
   const size_t mm_bytes = sizeof(double) * 2 * p.B * w.mm_n;
+  const size_t spart_bytes = w.head_splits > 1 ? align256(sizeof(double) * (size_t)w.head_splits * p.B * p.V) : 0;
   size_t off = 0;
-  w.off_qpart = off;  off = align256(off + sizeof(double) * p.B * p.H * w.q_chunks * p.d);
-  w.off_mm = off;     off = align256(off + std::max(sizeof(double) * p.B * p.Hkv * p.d, mm_bytes));
+  // the (min, max) pairs lie where the partial sums of the queries were: those have been read (k_qsplit)
+  // before the masses are formed
+  w.off_qpart = w.off_mm = off;
+  const size_t qpart_bytes = align256(sizeof(double) * p.B * p.H * w.q_chunks * p.d);
+  off = align256(off + std::max(qpart_bytes + sizeof(double) * p.B * p.Hkv * p.d, mm_bytes));
   w.off_qsplit = off; off = align256(off + sizeof(uint16_t) * p.B * p.Hkv * 4 * p.d);
   w.off_s64 = off;    off = align256(off + sizeof(double) * p.B * p.V);
   off = align256(off + sizeof(double) * 2 * p.B);
   w.off_pstat = off;  off = align256(off + sizeof(float) * (size_t)p.B * p.H * splits * 2 * NR);
+  // Many query heads on few kv heads leave more partial column sums than the two sweeps do (16 rows each
+  // instead of 64): where the scratch has a limit that these do not fit, the two sweeps run.
   if (w.one_sweep) {
-    w.row_pairs = (G * w.t_eff + 16 * w.one_sweep - 1) / (16 * w.one_sweep);
-    w.heads_per_wg = rows_heads_per_wg(p, w.row_pairs, w.one_sweep);
-    upart_rows = std::max(upart_rows, (size_t)((p.Hkv + w.heads_per_wg - 1) / w.heads_per_wg) * w.row_pairs);
+    const int blocks = (G * w.t_eff + 16 * w.one_sweep - 1) / (16 * w.one_sweep);
+    const int heads = rows_heads_per_wg(p, blocks, w.one_sweep);
+    const size_t rows_one = std::max(upart_rows, (size_t)((p.Hkv + heads - 1) / heads) * blocks);
+    if (align256(off + sizeof(float) * p.B * rows_one * p.V) + spart_bytes > budget) {
+      w.one_sweep = 0;
+    } else {
+      w.row_pairs = blocks;
+      w.heads_per_wg = heads;
+      upart_rows = rows_one;
+    }
   }
   w.off_upart = off;  off = align256(off + sizeof(float) * p.B * upart_rows * p.V);
   w.off_spart = off;
-  if (w.head_splits > 1) off = align256(off + sizeof(double) * (size_t)w.head_splits * p.B * p.V);
+  off += spart_bytes;
   w.off_zlog = off;
   if (w.store_logits && align256(off + zlog_bytes) > budget) w.store_logits = 0;
   if (w.ride || w.store_logits) off = align256(off + zlog_bytes);
-  if (w.one_sweep) w.store_logits = 0;
   w.total = off;
   return w;
 }

@@ -91,6 +91,35 @@ def test_static_scratch_too_small_for_the_stored_logits_of_f32_keys():
     ctx.close()
 
 
+def test_static_scratch_too_small_for_the_partial_sums_of_one_sweep():
+    """Sixteen query heads on one kv head: the one sweep over the keys leaves a row of partial column sums for
+    every 16 text rows, more than the 16 MiB array holds, where the two sweeps leave one for 64.  The static
+    call takes the two sweeps.  Mass and salience agree bit for bit.  A score is off by at most
+    rel = 2 (d + 1) u max sum |q k| / sqrt(d) + 2^-21 + 20 u, u = 2^-24 (logits, exponential, sums) in either
+    form, so the two differ by at most twice that."""
+    ctx = binding.Context(0)
+    B, H, d, V, T = 8, 16, 64, 4096, 128
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q = torch.randn(B, H, V + T, d, generator=g, device="cuda").bfloat16()
+    k = torch.randn(B, 1, V, d, generator=g, device="cuda").bfloat16()
+    text_len = torch.full((B,), T, dtype=torch.int32, device="cuda")
+    p = binding.make_params(B, H, 1, d, 64, 0, V, T, 512, "bf16", "bf16", "bf16")
+    assert binding.asap_workspace_bytes(p) > 16 << 20
+    outs = [[torch.full((B, V), float("nan"), device="cuda") for _ in range(3)] for _ in range(2)]
+    ctx.asap_score_static(p, q[:, :, :V], q[:, :, V:], k, text_len, None, *outs[0])
+    ws = torch.empty(binding.asap_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    ctx.asap_score(p, q[:, :, :V], q[:, :, V:], k, text_len, None, *outs[1], ws)
+    torch.cuda.synchronize()
+    for a, b in zip(outs[0][:2], outs[1][:2]):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    u = 2.0 ** -24
+    zmax = float((q[:, :, V:].float().abs().reshape(B, H * T, d).cpu() @ k[:, 0].float().abs().cpu().transpose(1, 2)).max())
+    rel = 2 * (d + 1) * u * zmax / d ** 0.5 + 2.0 ** -21 + 20 * u
+    a, b = outs[0][2].double(), outs[1][2].double()
+    assert bool(((a - b).abs() <= 2 * rel * b + 1e-37).all())
+    ctx.close()
+
+
 def test_static_scratch_refuses_what_does_not_fit():
     ctx = binding.Context(0)
     cfg = synth.CONFIGS["S0"]

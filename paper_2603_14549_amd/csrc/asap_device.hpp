@@ -8,6 +8,8 @@
 
 namespace asap {
 
+constexpr int NUM_XCD = 8;
+
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 

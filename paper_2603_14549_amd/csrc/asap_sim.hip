@@ -43,7 +43,6 @@ namespace asap {
 
 constexpr int SIM_BM = 128;
 constexpr int SIM_ROWB = 128;      // bytes of a row held in LDS per step
-constexpr int NUM_XCD = 8;
 // LDS ring slots for the source rows (NA) and the destination rows (NB) by tile width: as deep as
 // 160 KiB allow, NA > NB >= 2.  Narrow tiles belong to launches with few workgroups (small batches, the
 // search inside the kept set), whose steps last as long as a load takes to arrive divided by how many

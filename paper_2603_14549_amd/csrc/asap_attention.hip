@@ -147,20 +147,6 @@ enum { ATT_PLAIN = 0,     // every key precedes every query: no mask
        ATT_AHEAD = 1,     // every key follows every query and all queries are image rows: the key's discount
        ATT_GENERAL = 2 }; // anything else: decided per element
 
-// wait until only the loads of the newest `tiles_ahead` key tiles (cnt instructions each) are outstanding
-__device__ __forceinline__ void att_wait_tiles(int outstanding) {
-  switch (outstanding) {
-    case 0: wait_vmem_but<0>(); break;
-    case 1: wait_vmem_but<1>(); break;
-    case 2: wait_vmem_but<2>(); break;
-    case 3: wait_vmem_but<3>(); break;
-    case 4: wait_vmem_but<4>(); break;
-    case 5: wait_vmem_but<5>(); break;
-    case 6: wait_vmem_but<6>(); break;
-    default: wait_vmem_but<0>(); break;
-  }
-}
-
 // CH = 16-byte chunks of a row per lane half (row bytes = 32 * CH); PD = key tiles requested ahead
 template <typename T, int CH, int PD>
 __global__ __launch_bounds__(64 * ATT_NW) void k_attention(const T* __restrict__ q, Strides3 sq,
@@ -242,12 +228,13 @@ __global__ __launch_bounds__(64 * ATT_NW) void k_attention(const T* __restrict__
 #pragma unroll
     for (int u = 0; u < (TP + NW - 1) / NW; ++u) {
       const int pc = wave + NW * u;
-      if (pc < KLD) {
+      // (the first comparison of each pair is known when compiling and mostly decides)
+      if (NW * u < KLD && (NW * (u + 1) <= KLD || pc < KLD)) {
         const int off = pc * 1024 + 16 * lane, row = off / RB, slot = (off % RB) >> 4;
         const int piece = slot ^ att_kswz(row, RB);
         const uint32_t voff = (uint32_t)((int64_t)min(j0 + row, N - 1) * krow_bytes) + piece * 16;
         load_to_lds16(kg, voff, st + pc * 1024);
-      } else if (pc < KLD + VLD) {
+      } else if (NW * u < KLD + VLD && (NW * (u + 1) <= KLD + VLD || pc < KLD + VLD)) {
         const int pv = pc - KLD;
         if constexpr (TR) {
           // row-major values: 4 key rows of 256 bytes per instruction, piece p of row r in slot p ^ 4 (r & 3)
@@ -266,7 +253,15 @@ __global__ __launch_bounds__(64 * ATT_NW) void k_attention(const T* __restrict__
       }
     }
   };
-  const int my_loads = TP / NW + (wave < TP % NW ? 1 : 0);     // load instructions of this wave per tile
+  // (A constant for either kind of wave: the number as a run-time switch, and the tests of which piece a load
+  // instruction is for, were a dozen scalar branches per tile, 1.80 ms against 1.78.)
+  // wait until only the loads of the newest `tiles` tiles are outstanding: the first TP % NW waves issue one more
+  // per tile than the others
+  auto wait_tiles = [&](auto tiles) {
+    constexpr int few = decltype(tiles)::value * (TP / NW), most = decltype(tiles)::value * ((TP + NW - 1) / NW);
+    if (TP % NW != 0 && wave < TP % NW) wait_vmem_but<most>();
+    else wait_vmem_but<few>();
+  };
 
   f32x16_t o[DT];
 #pragma unroll
@@ -401,7 +396,7 @@ __global__ __launch_bounds__(64 * ATT_NW) void k_attention(const T* __restrict__
   for (int c = 0; c < CH; ++c) asm volatile("" ::"v"(qa[c].x), "v"(qa[c].y), "v"(qa[c].z), "v"(qa[c].w));
   static_assert(NS % 2 == 0, "the two score buffers swap roles every tile, the ring turns every NS tiles");
   static_for<PD + 1>([&](auto t_c) { issue_tile(t_c, decltype(t_c)::value); });
-  att_wait_tiles((PD - 1) * my_loads);
+  wait_tiles(std::integral_constant<int, PD - 1>{});
   barrier_keep_loads();
   // The loop runs over whole turns of the ring, so that a tile's slot is a compile-time constant, and
   // the raw scores alternate between two register sets instead of being copied.
@@ -417,7 +412,7 @@ __global__ __launch_bounds__(64 * ATT_NW) void k_attention(const T* __restrict__
           if constexpr (U % 2 == 0) step(u_c, t, s_even, s_odd);
           else step(u_c, t, s_odd, s_even);
         }
-        att_wait_tiles((PD - 1) * my_loads);
+        wait_tiles(std::integral_constant<int, PD - 1>{});
         barrier_keep_loads();
       }
     });

@@ -167,7 +167,9 @@ asap_status asap_score_from_hidden(asap_ctx* ctx, const asap_params* p,
  * hipMalloc.  Arguments, results and checks are those of asap_score without the workspace (with f32
  * keys asap_score keeps the logits of the text rows in its workspace and this call does so only
  * where the array can hold them; otherwise it forms them a second time, and the scores of the two
- * calls then differ by rounding, within the tolerance of either); the scratch is an array of ASAP_STATIC_SCRATCH_BYTES bytes that is part of the library's code object
+ * calls then differ by rounding, within the tolerance of either; the same holds for the partial column
+ * sums of bf16 keys with many query heads on few kv heads); the scratch is an array of
+ * ASAP_STATIC_SCRATCH_BYTES bytes that is part of the library's code object
  * (every GPU the library runs on holds its own copy until the process ends; asap_create looks up
  * its address on the context's device).  The call allocates and frees nothing.
  * ASAP_EWORKSPACE if the parameters need more scratch than the array holds (the message names both

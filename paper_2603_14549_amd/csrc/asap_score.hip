@@ -896,12 +896,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_colsum(AttnArgs a) {
 //   workgroups, 8.6 TB/s out of L2); 4 x 28 heads (4 kv heads) x 4096 keys, 48 rows: 49 -> 33 us; 1 x 16
 //   heads x 576 keys, 32 rows: 12 -> 8 us.
 //   Key tiles go to LDS by direct loads (whole rows, no registers), a ring of its own per wave.
-// Exponents: a lane's baseline for a row is its own first logit of that row, known before any other: the
-// term 2^(z - baseline) is then final when the logit is, whatever the other lanes and waves find, and
-// baselines meet once at the end, where the row's denominator and a factor per lane and row
-// (2^(baseline - M) / denominator) come out of one exchange through LDS.  fp32 leaves room for logits
-// 2^100 times the baseline's; should a lane's sum show that one was larger (or not finite), the wave looks
-// for the largest logits first and sweeps its keys again with those as baselines.
+// Exponents: the logits stay in the registers until the row's largest one is known to all waves (one exchange
+// through LDS), so every term is 2^(z - max) as in the two sweeps, whatever the spread of the logits; the terms
+// then take the logits' registers until a second exchange gives the denominator.  (A lane's own first logit as
+// the baseline of its terms saves the first exchange, but its correction underflows where logits lie 2^126 apart
+// and the smaller one has the larger discount, and the rounding grows with the distance from that baseline.)
+// The next head's first tiles are on their way during both exchanges.
 // Matrix tiles are 16 x 16 (queries x keys), 32 components of the contraction each: lane l supplies row /
 // key l % 16, components 8 (l / 16) .. + 7, and owns key l % 16 of a group of 16 and the rows 4 (l / 16) + v of
 // one: 4 rows per row group to keep statistics for and to exchange over 16 lanes.  (With 32 x 32 tiles, 16
@@ -958,7 +958,7 @@ __device__ __forceinline__ RowUnit find_row_unit(const AttnArgs& a, int B, int g
 constexpr int rows_slots(int rg, int tpw) { return rg * tpw <= 6 ? 1 : 2; }
 template <int NG, int RG, int TPW> constexpr size_t rows_lds_bytes() {
   return (size_t)rows_slots(RG, TPW) * ROWS_NW * 32 * NG * 32 + (size_t)16 * RG * (NG * 32 + 16) +
-         sizeof(float) * (2 * ROWS_NW * 16 * RG + 2 * 16 * RG + TPW * ROWS_NW * 32);
+         sizeof(float) * (2 * ROWS_NW * 16 * RG + 16 * RG + TPW * ROWS_NW * 32);
 }
 
 template <int NG, int RG, int TPW>
@@ -972,9 +972,8 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
   char* qlds = lds + NS * ROWS_NW * KTILE;
   float* st_m = reinterpret_cast<float*>(qlds + RB * QROW);                 // [8][RB]
   float* st_s = st_m + ROWS_NW * RB;                                         // [8][RB]
-  float* fin_o = st_s + ROWS_NW * RB;                                        // [RB]  -M (log2 units)
-  float* fin_i = fin_o + RB;                                                 // [RB]  1 / denominator
-  float* lam = fin_i + RB;                                                   // [256 TPW]  discounts of the keys
+  float* fin_l = st_s + ROWS_NW * RB;                                        // [RB]  rest of the row (log2 units)
+  float* lam = fin_l + RB;                                                   // [256 TPW]  discounts of the keys
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, q4 = lane >> 4;
@@ -1038,9 +1037,15 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
   const char* qsrc = reinterpret_cast<const char*>(static_cast<const bf16_t*>(a.qt) + b * a.sq.b +
                                                    (q_row ? qr / nrows : 0) * a.sq.h +
                                                    (int64_t)(row0 + (q_row ? qr % nrows : 0)) * a.sq.r) + qpc * 16;
+  // thread tid < RB also brings the rest of row tid (lse_extra, in log2 units; nothing: 2^-inf)
+  const int lr = rb * RB + tid;
+  const bool l_row = a.lse_extra != nullptr && tid < RB && lr < live;
+  const float* lsrc = a.lse_extra + (l_row ? ((int64_t)b * a.H + lr / nrows) * a.Tmax + row0 + lr % nrows : 0);
   uint4 qx;
+  float lx;
   auto load_q = [&](int g_) {
     qx = q_row ? ldg16(qsrc + (int64_t)g_ * G * a.sq.h * 2) : make_uint4(0, 0, 0, 0);
+    lx = l_row ? lsrc[(int64_t)g_ * G * a.Tmax] * 1.4426950408889634f : -INFINITY;
   };
   start(g);
   load_q(g);
@@ -1066,11 +1071,45 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
   float u[TPW][2];                             // column sums of this lane's keys over its rows and the heads
 #pragma unroll
   for (int i = 0; i < TPW; ++i) u[i][0] = u[i][1] = 0.0f;
+  // Exchange of a row value between the waves: wave w leaves its 4 RG values per 16 lanes in st[w][row], and lane n
+  // picks up those of 2 RG waves of row `mine`, so that a row's eight values lie in 4 / RG neighbouring lanes.
+  constexpr int LPW = 4 / RG, PICK = ROWS_NW / LPW;
+  const int mine = 16 * (n / LPW / 4) + 4 * q4 + (n / LPW) % 4;
+  auto leave = [&](float* st, const float (&x)[RG][4]) {
+    const int at = hidden(wave * RB + 4 * q4);
+    if (n == 0) {
+#pragma unroll
+      for (int r = 0; r < RG; ++r)
+        *reinterpret_cast<float4*>(st + at + r * 16) = make_float4(x[r][0], x[r][1], x[r][2], x[r][3]);
+    }
+  };
+  auto pick = [&](const float* st, float (&x)[PICK]) {
+    const int at = hidden((n % LPW) * PICK * RB + mine);
+#pragma unroll
+    for (int w = 0; w < PICK; ++w) x[w] = st[at + w * RB];
+  };
+  // f over the lanes of a row (one after the other: a step alone waits for itself)
+  auto over_row = [](float x, auto f) {
+    x = f(x, dpp_f32<0xB1>(x));                // quad_perm: the lane beside
+    if (LPW == 4) x = f(x, dpp_f32<0x4E>(x));  // ... and the pair beside
+    return x;
+  };
+  // the value of the lanes of row (r, v) in every lane of the 16 (row_newbcast)
+  auto spread = [&](float (&x)[RG][4], float y) {
+    static_for<4 * RG>([&](auto k) { x[decltype(k)::value / 4][decltype(k)::value % 4] = dpp_f32<0x150 + decltype(k)::value * LPW>(y); });
+  };
+  auto each = [](auto f) {
+#pragma unroll
+    for (int r = 0; r < RG; ++r)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) f(r, v);
+    __builtin_amdgcn_sched_barrier(0);
+  };
 
 #pragma unroll 1
   for (;; ++g) {
     f32x4_t e[TPW][RG][2];
-    float b2[RG][4], s[RG][4];
+    float m[RG][4];
     // logits of the tile in ring slot `slot`
     auto logits = [&](f32x4_t (&z)[RG][2], int slot) {
       const int ko = hidden(k_off);
@@ -1102,76 +1141,26 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
     auto ring_read = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };    // a slot may be filled again
 
     if (q_here) *reinterpret_cast<uint4*>(qlds + qm * QROW + qpc * 16) = qx;
+    if (tid < RB) fin_l[hidden(tid)] = lx;
     barrier_lds();
-    bool based = false;
-#pragma unroll 1
-    for (;;) {
-      if (!based) {
-#pragma unroll
-        for (int r = 0; r < RG; ++r)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) b2[r][v] = ATT_NEG;
-      }
-#pragma unroll
-      for (int r = 0; r < RG; ++r)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) s[r][v] = 0.0f;
-      static_for<TPW>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        if (active(i)) {
-          if (NS == 2 && i + 1 < TPW && active(i + 1)) wait_vmem_but<KLD>();
-          else wait_all_vmem();
-          logits(e[i], NS == 2 ? i & 1 : 0);
-          if (i + NS < TPW && active(i + NS)) {
-            ring_read();
-            issue(g, i + NS, NS == 2 ? i & 1 : 0);
-          }
-          if (i == 0 && !based) {
-#pragma unroll
-            for (int r = 0; r < RG; ++r)
-#pragma unroll
-              for (int v = 0; v < 4; ++v) b2[r][v] = e[0][r][0][v] * c2;
-          }
-          const int lt = hidden(wave * 32 + n);
-          const float l[2] = {lam[lt + ROWS_NW * 32 * i], lam[lt + ROWS_NW * 32 * i + 16]};
-#pragma unroll
-          for (int r = 0; r < RG; ++r)
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-              for (int v = 0; v < 4; ++v) {
-                e[i][r][x][v] = fast_exp2(fmaf(e[i][r][x][v], c2, -b2[r][v]));
-                s[r][v] = fmaf(l[x], e[i][r][x][v], s[r][v]);
-              }
+    each([&](int r, int v) { m[r][v] = ATT_NEG; });
+    static_for<TPW>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      if (active(i)) {
+        if (NS == 2 && i + 1 < TPW && active(i + 1)) wait_vmem_but<KLD>();
+        else wait_all_vmem();
+        logits(e[i], NS == 2 ? i & 1 : 0);
+        if (i + NS < TPW && active(i + NS)) {
+          ring_read();
+          issue(g, i + NS, NS == 2 ? i & 1 : 0);
         }
-      });
-      bool far = false;
-#pragma unroll
-      for (int r = 0; r < RG; ++r)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) far |= !(s[r][v] < 0x1p100f);
-      if (based || !__any(far)) break;
-      // see above: the largest logits, tile by tile, and once more
-      based = true;
-#pragma unroll
-      for (int r = 0; r < RG; ++r)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) b2[r][v] = ATT_NEG;
-#pragma unroll 1
-      for (int i = 0; active(i); ++i) {
-        ring_read();
-        issue(g, i, 0);
-        wait_all_vmem();
-        f32x4_t z[RG][2];
-        logits(z, 0);
+        // (keys past the end repeat the last one: no larger logit)
 #pragma unroll
         for (int r = 0; r < RG; ++r)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) b2[r][v] = fmaxf(b2[r][v], fmaxf(z[r][0][v], z[r][1][v]) * c2);
+          for (int v = 0; v < 4; ++v) m[r][v] = fmaxf(m[r][v], fmaxf(e[i][r][0][v], e[i][r][1][v]));
       }
-      ring_read();
-      start(g);
-    }
+    });
     const bool last = g + 1 >= g_end;
     if (!last) {
       ring_read();
@@ -1179,70 +1168,56 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
       load_q(g + 1);
     }
 
-    // the 16 lanes of a row and then the waves agree on a baseline and on the denominator of every row
+    // largest logit of every row, over the 16 lanes and then the waves; -M in log2 units, with the rest of the row
+    // (lse_extra, already in log2 units) in the comparison
+    each([&](int r, int v) { m[r][v] = fmaxf(m[r][v], dpp_f32<0x128>(m[r][v])); });     // row_ror:8, 4, 2, 1
+    each([&](int r, int v) { m[r][v] = fmaxf(m[r][v], dpp_f32<0x124>(m[r][v])); });
+    each([&](int r, int v) { m[r][v] = fmaxf(m[r][v], dpp_f32<0x122>(m[r][v])); });
+    each([&](int r, int v) { m[r][v] = fmaxf(m[r][v], dpp_f32<0x121>(m[r][v])); });
+    leave(st_m, m);
+    barrier_lds();
+    float rest;                                // the rest of the row in units of 2^M
     {
-      float m[RG][4], x[RG][4];                // step by step over all rows: a step alone waits for itself
+      float x[PICK];
+      pick(st_m, x);
+      const float l = fin_l[hidden(mine)];
 #pragma unroll
-      for (int r = 0; r < RG; ++r)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) m[r][v] = b2[r][v];
-      auto each = [&](auto f) {
+      for (int w = 1; w < PICK; ++w) x[0] = fmaxf(x[0], x[w]);
+      const float big = fmaxf(over_row(x[0], [](float p, float q) { return fmaxf(p, q); }) * c2, l);
+      rest = fast_exp2(l - big);
+      spread(m, -big);
+    }
+    float s[RG][4];
+    each([&](int r, int v) { s[r][v] = 0.0f; });
+    static_for<TPW>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      if (active(i)) {
+        const int lt = hidden(wave * 32 + n);
+        const float l[2] = {lam[lt + ROWS_NW * 32 * i], lam[lt + ROWS_NW * 32 * i + 16]};
 #pragma unroll
         for (int r = 0; r < RG; ++r)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) f(m[r][v], x[r][v], b2[r][v], s[r][v]);
-        __builtin_amdgcn_sched_barrier(0);
-      };
-      each([](float& m_, float&, float, float) { m_ = fmaxf(m_, dpp_f32<0x128>(m_)); });     // row_ror:8, 4, 2, 1
-      each([](float& m_, float&, float, float) { m_ = fmaxf(m_, dpp_f32<0x124>(m_)); });
-      each([](float& m_, float&, float, float) { m_ = fmaxf(m_, dpp_f32<0x122>(m_)); });
-      each([](float& m_, float&, float, float) { m_ = fmaxf(m_, dpp_f32<0x121>(m_)); });
-      each([](float& m_, float& x_, float b_, float s_) { x_ = s_ * fast_exp2(b_ - m_); });
-      each([](float&, float& x_, float, float) { x_ += dpp_f32<0x128>(x_); });
-      each([](float&, float& x_, float, float) { x_ += dpp_f32<0x124>(x_); });
-      each([](float&, float& x_, float, float) { x_ += dpp_f32<0x122>(x_); });
-      each([](float&, float& x_, float, float) { x_ += dpp_f32<0x121>(x_); });
-      const int at = hidden(wave * RB + 4 * q4);
-      if (n == 0) {
+          for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int r = 0; r < RG; ++r) {
-          *reinterpret_cast<float4*>(st_m + at + r * 16) = make_float4(m[r][0], m[r][1], m[r][2], m[r][3]);
-          *reinterpret_cast<float4*>(st_s + at + r * 16) = make_float4(x[r][0], x[r][1], x[r][2], x[r][3]);
-        }
+            for (int v = 0; v < 4; ++v) {
+              e[i][r][x][v] = fast_exp2(fmaf(e[i][r][x][v], c2, m[r][v]));
+              s[r][v] = fmaf(l[x], e[i][r][x][v], s[r][v]);
+            }
       }
-    }
+    });
+    each([&](int r, int v) { s[r][v] += dpp_f32<0x128>(s[r][v]); });
+    each([&](int r, int v) { s[r][v] += dpp_f32<0x124>(s[r][v]); });
+    each([&](int r, int v) { s[r][v] += dpp_f32<0x122>(s[r][v]); });
+    each([&](int r, int v) { s[r][v] += dpp_f32<0x121>(s[r][v]); });
+    leave(st_s, s);
     barrier_lds();
-    if (tid < RB) {
-      float o = -INFINITY, iv = 0.0f;          // rows past the end add nothing
-      const int tl = hidden(tid), r = rb * RB + tl;
-      if (r < live) {
-        float mw[ROWS_NW], m = st_m[tl], x = 0.0f;
+    {
+      float x[PICK];
+      pick(st_s, x);
 #pragma unroll
-        for (int w = 0; w < ROWS_NW; ++w) mw[w] = st_m[w * RB + tl];
-#pragma unroll
-        for (int w = 1; w < ROWS_NW; ++w) m = fmaxf(m, mw[w]);
-#pragma unroll
-        for (int w = 0; w < ROWS_NW; ++w) x = fmaf(st_s[w * RB + tl], fast_exp2(mw[w] - m), x);
-        if (a.lse_extra != nullptr) {
-          const float l = a.lse_extra[((int64_t)b * a.H + g * G + r / nrows) * a.Tmax + row0 + r % nrows];
-          merge_stat(m, x, l * 1.4426950408889634f, 1.0f, 1.0f);
-        }
-        o = -m;
-        iv = 1.0f / x;
-      }
-      fin_o[tl] = o;
-      fin_i[tl] = iv;
-    }
-    barrier_lds();
-    const int row_lo = hidden(4 * q4);
-#pragma unroll
-    for (int r = 0; r < RG; ++r) {
-      const float4 o = *reinterpret_cast<const float4*>(fin_o + row_lo + r * 16);
-      const float4 iv = *reinterpret_cast<const float4*>(fin_i + row_lo + r * 16);
-      b2[r][0] = fast_exp2(b2[r][0] + o.x) * iv.x;
-      b2[r][1] = fast_exp2(b2[r][1] + o.y) * iv.y;
-      b2[r][2] = fast_exp2(b2[r][2] + o.z) * iv.z;
-      b2[r][3] = fast_exp2(b2[r][3] + o.w) * iv.w;
+      for (int w = 1; w < PICK; ++w) x[0] += x[w];
+      const float all = over_row(x[0], [](float p, float q) { return p + q; }) + rest;
+      spread(s, rb * RB + hidden(mine) < live ? 1.0f / all : 0.0f);       // rows past the end add nothing
     }
 #pragma unroll
     for (int i = 0; i < TPW; ++i)
@@ -1252,7 +1227,7 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
 #pragma unroll
           for (int r = 0; r < RG; ++r)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) u[i][x] = fmaf(e[i][r][x][v], b2[r][v], u[i][x]);
+            for (int v = 0; v < 4; ++v) u[i][x] = fmaf(e[i][r][x][v], s[r][v], u[i][x]);
       }
     if (last) break;
   }

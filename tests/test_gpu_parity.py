@@ -1001,3 +1001,79 @@ def test_text_rows_in_one_sweep_over_the_keys(ctx, B, H, Hkv, d, V, Tmax, text_l
         err = (score[b].double().cpu() - ref).abs()
         bound = ref * (rel + 2 * sh / lam) + 1e-37
         assert bool((err <= bound).all()), (b, float((err / bound).max()))
+
+
+def _score_and_bound(q_txt, k_vis, s_raw, length, lam_max, eps, mask_on):
+    """The score of _score_reference and what a result may differ from it by, key by key.  A logit is a sum of d
+    exact products in fp32, off by at most (d - 1) u sum |q k| / sqrt(d), u = 2^-24, and by two roundings of the
+    scaled value; a weight by twice that, the exponential (2^-22, twice) and 20 roundings of the sums.  A discount is
+    taken from the masses before their rounding to f32, here after it: a salience is then off by
+    sh = 4 u max |s| / (max s - min s) and a discount by sh / lambda, in the weight itself and, with every key's own
+    weight in the row, in the denominator."""
+    H, d = q_txt.shape[0], q_txt.shape[-1]
+    u = 2.0 ** -24
+    _, lam, zmax = _score_reference(q_txt, k_vis, s_raw, length, lam_max, eps, mask_on)
+    q, k = q_txt[:, :length].double(), k_vis.double().repeat_interleave(H // k_vis.shape[0], 0)
+    a = torch.softmax(q @ k.transpose(1, 2) / math.sqrt(d) + torch.log(lam), -1)
+    rel = 2 * (d + 1) * u * zmax + 2.0 ** -21 + 20 * u
+    s = s_raw.double()
+    off = 4 * u * s.abs().max() / (s.max() - s.min()) / lam if mask_on else torch.zeros_like(lam)
+    each = a * (rel + 2 * off + 2 * (a * off).sum(-1, keepdim=True))
+    return a.mean((0, 1)), each.mean((0, 1)) + 1e-37
+
+
+@pytest.mark.parametrize("mask_on", [True, False])
+@pytest.mark.parametrize("size", [4.0, 10.0, 15.0, 18.0, 22.0, 40.0])
+@pytest.mark.parametrize("B,H,Hkv,d,V,Tmax,text_lo", [
+    (1, 1, 1, 128, 2304, 32, 32),                  # one row group, nine tiles per wave
+    (64, 7, 7, 64, 300, 64, 1),                    # two row groups, heads of an image in workgroups of 2, 2, 2, 1
+    (128, 31, 31, 64, 300, 64, 64),                # 16 and 15
+    (32, 15, 15, 64, 1300, 64, 5),                 # 4, 4, 4, 3
+])
+def test_text_rows_with_widely_spread_logits(ctx, B, H, Hkv, d, V, Tmax, text_lo, size, mask_on):
+    """Logits with a standard deviation of about 0.8 size nats: keys that share a lane, or waves that share a row, lie
+    2^100 and more apart, and their terms count all the same where the discount of the largest is small."""
+    g = torch.Generator(device="cuda").manual_seed(V + B)
+    k_all = torch.randn(B, Hkv, V, d, generator=g, device="cuda").bfloat16()
+    q_vis = torch.randn(B, H, V, d, generator=g, device="cuda").bfloat16()
+    q_txt = (size * torch.randn(B, H, Tmax, d, generator=g, device="cuda")).bfloat16()
+    text_len = torch.randint(text_lo, Tmax + 1, (B,), generator=g, device="cuda").to(torch.int32)
+    p = binding.make_params(B, H, Hkv, d, 64, 0, V, Tmax, max(1, V // 8), "bf16", "bf16", "bf16",
+                            mask_mode=binding.ASAP_MASK_KEYBIAS if mask_on else binding.ASAP_MASK_OFF)
+    s_raw, s_hat, score = (torch.empty(B, V, device="cuda") for _ in range(3))
+    ws = torch.empty(binding.asap_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    ctx.asap_score(p, q_vis, q_txt, k_all, text_len, None, s_raw, s_hat, score, ws)
+    for b in sorted({0, B - 1}):
+        ref, bound = _score_and_bound(q_txt[b].cpu(), k_all[b].cpu(), s_raw[b].cpu(), int(text_len[b]), p.lambda_max,
+                                      p.eps, mask_on)
+        err = (score[b].double().cpu() - ref).abs()
+        assert bool((err <= bound).all()), (b, float((err / bound).max()))
+
+
+@pytest.mark.parametrize("eps", [1e-6, 1e-12])
+def test_a_row_whose_largest_logit_has_the_smallest_discount(ctx, eps):
+    """Log2 logits 0, -130 and -32 at keys 0, 32 and 288, about -400 elsewhere; the discount is 0.5 except for key 0,
+    where it is eps.  Key 288 carries the row (nearly all of it at 1e-12), although key 32, the first one of
+    the lane that holds it, lies 130 below key 0."""
+    d, V, T = 128, 2304, 32
+    per = math.log2(math.e) / math.sqrt(d)
+    k = torch.zeros(1, 1, V, d)
+    k[0, 0, :, 0] = -400 / per
+    k[0, 0, 0, 0], k[0, 0, 32, 0], k[0, 0, 288, 0] = 0.0, -130 / per, -32 / per
+    k[0, 0, 1:, 1] = 1.0
+    q_vis, q_txt = torch.zeros(1, 1, V, d), torch.zeros(1, 1, T, d)
+    q_vis[..., 1], q_txt[..., 0] = 1.0, 1.0
+    k, q_vis, q_txt = (t.bfloat16().cuda() for t in (k, q_vis, q_txt))
+    p = binding.make_params(1, 1, 1, d, 64, 0, V, T, 8, "bf16", "bf16", "bf16", lambda_max=0.5, eps=eps)
+    s_raw, s_hat, score = (torch.empty(1, V, device="cuda") for _ in range(3))
+    ws = torch.empty(binding.asap_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    ctx.asap_score(p, q_vis, q_txt, k, torch.full((1,), T, dtype=torch.int32, device="cuda"), None, s_raw, s_hat, score, ws)
+    ref, _, zmax = _score_reference(q_txt[0].cpu(), k[0].cpu(), s_raw[0].cpu(), T, p.lambda_max, p.eps, True)
+    # one exact product per logit, rounded once where it is scaled: 2 u |z| (zmax nats) in numerator and
+    # denominator, the exponential and 20 roundings of the sums as above, and the f32 of s_hat
+    rel = 4 * 2.0 ** -24 * zmax + 2.0 ** -21 + 24 * 2.0 ** -24
+    got = score[0].double().cpu()
+    for j in (0, 288):
+        assert abs(float(got[j] - ref[j])) <= rel * float(ref[j]), (j, float(got[j]), float(ref[j]))
+    # terms below 2^-126 of the largest are lost: 0.5 * 2^-126 over a denominator of at least eps
+    assert bool(((got - ref).abs() <= rel * ref + 2.0 ** -127 / eps).all())

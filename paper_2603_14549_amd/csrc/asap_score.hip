@@ -553,6 +553,19 @@ template <int CTRL> __device__ __forceinline__ float dpp_f32(float x) {
   return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xF, 0xF, true));
 }
 
+// Sums of c[0..3] over the four groups of 16 lanes: group q gets that of c[q] (v_permlane32_swap exchanges the
+// upper half of the first operand with the lower half of the second, v_permlane16_swap the odd groups of
+// the first with the even groups of the second).
+__device__ __forceinline__ float sum_groups_of_16(const float (&c)[4]) {
+  auto swap32 = [](float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  };
+  const float lo = swap32(c[0], c[2]), hi = swap32(c[1], c[3]);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // online (max, sum) update of one row block from the 16 logits a lane holds
 __device__ __forceinline__ void stats_update(f32x16_t& acc, const float (&lam)[16], bool ragged, int tile, int hf, int V,
                                              float c2, float& m_run, float& s_run) {
@@ -1068,9 +1081,12 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
   }
   const int q_off = n * QROW + q4 * 16, k_off = n * KROW + ((q4 ^ kswz(n)) << 4);
 
-  float u[TPW][2];                             // column sums of this lane's keys over its rows and the heads
+  // Column sums over the heads, in fp64: entry t holds the sums 4 t + q4 of the 2 TPW (key n of half x of tile i has
+  // index 2 i + x), so that they take a quarter of the registers.
+  constexpr int NU = (2 * TPW + 3) / 4;
+  double u[NU];
 #pragma unroll
-  for (int i = 0; i < TPW; ++i) u[i][0] = u[i][1] = 0.0f;
+  for (int t = 0; t < NU; ++t) u[t] = 0.0;
   // Exchange of a row value between the waves: wave w leaves its 4 RG values per 16 lanes in st[w][row], and lane n
   // picks up those of 2 RG waves of row `mine`, so that a row's eight values lie in 4 / RG neighbouring lanes.
   constexpr int LPW = 4 / RG, PICK = ROWS_NW / LPW;
@@ -1219,30 +1235,31 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
       const float all = over_row(x[0], [](float p, float q) { return p + q; }) + rest;
       spread(s, rb * RB + hidden(mine) < live ? 1.0f / all : 0.0f);       // rows past the end add nothing
     }
+    // this head's column sums, first over a lane's 4 RG rows, then over the four groups of 16 lanes
 #pragma unroll
-    for (int i = 0; i < TPW; ++i)
-      if (active(i)) {
+    for (int t = 0; t < NU; ++t) {
+      if (active(2 * t)) {
+        float c[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+        for (int i = 2 * t; i < min(2 * t + 2, TPW); ++i)
+          if (i == 2 * t || active(i)) {
 #pragma unroll
-          for (int r = 0; r < RG; ++r)
+            for (int x = 0; x < 2; ++x)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) u[i][x] = fmaf(e[i][r][x][v], s[r][v], u[i][x]);
+              for (int r = 0; r < RG; ++r)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) c[2 * (i & 1) + x] = fmaf(e[i][r][x][v], s[r][v], c[2 * (i & 1) + x]);
+          }
+        u[t] += (double)sum_groups_of_16(c);
       }
+    }
     if (last) break;
   }
   float* out = a.upart + ((int64_t)b * groups * a.RP + (grp * nb + rb)) * a.V;
 #pragma unroll
-  for (int i = 0; i < TPW; ++i) {
-    if (active(i)) {
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        const int j = (wave + ROWS_NW * i) * 32 + 16 * x + n;
-        float r = u[i][x] + __shfl_xor(u[i][x], 16);
-        r += __shfl_xor(r, 32);
-        if (q4 == 0 && j < a.V) out[j] = r;
-      }
-    }
+  for (int t = 0; t < NU; ++t) {
+    const int j = (wave + ROWS_NW * (2 * t + (q4 >> 1))) * 32 + 16 * (q4 & 1) + n;
+    if (j < a.V) out[j] = (float)u[t];
   }
 }
 

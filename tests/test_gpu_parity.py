@@ -1077,3 +1077,19 @@ def test_a_row_whose_largest_logit_has_the_smallest_discount(ctx, eps):
         assert abs(float(got[j] - ref[j])) <= rel * float(ref[j]), (j, float(got[j]), float(ref[j]))
     # terms below 2^-126 of the largest are lost: 0.5 * 2^-126 over a denominator of at least eps
     assert bool(((got - ref).abs() <= rel * ref + 2.0 ** -127 / eps).all())
+
+
+@pytest.mark.parametrize("B,H,V", [(128, 31, 553), (128, 31, 491), (32, 15, 1783)])
+def test_head_sums_of_a_workgroup_in_64_bits(ctx, B, H, V):
+    """Equal logits and one text row: every weight is fl(1/V) and the score is the mean of H of them, 16 and 15 heads
+    (4, 4, 4 and 3) of which are added up by one workgroup.  With those sums in fp64 the score is off by the rounding of
+    1/V, of the two to four sums and of the result, 3 u in all (u = 2^-24); 16 terms added in fp32 are off by 4.7 u
+    at 553 tokens."""
+    d, T = 64, 64
+    k = torch.randn(B, H, V, d, generator=torch.Generator(device="cuda").manual_seed(V), device="cuda").bfloat16()
+    q_txt = torch.zeros(B, H, T, d, dtype=torch.bfloat16, device="cuda")
+    p = binding.make_params(B, H, H, d, 64, 0, V, T, 8, "bf16", "bf16", "bf16", mask_mode=binding.ASAP_MASK_OFF)
+    s_raw, s_hat, score = (torch.empty(B, V, device="cuda") for _ in range(3))
+    ws = torch.empty(binding.asap_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    ctx.asap_score(p, k, q_txt, k, torch.ones(B, dtype=torch.int32, device="cuda"), None, s_raw, s_hat, score, ws)
+    assert float((score.double() * V - 1.0).abs().max()) <= 3 * 2.0 ** -24

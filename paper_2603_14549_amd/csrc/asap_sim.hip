@@ -245,8 +245,11 @@ __device__ __forceinline__ void sim_tile_epilogue(f32x16_t (&acc)[2][NT], const 
 // The units are numbered image by image, source tile by source tile, the destination tiles of a slice
 // next to each other, and XCD x (= the workgroup ids with id % 8 == x) takes the x-th eighth of them:
 // every XCD has the same number to do whatever the batch (a whole image per XCD left three of the
-// eight idle at 5 images: the last-token stage of 5 x 2083 tokens took 158 us, now 125), and an image's kept panel is fetched by the one or
-// few XCDs that work on it.
+// eight idle at 5 images: the last-token stage of 5 x 2083 tokens took 158 us, now 125), and an image's
+// kept panel is fetched by the one or few XCDs that work on it.
+// `turn` is the number of the source tile, whichever XCD its units go to: the walk over the hidden dimension
+// starts from it, and all destination tiles of a source tile (and slice) must add up in the same order, so
+// that the similarities of equal kept rows are equal and the smallest slot wins.
 struct SimWork { int b, mt, pass, ks, turn; };
 __device__ __forceinline__ bool sim_work(int B, int mtiles, int ptiles, int ksplit, SimWork& w) {
   const int units = B * mtiles * ptiles * ksplit, per_xcd = (units + NUM_XCD - 1) / NUM_XCD;
@@ -257,7 +260,7 @@ __device__ __forceinline__ bool sim_work(int B, int mtiles, int ptiles, int kspl
   const int tile = u / (ptiles * ksplit);
   w.b = tile / mtiles;
   w.mt = tile % mtiles;
-  w.turn = slot / (ptiles * ksplit);           // the tile's position on its XCD
+  w.turn = tile;
   return true;
 }
 

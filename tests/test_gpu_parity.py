@@ -1093,3 +1093,36 @@ def test_head_sums_of_a_workgroup_in_64_bits(ctx, B, H, V):
     ws = torch.empty(binding.asap_workspace_bytes(p), dtype=torch.uint8, device="cuda")
     ctx.asap_score(p, k, q_txt, k, torch.ones(B, dtype=torch.int32, device="cuda"), None, s_raw, s_hat, score, ws)
     assert float((score.double() * V - 1.0).abs().max()) <= 3 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("dtype,B,V,k,D", [
+    ("f32", 9, 900, 350, 512), ("f32", 5, 1500, 600, 1024),     # two slices, two and three tiles of kept rows
+    ("bf16", 5, 2304, 400, 4096), ("bf16", 3, 2304, 576, 4096),  # three tiles; two slices
+])
+def test_equal_kept_rows_in_different_tiles_tie_to_the_smallest_slot(ctx, dtype, B, V, k, D):
+    """Sixteen different kept rows, each of them in every tile of kept rows: the similarities of equal rows are equal
+    to the bit wherever the rows stand, also where the tiles of a source tile go to two XCDs, so the smallest slot
+    wins.  (bf16: among the rows of the same half of a tile, whose sums run in the same order.  The other halves
+    hold rows of their own here: of 96 at 64, 128 and 192 columns per tile only the first 32 are used.)"""
+    tt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(V)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    base = rn(16, D).to(tt)
+    hidden = rn(B, V + 1, D).to(tt)
+    which = torch.randint(16, (B, V - k), generator=g, device="cuda")
+    hidden[:, k:V] = (base.float()[which] + 0.3 * rn(B, V - k, D)).to(tt)
+    slots = torch.arange(k, device="cuda")
+    p = binding.make_params(B, 1, 1, 64, D, 0, V, 1, k, dtype, dtype, dtype)
+    if dtype == "bf16":     # rows 0 .. 31 of every 64 n columns, the tile widths there are
+        slots = slots[(slots % 64 < 32) & (slots % 128 < 32) & (slots % 192 < 32) | (slots < 32)]
+        hidden[:, slots] = base[slots % 16]
+    else:
+        hidden[:, :k] = base[slots % 16]
+    i32 = dict(dtype=torch.int32, device="cuda")
+    kept = torch.arange(k, **i32).expand(B, k).contiguous()
+    pruned = torch.arange(k, V, **i32).expand(B, V - k).contiguous()
+    s_hat = torch.rand(B, V, generator=g, device="cuda")
+    buf = harness.StageBuffers(p, 0)
+    ctx.asap_merge(p, hidden, s_hat, s_hat, torch.ones(B, **i32), kept, pruned, buf.out_hidden, buf.pos_out, buf.new_len,
+                   buf.assign, buf.best_sim, buf.wsum, buf.final_idx, buf.workspace)
+    assert torch.equal(buf.assign, which.to(torch.int32)), int((buf.assign != which).sum())

@@ -45,6 +45,10 @@
 
 namespace asap {
 
+// Minimum and maximum of masses, NaN if one of them is (as the salience of the whole image then is).
+__device__ __forceinline__ double nan_min(double a, double b) { return (b < a || b != b) ? b : a; }
+__device__ __forceinline__ double nan_max(double a, double b) { return (b > a || b != b) ? b : a; }
+
 // Smallest and largest raw mass of image b (Eq. 3).  The mass kernel leaves one (min, max) pair per key
 // tile, n of them in mm [B, n, 2]; every wave that needs the range takes it over those (at most 512) pairs
 // itself.  Device-wide atomics on one pair per image were measured at about 13 us for 512 workgroups: they
@@ -65,13 +69,13 @@ struct MassRange {
     if (n == 1) return;
     for (int i = (threadIdx.x & 63) + 64; i < n; i += 64) {
       const double2 x = p[i];
-      lo = fmin(lo, x.x);
-      hi = fmax(hi, x.y);
+      lo = nan_min(lo, x.x);
+      hi = nan_max(hi, x.y);
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
-      lo = fmin(lo, shfl_xor_f64(lo, off));
-      hi = fmax(hi, shfl_xor_f64(hi, off));
+      lo = nan_min(lo, shfl_xor_f64(lo, off));
+      hi = nan_max(hi, shfl_xor_f64(hi, off));
     }
   }
 };
@@ -358,8 +362,8 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_ma
   if (HS == 1) {
 #pragma unroll
     for (int off = 16; off >= 1; off >>= 1) {
-      smin = fmin(smin, shfl_xor_f64(smin, off));
-      smax = fmax(smax, shfl_xor_f64(smax, off));
+      smin = nan_min(smin, shfl_xor_f64(smin, off));
+      smax = nan_max(smax, shfl_xor_f64(smax, off));
     }
     if (tid == 0) reinterpret_cast<double2*>(mm)[(int64_t)b * gridDim.x + blockIdx.x] = make_double2(smin, smax);
   }
@@ -386,18 +390,18 @@ __global__ __launch_bounds__(1024) void k_mass_finish(const double* __restrict__
     const double s = t * scale;
     s64[(int64_t)b * V + j] = s;
     s_raw[(int64_t)b * V + j] = (float)s;
-    smin = fmin(smin, s);
-    smax = fmax(smax, s);
+    smin = nan_min(smin, s);
+    smax = nan_max(smax, s);
   }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
-    smin = fmin(smin, shfl_xor_f64(smin, off));
-    smax = fmax(smax, shfl_xor_f64(smax, off));
+    smin = nan_min(smin, shfl_xor_f64(smin, off));
+    smax = nan_max(smax, shfl_xor_f64(smax, off));
   }
   if ((tid & 63) == 0) { wave_mm[tid >> 6][0] = smin; wave_mm[tid >> 6][1] = smax; }
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < 16; ++w) { smin = fmin(smin, wave_mm[w][0]); smax = fmax(smax, wave_mm[w][1]); }
+    for (int w = 1; w < 16; ++w) { smin = nan_min(smin, wave_mm[w][0]); smax = nan_max(smax, wave_mm[w][1]); }
     reinterpret_cast<double2*>(mm)[b] = make_double2(smin, smax);
   }
 }

@@ -1126,3 +1126,28 @@ def test_equal_kept_rows_in_different_tiles_tie_to_the_smallest_slot(ctx, dtype,
     ctx.asap_merge(p, hidden, s_hat, s_hat, torch.ones(B, **i32), kept, pruned, buf.out_hidden, buf.pos_out, buf.new_len,
                    buf.assign, buf.best_sim, buf.wsum, buf.final_idx, buf.workspace)
     assert torch.equal(buf.assign, which.to(torch.int32)), int((buf.assign != which).sum())
+
+
+@pytest.mark.parametrize("B,V", [(2, 600), (16, 700)])          # masses finished per image | (min, max) per key tile
+def test_a_nan_in_one_image_makes_its_whole_salience_nan(ctx, B, V):
+    """Eq. 3 takes the minimum and the maximum over all masses: with one that is NaN every salience of the image is, and
+    the other images keep theirs bit for bit."""
+    d, T = 64, 40
+    g = torch.Generator(device="cuda").manual_seed(V)
+    q = torch.randn(B, 8, V + T, d, generator=g, device="cuda").bfloat16()
+    k = torch.randn(B, 8, V, d, generator=g, device="cuda").bfloat16()
+    p = binding.make_params(B, 8, 8, d, 64, 0, V, T, 8, "bf16", "bf16", "bf16")
+    ws = torch.empty(binding.asap_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    outs = []
+    for bad in (False, True):
+        if bad:
+            k[1, 3, V - 5, 7] = float("nan")
+        s_raw, s_hat, score = (torch.empty(B, V, device="cuda") for _ in range(3))
+        ctx.asap_score(p, q[:, :, :V], q[:, :, V:], k, torch.full((B,), T, dtype=torch.int32, device="cuda"), None, s_raw,
+                       s_hat, score, ws)
+        outs.append((s_raw, s_hat, score))
+    assert torch.isfinite(outs[0][1]).all()
+    assert torch.isnan(outs[1][1][1]).all()
+    for a, b in zip(*outs):
+        others = [i for i in range(B) if i != 1]
+        assert torch.equal(a[others].view(torch.int32), b[others].view(torch.int32))

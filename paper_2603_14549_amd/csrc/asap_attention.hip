@@ -182,8 +182,9 @@ __global__ __launch_bounds__(64 * ATT_NW) void k_attention(const T* __restrict__
   // and values share its L2 (with an image's blocks dealt to all eight, every L2 held the keys and values of
   // some 26 heads at a time, 31 MB at 16 x 32 heads x 2403 positions: 1.94 ms, now 1.80).
   const int qblocks = (N + ATT_QWG - 1) / ATT_QWG, units = B * H * qblocks, per_xcd = (units + NUM_XCD - 1) / NUM_XCD;
-  const int unit = (blockIdx.x % NUM_XCD) * per_xcd + blockIdx.x / NUM_XCD;
-  if (unit >= units) return;                    // the same for the whole workgroup
+  const int block = linear_block(), slot = block / NUM_XCD;
+  const int unit = (block % NUM_XCD) * per_xcd + slot;
+  if (slot >= per_xcd || unit >= units) return; // the same for the whole workgroup
   const int bh = unit / qblocks, b = bh / H, h = bh - b * H, g = (h * Hkv) / H;
   const int iw = (unit - bh * qblocks) * ATT_QWG;       // first query of the workgroup
   const int i0 = iw + wave * 32;                // first query of the wave
@@ -468,7 +469,7 @@ static hipError_t attention_typed(const asap_params& p, const void* q, Strides3 
                 static_cast<const T*>(v), sv, N, Npad, p.d, vt);
   const float c2 = 1.4426950408889634f / sqrtf((float)p.d);
   const int units = p.B * p.H * ((N + ATT_QWG - 1) / ATT_QWG);
-  const dim3 grid(NUM_XCD * ((units + NUM_XCD - 1) / NUM_XCD));
+  const dim3 grid = grid_of(NUM_XCD * (int64_t)((units + NUM_XCD - 1) / NUM_XCD));
   const int ch = p.d / E / 2;
   constexpr int PD = ATT_PD;                   // key tiles requested ahead
   const size_t lds = (PD + 2) * ((size_t)(32 * 32 * ch + p.d * 32 * sizeof(T)) + ATT_BIASB);

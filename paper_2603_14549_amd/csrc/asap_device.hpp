@@ -10,6 +10,9 @@ namespace asap {
 
 constexpr int NUM_XCD = 8;
 
+// number of the workgroup in a grid of grid_of
+__device__ __forceinline__ uint32_t linear_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 

@@ -64,6 +64,15 @@ struct Timer {
   }
 };
 
+// Grid of n workgroups (the kernel's own number: linear_block).  One dimension of a grid holds fewer than 2^32
+// threads, so beyond 2^22 workgroups (of at most 1023 threads) there are several rows of them; the last row may
+// have workgroups past the n-th, which the kernel leaves alone.  2^22 is a multiple of the XCDs: consecutive
+// numbers go to them in turn either way.
+inline dim3 grid_of(int64_t n) {
+  constexpr int64_t row = int64_t(1) << 22;
+  return n <= row ? dim3((unsigned)n) : dim3((unsigned)row, (unsigned)((n + row - 1) / row));
+}
+
 // Launches `kern` and, if `tm` is set, times it under `name`.
 #define ASAP_LAUNCH(tm, name, kern, grid, block, lds, st, ...)                  \
   do {                                                                          \
@@ -126,7 +135,7 @@ struct MergeKv {
   KvPointers ptrs;
   int n_bufs;                 // 2 * layers
   int Hkv, row_bytes;
-  int gx;                     // blocks of rows per (cache, image, kv head), set by the launch
+  int gx, blocks;             // blocks of rows per (cache, image, kv head) and of all, set by the launch
 };
 
 // kv != nullptr: the launch also moves the K/V rows of the survivors.

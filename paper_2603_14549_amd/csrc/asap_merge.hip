@@ -42,10 +42,13 @@ __global__ __launch_bounds__(256) void k_merge(const T* __restrict__ hidden, int
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int Nout = P + k + Tmax;
-  const int unit = blockIdx.x / parts, part = blockIdx.x - unit * parts;
-  const int b = unit / Nout, nrow = unit - b * Nout;
+  const uint32_t block = linear_block();
+  const uint32_t unit = block / parts;
+  const int part = block - unit * parts;
+  const int b = unit / Nout, nrow = unit - (uint32_t)b * Nout;
   if (b >= B) {
-    int id = blockIdx.x - B * Nout * parts;
+    int id = block - (uint32_t)B * Nout * parts;
+    if (id >= kv.blocks) return;
     const int bx = id % kv.gx;
     id /= kv.gx;
     compact_block<KV_FROM_KEPT>(kv.ptrs, kept, text_len, kv.Hkv, P + V + Tmax, Nout, kv.row_bytes, P, V, k, bx,
@@ -203,19 +206,18 @@ static hipError_t merge_typed(const asap_params& p, const void* hidden, int64_t 
   const int nchunks = p.D / E;
   const int cpt = (nchunks + 255) / 256;
   MergeKv mk{};
-  int kv_blocks = 0;
   if (kv) {
     mk = *kv;
     mk.gx = (p.P + p.k + p.Tmax + kv_rows_per_block(mk.row_bytes) - 1) / kv_rows_per_block(mk.row_bytes);
-    kv_blocks = mk.gx * p.B * mk.Hkv * mk.n_bufs;
+    mk.blocks = mk.gx * p.B * mk.Hkv * mk.n_bufs;
   }
   // Few rows (at most about four workgroups per compute unit): pieces of 4 KB with workgroups of their own,
   // whose threads then have registers for 16 source rows in flight (one image, 2304 tokens: 15 -> 13 us,
   // 576 tokens in f32: 16 -> 12).  Many rows: whole rows, so that the lists are scanned once per row (16 x 2304:
   // 71 us, 78 in pieces).
-  const long rows = (long)p.B * (p.P + p.k + p.Tmax);
+  const int64_t rows = (int64_t)p.B * (p.P + p.k + p.Tmax);
   const int parts = rows <= MERGE_SPLIT_ROWS ? cpt : 1;
-  const dim3 grid((unsigned)(rows * parts + kv_blocks));
+  const dim3 grid = grid_of(rows * parts + mk.blocks);
 #define ASAP_MERGE(CPT, AHEAD)                                                                                 \
   ASAP_LAUNCH(tm, "k_merge", (k_merge<T, CPT, AHEAD>), grid, dim3(256), 0, st, h, hsb, hsr, p.D, p.P, p.V, p.k, \
               M, p.Tmax, p.merge_weight, s_hat, text_len, kept, cand, assign, static_cast<T*>(out_hidden),     \

@@ -1151,3 +1151,20 @@ def test_a_nan_in_one_image_makes_its_whole_salience_nan(ctx, B, V):
     for a, b in zip(*outs):
         others = [i for i in range(B) if i != 1]
         assert torch.equal(a[others].view(torch.int32), b[others].view(torch.int32))
+
+
+def test_merge_of_more_than_2_to_the_24_output_rows(ctx):
+    """A launch has fewer than 2^32 threads in one dimension of its grid: 65535 images of 257 rows need more."""
+    B, P, T, D = 65535, 128, 128, 64
+    p = binding.make_params(B, 1, 1, 64, D, P, 1, T, 1, "bf16", "bf16", "bf16")
+    hidden = torch.randn(B, P + 1 + T, D, dtype=torch.bfloat16, device="cuda")
+    i32 = dict(dtype=torch.int32, device="cuda")
+    text_len = torch.randint(0, T + 1, (B,), **i32)
+    buf = harness.StageBuffers(p, 0)
+    s = torch.ones(B, 1, device="cuda")
+    ctx.asap_merge(p, hidden, s, s, text_len, torch.zeros(B, 1, **i32), torch.zeros(B, 1, **i32), buf.out_hidden,
+                   buf.pos_out, buf.new_len, buf.assign, buf.best_sim, buf.wsum, buf.final_idx, buf.workspace)
+    assert torch.equal(buf.out_hidden[:, :P + 1], hidden[:, :P + 1])
+    valid = (torch.arange(T, device="cuda") < text_len[:, None])[..., None]
+    assert torch.equal(buf.out_hidden[:, P + 1:], torch.where(valid, hidden[:, P + 1:], buf.out_hidden.new_zeros(())))
+    assert torch.equal(buf.new_len, P + 1 + text_len)

@@ -40,7 +40,7 @@ typedef enum {
   ASAP_OK = 0,
   ASAP_EINVAL = 1,        /* bad shape / pointer / alignment / parameter          */
   ASAP_EUNSUPPORTED = 2,  /* legal request this build has no kernel for           */
-  ASAP_EWORKSPACE = 3,    /* workspace smaller than asap_workspace_bytes()        */
+  ASAP_EWORKSPACE = 3,    /* workspace too small (see asap_workspace_bytes)       */
   ASAP_EHIP = 4           /* the HIP runtime refused a launch or a query          */
 } asap_status;
 
@@ -102,7 +102,10 @@ asap_status asap_check_params(const asap_params* p, char* msg, size_t msg_len);
  * serves all four).  0 if the parameters are invalid.  The workspace must be 256-byte
  * aligned; its contents are undefined before and after each call.  With f32 queries and keys it
  * includes 4 B H Tmax V bytes for the text rows' logits (Eq. 5), which are then formed once instead
- * of twice, unless that alone would exceed 1 GiB. */
+ * of twice, unless that alone would exceed 1 GiB.  With bf16 ones and up to 4096 visual tokens the text
+ * rows' softmax is taken in one sweep over the keys, whose partial column sums can take more than the
+ * two sweeps would (many query heads on few kv heads): the calls accept a workspace without room for
+ * them and then take the two sweeps, with scores that differ by rounding, within the tolerance of either. */
 size_t asap_workspace_bytes(const asap_params* p);
 
 /*

@@ -4,6 +4,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "asap_launch.hpp"
@@ -266,17 +267,21 @@ asap_status asap_check_params(const asap_params* p, char* msg, size_t msg_len) {
   return check_params(p, msg, msg_len);
 }
 
+// what every call accepts as a workspace (valid parameters)
+static size_t least_workspace_bytes(const asap_params* p) {
+  return std::max(score_workspace_least(*p), paper_workspace_bytes(*p) + sim_workspace_bytes(*p));
+}
+
 size_t asap_workspace_bytes(const asap_params* p) {
   if (check_params(p, nullptr, 0) != ASAP_OK) return 0;
-  size_t a = score_workspace(*p).total, b = paper_workspace_bytes(*p) + sim_workspace_bytes(*p);
-  return a > b ? a : b;
+  return std::max(score_workspace(*p).total, least_workspace_bytes(p));
 }
 
 static asap_status score_checks(asap_ctx* ctx, const asap_params* p, const void* q_vis,
                                 const int64_t q_vis_stride[3], const void* q_txt, const int64_t q_txt_stride[3],
                                 const void* k_vis, const int64_t k_vis_stride[3], const int32_t* text_len,
                                 float* s_raw, float* s_hat, float* score, void* workspace, size_t workspace_bytes,
-                                size_t workspace_need) {
+                                size_t workspace_need = 0 /* 0: least_workspace_bytes */) {
   asap_status st = common_checks(ctx, p);
   if (st != ASAP_OK) return st;
   if (!q_vis || !q_txt || !k_vis || !text_len || !s_raw || !s_hat || !score)
@@ -292,7 +297,7 @@ static asap_status score_checks(asap_ctx* ctx, const asap_params* p, const void*
   if ((st = check_span(ctx, "q_vis", p->V, q_vis_stride[2], esz)) != ASAP_OK) return st;
   if ((st = check_span(ctx, "q_txt", p->Tmax, q_txt_stride[2], esz)) != ASAP_OK) return st;
   if ((st = check_span(ctx, "k_vis", p->V, k_vis_stride[2], esz)) != ASAP_OK) return st;
-  return check_workspace(ctx, workspace_need, workspace, workspace_bytes);
+  return check_workspace(ctx, workspace_need ? workspace_need : least_workspace_bytes(p), workspace, workspace_bytes);
 }
 
 asap_status asap_score(asap_ctx* ctx, const asap_params* p, const void* q_vis, const int64_t q_vis_stride[3],
@@ -301,21 +306,21 @@ asap_status asap_score(asap_ctx* ctx, const asap_params* p, const void* q_vis, c
                        float* s_raw, float* s_hat, float* score, void* workspace, size_t workspace_bytes,
                        void* stream) {
   asap_status st = score_checks(ctx, p, q_vis, q_vis_stride, q_txt, q_txt_stride, k_vis, k_vis_stride, text_len,
-                                s_raw, s_hat, score, workspace, workspace_bytes, asap_workspace_bytes(p));
+                                s_raw, s_hat, score, workspace, workspace_bytes);
   if (st != ASAP_OK) return st;
   Strides3 qv{q_vis_stride[0], q_vis_stride[1], q_vis_stride[2]};
   Strides3 qt{q_txt_stride[0], q_txt_stride[1], q_txt_stride[2]};
   Strides3 kv{k_vis_stride[0], k_vis_stride[1], k_vis_stride[2]};
   return hip_result(ctx,
                     launch_score(*p, q_vis, qv, q_txt, qt, k_vis, kv, text_len, lse_extra, s_raw, s_hat, score,
-                                 nullptr, nullptr, nullptr, nullptr, static_cast<char*>(workspace), ~size_t(0),
+                                 nullptr, nullptr, nullptr, nullptr, static_cast<char*>(workspace), workspace_bytes,
                                  static_cast<hipStream_t>(stream), ctx->timer),
                     "asap_score launch");
 }
 
 size_t asap_front_end_workspace_bytes(const asap_params* p) {
   if (check_params(p, nullptr, 0) != ASAP_OK) return 0;
-  return score_workspace(*p).total + front_workspace_bytes(*p);
+  return std::max(score_workspace(*p).total, score_workspace_least(*p)) + front_workspace_bytes(*p);
 }
 
 asap_status asap_score_from_hidden(asap_ctx* ctx, const asap_params* p, const void* hidden,
@@ -340,7 +345,7 @@ asap_status asap_score_from_hidden(asap_ctx* ctx, const asap_params* p, const vo
   const int64_t esz = dtype_size(p->qk_dtype);
   if ((st = check_span(ctx, "q_txt", p->Tmax, q_txt_stride[2], esz)) != ASAP_OK) return st;
   if ((st = check_span(ctx, "k_vis", p->V, k_vis_stride[2], esz)) != ASAP_OK) return st;
-  const size_t need = asap_front_end_workspace_bytes(p);
+  const size_t front_bytes = front_workspace_bytes(*p), need = score_workspace_least(*p) + front_bytes;
   if (!workspace) return fail(ctx, ASAP_EINVAL, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return fail(ctx, ASAP_EINVAL, "workspace is not 256-byte aligned");
   if (workspace_bytes < need)
@@ -348,14 +353,14 @@ asap_status asap_score_from_hidden(asap_ctx* ctx, const asap_params* p, const vo
   char* ws = static_cast<char*>(workspace);
   FrontArgs fe;
   fe.hidden = hidden; fe.hsb = hidden_stride[0]; fe.hsr = hidden_stride[1]; fe.wq = w_q; fe.rope_theta = rope_theta;
-  fe.vis_positions = vis_positions; fe.ws = ws + score_workspace(*p).total;
+  fe.vis_positions = vis_positions; fe.ws = ws + score_workspace(*p, workspace_bytes - front_bytes).total;
   Strides3 none{0, 0, 0};
   Strides3 qt{q_txt_stride[0], q_txt_stride[1], q_txt_stride[2]};
   Strides3 kv{k_vis_stride[0], k_vis_stride[1], k_vis_stride[2]};
   return hip_result(ctx,
                     launch_score(*p, nullptr, none, q_txt, qt, k_vis, kv, text_len, lse_extra, s_raw, s_hat, score,
-                                 nullptr, nullptr, &fe, nullptr, ws, ~size_t(0), static_cast<hipStream_t>(stream),
-                                 ctx->timer),
+                                 nullptr, nullptr, &fe, nullptr, ws, workspace_bytes - front_bytes,
+                                 static_cast<hipStream_t>(stream), ctx->timer),
                     "asap_score_from_hidden launch");
 }
 
@@ -440,7 +445,7 @@ static asap_status merge_checks(asap_ctx* ctx, const asap_params* p, const void*
     const char* b1 = b0 + (int64_t)p->B * (p->P + p->k + p->Tmax) * p->D * esz;
     if (a0 < b1 && b0 < a1) return fail(ctx, ASAP_EINVAL, "asap_merge: out_hidden overlaps hidden");
   }
-  return check_workspace(ctx, asap_workspace_bytes(p), workspace, workspace_bytes);
+  return check_workspace(ctx, least_workspace_bytes(p), workspace, workspace_bytes);
 }
 
 asap_status asap_merge(asap_ctx* ctx, const asap_params* p, const void* hidden, const int64_t hidden_stride[2],
@@ -554,7 +559,7 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
   // every check of the single calls first: a failed check launches nothing
   asap_status st = score_checks(ctx, p, io->q_vis, io->q_vis_stride, io->q_txt, io->q_txt_stride, io->k_vis,
                                 io->k_vis_stride, io->text_len, io->s_raw, io->s_hat, io->score, io->workspace,
-                                io->workspace_bytes, asap_workspace_bytes(p));
+                                io->workspace_bytes);
   if (st == ASAP_OK) st = select_checks(ctx, p, io->score, io->kept_idx, io->pruned_idx);
   if (st == ASAP_OK)
     st = merge_checks(ctx, p, io->hidden, io->hidden_stride, io->s_raw, io->s_hat, io->text_len, io->kept_idx,
@@ -611,7 +616,7 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
   if (e == hipSuccess)
     e = launch_score(*p, io->q_vis, qv, io->q_txt, qt, io->k_vis, kv, io->text_len, io->lse_extra, io->s_raw,
                      io->s_hat, io->score, io->kept_idx, io->pruned_idx, nullptr,
-                     fixed_with_selection ? &fixed : nullptr, ws, ~size_t(0), main, ctx->timer);
+                     fixed_with_selection ? &fixed : nullptr, ws, io->workspace_bytes, main, ctx->timer);
   if (e == hipSuccess && early) {
     e = hipEventRecord(ctx->ev_fork, main);
     if (e == hipSuccess) e = hipStreamWaitEvent(ctx->side, ctx->ev_fork, 0);

@@ -27,8 +27,9 @@ struct ScoreWorkspace {
   size_t off_qpart;  // double [B,H,q_chunks,d]  partial sums of visual queries
   size_t off_qsplit; // bf16   [B,Hkv,4,d]       their sums per kv head, split into four bf16 pieces per component
   size_t off_s64;    // double [B,V]             raw attention mass before rounding
-  int mm_n;          // (min, max) pairs of s per image: one per key tile, or one (head_splits > 1)
-  size_t off_mm;     // double [B,mm_n,2]        those pairs (in the place of qpart)
+  int finish;        // 1: k_mass_finish adds up partial masses and takes their (min, max)
+  int mm_n;          // (min, max) pairs of s per image: one per key tile, or one (finish)
+  size_t off_mm;     // double [B,mm_n,2]        those pairs (those of the key tiles in the place of qpart)
   size_t off_pstat;  // float  [B,H,splits,2,NR] per-split (max, sum) of every text row, NR = 64 row_pairs
   size_t off_upart;  // float  [B,H,row_pairs,V] column sums of normalised weights per head and row pair
                      //        (one_sweep: per group of kv heads and row block, those an image has one after the other)
@@ -36,10 +37,12 @@ struct ScoreWorkspace {
   size_t off_zlog;   // float  [B,H,t_eff,V]     raw logits of the ranking rows (ride, store_logits)
   size_t total;
 };
-// budget: the bytes the caller can give; optional parts of the workspace (the stored logits) are
-// planned only if the whole then fits.
+// budget: the bytes the caller gives; what is optional (the stored logits, the one sweep over the keys where its
+// column sums take more than the two sweeps do) is planned only if the whole then fits.
 constexpr size_t STORED_LOGITS_MAX_BYTES = size_t(1) << 30;
 ScoreWorkspace score_workspace(const asap_params& p, size_t budget = ~size_t(0));
+// Bytes that a caller's workspace must have: those of the two sweeps over the keys.
+size_t score_workspace_least(const asap_params& p);
 
 struct Strides3 { int64_t b, h, r; };
 
@@ -120,7 +123,7 @@ inline bool score_fuses_selection(const asap_params& p) { return p.B >= 12; }
 // call), writing kept [B,k] and pruned [B,V-k] exactly as launch_select would.  fixed != nullptr (only
 // with kept and score_fuses_selection(p)): further workgroups of that launch copy the K/V rows of the
 // prefix and of the valid text, which depend on no result, while the memory system is otherwise idle.
-// ws_budget: the budget score_workspace planned ws with (~0 for workspaces sized by asap_workspace_bytes).
+// ws_budget: the size of ws, which score_workspace plans with.
 hipError_t launch_score(const asap_params& p, const void* q_vis, Strides3 qv, const void* q_txt, Strides3 qt,
                         const void* k_vis, Strides3 kv, const int32_t* text_len, const float* lse_extra,
                         float* s_raw, float* s_hat, float* score, int32_t* kept, int32_t* pruned,

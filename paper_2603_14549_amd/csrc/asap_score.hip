@@ -199,8 +199,8 @@ struct RideArgs {
 // 6.0 TB/s for whole rows.  So a wave reads whole rows (LPR consecutive lanes per row) and turns the
 // tile into the operand layout through an LDS buffer of its own -- written and read by the same
 // wave, in order, so no barrier is involved.  NG = contraction groups of 8 elements (d = 16 NG).
-// HS == 1: writes s64, s_raw and the (min, max) of its keys to mm [B, ktiles, 2]; HS > 1: writes the group's partial mass to
-// spart [HS, B, V] for k_mass_finish.
+// With mm: writes s64, s_raw and the (min, max) of its keys to mm [B, ktiles, 2]; without: writes the group's partial
+// mass to spart [HS, B, V] for k_mass_finish.
 // ------------------------------------------------------------------------------------------
 template <typename T, int NG, bool RIDE>
 __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_mass_mfma(const T* __restrict__ kv, Strides3 sk,
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_ma
   const int j = j0 + n;
   if (j < V) {
     const double tot = ((part[0][n] + part[1][n]) + part[2][n]) + part[3][n];
-    if (HS == 1) {
+    if (mm != nullptr) {
       const double s = tot * scale;
       s64[(int64_t)b * V + j] = s;
       s_raw[(int64_t)b * V + j] = (float)s;
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_ma
       spart[((int64_t)hs * gridDim.y / HS + b) * V + j] = tot;
     }
   }
-  if (HS == 1) {
+  if (mm != nullptr) {
 #pragma unroll
     for (int off = 16; off >= 1; off >>= 1) {
       smin = nan_min(smin, shfl_xor_f64(smin, off));
@@ -370,9 +370,9 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_ma
 }
 
 // k_mass_finish: grid (B), 1024 threads: adds the HS partial masses of every key in group order,
-// scales, writes s64 / s_raw and the image's (min, max) to mm [B, 1, 2].
-__global__ __launch_bounds__(1024) void k_mass_finish(const double* __restrict__ spart, int HS, int B, int V,
-                                                       double scale, double* __restrict__ s64,
+// scales, writes s64 / s_raw and the image's (min, max) to mm [B, 1, 2].  With HS == 1 spart may be s64.
+__global__ __launch_bounds__(1024) void k_mass_finish(const double* spart, int HS, int B, int V, double scale,
+                                                       double* s64,
                                                        float* __restrict__ s_raw,
                                                        double* __restrict__ mm) {
   __shared__ double wave_mm[16][2];
@@ -1638,7 +1638,6 @@ ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
     for (int hs = p.Hkv; hs >= 1; --hs)
       if (p.Hkv % hs == 0 && hs <= want) { w.head_splits = hs; break; }
   }
-  w.mm_n = w.head_splits > 1 ? 1 : (p.V + 31) / 32;
   w.row_pairs = w.ride ? 1 : (w.t_eff + 63) / 64;
   // f32 keys: the first text-row sweep leaves its logits (4 bytes per ranking row and key, never more
   // than the key sweeps they replace at 512 bytes per key and 64 rows) and the column sums read them
@@ -1648,50 +1647,57 @@ ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
   w.store_logits = (!w.ride && p.qk_dtype != ASAP_BF16 && zlog_bytes <= STORED_LOGITS_MAX_BYTES) ? 1 : 0;
   const int NR = w.ride ? 32 : 64 * w.row_pairs;
   const int splits = w.ride ? 1 : w.attn_splits;
-  // One sweep over the keys where the softmax terms of 32 text rows fit a workgroup's registers.  It needs
-  // neither the row statistics nor the logits, but the size of the workspace is the caller's to plan
-  // with and stays what it was.
+  // One sweep over the keys where the softmax terms of 32 text rows fit a workgroup's registers.
   // Two row groups per workgroup read the keys half as often; one leaves twice the workgroups and half the
   // work in each, which is what a launch that leaves half the chip idle needs, and holds more keys.
   if (!w.ride && p.qk_dtype == ASAP_BF16) {
     const long units2 = (long)p.B * p.Hkv * ((G * w.t_eff + 31) / 32);
     w.one_sweep = p.V <= ROWS_V2 && units2 > 128 ? 2 : p.V <= ROWS_V1 ? 1 : 0;
   }
-  size_t upart_rows = (size_t)p.H * w.row_pairs;
-  const size_t mm_bytes = sizeof(double) * 2 * p.B * w.mm_n;
   const size_t spart_bytes = w.head_splits > 1 ? align256(sizeof(double) * (size_t)w.head_splits * p.B * p.V) : 0;
   size_t off = 0;
-  // the (min, max) pairs lie where the partial sums of the queries were: those have been read (k_qsplit)
-  // before the masses are formed
-  w.off_qpart = w.off_mm = off;
-  const size_t qpart_bytes = align256(sizeof(double) * p.B * p.H * w.q_chunks * p.d);
-  off = align256(off + std::max(qpart_bytes + sizeof(double) * p.B * p.Hkv * p.d, mm_bytes));
+  w.off_qpart = off;
+  off = align256(off + sizeof(double) * p.B * p.H * w.q_chunks * p.d);
+  off = align256(off + sizeof(double) * p.B * p.Hkv * p.d);
+  // The (min, max) pairs of the key tiles lie where the partial sums of the queries were: those have been read
+  // (k_qsplit) before the masses are formed.  Where they do not fit (fewer than 16 heads, thousands of tokens),
+  // k_mass_finish takes one pair per image.
+  const int ktiles = (p.V + 31) / 32;
+  w.finish = w.head_splits > 1 || sizeof(double) * 2 * p.B * ktiles > off;
+  w.mm_n = w.finish ? 1 : ktiles;
   w.off_qsplit = off; off = align256(off + sizeof(uint16_t) * p.B * p.Hkv * 4 * p.d);
   w.off_s64 = off;    off = align256(off + sizeof(double) * p.B * p.V);
+  w.off_mm = w.finish ? off : w.off_qpart;
   off = align256(off + sizeof(double) * 2 * p.B);
-  w.off_pstat = off;  off = align256(off + sizeof(float) * (size_t)p.B * p.H * splits * 2 * NR);
-  // Many query heads on few kv heads leave more partial column sums than the two sweeps do (16 rows each
-  // instead of 64): where the scratch has a limit that these do not fit, the two sweeps run.
+  // The one sweep has no row statistics, and its column sums take the place of the partial masses, which have
+  // been added up by then.  Many query heads on few kv heads leave more of those sums than the two sweeps do
+  // (one row for 16 or 32 text rows instead of 64): where the caller's scratch does not hold them, the two sweeps run.
   if (w.one_sweep) {
     const int blocks = (G * w.t_eff + 16 * w.one_sweep - 1) / (16 * w.one_sweep);
     const int heads = rows_heads_per_wg(p, blocks, w.one_sweep);
-    const size_t rows_one = std::max(upart_rows, (size_t)((p.Hkv + heads - 1) / heads) * blocks);
-    if (align256(off + sizeof(float) * p.B * rows_one * p.V) + spart_bytes > budget) {
-      w.one_sweep = 0;
-    } else {
+    const size_t rows = (size_t)((p.Hkv + heads - 1) / heads) * blocks;
+    const size_t total = off + std::max(align256(sizeof(float) * p.B * rows * p.V), spart_bytes);
+    if (total <= budget) {
       w.row_pairs = blocks;
       w.heads_per_wg = heads;
-      upart_rows = rows_one;
+      w.off_upart = w.off_spart = w.off_pstat = off;
+      w.off_zlog = w.total = total;
+      return w;
     }
+    w.one_sweep = 0;
   }
-  w.off_upart = off;  off = align256(off + sizeof(float) * p.B * upart_rows * p.V);
-  w.off_spart = off;
-  off += spart_bytes;
+  w.off_pstat = off;  off = align256(off + sizeof(float) * (size_t)p.B * p.H * splits * 2 * NR);
+  w.off_upart = off;  off = align256(off + sizeof(float) * (size_t)p.B * p.H * w.row_pairs * p.V);
+  w.off_spart = off;  off += spart_bytes;
   w.off_zlog = off;
   if (w.store_logits && align256(off + zlog_bytes) > budget) w.store_logits = 0;
   if (w.ride || w.store_logits) off = align256(off + zlog_bytes);
   w.total = off;
   return w;
+}
+
+size_t score_workspace_least(const asap_params& p) {
+  return score_workspace(p, p.qk_dtype == ASAP_BF16 ? 0 : ~size_t(0)).total;
 }
 
 template <typename T, int NG>
@@ -1791,7 +1797,7 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
   double* mm = reinterpret_cast<double*>(ws + w.off_mm);
   float* pstat = reinterpret_cast<float*>(ws + w.off_pstat);
   float* upart = reinterpret_cast<float*>(ws + w.off_upart);
-  double* spart = reinterpret_cast<double*>(ws + w.off_spart);
+  double* spart = w.head_splits > 1 ? reinterpret_cast<double*>(ws + w.off_spart) : s64;
   float* zlog = reinterpret_cast<float*>(ws + w.off_zlog);
   const int mask_on = p.mask_mode == ASAP_MASK_KEYBIAS;
   const int last_only = p.score_rows == ASAP_ROWS_LAST;
@@ -1816,10 +1822,11 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
   RideArgs ra;
   ra.qt = q_txt; ra.sq = qt; ra.text_len = text_len; ra.zlog = zlog;
   ra.H = p.H; ra.G = p.H / p.Hkv; ra.T_eff = w.t_eff; ra.Tmax = p.Tmax; ra.last_only = last_only;
-  hipError_t e = ng == 8 ? launch_mass<T, 8>(p, w, k_vis, kv, qsplit, scale, s64, s_raw, mm, spart, ra, st, tm)
-                         : launch_mass<T, 4>(p, w, k_vis, kv, qsplit, scale, s64, s_raw, mm, spart, ra, st, tm);
+  double* tile_mm = w.finish ? nullptr : mm;
+  hipError_t e = ng == 8 ? launch_mass<T, 8>(p, w, k_vis, kv, qsplit, scale, s64, s_raw, tile_mm, spart, ra, st, tm)
+                         : launch_mass<T, 4>(p, w, k_vis, kv, qsplit, scale, s64, s_raw, tile_mm, spart, ra, st, tm);
   if (e != hipSuccess) return e;
-  if (w.head_splits > 1)
+  if (w.finish)
     ASAP_LAUNCH(tm, "k_mass_finish", k_mass_finish, dim3(p.B), dim3(1024), 0, st, spart, w.head_splits, p.B, p.V,
                 scale, s64, s_raw, mm);
 

@@ -1168,3 +1168,36 @@ def test_merge_of_more_than_2_to_the_24_output_rows(ctx):
     valid = (torch.arange(T, device="cuda") < text_len[:, None])[..., None]
     assert torch.equal(buf.out_hidden[:, P + 1:], torch.where(valid, hidden[:, P + 1:], buf.out_hidden.new_zeros(())))
     assert torch.equal(buf.new_len, P + 1 + text_len)
+
+
+@pytest.mark.parametrize("B,H,Hkv,d,V,T,least", [
+    (16, 16, 1, 64, 4096, 128, 9453824), (4, 28, 4, 128, 4096, 48, 2801920), (600, 1, 1, 64, 3000, 64, 23452928),
+])
+def test_a_workspace_of_the_two_sweeps_is_accepted(ctx, B, H, Hkv, d, V, T, least):
+    """Where the column sums of the one sweep over the keys take more workspace than the two sweeps (least), a call
+    with as little as that takes the two sweeps; one byte less is refused.  The last shape also has no room for
+    the (min, max) pairs of its key tiles.  Mass and salience agree bit for bit, scores to twice the bound of either."""
+    g = torch.Generator(device="cuda").manual_seed(V)
+    q = torch.randn(B, H, V + T, d, generator=g, device="cuda").bfloat16()
+    k = torch.randn(B, Hkv, V, d, generator=g, device="cuda").bfloat16()
+    text_len = torch.randint(1, T + 1, (B,), generator=g, device="cuda").to(torch.int32)
+    p = binding.make_params(B, H, Hkv, d, 64, 0, V, T, 8, "bf16", "bf16", "bf16")
+    assert binding.asap_workspace_bytes(p) > least
+    outs = []
+    for size in (binding.asap_workspace_bytes(p), least):
+        outs.append([torch.full((B, V), float("nan"), device="cuda") for _ in range(3)])
+        ws = torch.zeros(size + 4096, dtype=torch.uint8, device="cuda")
+        ws[size:] = 77
+        ctx.asap_score(p, q[:, :, :V], q[:, :, V:], k, text_len, None, *outs[-1], ws[:size])
+        assert bool((ws[size:] == 77).all())
+    for a, b in zip(outs[0][:2], outs[1][:2]):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    assert bool((outs[0][1].amin(1) == 0).all()) and bool((outs[0][1].amax(1) > 0.999).all())
+    for b in (0, B - 1):
+        ref, bound = _score_and_bound(q[b, :, V:].cpu(), k[b].cpu(), outs[0][0][b].cpu(), int(text_len[b]), p.lambda_max,
+                                      p.eps, True)
+        for o in outs:
+            assert bool(((o[2][b].double().cpu() - ref).abs() <= bound).all()), b
+    with pytest.raises(binding.AsapError) as err:
+        ctx.asap_score(p, q[:, :, :V], q[:, :, V:], k, text_len, None, *outs[0], ws[:least - 1])
+    assert err.value.status == binding.ASAP_EWORKSPACE

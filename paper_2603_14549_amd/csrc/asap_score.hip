@@ -1614,6 +1614,27 @@ static int rows_heads_per_wg(const asap_params& p, int row_blocks, int rg) {
   return best;
 }
 
+// Above ROWS_V2 keys a block of the one sweep has 16 rows, half of what the two sweeps take per pass over a
+// key tile in LDS, and a wave walks up to 16 tiles in a row.  Both forms of asap_score, timed over 480 shapes
+// of 2305 to 4096 keys: the one sweep is 1.13 times as fast on average; the two sweeps are where
+//  * the launch is many rounds of 256 workgroups (blocks x kv heads x images) and the text rows fill the two sweeps'
+//    blocks of 64 (113 to 128, or 49 to 64 rows): from 16 rounds on with d = 64 or one query head per kv head
+//    (16 x 32 heads x 2560 keys, 128 rows: 326 us, two sweeps 300; with more query heads per kv head the
+//    one sweep stays ahead at d = 128: 8 x 28 on 4 x 4096 keys 1.16 times); with d = 64 from 7.5 rounds on where
+//    there are at most 64 rows (16 x 32 x 2560: 136 and 126 us) or 16 query heads share their keys (partial column sums
+//    then outweigh the keys; 16 x 16 on 1 x 4096, 128 rows: 144 and 117 us);
+//  * at most 32 workgroups walk more than 12 tiles of 256 bytes a row (1 x 8 heads x 3617 keys, 32 rows: 38 and 34 us;
+//    with seven query heads per kv head the one sweep is ahead again, 47.8 and 48.5 us).
+// Between 8 and 16 rounds of 113 to 128 rows either form is ahead, by up to 10 % for sizes close to each other.
+static bool two_sweeps_faster(const asap_params& p, int t_eff) {
+  const int G = p.H / p.Hkv;
+  const long wgs = (long)p.B * p.Hkv * ((G * t_eff + 15) / 16);
+  const bool full = (t_eff + 63) / 64 * 64 - t_eff < 16;
+  if (full && wgs >= 4096 && (p.d == 64 || G == 1)) return true;
+  if (full && wgs >= 1920 && p.d == 64 && (t_eff <= 64 || G >= 16)) return true;
+  return p.d == 128 && p.V > 12 * 256 && wgs <= 32 && G <= 4;
+}
+
 ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
   ScoreWorkspace w{};
   // rows per k_qsum block: whole image span unless that leaves the chip short of blocks
@@ -1652,7 +1673,7 @@ ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
   // work in each, which is what a launch that leaves half the chip idle needs, and holds more keys.
   if (!w.ride && p.qk_dtype == ASAP_BF16) {
     const long units2 = (long)p.B * p.Hkv * ((G * w.t_eff + 31) / 32);
-    w.one_sweep = p.V <= ROWS_V2 && units2 > 128 ? 2 : p.V <= ROWS_V1 ? 1 : 0;
+    w.one_sweep = p.V <= ROWS_V2 ? (units2 > 128 ? 2 : 1) : p.V <= ROWS_V1 && !two_sweeps_faster(p, w.t_eff) ? 1 : 0;
   }
   const size_t spart_bytes = w.head_splits > 1 ? align256(sizeof(double) * (size_t)w.head_splits * p.B * p.V) : 0;
   size_t off = 0;

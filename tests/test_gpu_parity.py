@@ -1171,7 +1171,7 @@ def test_merge_of_more_than_2_to_the_24_output_rows(ctx):
 
 
 @pytest.mark.parametrize("B,H,Hkv,d,V,T,least", [
-    (16, 16, 1, 64, 4096, 128, 9453824), (4, 28, 4, 128, 4096, 48, 2801920), (600, 1, 1, 64, 3000, 64, 23452928),
+    (8, 16, 1, 64, 4096, 128, 4989184), (4, 28, 4, 128, 4096, 48, 2801920), (600, 1, 1, 64, 3000, 40, 23452928),
 ])
 def test_a_workspace_of_the_two_sweeps_is_accepted(ctx, B, H, Hkv, d, V, T, least):
     """Where the column sums of the one sweep over the keys take more workspace than the two sweeps (least), a call
@@ -1201,3 +1201,24 @@ def test_a_workspace_of_the_two_sweeps_is_accepted(ctx, B, H, Hkv, d, V, T, leas
     with pytest.raises(binding.AsapError) as err:
         ctx.asap_score(p, q[:, :, :V], q[:, :, V:], k, text_len, None, *outs[0], ws[:least - 1])
     assert err.value.status == binding.ASAP_EWORKSPACE
+
+
+@pytest.mark.parametrize("B,H,Hkv,d,V,T", [
+    (1, 4, 4, 128, 3073, 128), (1, 4, 4, 128, 3072, 128), (1, 9, 9, 128, 3100, 64),      # two sweeps | one | one
+    (15, 16, 1, 64, 2400, 128), (14, 16, 1, 64, 2400, 128),                              # two | one
+    (60, 8, 8, 64, 2305, 50), (32, 16, 16, 64, 2310, 113), (32, 16, 16, 64, 2310, 112),  # two | two | one
+])
+def test_text_rows_above_2304_tokens(ctx, B, H, Hkv, d, V, T):
+    """Either side of the lines between the one sweep over the keys and the two."""
+    g = torch.Generator(device="cuda").manual_seed(V)
+    q = torch.randn(B, H, V + T, d, generator=g, device="cuda").bfloat16()
+    k = torch.randn(B, Hkv, V, d, generator=g, device="cuda").bfloat16()
+    text_len = torch.randint(1, T + 1, (B,), generator=g, device="cuda").to(torch.int32)
+    p = binding.make_params(B, H, Hkv, d, 64, 0, V, T, 8, "bf16", "bf16", "bf16")
+    s_raw, s_hat, score = (torch.empty(B, V, device="cuda") for _ in range(3))
+    ws = torch.empty(binding.asap_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    ctx.asap_score(p, q[:, :, :V], q[:, :, V:], k, text_len, None, s_raw, s_hat, score, ws)
+    for b in sorted({0, B - 1}):
+        ref, bound = _score_and_bound(q[b, :, V:].cpu(), k[b].cpu(), s_raw[b].cpu(), int(text_len[b]), p.lambda_max,
+                                      p.eps, True)
+        assert bool(((score[b].double().cpu() - ref).abs() <= bound).all()), b

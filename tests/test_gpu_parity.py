@@ -970,7 +970,7 @@ def _score_reference(q_txt, k_vis, s_raw, length, lam_max, eps, mask_on):
     (9, 8, 8, 128, 2304, 64, 64, 1.0), (9, 8, 8, 128, 2305, 64, 17, 1.0),  # 9 | one row group
     (66, 2, 2, 64, 96, 40, 1, 1.0),                                        # more images than lanes of a wave
     (1, 4, 4, 128, 1537, 32, 32, 1.0), (2, 12, 2, 64, 2304, 9, 1, 1.0),    # one row group: 6 | 9, six heads packed
-    (1, 4, 4, 128, 4096, 48, 48, 1.0), (1, 4, 4, 128, 4097, 48, 48, 1.0),  # 16 | the two sweeps
+    (1, 4, 4, 128, 4096, 48, 48, 1.0), (1, 4, 4, 128, 4097, 48, 48, 1.0),  # the two sweeps (few workgroups; too many keys)
     (1, 4, 4, 128, 700, 64, 64, 40.0), (9, 8, 8, 64, 600, 64, 20, 40.0),   # logits beyond 2^100 of one another
     (9, 8, 8, 128, 2300, 64, 64, 40.0),
 ])
@@ -1205,6 +1205,7 @@ def test_a_workspace_of_the_two_sweeps_is_accepted(ctx, B, H, Hkv, d, V, T, leas
 
 @pytest.mark.parametrize("B,H,Hkv,d,V,T", [
     (1, 4, 4, 128, 3073, 128), (1, 4, 4, 128, 3072, 128), (1, 9, 9, 128, 3100, 64),      # two sweeps | one | one
+    (2, 8, 8, 128, 4096, 48), (2, 4, 4, 64, 4096, 48), (1, 9, 9, 64, 4097, 64),          # one, all 16 tiles | one | two
     (15, 16, 1, 64, 2400, 128), (14, 16, 1, 64, 2400, 128),                              # two | one
     (60, 8, 8, 64, 2305, 50), (32, 16, 16, 64, 2310, 113), (32, 16, 16, 64, 2310, 112),  # two | two | one
 ])
@@ -1222,3 +1223,63 @@ def test_text_rows_above_2304_tokens(ctx, B, H, Hkv, d, V, T):
         ref, bound = _score_and_bound(q[b, :, V:].cpu(), k[b].cpu(), s_raw[b].cpu(), int(text_len[b]), p.lambda_max,
                                       p.eps, True)
         assert bool(((score[b].double().cpu() - ref).abs() <= bound).all()), b
+
+
+@pytest.mark.parametrize("dtype,B,P,V,k,T,D", [
+    ("bf16", 2, 3, 2100, 51, 5, 2048),      # 2049 sources: two segments of lists; one piece per row
+    ("bf16", 1, 0, 2560, 512, 4, 4096),     # 2048 sources, 516 rows in two pieces
+    ("bf16", 4, 0, 300, 200, 56, 4096),     # 1024 rows: the most that are cut in pieces
+    ("bf16", 5, 0, 300, 200, 5, 4096),      # 1025: whole rows
+    ("bf16", 9, 1, 260, 100, 20, 8192), ("f32", 9, 1, 260, 100, 20, 8192),     # rows of 16 and 32 KB, whole
+    ("f32", 1, 7, 4200, 40, 9, 8192),       # three segments, eight pieces
+])
+def test_merge_at_the_edges_of_its_launch_shapes(ctx, dtype, B, P, V, k, T, D):
+    """Eq. 6 in fp64 from the routing that the call reports.  A merged row is a sum of n products in fp32, off by
+    (n + 3) u sum |w x| / sum w, and for bf16 (8 significant bits) rounded to 2^-8 of itself."""
+    tt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(V + D)
+    # a few directions, so that some slots take hundreds of sources and most take none
+    base = torch.randn(12, D, generator=g, device="cuda")
+    which = torch.randint(12, (B, P + V + T), generator=g, device="cuda")
+    hidden = (base[which] + 0.2 * torch.randn(B, P + V + T, D, generator=g, device="cuda")).to(tt)
+    order = torch.rand(B, V, generator=g, device="cuda").argsort(1).to(torch.int32)
+    kept, pruned = order[:, :k].sort(1)[0].contiguous(), order[:, k:].sort(1)[0].contiguous()
+    s_hat = torch.rand(B, V, generator=g, device="cuda")
+    text_len = torch.randint(1, T + 1, (B,), generator=g, device="cuda").to(torch.int32)
+    mu = 0.7
+    p = binding.make_params(B, 1, 1, 64, D, P, V, T, k, dtype, dtype, dtype, merge_weight=mu)
+    buf = harness.StageBuffers(p, 0)
+    ctx.asap_merge(p, hidden, s_hat, s_hat, text_len, kept, pruned, buf.out_hidden, buf.pos_out, buf.new_len, buf.assign,
+                   buf.best_sim, buf.wsum, buf.final_idx, buf.workspace)
+    u = 2.0 ** -24
+    for b in range(B):
+        x, w, to = hidden[b, P:P + V].double().cpu(), s_hat[b].double().cpu(), buf.assign[b].cpu().long()
+        i, j = kept[b].cpu().long(), pruned[b].cpu().long()
+        assert int(to.min()) >= 0
+        num, mag = w[i, None] * x[i], w[i, None] * x[i].abs()
+        num.index_add_(0, to, mu * w[j, None] * x[j])
+        mag.index_add_(0, to, mu * w[j, None] * x[j].abs())
+        den, n = w[i].clone().index_add_(0, to, mu * w[j]), torch.bincount(to, minlength=k)[:, None].double() + 1
+        ref, off = num / den[:, None], (n + 3) * u * mag / den[:, None]
+        off = off + (2.0 ** -8 * (ref.abs() + off) if dtype == "bf16" else u * ref.abs())
+        got = buf.out_hidden[b].double().cpu()
+        assert bool(((got[P:P + k] - ref).abs() <= off).all()), b
+        assert bool(((buf.wsum[b].double().cpu() - den).abs() <= (n[:, 0] + 1) * u * den).all()), b
+        t = int(text_len[b])
+        assert torch.equal(buf.out_hidden[b, :P], hidden[b, :P])
+        assert torch.equal(buf.out_hidden[b, P + k:P + k + t], hidden[b, P + V:P + V + t])
+
+
+@pytest.mark.parametrize("route", [binding.ASAP_ROUTE_ABSORB, binding.ASAP_ROUTE_PAPER])
+@pytest.mark.parametrize("layers", [1, 16, 17, 33])
+def test_compaction_in_the_launch_of_the_merge(ctx, layers, route):
+    """On one stream the merge's launch moves the K/V rows of up to 16 layers; the others have launches of their own."""
+    cfg = dataclasses.replace(synth.CONFIGS["S1"], L_kv=layers, name=f"merge{layers}")
+    st = U.GpuStage(synth.make_inputs(cfg), ctx=ctx, overlap=False, route=route)
+    buf = st.run()
+    for b in range(cfg.B):
+        n = int(buf.new_len[b])
+        pos = buf.pos_out[b, :n].long()
+        for src, dst in zip(st.k_cache + st.v_cache, buf.k_dst + buf.v_dst):
+            assert torch.equal(dst[b, :, :n], src[b][:, pos])
+            assert int((dst[b, :, n:] != 0).sum()) == 0

@@ -19,6 +19,7 @@ from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import sys
 import time
@@ -58,6 +59,20 @@ def esize(dt: str) -> int:
     return 2 if dt == "bf16" else 4
 
 
+def column_sum_rows(cfg, mean_text: float) -> int:
+    """Rows of partial column sums per image that k_attn_rows leaves and the score reads back, as the library plans
+    them: one per block of 16 or 32 text rows of a kv head's query heads and per group of kv heads that a
+    workgroup walks (fewest rounds of workgroups times heads and a half; ties to the larger group)."""
+    B, Hkv, G, V = cfg.B, cfg.Hkv, cfg.H // cfg.Hkv, cfg.V
+    groups16 = 2 if V <= 2304 and B * Hkv * -(-G * cfg.Tmax // 32) > 128 else 1
+    tiles = -(-(-(-V // 32)) // 8)                      # key tiles per wave
+    slots = 512 if groups16 * tiles <= 6 else 256       # workgroups on the chip at a time
+    blocks = -(-G * cfg.Tmax // (16 * groups16))
+    cost = lambda n: -(-B * -(-Hkv // n) * blocks // slots) * (n + 0.5)
+    heads = min(range(1, Hkv + 1), key=lambda n: (cost(n), -n))
+    return -(-Hkv // heads) * math.ceil(G * mean_text / (16 * groups16))
+
+
 def algorithmic_bytes(cfg, mean_text: float, n_layers: int) -> dict:
     """Compulsory bytes (each input read once, each output written once) per kernel and for the
     whole stage, and the similarity flops."""
@@ -94,6 +109,11 @@ def algorithmic_bytes(cfg, mean_text: float, n_layers: int) -> dict:
     # this function adds them to k_attn_stats when it sees that kernel); bytes of work, not compulsory ones
     per_kernel["stored_logits"] = 4 * B * H * T * V
     per_kernel["k_colsum_rows"] = per_kernel["stored_logits"] + 4 * B * H * V
+    # one sweep over the keys: fewer or more partial column sums than one per head (the caller adds the difference to
+    # the kernel that reads them when it sees k_attn_rows)
+    sums = 4 * B * V * column_sum_rows(cfg, T)
+    per_kernel["k_attn_rows"] = k_vis + q_txt + 8 * B * V + sums
+    per_kernel["more_column_sums"] = sums - 4 * B * H * V
     stage = (q_vis + k_vis + q_txt + 12 * B * V) + 12 * B * V + (vis_h + 8 * B * (V - k)) \
         + (vis_h + B * (P + T) * D * eh + out_rows * D * eh) + per_kernel["k_compact"]
     return {"per_kernel": per_kernel, "stage": stage, "sim_flops": 2.0 * B * (V - k) * k * D}
@@ -511,6 +531,11 @@ def main():
         alg["per_kernel"]["k_compact"] -= alg["per_kernel"]["kv_fixed_rows"]
     if "k_colsum_rows" in timing:
         alg["per_kernel"]["k_attn_stats"] += alg["per_kernel"]["stored_logits"]
+    if "k_attn_rows" in timing:
+        for name in ("k_score", "k_score_select", "k_score_select_kv"):
+            alg["per_kernel"][name] += alg["per_kernel"]["more_column_sums"]
+    if not any(name.startswith("k_compact") for name in timing):      # the merge's launch moved the K/V rows
+        alg["per_kernel"]["k_merge"] += alg["per_kernel"]["k_compact"]
     kernels = {}
     for name, (ms, n) in timing.items():
         avg_us = 1e3 * ms / n

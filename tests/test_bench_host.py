@@ -39,6 +39,9 @@ def test_algorithmic_bytes_of_the_benchmark_configuration():
     assert a["per_kernel"]["kv_fixed_rows"] == B * 4 * 2 * H * (P + T) * d * e
     assert a["per_kernel"]["k_compact"] == kv
     assert a["per_kernel"]["k_score_select_kv"] - a["per_kernel"]["k_score_select"] == a["per_kernel"]["kv_fixed_rows"]
+    # text rows: two blocks of 32 rows, eight workgroups of four heads an image, so 16 rows of column sums for 32 heads
+    assert a["per_kernel"]["k_attn_rows"] == B * (V * d * H * e + H * T * d * e + 8 * V + 4 * 16 * V)
+    assert a["per_kernel"]["more_column_sums"] == 4 * B * V * (16 - 32)
 
 
 def test_measured_traffic_is_only_quoted_for_the_kernels_the_summary_lists(tmp_path, monkeypatch):
@@ -62,7 +65,7 @@ def test_measured_traffic_is_only_quoted_for_the_kernels_the_summary_lists(tmp_p
 
 
 def test_the_committed_counter_summaries_name_the_kernels_of_their_workloads():
-    c6 = ["k_qsum", "k_mass_mfma", "k_attn_stats", "k_attn_colsum", "k_score_select_kv", "k_compact", "k_sim", "k_merge"]
+    c6 = ["k_qsum", "k_mass_mfma", "k_attn_rows", "k_score_select_kv", "k_compact", "k_sim", "k_merge"]
     c3 = ["k_qsum", "k_mass_mfma", "k_attn_stats", "k_colsum_rows", "k_score_select", "k_compact", "k_sim_f32",
           "k_sim_reduce", "k_merge"]
     for workload, kernels in (("C6", c6), ("C3", c3)):

@@ -126,8 +126,8 @@ size_t asap_workspace_bytes(const asap_params* p);
  * final rounding of s_raw / s_hat, and per-row softmax terms in fp32.
  * Rows of q_txt at or past text_len[b] are padding: they are never used, whatever they hold.
  * When the rows that rank are few (ASAP_ROWS_LAST, or (H / Hkv) * Tmax <= 28 with bf16 keys), their
- * logits are taken in the sweep that computes s and kept in the workspace, and the keys are read
- * twice instead of three times.
+ * logits are taken in the sweep that computes s and kept in the workspace, and the keys are not read
+ * again.
  */
 asap_status asap_score(asap_ctx* ctx, const asap_params* p,
                        const void* q_vis, const int64_t q_vis_stride[3],

@@ -975,7 +975,7 @@ __device__ __forceinline__ RowUnit find_row_unit(const AttnArgs& a, int B, int g
 constexpr int rows_slots(int rg, int tpw) { return rg * tpw <= 6 ? 1 : 2; }
 template <int NG, int RG, int TPW> constexpr size_t rows_lds_bytes() {
   return (size_t)rows_slots(RG, TPW) * ROWS_NW * 32 * NG * 32 + (size_t)16 * RG * (NG * 32 + 16) +
-         sizeof(float) * (2 * ROWS_NW * 16 * RG + 16 * RG + TPW * ROWS_NW * 32);
+         sizeof(float) * (2 * ROWS_NW * 16 * RG + 2 * 16 * RG + TPW * ROWS_NW * 32);
 }
 
 template <int NG, int RG, int TPW>
@@ -989,8 +989,8 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
   char* qlds = lds + NS * ROWS_NW * KTILE;
   float* st_m = reinterpret_cast<float*>(qlds + RB * QROW);                 // [8][RB]
   float* st_s = st_m + ROWS_NW * RB;                                         // [8][RB]
-  float* fin_l = st_s + ROWS_NW * RB;                                        // [RB]  rest of the row (log2 units)
-  float* lam = fin_l + RB;                                                   // [256 TPW]  discounts of the keys
+  float* fin_l = st_s + ROWS_NW * RB;                                        // [2][RB]  rest of the row (log2 units)
+  float* lam = fin_l + 2 * RB;                                                   // [256 TPW]  discounts of the keys
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, q4 = lane >> 4;
@@ -1126,6 +1126,13 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
     __builtin_amdgcn_sched_barrier(0);
   };
 
+  int par = 0;
+  auto park_q = [&](int to) {
+    if (q_here) *reinterpret_cast<uint4*>(qlds + qm * QROW + qpc * 16) = qx;
+    if (tid < RB) fin_l[to * RB + hidden(tid)] = lx;
+  };
+  park_q(0);
+  barrier_lds();
 #pragma unroll 1
   for (;; ++g) {
     f32x4_t e[TPW][RG][2];
@@ -1160,9 +1167,6 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
     };
     auto ring_read = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };    // a slot may be filled again
 
-    if (q_here) *reinterpret_cast<uint4*>(qlds + qm * QROW + qpc * 16) = qx;
-    if (tid < RB) fin_l[hidden(tid)] = lx;
-    barrier_lds();
     each([&](int r, int v) { m[r][v] = ATT_NEG; });
     static_for<TPW>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
@@ -1183,9 +1187,9 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
     });
     const bool last = g + 1 >= g_end;
     if (!last) {
+      load_q(g + 1);
       ring_read();
       start(g + 1);
-      load_q(g + 1);
     }
 
     // largest logit of every row, over the 16 lanes and then the waves; -M in log2 units, with the rest of the row
@@ -1200,7 +1204,7 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
     {
       float x[PICK];
       pick(st_m, x);
-      const float l = fin_l[hidden(mine)];
+      const float l = fin_l[par * RB + hidden(mine)];
 #pragma unroll
       for (int w = 1; w < PICK; ++w) x[0] = fmaxf(x[0], x[w]);
       const float big = fmaxf(over_row(x[0], [](float p, float q) { return fmaxf(p, q); }) * c2, l);
@@ -1230,6 +1234,12 @@ __global__ __launch_bounds__(64 * ROWS_NW, (rows_slots(RG, TPW) == 1 ? 4 : 2)) v
     each([&](int r, int v) { s[r][v] += dpp_f32<0x122>(s[r][v]); });
     each([&](int r, int v) { s[r][v] += dpp_f32<0x121>(s[r][v]); });
     leave(st_s, s);
+    // the next head's queries: every wave is past the products with this head's (first exchange), and the barrier of
+    // this exchange is the one they need; fin_l has two places, as slower waves may still read this head's
+    if (!last) {
+      par ^= 1;
+      park_q(par);
+    }
     barrier_lds();
     {
       float x[PICK];

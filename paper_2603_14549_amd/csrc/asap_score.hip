@@ -909,7 +909,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_colsum(AttnArgs a) {
 //   A workgroup walks GPW kv heads of an image, one after the other, and leaves the sum of their column
 //   sums: with every compute unit busy, further workgroups would only add rows for k_score to read, and
 //   the next head's first tiles are on their way while this head's statistics are exchanged.
-//   16 images x 32 heads x 2304 keys, 64 rows: 113 us for the two sweeps, 70 us here (each key read by two
+//   16 images x 32 heads x 2304 keys, 64 rows: 113 us for the two sweeps, 67 us here (each key read by two
 //   workgroups, 628 MB of L2 requests, 313 MB from HBM); 4 x 28 heads (4 kv heads) x 4096 keys, 48 rows: 49 -> 33 us;
 //   1 x 32 heads x 2304 keys, 64 rows: 20 -> 14 us.
 //   Key tiles go to LDS by direct loads (whole rows, no registers), a ring of its own per wave.

@@ -1625,23 +1625,21 @@ static int rows_heads_per_wg(const asap_params& p, int row_blocks, int rg) {
 }
 
 // Above ROWS_V2 keys a block of the one sweep has 16 rows, half of what the two sweeps take per pass over a
-// key tile in LDS, and a wave walks up to 16 tiles in a row.  Both forms of asap_score, timed over 480 shapes
-// of 2305 to 4096 keys: the one sweep is 1.13 times as fast on average; the two sweeps are where
-//  * the launch is many rounds of 256 workgroups (blocks x kv heads x images) and the text rows fill the two sweeps'
-//    blocks of 64 (113 to 128, or 49 to 64 rows): from 16 rounds on with d = 64 or one query head per kv head
-//    (16 x 32 heads x 2560 keys, 128 rows: 326 us, two sweeps 300; with more query heads per kv head the
-//    one sweep stays ahead at d = 128: 8 x 28 on 4 x 4096 keys 1.16 times); with d = 64 from 7.5 rounds on where
-//    there are at most 64 rows (16 x 32 x 2560: 136 and 126 us) or 16 query heads share their keys (partial column sums
-//    then outweigh the keys; 16 x 16 on 1 x 4096, 128 rows: 144 and 117 us);
-//  * at most 32 workgroups walk more than 12 tiles of 256 bytes a row (1 x 8 heads x 3617 keys, 32 rows: 38 and 34 us;
-//    with seven query heads per kv head the one sweep is ahead again, 47.8 and 48.5 us).
-// Between 8 and 16 rounds of 113 to 128 rows either form is ahead, by up to 10 % for sizes close to each other.
+// key tile, and a wave walks up to 16 tiles in a row.  Both forms of asap_score, timed over 780 shapes of 2305
+// to 4096 keys: the one sweep is 1.13 times as fast on average, 1.00 times in full launches of 113 to 128 rows with a
+// kv head per query head (0.93 to 1.12 for sizes close to each other: 16 x 32 heads x 2560 keys 309 us, two sweeps 300;
+// 16 x 40 heads 385 and 402).  The two sweeps are taken where they are clearly ahead:
+//  * 16 or more query heads of 64 components on one kv head, more than four rounds of 256 workgroups and text rows
+//    that fill the two sweeps' blocks of 64: the partial column sums of 16 rows each then outweigh the keys
+//    (16 x 16 heads on 1 x 4096 keys, 128 rows: 145 and 117 us; 16 x 32 on 2 x 2560, 64 rows: 104 and 94; with 80 rows
+//    6 x 64 on 4 x 2305 the one sweep, 86 and 108);
+//  * at most 32 workgroups that walk more than 12 tiles of 256 bytes a row (1 x 8 heads x 3617 keys, 32 rows: 38 and 34 us;
+//    with seven query heads per kv head the one sweep is not behind, 48.4 and 48.6 us).
 static bool two_sweeps_faster(const asap_params& p, int t_eff) {
   const int G = p.H / p.Hkv;
   const long wgs = (long)p.B * p.Hkv * ((G * t_eff + 15) / 16);
   const bool full = (t_eff + 63) / 64 * 64 - t_eff < 16;
-  if (full && wgs >= 4096 && (p.d == 64 || G == 1)) return true;
-  if (full && wgs >= 1920 && p.d == 64 && (t_eff <= 64 || G >= 16)) return true;
+  if (p.d == 64 && G >= 16 && full && wgs > 1024) return true;
   return p.d == 128 && p.V > 12 * 256 && wgs <= 32 && G <= 4;
 }
 

@@ -13,20 +13,25 @@
 //                   with d = 128: there the values go to LDS row-major and the operand is fetched
 //                   with the chip's transposing LDS read (ds_read_b64_tr_b16), two per operand.
 //   k_attention     B H ceil(N/256) workgroups of 512 threads = 8 waves (two per SIMD) of 32 queries.  Per
-//                   32-key tile a wave computes S^T = K_tile Q^T (keys are the tile rows, so lane l owns
-//                   query l % 32 and holds 16 of the tile's keys: the softmax bookkeeping is per lane),
-//                   then O^T += V^T_tile P^T, where the P^T operand is taken straight from the
+//                   sub-tile of 32 keys a wave computes S^T = K Q^T (keys are the tile rows, so lane l owns
+//                   query l % 32 and holds 16 of the keys: the softmax bookkeeping is per lane),
+//                   then O^T += V^T P^T, where the P^T operand is taken straight from the
 //                   accumulator registers: the contraction slice a lane half supplies is defined as
 //                   the keys that lane half already holds, and the V^T operand is stored to match.
-//                   A tile (keys, values^T, 32 discounts) goes to LDS by direct global -> LDS loads,
-//                   once for the eight waves, into a ring of PD + 2 slots, PD tiles ahead; the waits
+//                   A turn is 64 keys (32 with 4-byte elements): one barrier, one look at the maxima and one
+//                   change of the baseline per turn.  Its keys, values and discounts go to LDS by direct
+//                   global -> LDS loads, once for the eight waves, into rings of four slots; the waits
 //                   for those loads are placed by hand and no other vector-memory instruction is left
 //                   in the loop, because any wait the compiler adds for one would drain the ring.
-//                   The raw scores of tile t + 1 are computed in the same basic block as the
-//                   exponentials of tile t.  Measured on this chip, plain VALU work overlaps with the
-//                   matrix pipe only up to about one VALU instruction per 8 MFMA cycles and SIMD, the
-//                   rest adds to the MFMA time: the ~115 VALU instructions of a tile against its 16
-//                   MFMAs are what bounds the kernel.
+//                   The products of a turn stand in a row, each with the LDS read of the operand five
+//                   products on, the turn's loads spread between them.
+//   What bounds it (16 x 32 heads x 2403 positions, d = 128, bf16): issue first, power next.  A turn takes 3700
+//   cycles for the two waves of a SIMD, 2100 of them matrix instructions, 2200 the softmax when alone, and the
+//   clock falls from 2.4 to 2.0 GHz on random data (the same instructions on zeros: 1.35 ms; the products and
+//   loads alone 1.24 ms at 1.7 GHz).  Turns of 32 keys with a barrier each, offsets and operand addresses formed anew
+//   and the halves' maxima exchanged through LDS took 1.71 ms, now 1.60 (28 heads on 4, 6 x 1337 positions: 204, now
+//   196 us; f32, 2 x 28 x 2352: 1.74, now 1.66 ms).  Two groups of waves half a turn apart with a barrier per phase,
+//   one group's products beside the other's softmax, measured the same as one barrier and no order between them.
 #include "asap_device.hpp"
 #include "asap_launch.hpp"
 
@@ -118,9 +123,8 @@ template <> __device__ __forceinline__ void store4<bf16_t>(bf16_t* dst, const fl
 // bytes; in each group of 16 lanes, lane 4 a + c receives the c-th 16-bit element of the pieces named
 // by lanes a, 4 + a, 8 + a and 12 + a, in that order.
 typedef short att_i16x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint2 att_tr_read(const char* lds_ptr) {
-  const att_i16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) att_i16x4*)(uintptr_t)lds_address(lds_ptr));
+__device__ __forceinline__ uint2 att_tr_read(uint32_t lds_addr) {
+  const att_i16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) att_i16x4*)(uintptr_t)lds_addr);
   uint2 u;
   __builtin_memcpy(&u, &r, 8);
   return u;
@@ -130,26 +134,29 @@ __device__ __forceinline__ uint2 att_tr_read(const char* lds_ptr) {
 __device__ __forceinline__ int att_key_of(int v, int hf) { return 8 * (v >> 2) + 4 * hf + (v & 3); }
 
 constexpr int ATT_QWG = 256;                   // queries per workgroup
-#ifndef ATT_PD
-#define ATT_PD 2                               /* key tiles requested ahead */
-#endif
 constexpr int ATT_NW = 8;                      // waves per workgroup (two per SIMD), 32 queries each
 constexpr float ATT_LAZY = 8.0f;               // growth of a row maximum (log2 units) that moves the baseline
-constexpr int ATT_BIASB = 128;                 // bytes of per-key log-discounts staged with a key tile
 
 // LDS swizzles: the 16-byte piece p of row r is stored in slot p ^ x(r), so that 16 consecutive rows
 // spread over all banks for the strided operand reads while the loads still write 1 KiB at a time
 __device__ __forceinline__ int att_kswz(int row, int row_bytes) { return row_bytes <= 128 ? (row >> 1) & 7 : row & 15; }
-__device__ __forceinline__ int att_vswz(int row, int row_bytes) { return row_bytes <= 64 ? (row >> 2) & 3 : (row >> 1) & 7; }
+__device__ __forceinline__ int att_vswz(int row) { return (row >> 1) & 7; }      // rows of 128 bytes
 
 // how the mask acts on one (32 keys x 32 queries) tile
 enum { ATT_PLAIN = 0,     // every key precedes every query: no mask
        ATT_AHEAD = 1,     // every key follows every query and all queries are image rows: the key's discount
        ATT_GENERAL = 2 }; // anything else: decided per element
 
-// CH = 16-byte chunks of a row per lane half (row bytes = 32 * CH); PD = key tiles requested ahead
-template <typename T, int CH, int PD>
-__global__ __launch_bounds__(64 * ATT_NW) void k_attention(const T* __restrict__ q, Strides3 sq,
+// Sub-tiles of 32 keys that a wave takes per turn, and the LDS ring: four turns of keys, values and discounts.
+template <typename T> constexpr int att_sub() { return sizeof(T) == 2 ? 2 : 1; }
+constexpr int ATT_NS = 4;
+template <typename T> constexpr size_t att_lds_bytes(int d) {
+  return (size_t)ATT_NS * 32 * att_sub<T>() * (2 * d * sizeof(T) + sizeof(float));
+}
+
+// CH = 16-byte chunks of a row per lane half (row bytes = 32 * CH)
+template <typename T, int CH>
+__global__ __launch_bounds__(64 * ATT_NW, 2) void k_attention(const T* __restrict__ q, Strides3 sq,
                                                             const T* __restrict__ k, Strides3 sk,
                                                             const T* __restrict__ vt, int Npad,
                                                             const T* __restrict__ vrm, Strides3 sv,
@@ -161,13 +168,17 @@ __global__ __launch_bounds__(64 * ATT_NW) void k_attention(const T* __restrict__
   constexpr int E = elem<T>::per16;            // elements per 16-byte chunk
   constexpr int D = CH * 2 * E;                // head dimension
   constexpr int DT = D / 32;                   // 32-row tiles of O^T
-  constexpr int NPS = 32 / (2 * E);            // contraction steps of the second product per key tile
+  constexpr int SUB = att_sub<T>(), KEYS = 32 * SUB;        // keys per turn
+  constexpr int NPS = KEYS / (2 * E);          // contraction steps of the second product per turn
   constexpr int RB = 32 * CH;                  // bytes of a key row
-  constexpr int VB = 32 * (int)sizeof(T);      // bytes of a values^T row per key tile
-  constexpr int KTILE = 32 * RB, VTILE = D * VB, STAGE = KTILE + VTILE + ATT_BIASB;
-  constexpr int KLD = KTILE / 1024, VLD = VTILE / 1024;     // 1 KiB load instructions per tile
-  constexpr int TP = KLD + VLD + 1;            // load instructions per tile: keys, values^T, discounts
-  constexpr int NS = PD + 2;                   // ring slots: tile t (values, discounts), t+1 (keys), PD in flight
+  constexpr int VB = KEYS * (int)sizeof(T);    // bytes of a values^T row per turn
+  static_assert(VB == 128, "att_vswz");
+  constexpr int KTILE = KEYS * RB, VTILE = D * VB, BTILE = KEYS * (int)sizeof(float);
+  constexpr int KLD = KTILE / 1024 / NW, VLD = VTILE / 1024 / NW;    // 1 KiB load instructions per wave and turn
+  static_assert(KLD >= 1 && VLD >= 1, "every wave loads");
+  constexpr int NS = ATT_NS;                   // slots of the three rings
+  constexpr int VRING = NS * KTILE, BRING = VRING + NS * VTILE;
+  static_assert((size_t)(BRING + NS * BTILE) == att_lds_bytes<T>(D), "LDS");
   // 2-byte elements with d = 128: the values stay row-major, as the caller has them, and the second
   // product's operand is fetched with the transposing LDS read of this chip (see att_tr_read)
   constexpr bool TR = (E == 8 && CH == 8);
@@ -201,8 +212,8 @@ __global__ __launch_bounds__(64 * ATT_NW) void k_attention(const T* __restrict__
     return first < N ? jl : -1;
   };
   const int jl_wg = last_key(iw, ATT_QWG), jl_w = last_key(i0, 32);
-  const int ntiles = jl_wg / 32 + 1;
-  const int my_tiles = jl_w / 32 + 1;           // this wave's tiles are 0 .. my_tiles-1 (none if its queries are past N)
+  const int turns = jl_wg / KEYS + 1;
+  const int my_turns = jl_w < 0 ? 0 : jl_w / KEYS + 1;      // this wave's turns are 0 .. my_turns-1 (none if its queries are past N)
 
   // queries: B operand of S^T, pieces 2c + hf of the row
   uint4 qa[CH];
@@ -214,54 +225,55 @@ __global__ __launch_bounds__(64 * ATT_NW) void k_attention(const T* __restrict__
     for (int c = 0; c < CH; ++c) qa[c] = ldg16(qrow + c * 32);
   }
 
-  // Tile loads: the 1 KiB pieces of a tile (keys, then values^T, then one piece with the 32 discounts)
-  // are dealt to the waves round-robin.  Tile numbers past the last one load the last tile again, so
-  // every iteration issues the same number of loads and one wait count serves the whole loop.
+  // Loads: a turn's keys and its values are 8 KLD and 8 VLD pieces of 1 KiB, wave w takes the pieces w, w + 8, ...; one
+  // wave also brings the discounts.  Offsets move on by a turn at a time and stop at the last row (keys and
+  // row-major values) or turn (values^T, discounts), so that every turn issues the same number of loads.
   const char* kg = reinterpret_cast<const char*>(k + b * sk.b + g * sk.h);
-  const int64_t krow_bytes = sk.r * (int64_t)sizeof(T);
   const char* vg = TR ? reinterpret_cast<const char*>(vrm + b * sv.b + g * sv.h)
                       : reinterpret_cast<const char*>(vt + ((int64_t)b * Hkv + g) * D * Npad);
-  const int64_t vrow_bytes = sv.r * (int64_t)sizeof(T);
   const char* bg = reinterpret_cast<const char*>(bias2 + (int64_t)b * Npad);
-  auto issue_tile = [&](auto slot_c, int t) {          // tile t goes to ring slot t % NS = slot_c
-    const uint32_t st = lds_addr + (uint32_t)decltype(slot_c)::value * STAGE;
-    const int j0 = min(t, ntiles - 1) * 32;
-#pragma unroll
-    for (int u = 0; u < (TP + NW - 1) / NW; ++u) {
-      const int pc = wave + NW * u;
-      // (the first comparison of each pair is known when compiling and mostly decides)
-      if (NW * u < KLD && (NW * (u + 1) <= KLD || pc < KLD)) {
-        const int off = pc * 1024 + 16 * lane, row = off / RB, slot = (off % RB) >> 4;
-        const int piece = slot ^ att_kswz(row, RB);
-        const uint32_t voff = (uint32_t)((int64_t)min(j0 + row, N - 1) * krow_bytes) + piece * 16;
-        load_to_lds16(kg, voff, st + pc * 1024);
-      } else if (NW * u < KLD + VLD && (NW * (u + 1) <= KLD + VLD || pc < KLD + VLD)) {
-        const int pv = pc - KLD;
-        if constexpr (TR) {
-          // row-major values: 4 key rows of 256 bytes per instruction, piece p of row r in slot p ^ 4 (r & 3)
-          const int off = pv * 1024 + 16 * lane, row = off / RB, slot = (off % RB) >> 4;
-          const int piece = slot ^ ((row & 3) << 2);
-          const uint32_t voff = (uint32_t)((int64_t)min(j0 + row, N - 1) * vrow_bytes) + piece * 16;
-          load_to_lds16(vg, voff, st + KTILE + pv * 1024);
-        } else {
-          const int off = pv * 1024 + 16 * lane, row = off / VB, slot = (off % VB) >> 4;
-          const int piece = slot ^ att_vswz(row, VB);
-          const uint32_t voff = (uint32_t)(((int64_t)row * Npad + j0) * sizeof(T)) + piece * 16;
-          load_to_lds16(vg, voff, st + KTILE + pv * 1024);
-        }
-      } else if (pc < TP) {
-        if (lane < ATT_BIASB / 16) load_to_lds16(bg, (uint32_t)(j0 * 4 + 16 * lane), st + KTILE + VTILE);
-      }
-    }
+  const int off0 = wave * 1024 + 16 * lane;    // of the wave's first piece in a slot
+  auto rows_ahead = [](int64_t bytes) { return (uint32_t)min(bytes, (int64_t)0x7fffffff); };
+  const int64_t krow_bytes = sk.r * (int64_t)sizeof(T), vrow_bytes = TR ? sv.r * (int64_t)sizeof(T) : Npad * (int64_t)sizeof(T);
+  constexpr int KSTEP = 1024 * NW / RB, VSTEP = 1024 * NW / (TR ? RB : VB);     // rows between two pieces of a wave
+  const int krow = off0 / RB, kpiece = ((off0 % RB) >> 4) ^ att_kswz(krow, RB);
+  const uint32_t kmax = (uint32_t)((N - 1) * krow_bytes) + kpiece * 16;
+  uint32_t koff = (uint32_t)min((int64_t)krow, (int64_t)N - 1) * (uint32_t)krow_bytes + kpiece * 16;
+  const uint32_t kturn = rows_ahead(KEYS * krow_bytes), kstep = rows_ahead(KSTEP * krow_bytes);
+  uint32_t voff, vmax, vturn, vstep;
+  if constexpr (TR) {
+    // row-major values: piece p of row r in slot p ^ 4 (r & 3)
+    const int row = off0 / RB, piece = ((off0 % RB) >> 4) ^ ((row & 3) << 2);
+    vmax = (uint32_t)((N - 1) * vrow_bytes) + piece * 16;
+    voff = (uint32_t)min(row, N - 1) * (uint32_t)vrow_bytes + piece * 16;
+    vturn = rows_ahead(KEYS * vrow_bytes);
+    vstep = rows_ahead(VSTEP * vrow_bytes);
+  } else {
+    const int row = off0 / VB, piece = ((off0 % VB) >> 4) ^ att_vswz(row);
+    voff = (uint32_t)(row * vrow_bytes) + piece * 16;
+    vmax = voff + (uint32_t)(turns - 1) * VB;
+    vturn = VB;
+    vstep = (uint32_t)(VSTEP * vrow_bytes);
+  }
+  auto issue_keys = [&](uint32_t slot, int u) {       // piece u of the next turn's
+    load_to_lds16(kg, u ? min(koff + u * kstep, kmax) : koff, lds_addr + slot * KTILE + wave * 1024 + u * NW * 1024);
+    if (u == KLD - 1) koff = min(koff + kturn, kmax);
   };
-  // (A constant for either kind of wave: the number as a run-time switch, and the tests of which piece a load
-  // instruction is for, were a dozen scalar branches per tile, 1.80 ms against 1.78.)
-  // wait until only the loads of the newest `tiles` tiles are outstanding: the first TP % NW waves issue one more
-  // per tile than the others
-  auto wait_tiles = [&](auto tiles) {
-    constexpr int few = decltype(tiles)::value * (TP / NW), most = decltype(tiles)::value * ((TP + NW - 1) / NW);
-    if (TP % NW != 0 && wave < TP % NW) wait_vmem_but<most>();
-    else wait_vmem_but<few>();
+  auto issue_values = [&](uint32_t slot, int u) {
+    load_to_lds16(vg, u ? (TR ? min(voff + u * vstep, vmax) : voff + u * vstep) : voff,
+                  lds_addr + VRING + slot * VTILE + wave * 1024 + u * NW * 1024);
+    if (u == VLD - 1) voff = min(voff + vturn, vmax);
+  };
+  static_assert(KLD <= 2 && VLD <= 2, "u * step stays below 2^32");
+  const bool bias_wave = wave == 0;            // the one that brings the discounts
+  auto issue_bias = [&](uint32_t slot, int t) {
+    if (bias_wave && lane < BTILE / 16)
+      load_to_lds16(bg, (uint32_t)(min(t, turns - 1) * BTILE + 16 * lane), lds_addr + BRING + slot * BTILE);
+  };
+  // all but the loads of the newest two turns
+  auto wait_turn = [&] {
+    if (bias_wave) wait_vmem_but<2 * (KLD + VLD + 1)>();
+    else wait_vmem_but<2 * (KLD + VLD)>();
   };
 
   f32x16_t o[DT];
@@ -271,74 +283,122 @@ __global__ __launch_bounds__(64 * ATT_NW) void k_attention(const T* __restrict__
     for (int v = 0; v < 16; ++v) o[t][v] = 0.0f;
   float m_run = -INFINITY, l_run = 0.0f;
 
-  // operand read offsets inside a tile.  The values^T swizzle of row tt * 32 + n does not depend on tt
-  // (it looks at row bits below 5 only), so one offset per contraction step serves all DT row tiles.
-  const int k_off = n * RB, k_x = att_kswz(n, RB);
-  int v_off[NPS];
+  // Operand addresses of slot 0, one register each: hidden from the compiler, which would otherwise form them
+  // anew for every turn; a turn's slot is then an immediate offset.
+  auto hidden = [](uint32_t x) { asm volatile("" : "+v"(x)); return x; };
+  auto lds_read16 = [](uint32_t addr) {
+    const auto x = *(const __attribute__((address_space(3))) u32x4_nt*)(uintptr_t)addr;
+    return make_uint4(x.x, x.y, x.z, x.w);
+  };
+  uint32_t k_at[CH];
 #pragma unroll
-  for (int c = 0; c < NPS; ++c) v_off[c] = n * VB + (((2 * c + hf) ^ att_vswz(n, VB)) << 4);
-
+  for (int c = 0; c < CH; ++c) k_at[c] = hidden(lds_addr + n * RB + (((2 * c + hf) ^ att_kswz(n, RB)) << 4));
   // Transposing read (TR): a lane is both a source -- it names 8 bytes, four consecutive columns of one key
   // row -- and a receiver.  Inside a group of 16 lanes, source 4 i + a names key i of four consecutive
   // keys and column block a, and lane 4 a + c receives column 4 a + c of those four keys: the 16 lanes
   // cover 16 consecutive columns (rows of values^T) with four keys each, which is half of the
   // operand.  The key of slot e of contraction step c for lane half hf is 16 c + 8 (e / 4) + 4 hf + e % 4,
   // the order in which the first product leaves P^T in the accumulators.
-  const int src16 = lane & 15, src_key = src16 >> 2;
-  const int vtr_base = (4 * hf + src_key) * RB + ((2 * ((lane >> 4) & 1) + ((src16 & 3) >> 1)) << 4) + 8 * (src16 & 1);
+  // Row tile tt of values^T = columns 32 tt .. 32 tt + 31 = 16-byte pieces 4 tt .. 4 tt + 3 of a key row, stored in
+  // slots (4 tt + x) ^ 4 (key & 3).
+  // (Otherwise: the values^T swizzle of row tt * 32 + n looks at row bits below 5 only, so one address per
+  // contraction step serves all DT row tiles.)
+  uint32_t v_at[TR ? DT : NPS];
+  if constexpr (TR) {
+    const int src16 = lane & 15, src_key = src16 >> 2;
+    const int base = (4 * hf + src_key) * RB + ((2 * ((lane >> 4) & 1) + ((src16 & 3) >> 1)) << 4) + 8 * (src16 & 1);
+#pragma unroll
+    for (int tt = 0; tt < DT; ++tt) v_at[tt] = hidden(lds_addr + VRING + base + ((tt ^ src_key) << 6));
+  } else {
+#pragma unroll
+    for (int c = 0; c < NPS; ++c) v_at[c] = hidden(lds_addr + VRING + n * VB + (((2 * c + hf) ^ att_vswz(n)) << 4));
+  }
 
-  // S^T of the wave's queries against key tile t, raw (unscaled) products
-  auto scores = [&](auto slot_c, f32x16_t& s) {
-    const char* Kt = lds + decltype(slot_c)::value * STAGE;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) s[v] = 0.0f;
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const uint4 a = *reinterpret_cast<const uint4*>(Kt + k_off + (((2 * c + hf) ^ k_x) << 4));
-      mma32<T>(s, a, qa[c]);
+  // The matrix phase in front of turn t + 1: S^T of the wave's queries against that turn's keys (raw, unscaled
+  // products), then O^T += V^T P^T of turn t: piece 2c + hf of a values^T row holds the keys this lane half has in
+  // P^T.  Item by item, in this order: one product, and the LDS read of the operand AHEAD products on -- the first ones
+  // in front of the barrier, so that no product waits for LDS (left to itself the compiler reads an operand right in
+  // front of its product).
+  constexpr int SI = CH * SUB, ITEMS = SI + NPS * DT, AHEAD = 5, RING = AHEAD + 1;
+  f32x16_t s[SUB];
+  uint4 pb[NPS], op[RING];
+  auto read_item = [&](auto i_c, auto next_c, auto cur_c) {
+    constexpr int I = decltype(i_c)::value, NEXT = decltype(next_c)::value, CUR = decltype(cur_c)::value;
+    if constexpr (I < SI) {
+      op[I % RING] = lds_read16(k_at[I / SUB] + NEXT * KTILE + (I % SUB) * 32 * RB);
+    } else if constexpr (I < ITEMS) {
+      constexpr int c = (I - SI) / DT, tt = (I - SI) % DT;
+      if constexpr (TR) {
+        const uint32_t src = v_at[tt] + CUR * VTILE + 16 * c * RB;
+        const uint2 lo = att_tr_read(src), hi = att_tr_read(src + 8 * RB);
+        op[I % RING] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      } else {
+        op[I % RING] = lds_read16(v_at[c] + CUR * VTILE + tt * 32 * VB);
+      }
     }
   };
-
-  // One key tile t, whose raw scores s arrive from the previous step: the mask, the softmax terms,
-  // the product with the values -- and the raw scores of tile t + 1, whose matrix instructions stand in
-  // the same basic block as the exponentials so that the two run side by side.
+  auto first_items = [&](auto next_c, auto cur_c) {
+    static_for<AHEAD>([&](auto i_c) { read_item(i_c, next_c, cur_c); });
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto multiply = [&](auto next_c, auto cur_c, auto count_c, auto loads) {
+#pragma unroll
+    for (int x = 0; x < SUB; ++x)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) s[x][v] = 0.0f;
+    static_for<decltype(count_c)::value>([&](auto i_c) {
+      constexpr int I = decltype(i_c)::value;
+      if constexpr (I < SI) mma32<T>(s[I % SUB], op[I % RING], qa[I / SUB]);
+      else mma32<T>(o[(I - SI) % DT], op[I % RING], pb[(I - SI) / DT]);
+      if constexpr (I + AHEAD < decltype(count_c)::value) read_item(std::integral_constant<int, I + AHEAD>{}, next_c, cur_c);
+      loads(i_c);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // The vector phase of turn t: the mask on the raw scores, the baseline, the softmax terms.
   // The exponent's baseline m_run of a query follows the running maximum lazily: it moves only when the
   // maximum has grown by more than ATT_LAZY (in log2 units), so that the accumulated columns are rescaled
-  // a few times per query instead of at most tiles; terms are then at most 2^ATT_LAZY, and the quotient
+  // a few times per query instead of at most turns; terms are then at most 2^ATT_LAZY, and the quotient
   // O / l does not depend on the baseline.
-  auto step = [&](auto slot_c, int t, f32x16_t& s, f32x16_t& s_next) {
-    constexpr int SLOT = decltype(slot_c)::value;         // t % NS, known at compile time: the LDS reads of the
-    const int j0 = t * 32;                                // tile then take their slot as an immediate offset
-    // the mask, by the kind of tile (a wave-uniform choice; only the few lines that apply it differ)
-    const int mode = (j0 + 31 <= i0) ? ATT_PLAIN
-                     : (j0 > i0 + 31 && bidir && i0 >= img_lo && i0 + 31 < img_hi) ? ATT_AHEAD : ATT_GENERAL;
-    if (mode != ATT_PLAIN) {                   // ATT_PLAIN: raw, the scale goes into the exponent below
-      // discounts of this lane's 16 keys, staged with the tile
-      const char* Bt = lds + SLOT * STAGE + KTILE + VTILE;
+  const bool wave_img = bidir && i0 >= img_lo && i0 + 31 < img_hi;
+  auto softmax = [&](auto slot_c, int t) {
+#pragma unroll
+    for (int x = 0; x < SUB; ++x) {
+      // the mask, by the kind of sub-tile (a wave-uniform choice; ATT_PLAIN: raw, the scale goes into the exponent)
+      const int j0 = t * KEYS + 32 * x;
+      const int mode = (j0 + 31 <= i0) ? ATT_PLAIN : (j0 > i0 + 31 && wave_img) ? ATT_AHEAD : ATT_GENERAL;
+      if (mode == ATT_PLAIN) continue;
+      // discounts of this lane's 16 keys
+      const char* Bt = lds + BRING + decltype(slot_c)::value * BTILE + 128 * x;
       float kbias[16];
 #pragma unroll
       for (int gq = 0; gq < 4; ++gq) {
-        const float4 x = *reinterpret_cast<const float4*>(Bt + (8 * gq + 4 * hf) * 4);
-        kbias[4 * gq] = x.x; kbias[4 * gq + 1] = x.y; kbias[4 * gq + 2] = x.z; kbias[4 * gq + 3] = x.w;
+        const float4 y = *reinterpret_cast<const float4*>(Bt + (8 * gq + 4 * hf) * 4);
+        kbias[4 * gq] = y.x; kbias[4 * gq + 1] = y.y; kbias[4 * gq + 2] = y.z; kbias[4 * gq + 3] = y.w;
       }
       if (mode == ATT_AHEAD) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[v] = fmaf(kbias[v], inv_c2, s[v]);
+        for (int v = 0; v < 16; ++v) s[x][v] = fmaf(kbias[v], inv_c2, s[x][v]);
       } else {
         const bool q_img = bidir && qi >= img_lo && qi < img_hi;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int j = j0 + att_key_of(v, hf);
           const float ahead = q_img ? kbias[v] : -INFINITY;      // a key after the query
-          s[v] += (j <= qi ? 0.0f : ahead) * inv_c2;
+          s[x][v] += (j <= qi ? 0.0f : ahead) * inv_c2;
         }
       }
     }
-    float mx = s[0];
+    float mx = s[0][0];
 #pragma unroll
-    for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32));        // both lane halves of a query see the same maximum
-    // maxima are kept in units of the raw products (finite from the first tile on: key 0 precedes
+    for (int x = 0; x < SUB; ++x)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[x][v]);
+    {
+      const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+      mx = fmaxf(__uint_as_float(y[0]), __uint_as_float(y[1]));      // both lane halves of a query see the same maximum
+    }
+    // maxima are kept in units of the raw products (finite from the first turn on: key 0 precedes
     // every query)
     const bool moved = mx > m_run + lazy_raw;
     if (__any(moved)) {
@@ -358,63 +418,83 @@ __global__ __launch_bounds__(64 * ATT_NW) void k_attention(const T* __restrict__
         }
     }
     const float m_c = m_run * c2;
-    scores(std::integral_constant<int, (SLOT + 1) % NS>{}, s_next);
-    float p[16], psum = 0.0f;
+    float psum[SUB];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      p[v] = fast_exp2_att(fmaf(s[v], c2, -m_c));
-      psum += p[v];
-    }
-    l_run += psum;
-    uint4 pb[NPS];
+    for (int x = 0; x < SUB; ++x) {
+      float p[16];
+      psum[x] = 0.0f;
 #pragma unroll
-    for (int c = 0; c < NPS; ++c) pb[c] = att_pack16<T>(&p[c * E]);
-    // O^T += V^T_tile P^T: piece 2c + hf of a values^T row holds the keys this lane half has in P^T
-    const char* Vt = lds + SLOT * STAGE + KTILE;
-#pragma unroll
-    for (int c = 0; c < NPS; ++c)
-#pragma unroll
-      for (int tt = 0; tt < DT; ++tt) {
-        uint4 va;
-        if constexpr (TR) {
-          // row tile tt of values^T = columns 32 tt .. 32 tt + 31 = 16-byte pieces 4 tt .. 4 tt + 3 of a key
-          // row, stored in slots (4 tt + x) ^ 4 (key & 3)
-          const char* src = Vt + vtr_base + 16 * c * RB + ((tt ^ src_key) << 6);
-          const uint2 lo = att_tr_read(src), hi = att_tr_read(src + 8 * RB);
-          va = make_uint4(lo.x, lo.y, hi.x, hi.y);
-        } else {
-          va = *reinterpret_cast<const uint4*>(Vt + v_off[c] + tt * 32 * VB);
-        }
-        mma32<T>(o[tt], va, pb[c]);
+      for (int v = 0; v < 16; ++v) {
+        p[v] = fast_exp2_att(fmaf(s[x][v], c2, -m_c));
+        psum[x] += p[v];
       }
+#pragma unroll
+      for (int c = 0; c < NPS / SUB; ++c) pb[x * (NPS / SUB) + c] = att_pack16<T>(&p[c * E]);
+    }
+    l_run += SUB == 2 ? psum[0] + psum[SUB - 1] : psum[0];
   };
 
-  // Tiles 0 .. PD are requested up front; iteration t requests tile t + 1 + PD and, before its barrier,
-  // waits for everything but the newest PD - 1 tiles: tile t + 2 has then landed.  The queries are
-  // touched here so that the compiler's wait for their loads stands in front of the loop, not inside
-  // it, where it would also wait for the tile requests.
+  // Turn t of a wave: the softmax of turn t, then the products in front of turn t + 1, then the turn's one barrier.
+  // Under the products the wave asks for its share of the keys of turn t + 4, of the values of turn t + 3 and of the
+  // discounts of turn t + 3, into slots that were last read before the previous barrier (keys of turn t, values and
+  // discounts of turn t - 1).  At the barrier everything but the newest two turns' loads has landed: the keys of
+  // turn t + 2, the values and discounts of turn t + 1, i.e. what turn t + 1 reads.
+  // The queries are touched here so that the compiler's wait for their loads stands in front of the loop, not
+  // inside it, where it would also wait for the ring.
 #pragma unroll
   for (int c = 0; c < CH; ++c) asm volatile("" ::"v"(qa[c].x), "v"(qa[c].y), "v"(qa[c].z), "v"(qa[c].w));
-  static_assert(NS % 2 == 0, "the two score buffers swap roles every tile, the ring turns every NS tiles");
-  static_for<PD + 1>([&](auto t_c) { issue_tile(t_c, decltype(t_c)::value); });
-  wait_tiles(std::integral_constant<int, PD - 1>{});
-  barrier_keep_loads();
-  // The loop runs over whole turns of the ring, so that a tile's slot is a compile-time constant, and
-  // the raw scores alternate between two register sets instead of being copied.
-  f32x16_t s_even, s_odd;
-  if (my_tiles > 0) scores(std::integral_constant<int, 0>{}, s_even);
-  for (int t0 = 0; t0 < ntiles; t0 += NS) {
+  static_for<3>([&](auto t_c) {
+    constexpr int U = decltype(t_c)::value;
+#pragma unroll
+    for (int u = 0; u < KLD; ++u) issue_keys(U, u);
+    issue_bias(U, U);
+    if constexpr (U > 0) {
+#pragma unroll
+      for (int u = 0; u < VLD; ++u) issue_values(U - 1, u);
+    }
+  });
+  auto end_turn = [&] {
+    wait_turn();
+    __builtin_amdgcn_sched_barrier(0);
+    barrier_keep_loads();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  end_turn();
+  {
+    constexpr std::integral_constant<int, 0> zero{};
+    first_items(zero, zero);
+    multiply(zero, zero, std::integral_constant<int, SI>{}, [&](auto i_c) {
+      constexpr int I = decltype(i_c)::value;
+      if constexpr (I < KLD) issue_keys(3, I);
+      else if constexpr (I < KLD + VLD) issue_values(2, I - KLD);
+      else if constexpr (I == KLD + VLD) issue_bias(2, 2);
+    });
+    end_turn();
+  }
+  for (int t0 = 0; t0 < turns; t0 += NS) {
     static_for<NS>([&](auto u_c) {
       constexpr int U = decltype(u_c)::value;
+      constexpr std::integral_constant<int, (U + 1) % NS> next{};
       const int t = t0 + U;
-      if (t < ntiles) {                        // the same for every wave of the workgroup
-        issue_tile(std::integral_constant<int, (U + 1 + PD) % NS>{}, t + 1 + PD);
-        if (t < my_tiles) {
-          if constexpr (U % 2 == 0) step(u_c, t, s_even, s_odd);
-          else step(u_c, t, s_odd, s_even);
+      if (t < turns) {                         // the same for every wave of the workgroup
+        auto loads = [&](auto i_c) {          // spread over the products
+          constexpr int I = decltype(i_c)::value, EVERY = ITEMS / (KLD + VLD), J = I / EVERY;
+          if constexpr (I % EVERY == 2) {
+            if constexpr (J < KLD) issue_keys(U % NS, J);
+            else if constexpr (J < KLD + VLD) issue_values((U + 3) % NS, J - KLD);
+          }
+          if constexpr (I == 4) issue_bias((U + 3) % NS, t + 3);
+        };
+        if (t < my_turns) {
+          softmax(u_c, t);
+          first_items(next, u_c);
+          __builtin_amdgcn_s_setprio(1);
+          multiply(next, u_c, std::integral_constant<int, ITEMS>{}, loads);
+          __builtin_amdgcn_s_setprio(0);
+        } else {
+          static_for<ITEMS>([&](auto i_c) { loads(i_c); });
         }
-        wait_tiles(std::integral_constant<int, PD - 1>{});
-        barrier_keep_loads();
+        end_turn();
       }
     });
   }
@@ -470,12 +550,10 @@ static hipError_t attention_typed(const asap_params& p, const void* q, Strides3 
   const float c2 = 1.4426950408889634f / sqrtf((float)p.d);
   const int units = p.B * p.H * ((N + ATT_QWG - 1) / ATT_QWG);
   const dim3 grid = grid_of(NUM_XCD * (int64_t)((units + NUM_XCD - 1) / NUM_XCD));
-  const int ch = p.d / E / 2;
-  constexpr int PD = ATT_PD;                   // key tiles requested ahead
-  const size_t lds = (PD + 2) * ((size_t)(32 * 32 * ch + p.d * 32 * sizeof(T)) + ATT_BIASB);
+  const size_t lds = att_lds_bytes<T>(p.d);
 #define ASAP_ATT(CHV)                                                                                          \
   do {                                                                                                         \
-    auto kern = k_attention<T, CHV, PD>;                                                                                    \
+    auto kern = k_attention<T, CHV>;                                                                           \
     if (lds > 48 * 1024) {                                                                                     \
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                  \
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                \
@@ -485,11 +563,9 @@ static hipError_t attention_typed(const asap_params& p, const void* q, Strides3 
                 static_cast<const T*>(k), sk, vt, Npad, static_cast<const T*>(v), sv, bias2, bidir ? 1 : 0,    \
                 static_cast<T*>(out), p.B, p.H, p.Hkv, N, p.P, p.V, c2);                                                                       \
   } while (0)
-  if (ch == 4) ASAP_ATT(4);
-  else if (ch == 8) ASAP_ATT(8);
-  else if (ch == 16 && E == 4) {
-    if constexpr (E == 4) ASAP_ATT(16);
-  } else return hipErrorInvalidValue;
+  if (p.d == 64) ASAP_ATT(32 / E);
+  else if (p.d == 128) ASAP_ATT(64 / E);
+  else return hipErrorInvalidValue;
 #undef ASAP_ATT
   return hipGetLastError();
 }

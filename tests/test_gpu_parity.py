@@ -703,6 +703,20 @@ def test_attention_forward_random_shapes(ctx, seed):
     _attention_case(ctx, cfg, mask, float(r.choice([1.0, 0.6])))
 
 
+@pytest.mark.parametrize("d,qk_dtype,mask", [(128, "bf16", True), (128, "bf16", False), (64, "bf16", True),
+                                             (128, "f32", True), (64, "f32", False)])
+@pytest.mark.parametrize("N", [2, 31, 33, 63, 64, 65, 129, 255, 256, 257, 320, 321, 577])
+def test_attention_forward_at_the_edges_of_a_turn(ctx, N, d, qk_dtype, mask):
+    """Sequence lengths around the 32 / 64 keys of a turn, the four turns of the LDS rings and the 256 queries of a
+    workgroup, where the loads stop at the last row and waves run out of turns before their workgroup does."""
+    P, Tmax = min(3, N // 3), 1
+    V = N - P - Tmax
+    cfg = synth.StageConfig(name="edge", B=1, D=128, H=2, Hkv=1, d=d, P=P, V=V, Tmax=Tmax, k=max(1, V // 3),
+                            qk_dtype=qk_dtype, h_dtype="bf16", kv_dtype="bf16", n_clusters=3, outliers=False, L_kv=0,
+                            seed=7900 + N)
+    _attention_case(ctx, cfg, binding.ASAP_MASK_KEYBIAS if mask else binding.ASAP_MASK_OFF, 1.0)
+
+
 def test_attention_argument_checks_and_strided_inputs(ctx):
     """asap_attention refuses a short workspace, a missing s_hat and an unaligned pointer before it
     launches anything, and takes q / k / v as strided views (here: slices of wider buffers)."""

@@ -88,7 +88,9 @@ def algorithmic_bytes(cfg, mean_text: float, n_layers: int) -> dict:
         "k_mass_mfma": k_vis + 12 * B * V,
         "k_attn_stats": k_vis + q_txt + 8 * B * V,
         "k_attn_colsum": k_vis + q_txt + 4 * B * H * V,
-        "k_mass_finish": 20 * B * V,
+        "k_mass_small": k_vis + 12 * B * V,
+        "k_mass_small_ride": k_vis + 12 * B * V,
+        "k_mass_finish": 8 * B * V,
         "k_rowstats_logits": 4 * B * H * V + 8 * B * V,
         "k_colsum_logits": 8 * B * H * V,
         "k_score": 4 * B * H * V + 16 * B * V,

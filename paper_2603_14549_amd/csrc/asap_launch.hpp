@@ -22,18 +22,18 @@ struct ScoreWorkspace {
   int row_pairs;     // pairs of 32-row blocks of text queries, each with sweep workgroups of its own
                      // (one_sweep: blocks of 16 one_sweep rows of all text rows of a kv head's query heads)
   int heads_per_wg;  // one_sweep: kv heads a workgroup walks
-  int head_splits;   // kv-head groups of the mass sweep with workgroups of their own (small batches)
+  int mass_small;    // 1: k_mass_small[_ride] sweeps the keys for the masses and adds up the query sums itself (small batches)
+  int mass_keys;     // ... in tiles of so many keys
   int store_logits;  // 1: the first text-row sweep leaves its logits and the column sums read those
   size_t off_qpart;  // double [B,H,q_chunks,d]  partial sums of visual queries
   size_t off_qsplit; // bf16   [B,Hkv,4,d]       their sums per kv head, split into four bf16 pieces per component
   size_t off_s64;    // double [B,V]             raw attention mass before rounding
-  int finish;        // 1: k_mass_finish adds up partial masses and takes their (min, max)
+  int finish;        // 1: k_mass_finish takes the (min, max) of an image
   int mm_n;          // (min, max) pairs of s per image: one per key tile, or one (finish)
-  size_t off_mm;     // double [B,mm_n,2]        those pairs (those of the key tiles in the place of qpart)
+  size_t off_mm;     // double [B,mm_n,2]        those pairs (those of the key tiles in the place of qpart or qsplit)
   size_t off_pstat;  // float  [B,H,splits,2,NR] per-split (max, sum) of every text row, NR = 64 row_pairs
   size_t off_upart;  // float  [B,H,row_pairs,V] column sums of normalised weights per head and row pair
                      //        (one_sweep: per group of kv heads and row block, those an image has one after the other)
-  size_t off_spart;  // double [head_splits,B,V] partial masses (head_splits > 1)
   size_t off_zlog;   // float  [B,H,t_eff,V]     raw logits of the ranking rows (ride, store_logits)
   size_t total;
 };

@@ -15,8 +15,9 @@
 //                 When the text rows that rank the tokens are few (rows of a kv head's query heads
 //                 <= 28, bf16), they ride in the free rows of that tile: the sweep then also leaves
 //                 their raw logits in the workspace, and no further sweep over the keys is needed.
-//                 Small batches cut the kv heads into groups with workgroups of their own, which
-//                 leave partial masses; k_mass_finish adds them and takes min / max.
+//   k_mass_small, k_mass_small_ride   the same for small batches: a wave per kv head (up to 16), which takes
+//                 the place of k_qsplit as well
+//   k_mass_finish the (min, max) of a whole image, where those of its key tiles have no room
 //   then, bf16 and up to 4096 keys (but see two_sweeps_faster),
 //   k_attn_rows   the softmax of the text rows in one sweep over the keys: terms stay in registers until
 //                 their row's denominator is known
@@ -189,8 +190,8 @@ struct RideArgs {
 };
 
 // ------------------------------------------------------------------------------------------
-// k_mass_mfma: grid (ceil(V/32), B * HS), 256 threads = 4 waves.  A workgroup owns one 32-key tile
-// and the kv heads of group hs (Hkv / HS of them); wave w walks the heads g_lo + w, g_lo + w + 4, ...
+// k_mass_mfma: grid (ceil(V/32), B), 256 threads = 4 waves.  A workgroup owns one 32-key tile; wave w walks
+// the kv heads w, w + 4, ...
 // The four bf16 pieces of qbar_g are rows 0..3 of the MFMA A tile (rows 4..31 are zero, or text
 // rows that ride along), the keys are the B tile, so lane n (< 32) finds the four partial dot
 // products of key n in its first four accumulator registers.
@@ -199,14 +200,13 @@ struct RideArgs {
 // 6.0 TB/s for whole rows.  So a wave reads whole rows (LPR consecutive lanes per row) and turns the
 // tile into the operand layout through an LDS buffer of its own -- written and read by the same
 // wave, in order, so no barrier is involved.  NG = contraction groups of 8 elements (d = 16 NG).
-// With mm: writes s64, s_raw and the (min, max) of its keys to mm [B, ktiles, 2]; without: writes the group's partial
-// mass to spart [HS, B, V] for k_mass_finish.
+// Writes s64, s_raw and, with mm, the (min, max) of its keys to mm [B, ktiles, 2].
 // ------------------------------------------------------------------------------------------
 template <typename T, int NG, bool RIDE>
 __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_mass_mfma(const T* __restrict__ kv, Strides3 sk,
-                                                    const uint16_t* __restrict__ qsplit, int Hkv, int V, int HS,
+                                                    const uint16_t* __restrict__ qsplit, int Hkv, int V,
                                                     double scale, double* __restrict__ s64, float* __restrict__ s_raw,
-                                                    double* __restrict__ mm, double* __restrict__ spart, RideArgs ra) {
+                                                    double* __restrict__ mm, RideArgs ra) {
   constexpr int GB = group_bytes<T>::value;
   constexpr int RBY = NG * 2 * GB;                    // row bytes
   constexpr int LPR = RBY / 16, RPI = 64 / LPR;       // lanes per row, rows per load instruction
@@ -222,8 +222,7 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_ma
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = lane & 31, hf = lane >> 5;
   const int piece = lane % LPR, r0 = lane / LPR;
-  const int b = blockIdx.y / HS, hs = blockIdx.y % HS, j0 = blockIdx.x * 32;
-  const int g_lo = hs * (Hkv / HS), g_hi = g_lo + Hkv / HS;
+  const int b = blockIdx.y, j0 = blockIdx.x * 32, g_hi = Hkv;
   const int64_t headb = sk.h * (int64_t)sizeof(T);
   // LDS: the 16-byte piece p of row r sits in slot p ^ x(r): whole-row writes and operand reads of 16
   // consecutive rows both cover all banks
@@ -279,7 +278,7 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_ma
   uint4 qa[NG], kb[NL], kn[NL];
 #pragma unroll
   for (int c = 0; c < NG; ++c) qa[c] = make_uint4(0, 0, 0, 0);
-  int g = g_lo + wave;
+  int g = wave;
   if (g < g_hi) {
 #pragma unroll
     for (int i = 0; i < NL; ++i) kb[i] = ldg16(kbase + g * headb + roff[i]);
@@ -349,15 +348,10 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_ma
   double smin = INFINITY, smax = -INFINITY;
   const int j = j0 + n;
   if (j < V) {
-    const double tot = ((part[0][n] + part[1][n]) + part[2][n]) + part[3][n];
-    if (mm != nullptr) {
-      const double s = tot * scale;
-      s64[(int64_t)b * V + j] = s;
-      s_raw[(int64_t)b * V + j] = (float)s;
-      smin = smax = s;
-    } else {
-      spart[((int64_t)hs * gridDim.y / HS + b) * V + j] = tot;
-    }
+    const double s = (((part[0][n] + part[1][n]) + part[2][n]) + part[3][n]) * scale;
+    s64[(int64_t)b * V + j] = s;
+    s_raw[(int64_t)b * V + j] = (float)s;
+    smin = smax = s;
   }
   if (mm != nullptr) {
 #pragma unroll
@@ -369,27 +363,192 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_ma
   }
 }
 
-// k_mass_finish: grid (B), 1024 threads: adds the HS partial masses of every key in group order,
-// scales, writes s64 / s_raw and the image's (min, max) to mm [B, 1, 2].  With HS == 1 spart may be s64.
-__global__ __launch_bounds__(1024) void k_mass_finish(const double* spart, int HS, int B, int V, double scale,
-                                                       double* s64,
-                                                       float* __restrict__ s_raw,
-                                                       double* __restrict__ mm) {
+// ------------------------------------------------------------------------------------------
+// The mass sweep of a small batch (fewer than 256 tiles of 32 keys), where not bytes count but the length of the
+// chain from the first load to the last sum: workgroups of a wave per kv head (up to 16), wave w with the heads w,
+// w + NW, ..., and qbar added up by every wave for its heads from the partial sums of k_qsum, in k_qsplit's order.
+//   1 x 32 heads x 2304 tokens: k_qsplit 3.3 us, heads cut into 8 groups of workgroups 6.1, their sums and (min, max) in
+//   a launch of one workgroup 5.4: 14.8 us; now 8.1.  1 x 32 x 576 in f32: 2.7 + 6.0 + 3.9, now 6.9.
+// ------------------------------------------------------------------------------------------
+constexpr int MASS_SMALL_NW = 16;
+
+// qbar of kv head bg = b Hkv + g: lane l gets components PL l .. PL l + PL - 1 (PL = D / 64) of the sum of the np partial
+// sums of its query heads, which lie one after the other (head-major); eight loads in flight.
+template <int D> struct FoldedQuery {
+  static constexpr int PL = D / 64;
+  double q[PL];
+  __device__ __forceinline__ FoldedQuery(const double* __restrict__ qpart, int bg, int np, int lane) {
+    const double* src = qpart + (int64_t)bg * np * D + lane * PL;
+#pragma unroll
+    for (int e = 0; e < PL; ++e) q[e] = 0.0;
+    for (int i0 = 0; i0 < np; i0 += 8) {
+      double x[8][PL];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int e = 0; e < PL; ++e) x[u][e] = i0 + u < np ? src[(int64_t)(i0 + u) * D + e] : 0.0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int e = 0; e < PL; ++e) q[e] += x[u][e];
+    }
+  }
+};
+
+// The end of both kernels: part[w][i] = wave w's sum for key i of the tile of KT keys; adds them in wave order and
+// leaves s64, s_raw and, with mm, the tile's (min, max).
+template <int KT>
+__device__ __forceinline__ void mass_tile_end(const double (*part)[KT], int NW, int b, int V, double scale,
+                                              double* __restrict__ s64, float* __restrict__ s_raw,
+                                              double* __restrict__ mm) {
+  __syncthreads();
+  const int n = threadIdx.x, j = blockIdx.x * KT + n;
+  if (n >= KT) return;
+  double smin = INFINITY, smax = -INFINITY;
+  if (j < V) {
+    double s = part[0][n];
+    for (int w = 1; w < NW; ++w) s += part[w][n];
+    s *= scale;
+    s64[(int64_t)b * V + j] = s;
+    s_raw[(int64_t)b * V + j] = (float)s;
+    smin = smax = s;
+  }
+#pragma unroll
+  for (int off = KT / 2; off >= 1; off >>= 1) {
+    smin = nan_min(smin, shfl_xor_f64(smin, off));
+    smax = nan_max(smax, shfl_xor_f64(smax, off));
+  }
+  if (n == 0 && mm != nullptr) reinterpret_cast<double2*>(mm)[(int64_t)b * gridDim.x + blockIdx.x] = make_double2(smin, smax);
+}
+
+// k_mass_small: grid (ceil(V/KT), B), 64 NW threads.  Products and sums in fp64 on the vector ALUs: a lane keeps the 16-byte
+// piece l % LPR of its head's qbar and of RPI rows per load instruction, and the lanes of a row meet once, after
+// the last head.  (As bf16 pieces on the matrix cores the cutting alone took 8 us for 576 keys in f32, on 36 CUs.)
+template <typename T, int D, int KT>
+__global__ __launch_bounds__(64 * MASS_SMALL_NW) void k_mass_small(const T* __restrict__ kv, Strides3 sk,
+                                                                    const double* __restrict__ qpart, int Hkv, int np,
+                                                                    int V, double scale, double* __restrict__ s64,
+                                                                    float* __restrict__ s_raw, double* __restrict__ mm) {
+  constexpr int E = elem<T>::per16, LPR = D / E, RPI = 64 / LPR, NI = KT / RPI;
+  static_assert(NI >= 1, "at least one load instruction");
+  __shared__ __align__(16) double qs[MASS_SMALL_NW][D];        // each row written and read by one wave, in order
+  __shared__ double part[MASS_SMALL_NW][KT];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, NW = blockDim.x >> 6;
+  const int piece = lane % LPR, r0 = lane / LPR, b = blockIdx.y, j0 = blockIdx.x * KT;
+  const char* base = reinterpret_cast<const char*>(kv + b * sk.b) + piece * 16;
+  const int64_t headb = sk.h * (int64_t)sizeof(T);
+  uint32_t roff[NI];          // byte offsets inside one head of one image (< 2 GiB, checked on the host)
+  double acc[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    roff[i] = (uint32_t)(min(j0 + r0 + RPI * i, V - 1) * (int)sk.r * (int)sizeof(T));
+    acc[i] = 0.0;
+  }
+  for (int g = wave; g < Hkv; g += NW) {
+    uint4 kb[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) kb[i] = ldg16(base + g * headb + roff[i]);
+    const FoldedQuery<D> f(qpart, b * Hkv + g, np, lane);
+#pragma unroll
+    for (int e = 0; e < f.PL; ++e) qs[wave][lane * f.PL + e] = f.q[e];
+    double q[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) q[e] = qs[wave][piece * E + e];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      float x[E];
+      unpack16<T>(kb[i], x);
+#pragma unroll
+      for (int e = 0; e < E; ++e) acc[i] = fma(q[e], (double)x[e], acc[i]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+#pragma unroll
+    for (int off = LPR / 2; off >= 1; off >>= 1) acc[i] += shfl_xor_f64(acc[i], off);
+    if (piece == 0) part[wave][r0 + RPI * i] = acc[i];
+  }
+  mass_tile_end<KT>(part, NW, b, V, scale, s64, s_raw, mm);
+}
+
+// k_mass_small_ride (bf16): the same with text rows that ride along (see k_mass_mfma), on the matrix cores.  Tiles of
+// 16 x 16: the four pieces of qbar are rows 0 .. 3 of two tiles of query rows, rows 4 .. 31 text rows; the operands come
+// straight from memory, two sectors of 64 bytes of 16 rows per instruction.
+template <int NG>
+__global__ __launch_bounds__(64 * MASS_SMALL_NW) void k_mass_small_ride(const bf16_t* __restrict__ kv, Strides3 sk,
+                                                                         const double* __restrict__ qpart, int Hkv,
+                                                                         int np, int V, double scale,
+                                                                         double* __restrict__ s64,
+                                                                         float* __restrict__ s_raw,
+                                                                         double* __restrict__ mm, RideArgs ra) {
+  constexpr int D = 16 * NG, NC = D / 32, KT = 16;   // contraction steps of 32 components, keys of a tile
+  __shared__ __align__(16) uint16_t pieces[MASS_SMALL_NW][4 * D];
+  __shared__ double part[MASS_SMALL_NW][KT];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, NW = blockDim.x >> 6;
+  const int n = lane & 15, q4 = lane >> 4;
+  const int b = blockIdx.y, j0 = blockIdx.x * KT;
+  const char* krow = reinterpret_cast<const char*>(kv + b * sk.b) + (int64_t)min(j0 + n, V - 1) * sk.r * 2 + q4 * 16;
+  const int64_t headb = sk.h * 2;
+  // lane n supplies row 16 a + n of tile a: row 4 + r is text row r (t = r % T_eff of query head g G + r / T_eff)
+  const char* tbase[2];
+  const int ride_rows = ra.G * ra.T_eff, len = min(max(ra.text_len[b], 0), ra.Tmax);
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const int r = 16 * a + n - 4, t = r % ra.T_eff, src = ra.last_only ? len - 1 : t;
+    const bool here = r >= 0 && r < ride_rows && (ra.last_only ? len >= 1 : t < len);   // padding rows: zero operands
+    tbase[a] = here ? reinterpret_cast<const char*>(static_cast<const bf16_t*>(ra.qt) + b * ra.sq.b +
+                                                    (int64_t)(r / ra.T_eff) * ra.sq.h + (int64_t)src * ra.sq.r) + q4 * 16
+                    : nullptr;
+  }
+  double sum = 0.0;
+  for (int g = wave; g < Hkv; g += NW) {
+    uint4 kb[NC], qa[2][NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) kb[c] = ldg16(krow + g * headb + c * 64);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        qa[a][c] = tbase[a] != nullptr ? ldg16(tbase[a] + (int64_t)g * ra.G * ra.sq.h * 2 + c * 64) : make_uint4(0, 0, 0, 0);
+    const FoldedQuery<D> f(qpart, b * Hkv + g, np, lane);
+    uint16_t* pw = pieces[wave];                // written and read by this wave alone, in order
+#pragma unroll
+    for (int e = 0; e < f.PL; ++e) split_bf16x4(f.q[e], pw + lane * f.PL + e, D);
+    if (n < 4) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) qa[0][c] = *reinterpret_cast<const uint4*>(pw + n * D + c * 32 + q4 * 8);
+    }
+    f32x4_t acc[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      acc[a] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int c = 0; c < NC; ++c) mma16(acc[a], qa[a][c], kb[c]);
+    }
+    // rows 0 .. 3 of a tile lie in the first 16 lanes
+    sum += ((double)acc[0][0] + (double)acc[0][1]) + ((double)acc[0][2] + (double)acc[0][3]);
+    if (j0 + n < V) {
+      float* zl = ra.zlog + ((int64_t)(b * ra.H + g * ra.G) * ra.T_eff) * V + j0 + n;
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = 16 * a + 4 * q4 + v - 4;
+          if (r >= 0 && r < ride_rows) zl[(int64_t)r * V] = acc[a][v];
+        }
+    }
+  }
+  if (q4 == 0) part[wave][n] = sum;
+  mass_tile_end<KT>(part, NW, b, V, scale, s64, s_raw, mm);
+}
+
+// k_mass_finish: grid (B), 1024 threads: the image's (min, max) to mm [B, 1, 2].
+__global__ __launch_bounds__(1024) void k_mass_finish(const double* __restrict__ s64, int V, double* __restrict__ mm) {
   __shared__ double wave_mm[16][2];
   const int b = blockIdx.x, tid = threadIdx.x;
   double smin = INFINITY, smax = -INFINITY;
   for (int j = tid; j < V; j += 1024) {
-    double t = 0.0;
-    for (int q0 = 0; q0 < HS; q0 += 8) {       // eight loads in flight, added in group order
-      double part[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) part[u] = q0 + u < HS ? spart[((int64_t)(q0 + u) * B + b) * V + j] : 0.0;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) t += part[u];
-    }
-    const double s = t * scale;
-    s64[(int64_t)b * V + j] = s;
-    s_raw[(int64_t)b * V + j] = (float)s;
+    const double s = s64[(int64_t)b * V + j];
     smin = nan_min(smin, s);
     smax = nan_max(smax, s);
   }
@@ -1645,8 +1804,15 @@ static bool two_sweeps_faster(const asap_params& p, int t_eff) {
 
 ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
   ScoreWorkspace w{};
-  // rows per k_qsum block: whole image span unless that leaves the chip short of blocks
-  int chunks = (512 + p.B * p.H - 1) / (p.B * p.H);
+  // The mass sweep of few keys: smaller tiles, a wave per head.  8 keys per workgroup where 16 would leave more than half
+  // of the chip idle (1 x 32 heads x 576 tokens in f32: 76.0 us per stage, 78.3 with 16; 1 x 2304: 87.6, 89.8 with 8).
+  const long tiles = (long)((p.V + 31) / 32) * p.B;
+  w.mass_small = tiles < 256 ? 1 : 0;
+  // rows per k_qsum block: whole image span unless that leaves the chip short of blocks.  Small batches, whose
+  // workgroups all read every partial sum, take no more than 128 blocks (6 x 28 heads x 1225 tokens: 123.4 us per
+  // stage, 125.0 with 256 blocks, 128.5 with 512; 1 x 32 x 2304: 87.6, 87.2, 90.4).
+  const int want = w.mass_small ? 128 : 512;
+  int chunks = (want + p.B * p.H - 1) / (p.B * p.H);
   if (chunks > (p.V + 255) / 256) chunks = (p.V + 255) / 256;
   if (chunks < 1) chunks = 1;
   w.q_rows = (p.V + chunks - 1) / chunks;
@@ -1659,14 +1825,7 @@ ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
   const int G = p.H / p.Hkv, rows = G * w.t_eff;
   const int row_bytes = p.d * (p.qk_dtype == ASAP_BF16 ? 2 : 4);
   w.ride = (p.qk_dtype == ASAP_BF16 && rows <= 28 && 12 * rows < 2 * row_bytes) ? 1 : 0;
-  // kv-head groups of the mass sweep: 1 unless the key tiles alone leave most of the chip idle
-  const long tiles = (long)((p.V + 31) / 32) * p.B;
-  w.head_splits = 1;
-  if (tiles < 256) {
-    int want = (int)((512 + tiles - 1) / tiles);
-    for (int hs = p.Hkv; hs >= 1; --hs)
-      if (p.Hkv % hs == 0 && hs <= want) { w.head_splits = hs; break; }
-  }
+  w.mass_keys = 2 * tiles >= 128 || w.ride ? 16 : 8;
   w.row_pairs = w.ride ? 1 : (w.t_eff + 63) / 64;
   // f32 keys: the first text-row sweep leaves its logits (4 bytes per ranking row and key, never more
   // than the key sweeps they replace at 512 bytes per key and 64 rows) and the column sums read them
@@ -1683,33 +1842,31 @@ ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
     const long units2 = (long)p.B * p.Hkv * ((G * w.t_eff + 31) / 32);
     w.one_sweep = p.V <= ROWS_V2 ? (units2 > 128 ? 2 : 1) : p.V <= ROWS_V1 && !two_sweeps_faster(p, w.t_eff) ? 1 : 0;
   }
-  const size_t spart_bytes = w.head_splits > 1 ? align256(sizeof(double) * (size_t)w.head_splits * p.B * p.V) : 0;
   size_t off = 0;
   w.off_qpart = off;
   off = align256(off + sizeof(double) * p.B * p.H * w.q_chunks * p.d);
   off = align256(off + sizeof(double) * p.B * p.Hkv * p.d);
-  // The (min, max) pairs of the key tiles lie where the partial sums of the queries were: those have been read
-  // (k_qsplit) before the masses are formed.  Where they do not fit (fewer than 16 heads, thousands of tokens),
-  // k_mass_finish takes one pair per image.
-  const int ktiles = (p.V + 31) / 32;
-  w.finish = w.head_splits > 1 || sizeof(double) * 2 * p.B * ktiles > off;
-  w.mm_n = w.finish ? 1 : ktiles;
   w.off_qsplit = off; off = align256(off + sizeof(uint16_t) * p.B * p.Hkv * 4 * p.d);
   w.off_s64 = off;    off = align256(off + sizeof(double) * p.B * p.V);
-  w.off_mm = w.finish ? off : w.off_qpart;
+  // The (min, max) pairs of the key tiles lie where nothing is read any more when the masses are formed: in the place
+  // of the partial sums of the queries (k_qsplit is through with them), or of the pieces of their sums (which
+  // a small batch does not use).  Where they do not fit (few heads, thousands of tokens), k_mass_finish takes one pair per image.
+  const int ktiles = w.mass_small ? (p.V + w.mass_keys - 1) / w.mass_keys : (p.V + 31) / 32;
+  w.finish = sizeof(double) * 2 * (size_t)p.B * ktiles > (w.mass_small ? w.off_s64 - w.off_qsplit : w.off_qsplit);
+  w.mm_n = w.finish ? 1 : ktiles;
+  w.off_mm = w.finish ? off : w.mass_small ? w.off_qsplit : w.off_qpart;
   off = align256(off + sizeof(double) * 2 * p.B);
-  // The one sweep has no row statistics, and its column sums take the place of the partial masses, which have
-  // been added up by then.  Many query heads on few kv heads leave more of those sums than the two sweeps do
+  // The one sweep has no row statistics.  Many query heads on few kv heads leave more of those sums than the two sweeps do
   // (one row for 16 or 32 text rows instead of 64): where the caller's scratch does not hold them, the two sweeps run.
   if (w.one_sweep) {
     const int blocks = (G * w.t_eff + 16 * w.one_sweep - 1) / (16 * w.one_sweep);
     const int heads = rows_heads_per_wg(p, blocks, w.one_sweep);
     const size_t rows = (size_t)((p.Hkv + heads - 1) / heads) * blocks;
-    const size_t total = off + std::max(align256(sizeof(float) * p.B * rows * p.V), spart_bytes);
+    const size_t total = off + align256(sizeof(float) * p.B * rows * p.V);
     if (total <= budget) {
       w.row_pairs = blocks;
       w.heads_per_wg = heads;
-      w.off_upart = w.off_spart = w.off_pstat = off;
+      w.off_upart = w.off_pstat = off;
       w.off_zlog = w.total = total;
       return w;
     }
@@ -1717,7 +1874,6 @@ ScoreWorkspace score_workspace(const asap_params& p, size_t budget) {
   }
   w.off_pstat = off;  off = align256(off + sizeof(float) * (size_t)p.B * p.H * splits * 2 * NR);
   w.off_upart = off;  off = align256(off + sizeof(float) * (size_t)p.B * p.H * w.row_pairs * p.V);
-  w.off_spart = off;  off += spart_bytes;
   w.off_zlog = off;
   if (w.store_logits && align256(off + zlog_bytes) > budget) w.store_logits = 0;
   if (w.ride || w.store_logits) off = align256(off + zlog_bytes);
@@ -1795,21 +1951,37 @@ static hipError_t launch_attn_rows(const asap_params& p, const ScoreWorkspace& w
 
 template <typename T, int NG>
 static hipError_t launch_mass(const asap_params& p, const ScoreWorkspace& w, const void* k_vis, Strides3 kv,
-                              const uint16_t* qsplit, double scale, double* s64, float* s_raw,
-                              double* mm, double* spart, const RideArgs& ra, hipStream_t st,
-                              Timer* tm) {
-  const int ktiles = (p.V + 31) / 32;
-  const dim3 grid(ktiles, p.B * w.head_splits);
+                              const uint16_t* qsplit, const double* qpart, int q_chunks, double scale, double* s64,
+                              float* s_raw, double* mm, const RideArgs& ra, hipStream_t st, Timer* tm) {
   const T* kp = static_cast<const T*>(k_vis);
+  if (w.mass_small) {
+    const dim3 grid((p.V + w.mass_keys - 1) / w.mass_keys, p.B), block(64 * std::min(p.Hkv, MASS_SMALL_NW));
+    const int np = p.H / p.Hkv * q_chunks;
+    if constexpr (sizeof(T) == 2) {
+      if (w.ride) {
+        ASAP_LAUNCH(tm, "k_mass_small_ride", k_mass_small_ride<NG>, grid, block, 0, st, kp, kv, qpart, p.Hkv, np, p.V, scale,
+                    s64, s_raw, mm, ra);
+        return hipGetLastError();
+      }
+    }
+    if (w.mass_keys == 16)
+      ASAP_LAUNCH(tm, "k_mass_small", (k_mass_small<T, 16 * NG, 16>), grid, block, 0, st, kp, kv, qpart, p.Hkv, np, p.V, scale,
+                  s64, s_raw, mm);
+    else
+      ASAP_LAUNCH(tm, "k_mass_small", (k_mass_small<T, 16 * NG, 8>), grid, block, 0, st, kp, kv, qpart, p.Hkv, np, p.V, scale,
+                  s64, s_raw, mm);
+    return hipGetLastError();
+  }
+  const dim3 grid((p.V + 31) / 32, p.B);
   if constexpr (sizeof(T) == 2) {
     if (w.ride) {
-      ASAP_LAUNCH(tm, "k_mass_mfma", (k_mass_mfma<T, NG, true>), grid, dim3(256), 0, st, kp, kv, qsplit, p.Hkv, p.V,
-                  w.head_splits, scale, s64, s_raw, mm, spart, ra);
+      ASAP_LAUNCH(tm, "k_mass_mfma", (k_mass_mfma<T, NG, true>), grid, dim3(256), 0, st, kp, kv, qsplit, p.Hkv, p.V, scale,
+                  s64, s_raw, mm, ra);
       return hipGetLastError();
     }
   }
-  ASAP_LAUNCH(tm, "k_mass_mfma", (k_mass_mfma<T, NG, false>), grid, dim3(256), 0, st, kp, kv, qsplit, p.Hkv, p.V,
-              w.head_splits, scale, s64, s_raw, mm, spart, ra);
+  ASAP_LAUNCH(tm, "k_mass_mfma", (k_mass_mfma<T, NG, false>), grid, dim3(256), 0, st, kp, kv, qsplit, p.Hkv, p.V, scale, s64,
+              s_raw, mm, ra);
   return hipGetLastError();
 }
 
@@ -1826,24 +1998,25 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
   double* mm = reinterpret_cast<double*>(ws + w.off_mm);
   float* pstat = reinterpret_cast<float*>(ws + w.off_pstat);
   float* upart = reinterpret_cast<float*>(ws + w.off_upart);
-  double* spart = w.head_splits > 1 ? reinterpret_cast<double*>(ws + w.off_spart) : s64;
   float* zlog = reinterpret_cast<float*>(ws + w.off_zlog);
   const int mask_on = p.mask_mode == ASAP_MASK_KEYBIAS;
   const int last_only = p.score_rows == ASAP_ROWS_LAST;
   const int ng = p.d / 16;      // contraction groups of 8 elements per lane half
   const int ktiles = (p.V + 31) / 32;
+  const int q_chunks = fe != nullptr ? 1 : w.q_chunks;
 
   if (fe != nullptr) {
     // the summed visual queries come from the hidden states (asap_front.hip), one chunk per head
     hipError_t e0 = launch_front_end(p, fe->hidden, fe->hsb, fe->hsr, fe->wq, fe->rope_theta, fe->vis_positions,
                                      qpart, fe->ws, st, tm);
     if (e0 != hipSuccess) return e0;
-    ASAP_LAUNCH(tm, "k_qsplit", k_qsplit, dim3(p.Hkv, p.B), dim3(p.d), 0, st, qpart, qsplit, p.H, p.Hkv, 1, p.d);
+    if (!w.mass_small)
+      ASAP_LAUNCH(tm, "k_qsplit", k_qsplit, dim3(p.Hkv, p.B), dim3(p.d), 0, st, qpart, qsplit, p.H, p.Hkv, 1, p.d);
   } else {
-    const int direct = (w.q_chunks == 1 && p.H == p.Hkv) ? 1 : 0;
+    const int direct = (!w.mass_small && w.q_chunks == 1 && p.H == p.Hkv) ? 1 : 0;
     ASAP_LAUNCH(tm, "k_qsum", k_qsum<T>, dim3(w.q_chunks, p.H, p.B), dim3(1024), 0, st, static_cast<const T*>(q_vis),
                 qv, p.V, p.d, w.q_rows, qpart, qsplit, direct);
-    if (!direct)
+    if (!direct && !w.mass_small)
       ASAP_LAUNCH(tm, "k_qsplit", k_qsplit, dim3(p.Hkv, p.B), dim3(p.d), 0, st, qpart, qsplit, p.H, p.Hkv,
                   w.q_chunks, p.d);
   }
@@ -1852,12 +2025,12 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
   ra.qt = q_txt; ra.sq = qt; ra.text_len = text_len; ra.zlog = zlog;
   ra.H = p.H; ra.G = p.H / p.Hkv; ra.T_eff = w.t_eff; ra.Tmax = p.Tmax; ra.last_only = last_only;
   double* tile_mm = w.finish ? nullptr : mm;
-  hipError_t e = ng == 8 ? launch_mass<T, 8>(p, w, k_vis, kv, qsplit, scale, s64, s_raw, tile_mm, spart, ra, st, tm)
-                         : launch_mass<T, 4>(p, w, k_vis, kv, qsplit, scale, s64, s_raw, tile_mm, spart, ra, st, tm);
+  hipError_t e = ng == 8
+                     ? launch_mass<T, 8>(p, w, k_vis, kv, qsplit, qpart, q_chunks, scale, s64, s_raw, tile_mm, ra, st, tm)
+                     : launch_mass<T, 4>(p, w, k_vis, kv, qsplit, qpart, q_chunks, scale, s64, s_raw, tile_mm, ra, st, tm);
   if (e != hipSuccess) return e;
   if (w.finish)
-    ASAP_LAUNCH(tm, "k_mass_finish", k_mass_finish, dim3(p.B), dim3(1024), 0, st, spart, w.head_splits, p.B, p.V,
-                scale, s64, s_raw, mm);
+    ASAP_LAUNCH(tm, "k_mass_finish", k_mass_finish, dim3(p.B), dim3(1024), 0, st, s64, p.V, mm);
 
   AttnArgs a;
   a.qt = q_txt; a.sq = qt; a.kv = k_vis; a.sk = kv; a.s64 = s64; a.mm = mm; a.mm_n = w.mm_n; a.text_len = text_len;

@@ -703,6 +703,19 @@ def test_attention_forward_random_shapes(ctx, seed):
     _attention_case(ctx, cfg, mask, float(r.choice([1.0, 0.6])))
 
 
+@pytest.mark.parametrize("B,V", [(1, 1), (1, 7), (1, 9), (2, 31), (1, 1009), (1, 1024), (1, 1041), (5, 1615), (4, 2033)])
+@pytest.mark.parametrize("H,Hkv,d,qk_dtype,last", [(17, 17, 64, "bf16", False), (6, 3, 128, "f32", False),
+                                                   (2, 1, 64, "f32", False), (20, 4, 128, "bf16", True)])
+def test_mass_of_small_batches(ctx, B, V, H, Hkv, d, qk_dtype, last):
+    """The mass sweep of fewer than 256 tiles of 32 keys (5 x 1615 is the last such batch, 4 x 2033 the first larger one):
+    tiles of 8 and 16 keys that the span does not fill, fewer and more kv heads than waves, several partial sums of
+    the queries per head, (min, max) pairs that do and do not fit, text rows that ride along."""
+    cfg = synth.StageConfig(name="mass", B=B, D=64, H=H, Hkv=Hkv, d=d, P=3, V=V, Tmax=5, k=max(1, V // 4),
+                            qk_dtype=qk_dtype, h_dtype="f32", kv_dtype="bf16", n_clusters=4, outliers=False, L_kv=0,
+                            seed=8100 + V)
+    U.run_and_compare(cfg, ctx=ctx, last_token=last)
+
+
 @pytest.mark.parametrize("d,qk_dtype,mask", [(128, "bf16", True), (128, "bf16", False), (64, "bf16", True),
                                              (128, "f32", True), (64, "f32", False)])
 @pytest.mark.parametrize("N", [2, 31, 33, 63, 64, 65, 129, 255, 256, 257, 320, 321, 577])

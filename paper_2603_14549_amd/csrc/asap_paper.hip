@@ -18,6 +18,7 @@ namespace asap {
 // slot_of[] states before the final positions are known
 constexpr int TOK_PRUNED = -1, TOK_ROOT = -2, TOK_SOURCE = -3;
 
+template <int IPT>
 __global__ __launch_bounds__(SEL_THREADS) void k_paper_plan(const int32_t* __restrict__ dest,
                                                              const int32_t* __restrict__ kept,
                                                              const float* __restrict__ s_raw, int V, int k,
@@ -34,7 +35,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_paper_plan(const int32_t* __res
   for (int i = tid; i < V; i += SEL_THREADS) slot_of[i] = TOK_PRUNED;
   __syncthreads();
   // roots: at most k-1 hops (the bound only guards against a malformed destination list)
-  constexpr int SPT = (SEL_IPT * SEL_THREADS / 2 + SEL_THREADS - 1) / SEL_THREADS;   // kept slots per thread, k <= V/2
+  constexpr int SPT = (IPT * SEL_THREADS / 2 + SEL_THREADS - 1) / SEL_THREADS;   // kept slots per thread, k <= V/2
   int rt[SPT];
   int n_src = 0;
 #pragma unroll
@@ -63,27 +64,27 @@ __global__ __launch_bounds__(SEL_THREADS) void k_paper_plan(const int32_t* __res
   // refill: the n_vacated largest s_raw among the pruned tokens
   const int ipt = (V + SEL_THREADS - 1) / SEL_THREADS;      // items per thread, blocked layout
   const int i0 = tid * ipt;
-  uint32_t key[SEL_IPT];
+  uint32_t key[IPT];
 #pragma unroll
-  for (int e = 0; e < SEL_IPT; ++e) {
+  for (int e = 0; e < IPT; ++e) {
     const int i = i0 + e;
     key[e] = (e < ipt && i < V && slot_of[i] == TOK_PRUNED) ? float_key(s_raw[(int64_t)b * V + i]) : 0u;
   }
   int n_mine;
-  const uint32_t refill = radix_topk(key, ipt, i0, V, n_vacated, sh, &n_mine);
+  const uint32_t refill = topk(key, ipt, i0, V, n_vacated, sh, &n_mine);
 
   // final list, ascending
   int n_fin = 0;
   uint32_t fin = 0;
 #pragma unroll
-  for (int e = 0; e < SEL_IPT; ++e) {
+  for (int e = 0; e < IPT; ++e) {
     const int i = i0 + e;
     if (e < ipt && i < V && ((refill >> e & 1u) || slot_of[i] == TOK_ROOT)) { fin |= 1u << e; ++n_fin; }
   }
   int tot;
   int pos = block_scan_excl(n_fin, sh.wave_sums, &tot);
 #pragma unroll
-  for (int e = 0; e < SEL_IPT; ++e) {
+  for (int e = 0; e < IPT; ++e) {
     const int i = i0 + e;
     if (fin >> e & 1u) {
       if (pos < k) final_idx[(int64_t)b * k + pos] = i;
@@ -105,14 +106,17 @@ size_t paper_workspace_bytes(const asap_params& p) {
 hipError_t launch_paper_plan(const asap_params& p, const int32_t* dest, const int32_t* kept, const float* s_raw,
                              int32_t* final_idx, int32_t* assign, hipStream_t st, Timer* tm) {
   const size_t lds = sizeof(int32_t) * ((size_t)p.k + p.V);
-  if (lds > 48 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_paper_plan),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  ASAP_LAUNCH(tm, "k_paper_plan", k_paper_plan, dim3(p.B), dim3(SEL_THREADS), lds, st, dest, kept, s_raw, p.V, p.k,
-              final_idx, assign);
-  return hipGetLastError();
+  return with_ipt(p.V, [&](auto ipt) {
+    auto kern = k_paper_plan<decltype(ipt)::value>;
+    if (lds > 48 * 1024) {
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    ASAP_LAUNCH(tm, "k_paper_plan", kern, dim3(p.B), dim3(SEL_THREADS), lds, st, dest, kept, s_raw, p.V, p.k,
+                final_idx, assign);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace asap

@@ -1620,6 +1620,7 @@ __global__ __launch_bounds__(256) void k_score(const float* __restrict__ upart, 
 // k_score's; the scores change hands through LDS to the blocked layout of the selection (thread t owns
 // keys t*ipt .. t*ipt+ipt-1), and the workgroup then selects exactly as k_select does.
 // ------------------------------------------------------------------------------------------
+template <int IPT>
 __device__ __forceinline__ void score_select_image(const int b, const float* __restrict__ upart,
                                                    const double* __restrict__ s64,
                                                    const double* __restrict__ mm, int mm_n,
@@ -1662,20 +1663,20 @@ __device__ __forceinline__ void score_select_image(const int b, const float* __r
     else mine = sc;
   }
   if (ipt > 1) __syncthreads();
-  uint32_t key[SEL_IPT];
+  uint32_t key[IPT];
 #pragma unroll
-  for (int e = 0; e < SEL_IPT; ++e) {
+  for (int e = 0; e < IPT; ++e) {
     const int i = i0 + e;
     key[e] = (e < ipt && i < V) ? float_key(ipt > 1 ? sc_lds[i] : mine) : 0u;
   }
   int n_keep;
-  const uint32_t keep_bits = radix_topk(key, ipt, i0, V, k, sh, &n_keep);
+  const uint32_t keep_bits = topk(key, ipt, i0, V, k, sh, &n_keep);
   int tot;
   int kept_before = block_scan_excl(n_keep, sh.wave_sums, &tot);
   int32_t* kout = kept + (int64_t)b * k;
   int32_t* pout = pruned + (int64_t)b * (V - k);
 #pragma unroll
-  for (int e = 0; e < SEL_IPT; ++e) {
+  for (int e = 0; e < IPT; ++e) {
     const int i = i0 + e;
     if (e < ipt && i < V) {
       if (keep_bits & (1u << e)) kout[kept_before++] = i;
@@ -1684,6 +1685,7 @@ __device__ __forceinline__ void score_select_image(const int b, const float* __r
   }
 }
 
+template <int IPT>
 __global__ __launch_bounds__(SEL_THREADS) void k_score_select(const float* __restrict__ upart,
                                                                const double* __restrict__ s64,
                                                                const double* __restrict__ mm, int mm_n,
@@ -1692,7 +1694,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_score_select(const float* __res
                                                                double eps, int mask_on, float* __restrict__ s_hat,
                                                                float* __restrict__ score, int32_t* __restrict__ kept,
                                                                int32_t* __restrict__ pruned) {
-  score_select_image(blockIdx.x, upart, s64, mm, mm_n, text_len, H, HV, packed, G, block, V, k, Tmax, last_only, lambda_max, eps, mask_on,
+  score_select_image<IPT>(blockIdx.x, upart, s64, mm, mm_n, text_len, H, HV, packed, G, block, V, k, Tmax, last_only, lambda_max, eps, mask_on,
                      s_hat, score, kept, pruned);
 }
 
@@ -1701,13 +1703,14 @@ __global__ __launch_bounds__(SEL_THREADS) void k_score_select(const float* __res
 // (Fig. 3: prefix rows stay where they are, valid text row t moves from P + V + t to P + k + t): they
 // depend on no result of the stage, and the B selecting workgroups leave the memory system idle.
 // A row is row_bytes / 16 pieces of 16 bytes; two rows per thread are in flight.
+template <int IPT>
 __global__ __launch_bounds__(SEL_THREADS) void k_score_select_kv(
     const float* __restrict__ upart, const double* __restrict__ s64, const double* __restrict__ mm, int mm_n,
     const int32_t* __restrict__ text_len, int H, int HV, int packed, int G, int block, int V, int k, int Tmax, int last_only,
     double lambda_max, double eps, int mask_on, float* __restrict__ s_hat, float* __restrict__ score, int32_t* __restrict__ kept,
     int32_t* __restrict__ pruned, int B, KvFixedRows fx) {
   if ((int)blockIdx.x < B) {
-    score_select_image(blockIdx.x, upart, s64, mm, mm_n, text_len, H, HV, packed, G, block, V, k, Tmax, last_only, lambda_max, eps,
+    score_select_image<IPT>(blockIdx.x, upart, s64, mm, mm_n, text_len, H, HV, packed, G, block, V, k, Tmax, last_only, lambda_max, eps,
                        mask_on, s_hat, score, kept, pruned);
     return;
   }
@@ -2054,7 +2057,11 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
   if (e != hipSuccess) return e;
   const int packed = w.one_sweep ? (p.Hkv + w.heads_per_wg - 1) / w.heads_per_wg : 0;
   const int u_rows = w.one_sweep ? packed * w.row_pairs : p.H * (w.store_logits ? 1 : w.row_pairs);  // rows of upart per image
-  if (kept != nullptr && !score_fuses_selection(p)) {
+  // One workgroup per image fetches the column sums slowly, so in small batches the selection rides along only where they
+  // are few: up to 96 KB saves about a microsecond (1 x 16 x 576: 50.0 -> 49.1 us per stage, 1 x 32 x 576 in f32: 72.4 ->
+  // 71.5), 2 x 8 heads of 2000 tokens with as many bytes cost four (64.6 -> 68.8), 5 x 28 x 2083 with 230 KB eight.
+  const bool fuse = score_fuses_selection(p) || (p.V <= SEL_THREADS && sizeof(float) * u_rows * p.V <= 96 * 1024);
+  if (kept != nullptr && !fuse) {
     ASAP_LAUNCH(tm, "k_score", k_score, dim3((p.V + 63) / 64, p.B), dim3(256), 0, st, upart, s64, mm, w.mm_n, text_len,
                 p.H, u_rows, packed, p.H / p.Hkv, 16 * w.one_sweep, p.V, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps, mask_on, s_hat, score);
     hipError_t e2 = hipGetLastError();
@@ -2062,20 +2069,24 @@ static hipError_t score_typed(const asap_params& p, const void* q_vis, Strides3 
   }
   if (kept != nullptr) {
     const size_t lds = p.V > SEL_THREADS ? sizeof(float) * (size_t)p.V : 0;
-    const void* fn = fixed ? reinterpret_cast<const void*>(k_score_select_kv)
-                           : reinterpret_cast<const void*>(k_score_select);
-    if (lds > 32 * 1024) {
-      e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-    }
-    if (fixed)
-      ASAP_LAUNCH(tm, "k_score_select_kv", k_score_select_kv, dim3(p.B + fixed->n_bufs * p.B * p.Hkv),
-                  dim3(SEL_THREADS), lds, st, upart, s64, mm, w.mm_n, text_len, p.H, u_rows, packed, p.H / p.Hkv, 16 * w.one_sweep, p.V, p.k, p.Tmax,
-                  last_only, (double)p.lambda_max, (double)p.eps, mask_on, s_hat, score, kept, pruned, p.B, *fixed);
-    else
-      ASAP_LAUNCH(tm, "k_score_select", k_score_select, dim3(p.B), dim3(SEL_THREADS), lds, st, upart, s64, mm, w.mm_n,
-                  text_len, p.H, u_rows, packed, p.H / p.Hkv, 16 * w.one_sweep, p.V, p.k, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps,
-                  mask_on, s_hat, score, kept, pruned);
+    return with_ipt(p.V, [&](auto ipt) {
+      constexpr int IPT = decltype(ipt)::value;
+      const void* fn = fixed ? reinterpret_cast<const void*>(k_score_select_kv<IPT>)
+                             : reinterpret_cast<const void*>(k_score_select<IPT>);
+      if (lds > 32 * 1024) {
+        hipError_t e2 = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e2 != hipSuccess) return e2;
+      }
+      if (fixed)
+        ASAP_LAUNCH(tm, "k_score_select_kv", k_score_select_kv<IPT>, dim3(p.B + fixed->n_bufs * p.B * p.Hkv),
+                    dim3(SEL_THREADS), lds, st, upart, s64, mm, w.mm_n, text_len, p.H, u_rows, packed, p.H / p.Hkv, 16 * w.one_sweep, p.V, p.k, p.Tmax,
+                    last_only, (double)p.lambda_max, (double)p.eps, mask_on, s_hat, score, kept, pruned, p.B, *fixed);
+      else
+        ASAP_LAUNCH(tm, "k_score_select", k_score_select<IPT>, dim3(p.B), dim3(SEL_THREADS), lds, st, upart, s64, mm, w.mm_n,
+                    text_len, p.H, u_rows, packed, p.H / p.Hkv, 16 * w.one_sweep, p.V, p.k, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps,
+                    mask_on, s_hat, score, kept, pruned);
+      return hipGetLastError();
+    });
   } else {
     ASAP_LAUNCH(tm, "k_score", k_score, dim3((p.V + 63) / 64, p.B), dim3(256), 0, st, upart, s64, mm, w.mm_n, text_len,
                 p.H, u_rows, packed, p.H / p.Hkv, 16 * w.one_sweep, p.V, p.Tmax, last_only, (double)p.lambda_max, (double)p.eps, mask_on, s_hat, score);

@@ -1,7 +1,12 @@
-// Exact top-k selection inside one 1024-thread workgroup, shared by the selection kernel and by the
-// budget reallocation of the paper's routing: a 4-pass, 8-bit radix search finds the k-th largest
-// key, a block scan then decides which of the keys equal to it are taken (smallest index first).
-// Integer work throughout.
+// Exact top-k selection inside one 1024-thread workgroup, shared by the selection kernels and by the
+// budget reallocation of the paper's routing.  Integer work throughout.
+//   What bounds it: the chain of barriers and LDS round trips of one workgroup.  So the keys are dealt to 256 bins of equal
+//   width between the smallest and the largest, the bin of the k-th largest is found by every wave for itself, and the
+//   bin's keys are dealt again until at most 64 are left, which one wave ranks against each other.  (A radix search over
+//   the 32 bits takes four such passes with a wave that the others wait for in each, and its first digit, sign and
+//   exponent, puts nearly every score into two or three bins, whose atomics queue up.)
+//   k_select, 1 x 2304 tokens: 10.9 -> 5.9 us; 4 x 4096: 13.5 -> 9; the plan of the paper's routing 16 x 2304: stage 348 ->
+//   337 us.
 #pragma once
 #include "asap_device.hpp"
 
@@ -9,6 +14,13 @@ namespace asap {
 
 constexpr int SEL_THREADS = 1024;
 constexpr int SEL_IPT = 16;   // V <= 16384
+// Items per thread that a kernel is compiled for (1, 4 or 16): one workgroup runs its code once, and fetching unrolled
+// steps that it skips is a good part of its time (1 x 576 tokens: 9.8 us compiled for 16 items, 8.1 for one; 1 x 2304: 7.6 and, for four, 5.9).
+template <typename F> static auto with_ipt(int V, F&& f) {
+  if (V <= SEL_THREADS) return f(std::integral_constant<int, 1>{});
+  if (V <= 4 * SEL_THREADS) return f(std::integral_constant<int, 4>{});
+  return f(std::integral_constant<int, SEL_IPT>{});
+}
 
 // order-preserving map float -> uint32 (larger float, larger key); every finite float maps above 0
 __device__ __forceinline__ uint32_t float_key(float f) {
@@ -20,15 +32,21 @@ __device__ __forceinline__ float float_unkey(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
+// inclusive sums over the lanes of a wave
+__device__ __forceinline__ int wave_scan_incl(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);      // row_bcast:15 to rows 1 and 3, row_bcast:31 to
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);      // rows 2 and 3
+  return x;
+}
+
 // exclusive block scan of one int per thread; returns the exclusive prefix, total via *total.
 __device__ __forceinline__ int block_scan_excl(int x, int* wave_sums /*[17]*/, int* total) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int incl = x;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    int y = __shfl_up(incl, off);
-    if (lane >= off) incl += y;
-  }
+  const int incl = wave_scan_incl(x);
   __syncthreads();                       // protects wave_sums against the previous use
   if (lane == 63) wave_sums[wave] = incl;
   __syncthreads();
@@ -44,83 +62,135 @@ __device__ __forceinline__ int block_scan_excl(int x, int* wave_sums /*[17]*/, i
 }
 
 // LDS the selection needs
+constexpr int SEL_LIST = 64;
 struct SelectShared {
-  int hist[512];        // two 256-bin histograms used alternately
+  uint4 hist[2][64];      // two histograms of 256 bins used alternately
+  uint2 list[SEL_LIST];   // (key, item) of the bin that holds the take-th largest
+  uint2 wave_range[SEL_THREADS / 64];      // (smallest, largest) key
   int wave_sums[17];
-  int sel_bin, sel_remaining;
+  int listed;
+  uint2 last;             // the take-th largest (key, item)
 };
 
 // Thread tid holds the keys of items i0 .. i0+ipt-1 (blocked layout, so index order = thread order);
 // items past V or not taking part carry key 0 and `take` must not exceed the number of keys > 0.
 // Returns the bit mask of this thread's items among the `take` largest (ties: smaller index) and
 // their count.  All threads of the workgroup must call it; take is the same for all.
-__device__ __forceinline__ uint32_t radix_topk(const uint32_t (&key)[SEL_IPT], int ipt, int i0, int V, int take,
-                                               SelectShared& sh, int* n_mine) {
-  const int tid = threadIdx.x;
+template <int IPT>
+__device__ __forceinline__ uint32_t topk(const uint32_t (&key)[IPT], int ipt, int i0, int V, int take, SelectShared& sh,
+                                         int* n_mine) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   *n_mine = 0;
   if (take <= 0) return 0u;
-  uint32_t prefix = 0, mask = 0;
-  int remaining = take;
-  __syncthreads();                       // the histograms may still be read from an earlier call
-  if (tid < 512) sh.hist[tid] = 0;
+  // smallest and largest key (of those that take part), first of the wave, then of all
+  uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+  for (int e = 0; e < IPT; ++e)
+    if (e < ipt && i0 + e < V && key[e] != 0u) { lo = min(lo, key[e]); hi = max(hi, key[e]); }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
+  }
+  __syncthreads();                       // the arrays may still be read from an earlier call
+  if (lane == 0) sh.wave_range[wave] = make_uint2(lo, hi);
+  if (tid < 128) (&sh.hist[0][0])[tid] = make_uint4(0, 0, 0, 0);
+  if (tid == 0) sh.listed = 0;
   __syncthreads();
-  for (int pass = 3; pass >= 0; --pass) {
-    const int shift = 8 * pass;
-    int* hcur = sh.hist + (pass & 1) * 256;
+  {
+    const uint2 r = sh.wave_range[lane & (SEL_THREADS / 64 - 1)];
+    lo = r.x;
+    hi = r.y;
 #pragma unroll
-    for (int e = 0; e < SEL_IPT; ++e) {
-      int i = i0 + e;
-      if (e < ipt && i < V && (key[e] & mask) == prefix) atomicAdd(&hcur[(key[e] >> shift) & 255u], 1);
+    for (int off = SEL_THREADS / 128; off >= 1; off >>= 1) {
+      lo = min(lo, (uint32_t)__shfl_xor((int)lo, off));
+      hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
+    }
+  }
+  // The window [lo, lo + 256 2^shift) in 256 bins; the first holds every key, the next one bin of the one before.  (Keys
+  // 0 lie below the first window and count with its first bin: they are never taken while others are left.)
+  const uint32_t width = hi > lo ? hi - lo : 0u;
+  int shift = width < 256u ? 0 : 24 - __clz((int)width), left = take, size, pass = 0;
+  uint32_t at;
+  auto bin = [&](uint32_t k) { return k < lo ? (pass == 0 ? 0u : 256u) : (k - lo) >> shift; };
+  for (;; ++pass) {
+    int* h = reinterpret_cast<int*>(sh.hist[pass & 1]);
+#pragma unroll
+    for (int e = 0; e < IPT; ++e) {
+      if (e < ipt && i0 + e < V) {
+        const uint32_t x = bin(key[e]);
+        if (x < 256u) atomicAdd(&h[x], 1);
+      }
     }
     __syncthreads();
-    if (tid < 64) {
-      // one wave walks the digits from 255 down: lane l holds digits 255-4l .. 252-4l
-      int c[4], incl[4];
+    // every wave walks the bins from 255 down: lane l holds bins 255 - 4l .. 252 - 4l
+    const uint4 q4 = sh.hist[pass & 1][63 - lane];
+    const int c[4] = {(int)q4.w, (int)q4.z, (int)q4.y, (int)q4.x};
+    const int all = c[0] + c[1] + c[2] + c[3];
+    int above = wave_scan_incl(all) - all, b = -1, l = 0, n = 0;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) c[q] = hcur[255 - (4 * tid + q)];
-      incl[0] = c[0]; incl[1] = incl[0] + c[1]; incl[2] = incl[1] + c[2]; incl[3] = incl[2] + c[3];
-      int run = incl[3];
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        int y = __shfl_up(run, off);
-        if (tid >= off) run += y;
-      }
-      const int before = run - incl[3];         // candidates with a digit above this lane's four
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int upto = before + incl[q], above = upto - c[q];
-        if (upto >= remaining && above < remaining) {
-          sh.sel_bin = 255 - (4 * tid + q);
-          sh.sel_remaining = remaining - above;
-        }
-      }
-    } else if (tid >= 256 && tid < 512) {
-      sh.hist[((pass + 1) & 1) * 256 + (tid - 256)] = 0;    // the other histogram, for the next pass
+    for (int q = 0; q < 4; ++q) {
+      if (above < left && above + c[q] >= left) { b = 255 - (4 * lane + q); l = left - above; n = c[q]; }
+      above += c[q];
     }
-    __syncthreads();
-    prefix |= (uint32_t)sh.sel_bin << shift;
-    mask |= 255u << shift;
-    remaining = sh.sel_remaining;
+    const int who = __ffsll((unsigned long long)__ballot(b >= 0)) - 1;
+    at = (uint32_t)__builtin_amdgcn_readlane(b, who);
+    left = __builtin_amdgcn_readlane(l, who);
+    size = __builtin_amdgcn_readlane(n, who);
+    if (size <= SEL_LIST || shift == 0) break;                  // the same for all
+    if (pass > 0) {                                             // both histograms have been used
+      __syncthreads();
+      if (tid < 64) sh.hist[(pass + 1) & 1][tid] = make_uint4(0, 0, 0, 0);
+      __syncthreads();
+    }
+    lo += at << shift;
+    shift = max(shift - 8, 0);
   }
-  // prefix = the take-th largest key; `remaining` of the keys equal to it are taken, smallest index first
-  const uint32_t thr = prefix;
-  int n_eq = 0;
-#pragma unroll
-  for (int e = 0; e < SEL_IPT; ++e) {
-    int i = i0 + e;
-    if (e < ipt && i < V && key[e] == thr) ++n_eq;
-  }
-  int tot;
-  int eq_before = block_scan_excl(n_eq, sh.wave_sums, &tot);
   uint32_t bits = 0;
   int n = 0;
+  if (size <= SEL_LIST) {
+    // the keys of that bin, ranked against each other: the one with left - 1 in front of it is the last taken
 #pragma unroll
-  for (int e = 0; e < SEL_IPT; ++e) {
-    int i = i0 + e;
-    if (e < ipt && i < V) {
-      bool keep = key[e] > thr;
-      if (key[e] == thr) { keep = eq_before < remaining; ++eq_before; }
-      if (keep) { bits |= 1u << e; ++n; }
+    for (int e = 0; e < IPT; ++e) {
+      if (e < ipt && i0 + e < V) {
+        if (bin(key[e]) == at) sh.list[atomicAdd(&sh.listed, 1)] = make_uint2(key[e], (uint32_t)(i0 + e));
+      }
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const uint2 mine = sh.list[lane];
+      int rank = lane < size ? 0 : SEL_LIST;
+      for (int x = 0; x < size; ++x) {
+        const uint32_t ok = (uint32_t)__builtin_amdgcn_readlane((int)mine.x, x), oi = (uint32_t)__builtin_amdgcn_readlane((int)mine.y, x);
+        rank += (ok > mine.x || (ok == mine.x && oi < mine.y)) ? 1 : 0;
+      }
+      if (rank == left - 1) sh.last = mine;
+    }
+    __syncthreads();
+    const uint2 last = sh.last;
+#pragma unroll
+    for (int e = 0; e < IPT; ++e) {
+      const int i = i0 + e;
+      if (e < ipt && i < V && (key[e] > last.x || (key[e] == last.x && (uint32_t)i <= last.y))) { bits |= 1u << e; ++n; }
+    }
+  } else {
+    // a bin of one key value (shift is 0), more than SEL_LIST times: `left` of them are taken, smallest index first.  (In
+    // the first window the keys 0 count with the smallest key; they come after it.)
+    const uint32_t thr = lo + at;
+    int n_eq = 0;
+#pragma unroll
+    for (int e = 0; e < IPT; ++e)
+      if (e < ipt && i0 + e < V && key[e] == thr) ++n_eq;
+    int tot;
+    int eq_before = block_scan_excl(n_eq, sh.wave_sums, &tot);
+#pragma unroll
+    for (int e = 0; e < IPT; ++e) {
+      const int i = i0 + e;
+      if (e < ipt && i < V) {
+        bool keep = key[e] > thr;
+        if (key[e] == thr) { keep = eq_before < left; ++eq_before; }
+        if (keep) { bits |= 1u << e; ++n; }
+      }
     }
   }
   *n_mine = n;

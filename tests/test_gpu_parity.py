@@ -271,6 +271,34 @@ def test_ties_all_equal_scores_and_duplicate_rows(ctx):
     assert torch.equal(buf.out_hidden[0, P:P + cfg.k], st.hidden[0, P:P + cfg.k])
 
 
+@pytest.mark.parametrize("V", [1, 2, 63, 64, 65, 300, 1023, 1024, 1025, 2304, 4096, 4097, 16384])
+@pytest.mark.parametrize("kind", ["spread", "narrow", "equal", "few values", "far ones", "special"])
+def test_selection_of_given_scores(ctx, V, kind):
+    """asap_select against a sort (larger first, ties to the smaller index): one and several rounds of bins, a bin of
+    one value that more than a wave of tokens share, infinities, zeros of both signs and denormals, at the edges of
+    what a thread holds (1, 4 and 16 items)."""
+    r = np.random.default_rng(V)
+    draw = {"spread": lambda n: 2.0 ** r.uniform(-60, 0, n), "narrow": lambda n: 1e-3 * (1 + 1e-5 * r.random(n)),
+            "equal": lambda n: np.full(n, 0.25), "few values": lambda n: r.choice([0.1, 0.2, 0.3], n),
+            "far ones": lambda n: np.where(r.random(n) < 0.01, 1e30, 1e-3) * r.random(n),
+            "special": lambda n: r.choice([np.inf, -np.inf, 0.0, -0.0, 1e-45, 1e-40, 3.0, -3.0], n)}[kind]
+    for k in sorted({1, max(1, V // 7), (V + 1) // 2, V}):
+        p = binding.make_params(3, 1, 1, 64, 64, 0, V, 1, k, "bf16", "bf16", "bf16")
+        score = np.stack([draw(V) for _ in range(3)]).astype(np.float32)
+        bits = score.view(np.uint32)
+        key = np.where(bits >> 31, ~bits, bits | 0x80000000)              # float order, -0 below +0
+        kept = torch.full((3, k), -1, dtype=torch.int32, device="cuda")
+        pruned = torch.full((3, max(V - k, 1)), -1, dtype=torch.int32, device="cuda")
+        ctx.asap_select(p, torch.from_numpy(score).cuda(), kept, pruned.view(-1)[:3 * (V - k)].view(3, V - k),
+                        torch.empty(256, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        for b in range(3):
+            want = np.sort(np.lexsort((np.arange(V), -key[b].astype(np.int64)))[:k])
+            assert kept[b].cpu().numpy().tolist() == want.tolist()
+            rest = pruned.view(-1)[:3 * (V - k)].view(3, V - k)[b].cpu().numpy()
+            assert rest.tolist() == np.setdiff1d(np.arange(V), want).tolist()
+
+
 def test_determinism(ctx):
     cfg = synth.CONFIGS["S2"]
     inp = synth.make_inputs(cfg)

@@ -73,24 +73,10 @@ template <> __device__ __forceinline__ void sumsq16<float>(const uint4& c, SumSq
   acc.p[2] = fmaf(f[2], f[2], acc.p[2]); acc.p[3] = fmaf(f[3], f[3], acc.p[3]);
 }
 
-// all-reduce over a row of 16 lanes by rotations inside the row (the caller joins the two rows of a
-// 32-lane half with one exchange)
-template <int CTRL> __device__ __forceinline__ uint32_t dpp_u32(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xF, 0xF, false);
-}
-__device__ __forceinline__ float rowmax16(float x) {
-  x = fmaxf(x, __uint_as_float(dpp_u32<0x128>(__float_as_uint(x))));   // row_ror:8
-  x = fmaxf(x, __uint_as_float(dpp_u32<0x124>(__float_as_uint(x))));   // row_ror:4
-  x = fmaxf(x, __uint_as_float(dpp_u32<0x122>(__float_as_uint(x))));   // row_ror:2
-  x = fmaxf(x, __uint_as_float(dpp_u32<0x121>(__float_as_uint(x))));   // row_ror:1
-  return x;
-}
-__device__ __forceinline__ int rowmin16(int x) {
-  x = min(x, (int)dpp_u32<0x128>((uint32_t)x));
-  x = min(x, (int)dpp_u32<0x124>((uint32_t)x));
-  x = min(x, (int)dpp_u32<0x122>((uint32_t)x));
-  x = min(x, (int)dpp_u32<0x121>((uint32_t)x));
-  return x;
+// Sum over the two lane halves of a wave, in every lane (v_permlane32_swap).
+__device__ __forceinline__ float sum_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // What a workgroup knows about its tile once the products are done, and where the results go.
@@ -111,12 +97,17 @@ struct SimTile {
 };
 
 // Epilogue of a 128 x 64 NT tile held as 2 x NT accumulators per wave (waves 2 x 2 over the tile):
-// norm2 [128] / normk [64 NT] hold the squared norms of its rows / columns (this slice's share),
-// part [2][128] is LDS scratch, srow [128] the salience of the source rows (ANCHORED).  The caller
-// has put a barrier after the writes of norm2, normk and srow.
-template <int NT, bool ANCHORED>
+// norm2 [HALVES][128] / normk [HALVES][64 NT] hold the squared norms of its rows / columns (this slice's share, in one
+// or two parts), part [2][128] and best [4][64][BEST_ROW] are LDS scratch, srow [128] the salience of the source rows
+// (ANCHORED).  The caller has put a barrier after the writes of norm2, normk and srow and the last use of best's place.
+// The 32 lanes that share a row meet through LDS: each leaves the best of its NT columns, and then a lane takes a whole
+// row (butterflies over 32 rows one by one, value and column each, took 6.6 of the 103 us of 16 x 2304 tokens, now
+// 4.6; 5 x 2083 on 301: 4.5, now 3.1).
+constexpr int BEST_ROW = 34;                   // pairs per row: 32 lanes, and rows that start on 16 bytes
+constexpr size_t BEST_BYTES = (size_t)4 * 64 * BEST_ROW * sizeof(uint2);
+template <int NT, bool ANCHORED, int HALVES>
 __device__ __forceinline__ void sim_tile_epilogue(f32x16_t (&acc)[2][NT], const float* norm2, const float* normk,
-                                                  uint2* part, const float* srow, const SimTile& T_) {
+                                                  uint2* part, const float* srow, uint2* best, const SimTile& T_) {
   constexpr int BN = 64 * NT;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -127,16 +118,18 @@ __device__ __forceinline__ void sim_tile_epilogue(f32x16_t (&acc)[2][NT], const 
   const float threshold = T_.threshold;
   const int32_t* __restrict__ kept = T_.kept;
   const float* __restrict__ s_hat = T_.s_hat;
+  auto row_norm2 = [&](int r) { return HALVES == 2 ? norm2[r] + norm2[SIM_BM + r] : norm2[r]; };
+  auto col_norm2 = [&](int c) { return HALVES == 2 ? normk[c] + normk[BN + c] : normk[c]; };
   float run_v = -INFINITY;   // best of this workgroup's destination tile (threads < BM)
   int run_c = 0;
   {
     if (ksplit > 1) {
       // this slice's share of the products and of the squared norms; k_sim_reduce adds the slices up
       const int64_t img = (int64_t)ks * B + b;
-      if (pass == 0 && tid < SIM_BM && m0 + tid < M) T_.src_norm2[img * M + m0 + tid] = norm2[tid];
+      if (pass == 0 && tid < SIM_BM && m0 + tid < M) T_.src_norm2[img * M + m0 + tid] = row_norm2(tid);
       if (mt == 0)
         for (int c = tid; c < BN; c += 256)        // BN may exceed the workgroup size
-          if (n0 + c < k) T_.kept_norm2[img * k + n0 + c] = normk[c];
+          if (n0 + c < k) T_.kept_norm2[img * k + n0 + c] = col_norm2(c);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -152,8 +145,7 @@ __device__ __forceinline__ void sim_tile_epilogue(f32x16_t (&acc)[2][NT], const 
     }
 
     // Row arg-max of dot / |x_j| over this pass's destinations (|x_i| > 0 does not move it).
-    // A lane first takes the best of its NT columns of a row (columns past k get -inf), then the 32
-    // lanes that share the row agree on the maximum and on the smallest column that reaches it.
+    // A lane first takes the best of its NT columns of a row (columns past k get -inf).
     float invk[NT], bias[NT];
     int colv[NT];
 #pragma unroll
@@ -161,7 +153,7 @@ __device__ __forceinline__ void sim_tile_epilogue(f32x16_t (&acc)[2][NT], const 
       const int cl = wn * (BN / 2) + t * 32 + n;
       colv[t] = n0 + cl;
       const bool valid = colv[t] < k;
-      invk[t] = valid ? 1.0f / fmaxf(sqrtf(normk[cl]), 1e-8f) : 0.0f;
+      invk[t] = valid ? 1.0f / fmaxf(sqrtf(col_norm2(cl)), 1e-8f) : 0.0f;
       bias[t] = valid ? 0.0f : -INFINITY;
     }
     float scol[NT];            // ANCHORED: salience of this lane's destination columns
@@ -170,10 +162,7 @@ __device__ __forceinline__ void sim_tile_epilogue(f32x16_t (&acc)[2][NT], const 
       scol[t] = (ANCHORED && colv[t] < k) ? s_hat[(int64_t)b * V + kept[(int64_t)b * k + colv[t]]] : 0.0f;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      // stage by stage over the 16 rows a lane holds, so that the cross-lane exchanges of
-      // different rows overlap instead of waiting for one another
-      float bv[16], mv[16], ov[16];
-      int bc[16], mc[16], oc[16];
+      uint2* rows = best + (wave * 64 + i * 32) * BEST_ROW + n;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         float c[NT];
@@ -189,30 +178,37 @@ __device__ __forceinline__ void sim_tile_epilogue(f32x16_t (&acc)[2][NT], const 
             c[t] = stronger ? c[t] : -INFINITY;
           }
         }
-        bv[v] = c[0];
+        float bv = c[0];
 #pragma unroll
-        for (int t = 1; t < NT; ++t) bv[v] = fmaxf(bv[v], c[t]);
-        bc[v] = 0x7fffffff;
+        for (int t = 1; t < NT; ++t) bv = fmaxf(bv, c[t]);
+        int bc = 0x7fffffff;
 #pragma unroll
-        for (int t = NT - 1; t >= 0; --t) bc[v] = (c[t] == bv[v]) ? colv[t] : bc[v];   // columns ascend with t
+        for (int t = NT - 1; t >= 0; --t) bc = (c[t] == bv) ? colv[t] : bc;       // columns ascend with t
+        rows[mma32_row(v, lane) * BEST_ROW] = make_uint2(__float_as_uint(bv), (uint32_t)bc);
       }
+    }
+    // lane l: row l of the wave's 64 (its own wave's writes, in order); the largest value and its smallest column
+    {
+      const uint4* row = reinterpret_cast<const uint4*>(best + (wave * 64 + lane) * BEST_ROW);
+      float mv = -INFINITY;
+      int mc = 0x7fffffff;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) mv[v] = rowmax16(bv[v]);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) ov[v] = __shfl_xor(mv[v], 16);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        mv[v] = fmaxf(mv[v], ov[v]);
-        mc[v] = rowmin16(bv[v] == mv[v] ? bc[v] : 0x7fffffff);
+      for (int x = 0; x < 16; ++x) {
+        const uint4 q = row[x];
+        auto take = [&](float v, int c) {
+          const float nv = fmaxf(mv, v);
+          mc = (v == nv && (mv != nv || c < mc)) ? c : mc;
+          mv = nv;
+        };
+        if (x == 0) {
+          mv = __uint_as_float(q.x);
+          mc = (int)q.y;
+        } else {
+          take(__uint_as_float(q.x), (int)q.y);
+        }
+        take(__uint_as_float(q.z), (int)q.w);
       }
-#pragma unroll
-      for (int v = 0; v < 16; ++v) oc[v] = __shfl_xor(mc[v], 16);
-      if (n == 0) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          part[wn * SIM_BM + wm * 64 + i * 32 + mma32_row(v, lane)] =
-              make_uint2(__float_as_uint(mv[v]), (uint32_t)min(mc[v], oc[v]));
-      }
+      part[wn * SIM_BM + wm * 64 + lane] = make_uint2(__float_as_uint(mv), (uint32_t)mc);
     }
     __syncthreads();
     if (tid < SIM_BM) {
@@ -227,7 +223,7 @@ __device__ __forceinline__ void sim_tile_epilogue(f32x16_t (&acc)[2][NT], const 
   if (tid < SIM_BM && m0 + tid < M) {
     const int64_t o = (int64_t)b * M + m0 + tid;
     if (ptiles == 1) {
-      float c = run_v / fmaxf(sqrtf(norm2[tid]), 1e-8f);
+      float c = run_v / fmaxf(sqrtf(row_norm2(tid)), 1e-8f);
       T_.best_sim[o] = c;
       T_.assign[o] = (c > threshold) ? run_c : -1;
     } else {
@@ -236,7 +232,7 @@ __device__ __forceinline__ void sim_tile_epilogue(f32x16_t (&acc)[2][NT], const 
       // largest key of a row and turns it into assign / best_sim
       const unsigned long long key = ((unsigned long long)float_key(run_v) << 32) | (0xFFFFFFFFu - (uint32_t)run_c);
       T_.best_key[(int64_t)pass * ((int64_t)B * M) + o] = key;
-      if (pass == 0) T_.src_norm2[o] = norm2[tid];
+      if (pass == 0) T_.src_norm2[o] = row_norm2(tid);
     }
   }
 }
@@ -287,9 +283,9 @@ __global__ __launch_bounds__(256) void k_sim(const T* __restrict__ xv, int64_t s
   extern __shared__ __align__(16) char lds[];
   char* ldsB = lds + NA * ASTAGE;
   const uint32_t lds_addr = lds_address(lds), ldsB_addr = lds_addr + NA * ASTAGE;
-  float* norm2 = reinterpret_cast<float*>(ldsB + NB * BSTAGE);   // [BM] squared norms of the source rows
-  float* normk = norm2 + SIM_BM;                                 // [BN] squared norms of this pass's kept rows
-  uint2* part = reinterpret_cast<uint2*>(normk + BN);            // [2][BM] (value, column) per column half
+  float* norm2 = reinterpret_cast<float*>(ldsB + NB * BSTAGE);   // [2][BM] squared norms of the source rows
+  float* normk = norm2 + 2 * SIM_BM;                             // [2][BN] squared norms of this pass's kept rows
+  uint2* part = reinterpret_cast<uint2*>(normk + 2 * BN);        // [2][BM] (value, column) per column half
   float* srow = reinterpret_cast<float*>(part + 2 * SIM_BM);     // [BM] salience of the source rows (ANCHORED)
 
   // With ksplit > 1 (launches that would leave most of the chip idle) the hidden dimension is cut into
@@ -443,39 +439,28 @@ __global__ __launch_bounds__(256) void k_sim(const T* __restrict__ xv, int64_t s
       barrier_keep_loads();
     }
 
-    wait_all_vmem();   // the repeated loads of the last steps
     // The two lane halves hold the two halves of every 128-byte slice, and the wave beside (source
-    // rows) or below (destination rows) the other two contraction slices of every step: it adds its
-    // half in a second turn.
+    // rows) or below (destination rows) the other two contraction slices of every step.
 #pragma unroll
-    for (int turn = 0; turn < 2; ++turn) {
-      if (wn == turn) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          float v = ss_a[i].total();
-          v += __shfl_xor(v, 32);
-          float* o = &norm2[wm * 64 + i * 32 + n];
-          if (hf == 0) *o = turn == 0 ? v : *o + v;
-        }
-      }
-      if (wm == turn) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          float v = ss_b[t].total();
-          v += __shfl_xor(v, 32);
-          float* o = &normk[wn * (BN / 2) + t * 32 + n];
-          if (hf == 0) *o = turn == 0 ? v : *o + v;
-        }
-      }
-      __syncthreads();   // after the second turn: norms visible
+    for (int i = 0; i < 2; ++i) {
+      const float v = sum_halves(ss_a[i].total());
+      if (hf == 0) norm2[wn * SIM_BM + wm * 64 + i * 32 + n] = v;
     }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const float v = sum_halves(ss_b[t].total());
+      if (hf == 0) normk[wm * BN + wn * (BN / 2) + t * 32 + n] = v;
+    }
+    wait_all_vmem();   // the repeated loads of the last steps: the rings become the epilogue's scratch
+    __syncthreads();
 
     SimTile tile;
     tile.b = b; tile.B = B; tile.M = M; tile.k = k; tile.V = V; tile.m0 = m0; tile.n0 = n0; tile.pass = pass;
     tile.ptiles = ptiles; tile.mt = mt; tile.ks = ks; tile.ksplit = ksplit; tile.threshold = threshold;
     tile.kept = kept; tile.s_hat = s_hat; tile.assign = assign; tile.best_sim = best_sim; tile.best_key = best_key;
     tile.src_norm2 = src_norm2; tile.dots = dots; tile.kept_norm2 = kept_norm2;
-    sim_tile_epilogue<NT, ANCHORED>(acc, norm2, normk, part, srow, tile);
+    static_assert(NA * ASTAGE + NB * BSTAGE >= BEST_BYTES, "the epilogue's scratch");
+    sim_tile_epilogue<NT, ANCHORED, 2>(acc, norm2, normk, part, srow, reinterpret_cast<uint2*>(lds), tile);
   }
 }
 
@@ -714,7 +699,9 @@ __global__ __launch_bounds__(256) void k_sim_f32(const float* __restrict__ xv, i
   tile.ptiles = ptiles; tile.mt = mt; tile.ks = ks; tile.ksplit = ksplit; tile.threshold = threshold;
   tile.kept = kept; tile.s_hat = s_hat; tile.assign = assign; tile.best_sim = best_sim; tile.best_key = best_key;
   tile.src_norm2 = src_norm2; tile.dots = dots; tile.kept_norm2 = kept_norm2;
-  sim_tile_epilogue<NT, ANCHORED>(acc, norm2, normk, part, srow, tile);
+  constexpr int BEST_AT = (4 * (2 * SIM_BM + BN) + 2 * SIM_BM * 8 + 15) / 16 * 16;      // behind those arrays
+  static_assert(2 * STAGE >= BEST_AT + BEST_BYTES, "the epilogue's scratch");
+  sim_tile_epilogue<NT, ANCHORED, 1>(acc, norm2, normk, part, srow, reinterpret_cast<uint2*>(lds + BEST_AT), tile);
 }
 
 // grid (ceil(n / 256)): the largest key over the destination tiles of a row -> assign, best_sim
@@ -841,7 +828,7 @@ static hipError_t launch_sim_nt(const asap_params& p, const T* xv, int64_t sb, i
   constexpr bool F32 = sizeof(T) == 4;
   static_assert(!F32 || NT <= SIMF_MAX_NT, "two steps of f32 pieces must fit LDS");
   const size_t lds = F32 ? (size_t)2 * (SIM_BM + BN) * SIMF_ROWP
-                         : (size_t)(sim_na(NT) * SIM_BM + sim_nb(NT) * BN) * SIM_ROWB + sizeof(float) * (6 * SIM_BM + BN);
+                         : (size_t)(sim_na(NT) * SIM_BM + sim_nb(NT) * BN) * SIM_ROWB + sizeof(float) * (7 * SIM_BM + 2 * BN);
   auto kern = [] {
     if constexpr (F32) return k_sim_f32<NT, ANCHORED>;
     else return k_sim<T, NT, ANCHORED>;

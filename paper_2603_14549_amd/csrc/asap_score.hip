@@ -219,7 +219,8 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 2 : RIDE ? 3 : 1)) void k_ma
   constexpr bool REUSE = F32 || RIDE;
   __shared__ __align__(16) char stage[4][32 * RBY];
   __shared__ double part[4][32];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, hf = lane >> 5;
   const int piece = lane % LPR, r0 = lane / LPR;
   const int b = blockIdx.y, j0 = blockIdx.x * 32, g_hi = Hkv;

@@ -592,6 +592,9 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
   //    compute units busy and moves next to nothing, so further workgroups of it copy those rows.
   const int64_t hidden_bytes = (int64_t)p->B * p->V * p->D * (p->h_dtype == ASAP_BF16 ? 2 : 4);
   const bool fixed_first = early && kv_bytes > 4 * hidden_bytes;
+  // Caches so deep that the search is over long before the copy give it all the room there is (16 layers of 8 x 576
+  // tokens, 25 times the hidden states: 276 us per stage, 279 with a bound; 4 layers of 10 x 1500, 5 times: 309 and 299).
+  const bool outlasts = kv_bytes > 16 * hidden_bytes;
   const bool fixed_with_selection = early && !fixed_first && score_fuses_selection(*p) && p->h_dtype == ASAP_BF16 &&
                                     io->n_layers <= KV_LAYERS_PER_LAUNCH;
   hipError_t e = hipSuccess;
@@ -624,7 +627,7 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
       forked = true;
       e = launch_compact_kv(*p, (fixed_first || fixed_with_selection) ? KV_KEPT_ONLY : KV_FROM_KEPT, io->n_layers,
                             io->k_src, io->v_src, io->k_dst, io->v_dst, io->kept_idx, io->text_len, ctx->side,
-                            ctx->timer);
+                            ctx->timer, outlasts ? 0 : KV_BESIDE_SIM_LDS);
     }
   }
   // On one stream the merge's launch takes the compaction of (up to 16) layers along: whichever routing, the

@@ -107,7 +107,7 @@ hipError_t launch_positions(const asap_params& p, const int32_t* kept, const int
 // mode: KV_BY_POS (idx = pos_out, len = new_len) or KV_FROM_KEPT (idx = kept list, len = text_len)
 hipError_t launch_compact_kv(const asap_params& p, int mode, int n_layers, const void* const* k_src,
                              const void* const* v_src, void* const* k_dst, void* const* v_dst,
-                             const int32_t* idx, const int32_t* len, hipStream_t st, Timer* tm) {
+                             const int32_t* idx, const int32_t* len, hipStream_t st, Timer* tm, size_t lds) {
   const int row_bytes = p.d * (p.kv_dtype == ASAP_BF16 ? 2 : 4);
   const int N = p.P + p.V + p.Tmax, Nout = p.P + p.k + p.Tmax;
   const int rows_per_block = kv_rows_per_block(row_bytes);
@@ -121,10 +121,10 @@ hipError_t launch_compact_kv(const asap_params& p, int mode, int n_layers, const
       ASAP_LAUNCH(tm, "k_compact", k_compact<KV_BY_POS>, grid, dim3(256), 0, st, ptrs, idx, len, p.Hkv, N, Nout,
                   row_bytes, p.P, p.V, p.k);
     else if (mode == KV_FROM_KEPT)
-      ASAP_LAUNCH(tm, "k_compact", k_compact<KV_FROM_KEPT>, grid, dim3(256), 0, st, ptrs, idx, len, p.Hkv, N, Nout,
+      ASAP_LAUNCH(tm, "k_compact", k_compact<KV_FROM_KEPT>, grid, dim3(256), lds, st, ptrs, idx, len, p.Hkv, N, Nout,
                   row_bytes, p.P, p.V, p.k);
     else if (mode == KV_KEPT_ONLY)
-      ASAP_LAUNCH(tm, "k_compact", k_compact<KV_KEPT_ONLY>, grid, dim3(256), 0, st, ptrs, idx, len, p.Hkv, N, Nout,
+      ASAP_LAUNCH(tm, "k_compact", k_compact<KV_KEPT_ONLY>, grid, dim3(256), lds, st, ptrs, idx, len, p.Hkv, N, Nout,
                   row_bytes, p.P, p.V, p.k);
     else {
       const long total = (long)grid.x * grid.y * grid.z;

@@ -171,9 +171,14 @@ hipError_t launch_positions(const asap_params& p, const int32_t* kept, const int
 // rows (prefix, valid text), which need no index list.  The last two together move what KV_FROM_KEPT
 // moves.
 enum { KV_BY_POS = 0, KV_FROM_KEPT = 1, KV_KEPT_ONLY = 2, KV_FIXED_ONLY = 3 };
+// lds: bytes of LDS that a workgroup claims without using them.  Beside the similarity search, on another stream, they
+// decide how many workgroups share a compute unit with it, and with that which of the two gets on: k_sim's widest tile
+// leaves 10 KB, and two workgroups there bring both to their end together (16 x 2304 tokens on 320, stage: 405 us with
+// the five that registers let in, 399 with two, 404 with one; 8 x 2304 on 576: 356, 349, 350).
+constexpr size_t KV_BESIDE_SIM_LDS = 5 * 1024;
 hipError_t launch_compact_kv(const asap_params& p, int mode, int n_layers, const void* const* k_src,
                              const void* const* v_src, void* const* k_dst, void* const* v_dst,
-                             const int32_t* idx, const int32_t* len, hipStream_t st, Timer* tm);
+                             const int32_t* idx, const int32_t* len, hipStream_t st, Timer* tm, size_t lds = 0);
 hipError_t launch_compact_kv_paged(const asap_params& p, int n_layers, const void* const* k_src,
                                    const void* const* v_src, void* const* k_dst, void* const* v_dst, int page_size,
                                    const int32_t* src_table, int src_stride, const int32_t* dst_table,

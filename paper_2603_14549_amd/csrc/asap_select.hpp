@@ -107,11 +107,12 @@ __device__ __forceinline__ uint32_t topk(const uint32_t (&key)[IPT], int ipt, in
       hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
     }
   }
-  // The window [lo, lo + 256 2^shift) in 256 bins; the first holds every key, the next one bin of the one before.  (Keys
-  // 0 lie below the first window and count with its first bin: they are never taken while others are left.)
+  // The window [lo, lo + bins 2^shift); the first holds every key, the next one bin of the one before and no key above it
+  // (those are counted already), so it has fewer than 256 bins where that bin is narrower.  (Keys 0 lie below the first
+  // window and count with its first bin: they are never taken while others are left.)
   const uint32_t width = hi > lo ? hi - lo : 0u;
   int shift = width < 256u ? 0 : 24 - __clz((int)width), left = take, size, pass = 0;
-  uint32_t at;
+  uint32_t at, bins = 256u;
   auto bin = [&](uint32_t k) { return k < lo ? (pass == 0 ? 0u : 256u) : (k - lo) >> shift; };
   for (;; ++pass) {
     int* h = reinterpret_cast<int*>(sh.hist[pass & 1]);
@@ -119,7 +120,7 @@ __device__ __forceinline__ uint32_t topk(const uint32_t (&key)[IPT], int ipt, in
     for (int e = 0; e < IPT; ++e) {
       if (e < ipt && i0 + e < V) {
         const uint32_t x = bin(key[e]);
-        if (x < 256u) atomicAdd(&h[x], 1);
+        if (x < bins) atomicAdd(&h[x], 1);
       }
     }
     __syncthreads();
@@ -144,6 +145,7 @@ __device__ __forceinline__ uint32_t topk(const uint32_t (&key)[IPT], int ipt, in
       __syncthreads();
     }
     lo += at << shift;
+    bins = 1u << min(shift, 8);
     shift = max(shift - 8, 0);
   }
   uint32_t bits = 0;

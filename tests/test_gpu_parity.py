@@ -272,15 +272,21 @@ def test_ties_all_equal_scores_and_duplicate_rows(ctx):
 
 
 @pytest.mark.parametrize("V", [1, 2, 63, 64, 65, 300, 1023, 1024, 1025, 2304, 4096, 4097, 16384])
-@pytest.mark.parametrize("kind", ["spread", "narrow", "equal", "few values", "far ones", "special"])
+@pytest.mark.parametrize("kind", ["spread", "narrow", "equal", "few values", "far ones", "special", "close",
+                                  "crowd"])
 def test_selection_of_given_scores(ctx, V, kind):
     """asap_select against a sort (larger first, ties to the smaller index): one and several rounds of bins, a bin of
     one value that more than a wave of tokens share, infinities, zeros of both signs and denormals, at the edges of
-    what a thread holds (1, 4 and 16 items)."""
+    what a thread holds (1, 4 and 16 items).  "close" and "crowd" leave more than a wave of keys in a bin narrower than
+    256 with others just above it, which the next round must not count again."""
     r = np.random.default_rng(V)
+    ulps = lambda n: (np.float32(0.01).view(np.uint32) + n.astype(np.int64)).astype(np.uint32).view(np.float32)
     draw = {"spread": lambda n: 2.0 ** r.uniform(-60, 0, n), "narrow": lambda n: 1e-3 * (1 + 1e-5 * r.random(n)),
             "equal": lambda n: np.full(n, 0.25), "few values": lambda n: r.choice([0.1, 0.2, 0.3], n),
             "far ones": lambda n: np.where(r.random(n) < 0.01, 1e30, 1e-3) * r.random(n),
+            "close": lambda n: ulps(r.integers(0, 2000, n)),
+            "crowd": lambda n: ulps(np.where(r.random(n) < 0.2, r.integers(-10**7, 10**7, n),
+                                             r.integers(0, 255, n) * (r.random(n) < 0.6))),
             "special": lambda n: r.choice([np.inf, -np.inf, 0.0, -0.0, 1e-45, 1e-40, 3.0, -3.0], n)}[kind]
     for k in sorted({1, max(1, V // 7), (V + 1) // 2, V}):
         p = binding.make_params(3, 1, 1, 64, 64, 0, V, 1, k, "bf16", "bf16", "bf16")

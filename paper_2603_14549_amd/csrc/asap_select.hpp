@@ -22,10 +22,10 @@ template <typename F> static auto with_ipt(int V, F&& f) {
   return f(std::integral_constant<int, SEL_IPT>{});
 }
 
-// order-preserving map float -> uint32 (larger float, larger key); every finite float maps above 0
+// order-preserving map float -> uint32 (larger float, larger key); every float maps above 0, the NaN of all ones too
 __device__ __forceinline__ uint32_t float_key(float f) {
   uint32_t u = __float_as_uint(f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return (u & 0x80000000u) ? max(~u, 1u) : (u | 0x80000000u);
 }
 
 __device__ __forceinline__ float float_unkey(uint32_t k) {

@@ -273,7 +273,7 @@ def test_ties_all_equal_scores_and_duplicate_rows(ctx):
 
 @pytest.mark.parametrize("V", [1, 2, 63, 64, 65, 300, 1023, 1024, 1025, 2304, 4096, 4097, 16384])
 @pytest.mark.parametrize("kind", ["spread", "narrow", "equal", "few values", "far ones", "special", "close",
-                                  "crowd"])
+                                  "crowd", "no numbers"])
 def test_selection_of_given_scores(ctx, V, kind):
     """asap_select against a sort (larger first, ties to the smaller index): one and several rounds of bins, a bin of
     one value that more than a wave of tokens share, infinities, zeros of both signs and denormals, at the edges of
@@ -287,12 +287,14 @@ def test_selection_of_given_scores(ctx, V, kind):
             "close": lambda n: ulps(r.integers(0, 2000, n)),
             "crowd": lambda n: ulps(np.where(r.random(n) < 0.2, r.integers(-10**7, 10**7, n),
                                              r.integers(0, 255, n) * (r.random(n) < 0.6))),
+            "no numbers": lambda n: r.choice(np.array([0xffffffff, 0xffc00000, 0x7fc00000, 0xff800000], np.uint32),
+                                             n, p=[0.7, 0.1, 0.1, 0.1]).view(np.float32),
             "special": lambda n: r.choice([np.inf, -np.inf, 0.0, -0.0, 1e-45, 1e-40, 3.0, -3.0], n)}[kind]
     for k in sorted({1, max(1, V // 7), (V + 1) // 2, V}):
         p = binding.make_params(3, 1, 1, 64, 64, 0, V, 1, k, "bf16", "bf16", "bf16")
         score = np.stack([draw(V) for _ in range(3)]).astype(np.float32)
         bits = score.view(np.uint32)
-        key = np.where(bits >> 31, ~bits, bits | 0x80000000)              # float order, -0 below +0
+        key = np.maximum(np.where(bits >> 31, ~bits, bits | 0x80000000), 1)      # float order, -0 below +0
         kept = torch.full((3, k), -1, dtype=torch.int32, device="cuda")
         pruned = torch.full((3, max(V - k, 1)), -1, dtype=torch.int32, device="cuda")
         ctx.asap_select(p, torch.from_numpy(score).cuda(), kept, pruned.view(-1)[:3 * (V - k)].view(3, V - k),

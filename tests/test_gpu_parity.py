@@ -1447,3 +1447,51 @@ def test_compaction_in_the_launch_of_the_merge(ctx, layers, route):
         for src, dst in zip(st.k_cache + st.v_cache, buf.k_dst + buf.v_dst):
             assert torch.equal(dst[b, :, :n], src[b][:, pos])
             assert int((dst[b, :, n:] != 0).sum()) == 0
+
+
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (64, "f32"), (128, "f32")])
+@pytest.mark.parametrize("over", [-1, 0, 1])
+def test_compaction_at_the_edges_of_its_blocks(ctx, d, dtype, over):
+    """Contiguous and paged copies whose row counts end one row before, at and one row behind a workgroup's share."""
+    B, H, P, T, k = 3, 2, 3, 5, 0
+    row_bytes = d * (2 if dtype == "bf16" else 4)
+    k = 4 * 4096 // row_bytes + over - P - T
+    V = k + 9
+    p = binding.make_params(B, H, H, d, 128, P, V, T, k, dtype, "bf16", dtype)
+    N, Nout = P + V + T, P + k + T
+    g = torch.Generator(device="cuda").manual_seed(41)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    src = [torch.randn(B, H, N, d, generator=g, device="cuda").to(tdt) for _ in range(2)]
+    kept = torch.stack([torch.randperm(V, generator=g, device="cuda")[:k].sort().values for _ in range(B)]).to(torch.int32)
+    text_len = torch.tensor([T, 1, 3], dtype=torch.int32, device="cuda")
+    pos = torch.empty(B, Nout, dtype=torch.int32, device="cuda")
+    new_len = torch.empty(B, dtype=torch.int32, device="cuda")
+    ctx.asap_positions(p, kept, text_len, pos, new_len)
+    outs = []
+    for how in ("positions", "kept"):
+        dst = [torch.full((B, H, Nout, d), 7.0, dtype=tdt, device="cuda") for _ in range(2)]
+        if how == "positions":
+            ctx.asap_compact_kv(p, src[:1], src[1:], dst[:1], dst[1:], pos, new_len)
+        else:
+            ctx.asap_compact_kv_from_kept(p, src[:1], src[1:], dst[:1], dst[1:], kept, text_len)
+        outs.append(dst)
+    page = 8
+    sp, dp = -(-N // page), -(-Nout // page)
+    perm = torch.randperm(B * (sp + dp), generator=g, device="cuda").to(torch.int32)
+    st, dt = perm[:B * sp].view(B, sp), perm[B * sp:].view(B, dp)
+    pools = [torch.full((B * (sp + dp), H, page, d), 7.0, dtype=tdt, device="cuda") for _ in range(2)]
+    for pool, s in zip(pools, src):
+        padded = torch.cat([s, torch.full((B, H, sp * page - N, d), 7.0, dtype=tdt, device="cuda")], 2)
+        pool[st.reshape(-1).long()] = padded.view(B, H, sp, page, d).transpose(1, 2).reshape(B * sp, H, page, d)
+    ctx.asap_compact_kv_paged(p, pools[:1], pools[1:], pools[:1], pools[1:], page, st.contiguous(), dt.contiguous(), pos, new_len)
+    outs.append([pool[dt.reshape(-1).long()].view(B, dp, H, page, d).transpose(1, 2).reshape(B, H, dp * page, d)[:, :, :Nout]
+                 for pool in pools])
+    torch.cuda.synchronize()
+    for dst in outs:
+        for s, t in zip(src, dst):
+            for b in range(B):
+                n = P + k + int(text_len[b])
+                assert int(new_len[b]) == n
+                want = torch.cat([s[b][:, :P], s[b][:, P + kept[b].long()], s[b][:, P + V:P + V + int(text_len[b])]], 1)
+                assert torch.equal(t[b][:, :n], want)
+                assert bool((t[b][:, n:] == 7.0).all())

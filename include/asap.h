@@ -297,12 +297,14 @@ typedef enum { ASAP_STREAMS_ONE = 0, ASAP_STREAMS_AUTO = 1, ASAP_STREAMS_TWO = 2
  * kernels; `stream` waits for it at the end: work enqueued on `stream` after the call sees all
  * outputs.  The similarity kernel is bound on chip and the compaction by HBM, which is why the two
  * go well side by side.  ASAP_STREAMS_ONE never does this, ASAP_STREAMS_TWO always, and
- * ASAP_STREAMS_AUTO when the compaction moves at least 64 MiB (bytes read + written): below that
- * the two hand-overs between the streams cost more than they save.
+ * ASAP_STREAMS_AUTO when the compaction moves at least 64 MiB (bytes read + written) and, with half the bytes of
+ * the hidden states (twice those of f32 ones), 250 MiB: below that the two hand-overs between the streams cost more
+ * than they save.
  * The K/V rows that no selection can change (prefix, valid text; Fig. 3) do not wait for the
  * selection: when the caches are deep (the compaction moves more than four times the bytes of the
  * hidden states) the second stream starts on them at the beginning of the call, beside the score
- * kernels; else, for bf16 hidden states, B >= 12 and n_layers <= 16, further workgroups of the
+ * kernels, as many layers of them as those leave time for, and `stream` takes some layers after the merge so that both end
+ * together; else, for bf16 hidden states, B >= 12 and n_layers <= 16, further workgroups of the
  * launch that selects copy them.  The second stream then moves the rows of the kept tokens only;
  * the bytes written are the same in every case.
  * With ASAP_ROUTE_PAPER (final_idx exists only after the merge) everything runs on `stream` in

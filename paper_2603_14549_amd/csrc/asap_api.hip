@@ -550,6 +550,32 @@ static asap_status stage_resources(asap_ctx* ctx) {
   return ASAP_OK;
 }
 
+// How asap_stage deals the K/V copy of deep caches out.
+struct KvDeal {
+  int fixed;      // layers 0 .. fixed - 1: their prefix and text rows go before the selection, beside the score kernels
+  int side;       // layers 0 .. side - 1: what is left of them goes on the second stream, the others' follows the merge
+};
+// `fixed`: what the score kernels leave time for, about 4.4 MB per us of 40 us and three sweeps over the visual queries (text rows
+// at three quarters of their room).  Beyond that the copy of those rows would only hold up the others' on its stream: 11 x
+// 384 tokens on 64, prefix 45, text 48, 16 layers 255 us per stage with all layers, 222 with 4 or 8 (8 x 576 on 160, no prefix, text 64, where
+// all fit: 264 with 16, 274 with 8).
+// `side`: a wait for the second stream that finds it done costs the caller's stream 7 us, one that has to wait for it 17.  So
+// where the copy outlasts search and merge, the caller's stream takes half of what is left when the merge ends.  us per stage with
+// 0 / 4 / 8 of 16 layers after the merge: 8 x 576 on 160, 40 heads 269 / 264 / 267;  10 x 328 on 84 186 / 181 / 181;  5 x 1435 on
+// 315 304 / 299 / 296;  3 x 512 on 176, 40 heads, where the search is nearly as long 159 / 158 / 162.
+static KvDeal deal_kv(const asap_params& p, int n_layers, int64_t kv_row_bytes, int64_t hidden_bytes) {
+  const double layer = 4.0 * p.B * p.Hkv * kv_row_bytes;                     // bytes moved per row of K and V of a layer
+  const double fixed = layer * (p.P + 0.75 * p.Tmax);
+  const double q_bytes = (double)p.B * p.H * p.V * p.d * (p.qk_dtype == ASAP_BF16 ? 2 : 4);
+  const double score_us = 40 + 3 * q_bytes / 4e6;
+  KvDeal deal{n_layers, n_layers};
+  if (fixed * n_layers > 4.4e6 * score_us) deal.fixed = (int)(4.4e6 * score_us / fixed);
+  const double copy_us = (layer * p.k * n_layers + fixed * (n_layers - deal.fixed)) / 6e6;
+  const double merge_us = 3.5e-3 * sim_row_steps(p) + hidden_bytes / 5e6;
+  if (copy_us > merge_us) deal.side -= (int)((0.5 - 0.5 * merge_us / copy_us) * n_layers + 0.5);
+  return deal;
+}
+
 asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io* io, int32_t two_streams,
                        void* stream) {
   if (!ctx) return ASAP_EINVAL;
@@ -569,14 +595,22 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
   if (st == ASAP_OK && has_kv)
     st = check_kv_buffers(ctx, p, "asap_stage", io->n_layers, io->k_src, io->v_src, io->k_dst, io->v_dst);
   if (st != ASAP_OK) return st;
-  // With ASAP_ROUTE_ABSORB the kept set is final after the selection: the K/V rows can move while the merge
-  // runs.  The two hand-overs between the streams cost the caller's stream about as much as copying 64 MB
-  // does (measured: single images and batches of 4 ran 3 to 9 % faster on one stream), so with
-  // ASAP_STREAMS_AUTO smaller compactions stay on the caller's stream.
+  // With ASAP_ROUTE_ABSORB the kept set is final after the selection: the K/V rows can move while the merge runs.
+  // What that hides is at most the search's time; the hand-overs between the streams cost the caller's stream 13 us or more
+  // and the host 50, and a copy alone runs at 6.2 TB/s.  So with ASAP_STREAMS_AUTO the second stream is used for 64 MB and more
+  // where the copy and the hidden states together are large; f32 states, whose search takes longer for its bytes, count
+  // four times as much.  The line through 110 shapes of up to 1.3 GB (us per stage on one stream / on two; MB copied and of hidden states):
+  //   bf16  141 and 3: 67 / 76;  168 and 38: 117 / 120;  194 and 16: 110 / 117;  207 and 47: 143 / 147;  240 and 54: 159 / 161;  249 and
+  //         140: 216 / 205;  275 and 20: 121 / 118;  354 and 119: 313 / 295;  702 and 18: 195 / 177;  the worst beyond it 312 and 4: 103 / 110
+  //   f32   72 and 63: 166 / 168;  141 and 20: 101 / 106;  228 and 5: 94 / 101;  134 and 117: 201 / 196;  309 and 7: 111 / 103;
+  //         184 and 69: 181 / 170
   const int64_t kv_row_bytes = p->d * (p->kv_dtype == ASAP_BF16 ? 2 : 4);
   const int64_t kv_bytes = 4 * (int64_t)io->n_layers * p->B * p->Hkv * (p->P + p->k + p->Tmax) * kv_row_bytes;
+  const int64_t hidden_bytes = (int64_t)p->B * p->V * p->D * (p->h_dtype == ASAP_BF16 ? 2 : 4);
+  const bool worth_forking = kv_bytes >= (64ll << 20) &&
+                             kv_bytes + (p->h_dtype == ASAP_BF16 ? hidden_bytes / 2 : 2 * hidden_bytes) >= (250ll << 20);
   const bool early = has_kv && p->route == ASAP_ROUTE_ABSORB &&
-                     (two_streams == ASAP_STREAMS_TWO || (two_streams == ASAP_STREAMS_AUTO && kv_bytes >= (64ll << 20)));
+                     (two_streams == ASAP_STREAMS_TWO || (two_streams == ASAP_STREAMS_AUTO && worth_forking));
   if (early && (st = stage_resources(ctx)) != ASAP_OK) return st;
 
   hipStream_t main = static_cast<hipStream_t>(stream);
@@ -590,7 +624,6 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
   //    the score kernels, and takes the kept tokens' rows after the selection.
   //  * Otherwise, for large bf16 batches: the launch that finishes the score and selects keeps B
   //    compute units busy and moves next to nothing, so further workgroups of it copy those rows.
-  const int64_t hidden_bytes = (int64_t)p->B * p->V * p->D * (p->h_dtype == ASAP_BF16 ? 2 : 4);
   const bool fixed_first = early && kv_bytes > 4 * hidden_bytes;
   // That copy's 512 workgroups walk their blocks to the end where they were placed, beside the first kernel of the score.
   // A compute unit holds two of that one's (1024 threads), or one and four of the copy's: where 128 units or fewer have one
@@ -602,15 +635,23 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
   const size_t fixed_lds = first_wgs >= 384 && first_wgs < 512 ? 32000 : 0;
   const bool fixed_with_selection = early && !fixed_first && score_fuses_selection(*p) && p->h_dtype == ASAP_BF16 &&
                                     io->n_layers <= KV_LAYERS_PER_LAUNCH;
+  KvDeal deal{0, io->n_layers};
+  if (fixed_first) deal = deal_kv(*p, io->n_layers, kv_row_bytes, hidden_bytes);
+  else if (fixed_with_selection) deal.fixed = io->n_layers;
+  // layers lo .. hi - 1
+  auto copy_layers = [&](int mode, int lo, int hi, hipStream_t s, size_t lds) {
+    return lo >= hi ? hipSuccess
+                    : launch_compact_kv(*p, mode, hi - lo, io->k_src + lo, io->v_src + lo, io->k_dst + lo, io->v_dst + lo,
+                                        io->kept_idx, io->text_len, s, ctx->timer, s == ctx->side, lds);
+  };
   hipError_t e = hipSuccess;
   bool forked = false;
-  if (fixed_first) {
+  if (fixed_first && deal.fixed > 0) {
     e = hipEventRecord(ctx->ev_start, main);
     if (e == hipSuccess) e = hipStreamWaitEvent(ctx->side, ctx->ev_start, 0);
     if (e == hipSuccess) {
       forked = true;
-      e = launch_compact_kv(*p, KV_FIXED_ONLY, io->n_layers, io->k_src, io->v_src, io->k_dst, io->v_dst,
-                            io->kept_idx /* not read in this mode */, io->text_len, ctx->side, ctx->timer, fixed_lds);
+      e = copy_layers(KV_FIXED_ONLY, 0, deal.fixed, ctx->side, fixed_lds);
     }
   }
   KvFixedRows fixed;
@@ -630,17 +671,18 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
     if (e == hipSuccess) e = hipStreamWaitEvent(ctx->side, ctx->ev_fork, 0);
     if (e == hipSuccess) {
       forked = true;
-      e = launch_compact_kv(*p, (fixed_first || fixed_with_selection) ? KV_KEPT_ONLY : KV_FROM_KEPT, io->n_layers,
-                            io->k_src, io->v_src, io->k_dst, io->v_dst, io->kept_idx, io->text_len, ctx->side,
-                            ctx->timer, compact_lds_beside_sim(*p, kv_bytes));
+      const size_t lds = compact_lds_beside_sim(*p, kv_bytes);
+      e = copy_layers(KV_KEPT_ONLY, 0, std::min(deal.fixed, deal.side), ctx->side, lds);
+      if (e == hipSuccess) e = copy_layers(KV_FROM_KEPT, deal.fixed, deal.side, ctx->side, lds);
     }
   }
   // On one stream the merge's launch takes the compaction of (up to 16) layers along: whichever routing, the
   // list of survivors is final before it.  Large copies keep a launch of their own, whose workgroups need few
-  // registers and fill the chip better (16 images, paper's routing, 440 MB: 131 us in one launch, 118 in two).
+  // registers and fill the chip better (16 images, paper's routing, 440 MB: 131 us in one launch, 118 in two; us per stage
+  // with the copy in the merge's launch / in one of its own: 64 MB 62 / 69, 74 MB 114 / 115, 89 MB 91 / 86, 132 MB 195 / 188).
   MergeKv mkv;
   int taken = 0;
-  if (has_kv && !early && kv_bytes < (64ll << 20)) {
+  if (has_kv && !early && kv_bytes < (80ll << 20)) {
     taken = io->n_layers < KV_LAYERS_PER_LAUNCH ? io->n_layers : KV_LAYERS_PER_LAUNCH;
     fill_kv_pointers(&mkv.ptrs, taken, io->k_src, io->v_src, io->k_dst, io->v_dst);
     mkv.n_bufs = 2 * taken;
@@ -651,6 +693,8 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
     e = launch_merge(*p, io->hidden, io->hidden_stride[0], io->hidden_stride[1], io->s_raw, io->s_hat, io->text_len,
                      io->kept_idx, io->pruned_idx, io->out_hidden, io->pos_out, io->new_len, io->assign, io->best_sim,
                      io->wsum, io->final_idx, taken ? &mkv : nullptr, ws, main, ctx->timer);
+  if (e == hipSuccess && early) e = copy_layers(KV_KEPT_ONLY, deal.side, deal.fixed, main, 0);
+  if (e == hipSuccess && early) e = copy_layers(KV_FROM_KEPT, std::max(deal.fixed, deal.side), io->n_layers, main, 0);
   if (forked) {      // also after an error: the caller's stream must not run ahead of the second one
     hipError_t e2 = hipEventRecord(ctx->ev_join, ctx->side);
     if (e2 == hipSuccess) e2 = hipStreamWaitEvent(main, ctx->ev_join, 0);

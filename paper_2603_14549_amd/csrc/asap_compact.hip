@@ -111,14 +111,16 @@ hipError_t launch_positions(const asap_params& p, const int32_t* kept, const int
 // What bounds it: HBM.  With one row per thread in as many workgroups as that takes, which all ask at once, the copy runs at 6.2
 // TB/s (5.6 with four rows; a plain copy 6.5 and 6.0): 16 x 2304 tokens, 440 MB on a stream of its own 78 -> 71 us; us per
 // stage on one stream, 8 x 576 on 160, 16 layers 323 -> 290, 12 x 448 on 72, 16 layers 205 -> 187.  Four rows stay where
-// few workgroups have to keep enough in flight: beside the search with two of them per compute unit (lds), and in
-// k_compact_fixed's walk (8 x 576, 16 layers, two streams: 282 with one row in that walk, 266 with four).
+// few workgroups have to keep enough in flight: beside the search with two of them per compute unit (lds) or of f32 states, which
+// outlasts the copy (3 x 2304 tokens of 40 heads on 500, 2 layers: 345 with one, 341 with four), and in k_compact_fixed's walk (8
+// x 576, 16 layers, two streams: 282 with one row in that walk, 266 with four).
 hipError_t launch_compact_kv(const asap_params& p, int mode, int n_layers, const void* const* k_src,
                              const void* const* v_src, void* const* k_dst, void* const* v_dst,
-                             const int32_t* idx, const int32_t* len, hipStream_t st, Timer* tm, size_t lds) {
+                             const int32_t* idx, const int32_t* len, hipStream_t st, Timer* tm, bool beside_search, size_t lds) {
   const int row_bytes = p.d * (p.kv_dtype == ASAP_BF16 ? 2 : 4);
   const int N = p.P + p.V + p.Tmax, Nout = p.P + p.k + p.Tmax;
-  const int per_thread = mode == KV_FIXED_ONLY || lds ? KV_ROWS_PER_THREAD : 1;
+  const bool few = lds != 0 || (beside_search && p.h_dtype == ASAP_F32);
+  const int per_thread = mode == KV_FIXED_ONLY || few ? KV_ROWS_PER_THREAD : 1;
   const int rows_per_block = kv_rows_per_block(row_bytes, per_thread);
   const int rows = mode == KV_KEPT_ONLY ? p.k : mode == KV_FIXED_ONLY ? p.P + p.Tmax : Nout;
   for (int l0 = 0; l0 < n_layers; l0 += KV_LAYERS_PER_LAUNCH) {
@@ -136,10 +138,10 @@ hipError_t launch_compact_kv(const asap_params& p, int mode, int n_layers, const
     } else if (mode == KV_BY_POS) {
       ASAP_COMPACT(KV_BY_POS, 1);
     } else if (mode == KV_FROM_KEPT) {
-      if (lds) ASAP_COMPACT(KV_FROM_KEPT, KV_ROWS_PER_THREAD);
+      if (few) ASAP_COMPACT(KV_FROM_KEPT, KV_ROWS_PER_THREAD);
       else ASAP_COMPACT(KV_FROM_KEPT, 1);
     } else {
-      if (lds) ASAP_COMPACT(KV_KEPT_ONLY, KV_ROWS_PER_THREAD);
+      if (few) ASAP_COMPACT(KV_KEPT_ONLY, KV_ROWS_PER_THREAD);
       else ASAP_COMPACT(KV_KEPT_ONLY, 1);
     }
 #undef ASAP_COMPACT

@@ -156,6 +156,9 @@ hipError_t launch_similarity(const asap_params& p, const void* hidden, int64_t h
                              const int32_t* kept, const int32_t* srcs, int M, bool anchored, const float* s_hat,
                              int32_t* assign, float* best_sim, char* ws, hipStream_t st, Timer* tm);
 
+// Rounds of workgroups x steps x rows per step of launch_similarity's search (pruned -> kept): about 3.5 ns each.
+int64_t sim_row_steps(const asap_params& p);
+
 // What a workgroup of a copy of `bytes` (read and written) beside launch_similarity claims of a compute unit's LDS, on
 // top of what it needs (asap_sim.hip).
 size_t compact_lds_beside_sim(const asap_params& p, int64_t bytes);
@@ -175,10 +178,12 @@ hipError_t launch_positions(const asap_params& p, const int32_t* kept, const int
 // rows (prefix, valid text), which need no index list.  The last two together move what KV_FROM_KEPT
 // moves.
 enum { KV_BY_POS = 0, KV_FROM_KEPT = 1, KV_KEPT_ONLY = 2, KV_FIXED_ONLY = 3 };
-// lds: bytes of LDS that a workgroup claims without using them (all but KV_BY_POS; see compact_lds_beside_sim).
+// beside_search: launch_similarity's kernels run meanwhile on another stream.  lds: bytes of LDS that a workgroup claims without
+// using them (all but KV_BY_POS; see compact_lds_beside_sim).
 hipError_t launch_compact_kv(const asap_params& p, int mode, int n_layers, const void* const* k_src,
                              const void* const* v_src, void* const* k_dst, void* const* v_dst,
-                             const int32_t* idx, const int32_t* len, hipStream_t st, Timer* tm, size_t lds = 0);
+                             const int32_t* idx, const int32_t* len, hipStream_t st, Timer* tm, bool beside_search = false,
+                             size_t lds = 0);
 hipError_t launch_compact_kv_paged(const asap_params& p, int n_layers, const void* const* k_src,
                                    const void* const* v_src, void* const* k_dst, void* const* v_dst, int page_size,
                                    const int32_t* src_table, int src_stride, const int32_t* dst_table,

@@ -896,6 +896,11 @@ static int pick_nt(const asap_params& p, int M) {
   return best_nt;
 }
 
+int64_t sim_row_steps(const asap_params& p) {
+  const int M = p.V - p.k;
+  return M > 0 ? sim_cost(p, M, pick_nt(p, M)).row_steps : 0;
+}
+
 // The K/V compaction beside the search, on another stream.  LDS that a workgroup of the copy claims decides how many of
 // them share a compute unit with one of the search: as many as registers let in (five), or two, half each of what
 // the search's tile leaves.  Two bring both to their end together where the search has one round of workgroups and the copy

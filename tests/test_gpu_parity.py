@@ -1495,3 +1495,35 @@ def test_compaction_at_the_edges_of_its_blocks(ctx, d, dtype, over):
                 want = torch.cat([s[b][:, :P], s[b][:, P + kept[b].long()], s[b][:, P + V:P + V + int(text_len[b])]], 1)
                 assert torch.equal(t[b][:, :n], want)
                 assert bool((t[b][:, n:] == 7.0).all())
+
+
+@pytest.mark.parametrize("layers,P,T,k", [(16, 40, 64, 16), (16, 64, 120, 4), (17, 0, 8, 90), (33, 3, 5, 100), (1, 64, 120, 110)])
+def test_deep_caches_dealt_to_two_streams(ctx, layers, P, T, k):
+    """Copies that outlast search and merge: layers whose prefix and text rows go first, wholly after the selection, on
+    the second stream and behind the merge leave the rows that one stream leaves."""
+    B, H, d, D, V = 8, 16, 128, 128, 128
+    p = binding.make_params(B, H, H, d, D, P, V, T, k, "bf16", "bf16", "bf16")
+    N, g = P + V + T, torch.Generator(device="cuda").manual_seed(43)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    q, key, hidden = rn(B, H, N, d), rn(B, H, N, d), rn(B, N, D)
+    text_len = torch.randint(1, T + 1, (B,), generator=g, device="cuda").to(torch.int32)
+    kc, vc = [rn(B, H, N, d) for _ in range(layers)], [rn(B, H, N, d) for _ in range(layers)]
+    got = []
+    for mode in (binding.ASAP_STREAMS_ONE, binding.ASAP_STREAMS_TWO, binding.ASAP_STREAMS_AUTO):
+        buf = harness.StageBuffers(p, layers)
+        for t in buf.k_dst + buf.v_dst:
+            t.fill_(7.0)
+        io = harness.stage_io(p, q, key, hidden, text_len, kc, vc, buf)
+        ctx.asap_stage(p, io, mode)
+        torch.cuda.synchronize()
+        got.append(buf)
+    for buf in got[1:]:
+        for n in ("kept_idx", "assign", "pos_out", "new_len"):
+            assert torch.equal(getattr(buf, n), getattr(got[0], n))
+        for a, b in zip(buf.k_dst + buf.v_dst, got[0].k_dst + got[0].v_dst):
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    for src, dst in zip(kc + vc, got[0].k_dst + got[0].v_dst):
+        for b in range(B):
+            n = int(got[0].new_len[b])
+            assert torch.equal(dst[b, :, :n], src[b][:, got[0].pos_out[b, :n].long()])
+            assert bool((dst[b, :, n:] == 7.0).all())

@@ -425,7 +425,10 @@ __global__ __launch_bounds__(64 * ATT_NW, (att_steps<T>(32 * CH / (int)sizeof(T)
     const bool moved = mx > m_run + lazy_raw;
     if (__any(moved)) {
       const float m_new = moved ? mx : m_run;
-      const float alpha = fast_exp2_att((m_run - m_new) * c2);
+      float alpha = fast_exp2_att((m_run - m_new) * c2);
+      // The products below are assembly, for which the compiler keeps none of the distances that a use of an exponential's
+      // result, or of a matrix product's, needs.
+      asm volatile("s_nop 15\n\ts_nop 15" : "+v"(alpha));
       m_run = m_new;
       l_run *= alpha;
       // in place, as assembly: a plain product is hoisted above the branch and the untouched

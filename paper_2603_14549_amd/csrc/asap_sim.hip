@@ -44,11 +44,18 @@ namespace asap {
 constexpr int SIM_BM = 128;
 constexpr int SIM_ROWB = 128;      // bytes of a row held in LDS per step
 // LDS ring slots for the source rows (NA) and the destination rows (NB) by tile width: as deep as
-// 160 KiB allow, NA > NB >= 2.  Narrow tiles belong to launches with few workgroups (small batches, the
+// 160 KiB allow, NA >= NB >= 2.  Narrow tiles belong to launches with few workgroups (small batches, the
 // search inside the kept set), whose steps last as long as a load takes to arrive divided by how many
-// steps ahead it was asked for.
-constexpr int sim_na(int nt) { return nt == 1 ? 6 : nt == 2 ? 5 : 4; }
-constexpr int sim_nb(int nt) { return nt == 1 ? 4 : nt <= 3 ? 3 : 2; }
+// steps ahead it was asked for.  Loads return in the order they were asked for, on the whole compute unit: destination rows
+// that come from L2 arrive behind the source rows from HBM that were asked for before them, so that what is needed first and
+// asked for last sets the pace.  256 columns with three slots of each (all loads two steps ahead) instead of four and two: search
+// and merge of 4 x 4096 tokens on 512 98.3 -> 94.1 us, 3 x 3072 on 769 89.2 -> 83.5, 8 x 1024 on 256 56.9 -> 54.7.  (320 columns have
+// no room for that.)
+constexpr int sim_na(int nt) { return nt == 1 ? 6 : nt == 2 ? 5 : nt == 4 ? 3 : 4; }
+constexpr int sim_nb(int nt) { return nt == 1 ? 4 : nt <= 4 ? 3 : 2; }
+// Loads of a wave that may be on their way at the end of a step, all after those that the next step needs: steps s
+// ask for the destination rows of step s + NB - 1, then for the source rows of step s + NA - 1.
+constexpr int sim_open(int nt) { return (sim_na(nt) > sim_nb(nt) ? SIM_BM / 32 : 0) + (sim_nb(nt) - 2) * (SIM_BM / 32 + 2 * nt); }
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
@@ -279,7 +286,7 @@ __global__ __launch_bounds__(256) void k_sim(const T* __restrict__ xv, int64_t s
   constexpr int PB = BN / 32;                    // destination-row loads
   constexpr int ASTAGE = SIM_BM * SIM_ROWB, BSTAGE = BN * SIM_ROWB;
   constexpr int NA = sim_na(NT), NB = sim_nb(NT);
-  static_assert(NA > NB && NB >= 2, "ring depths");
+  static_assert(NA >= NB && NB >= 2, "ring depths");
   static_assert(PA + PB <= 8 * NT, "one load per MFMA slot");
   extern __shared__ __align__(16) char lds[];
   char* ldsB = lds + NA * ASTAGE;
@@ -353,28 +360,23 @@ __global__ __launch_bounds__(256) void k_sim(const T* __restrict__ xv, int64_t s
         for (int v = 0; v < 16; ++v) acc[i][t][v] = 0.0f;
     SumSq4 ss_a[2], ss_b[NT];
 
-    // fill: destination slices 0 .. NB-2, source slices 0 .. NA-2
+    // fill: destination slices 0 .. NB-2, source slices 0 .. NA-2, as the steps before the first would ask for them (a short
+    // walk asks for its last slices again), until the first have landed
     {
 #pragma unroll
-      for (int a = 0; a < NB - 1; ++a) {
-        if (a < steps) {
-          const char* g = step_base(a);
+      for (int x = 1 - NA; x < 0; ++x) {
+        const int xb_ = x + NB - 1, xa = x + NA - 1;
+        if (xb_ >= 0) {
+          const char* g = step_base(min(xb_, steps - 1));
 #pragma unroll
-          for (int j = 0; j < PB; ++j)
-            load_to_lds16(g, offb[j], ldsB_addr + a * BSTAGE + (8 * wave + 32 * j) * SIM_ROWB);
+          for (int j = 0; j < PB; ++j) load_to_lds16(g, offb[j], ldsB_addr + xb_ * BSTAGE + (8 * wave + 32 * j) * SIM_ROWB);
         }
-      }
+        const char* ga = step_base(min(xa, steps - 1));
 #pragma unroll
-      for (int a = 0; a < NA - 1; ++a) {
-        if (a < steps) {
-          const char* ga = step_base(a);
-#pragma unroll
-          for (int i = 0; i < PA; ++i)
-            load_to_lds16(ga, offa[i], lds_addr + a * ASTAGE + (8 * wave + 32 * i) * SIM_ROWB);
-        }
+        for (int i = 0; i < PA; ++i) load_to_lds16(ga, offa[i], lds_addr + xa * ASTAGE + (8 * wave + 32 * i) * SIM_ROWB);
       }
-      wait_all_vmem();
-      __syncthreads();
+      wait_vmem_but<sim_open(NT)>();
+      barrier_lds();
     }
 
     int sa = 0, sb_ = 0;       // ring slots of the current step: s % NA, s % NB
@@ -382,8 +384,7 @@ __global__ __launch_bounds__(256) void k_sim(const T* __restrict__ xv, int64_t s
       // During step s the waves read source slot s % NA and destination slot s % NB.  Meanwhile the
       // destination rows of step s+NB-1 are asked for first, then the source rows of step s+NA-1, each
       // into the slot the previous step has just left.  Loads retire in order, so what step s+1 needs
-      // has landed once nothing older than the source loads of step s-NB+2 is outstanding: those PA
-      // loads and the PA+PB loads of each of the NB-2 steps since.
+      // has landed once only the newest sim_open are outstanding.
       const char* A = lds + sa * ASTAGE + (wm * 64 + n) * SIM_ROWB;
       const char* Bp = ldsB + sb_ * BSTAGE + (wn * (BN / 2) + n) * SIM_ROWB;
       // Past the last step the loads repeat the current step into a slot nobody reads any more:
@@ -436,7 +437,7 @@ __global__ __launch_bounds__(256) void k_sim(const T* __restrict__ xv, int64_t s
           for (int u = 2 * NT; u < NT + 2; ++u) load_op((kk + 1) & 1, kk + 1, u);     // NT == 1 only
         }
       }
-      wait_vmem_but<PA + (NB - 2) * (PA + PB)>();
+      wait_vmem_but<sim_open(NT)>();
       barrier_keep_loads();
     }
 

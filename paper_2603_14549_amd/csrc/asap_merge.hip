@@ -19,8 +19,7 @@ namespace asap {
 // under the latency of the gathers, and a launch is saved (8 us of a single image's stage).
 //   What bounds it: HBM where the batch is large (every visual row of the hidden states once); a chain of
 //   dependent loads -- lists, weights, rows -- where it is not.  So the lists are read with whole
-//   coalesced loads before anything is known about them, the weights are fetched by the threads that
-//   found the sources, and AHEAD source rows are in flight at a time: a slot's sources (V / k - 1 on
+//   coalesced loads before anything is known about them, and AHEAD source rows are in flight at a time: a slot's sources (V / k - 1 on
 //   average, 30 to 70 for the most similar) mostly come in one turn.
 // ------------------------------------------------------------------------------------------
 constexpr int MERGE_SEG = 2048;   // entries of assign[] scanned per round
@@ -37,7 +36,11 @@ __global__ __launch_bounds__(256) void k_merge(const T* __restrict__ hidden, int
                                                 float* __restrict__ wsum, int32_t* final_idx, int B, int parts, MergeKv kv) {
   constexpr int E = elem<T>::per16;
   __shared__ int list[MERGE_SEG];
-  __shared__ float weight[MERGE_SEG];
+  // Weights of the sources: whole rows ask for them with the row, one scalar load each, which takes a load out of the chain in
+  // front of the first row (k_merge of 16 x 2304 tokens 69.8 -> 66.0 us, 5 x 2083 23.5 -> 22.1); pieces, whose threads
+  // have 16 rows in flight, find them in LDS (2 x 904 with the scalar loads 9.4 -> 9.9).
+  constexpr bool LATE = CPT > 1;
+  __shared__ float weight[LATE ? 1 : MERGE_SEG];
   __shared__ int wave_cnt[4];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -115,7 +118,7 @@ __global__ __launch_bounds__(256) void k_merge(const T* __restrict__ hidden, int
     }
     float w[PER];
 #pragma unroll
-    for (int e = 0; e < PER; ++e) w[e] = to[e] == slot ? mu * sh[tok[e]] : 0.0f;
+    for (int e = 0; e < PER; ++e) w[e] = !LATE && to[e] == slot ? mu * sh[tok[e]] : 0.0f;
     if (seg) __syncthreads();                  // the previous round's lists have been used
     if (lane == 0) wave_cnt[wave] = cnt;
     __syncthreads();
@@ -129,7 +132,7 @@ __global__ __launch_bounds__(256) void k_merge(const T* __restrict__ hidden, int
     for (int e = 0; e < PER; ++e)
       if (to[e] == slot) {
         list[base + before[e]] = tok[e];
-        weight[base + before[e]] = w[e];
+        if (!LATE) weight[base + before[e]] = w[e];
       }
     __syncthreads();
     total = __builtin_amdgcn_readfirstlane(total);
@@ -144,11 +147,13 @@ __global__ __launch_bounds__(256) void k_merge(const T* __restrict__ hidden, int
     }
     for (int s0 = 0; s0 < total; s0 += AHEAD) {
       uint4 ch[AHEAD][CPT];
+      float wt[AHEAD];
 #pragma unroll
       for (int u = 0; u < AHEAD; ++u) {
         if (s0 + u < total) {
           const int j = __builtin_amdgcn_readfirstlane(list[s0 + u]);
           const char* srow = hb + (int64_t)(P + j) * rowb;
+          if (LATE) wt[u] = mu * sh[j];
 #pragma unroll
           for (int q = 0; q < CPT; ++q)
             if (tid + q * 256 < nchunks) ch[u][q] = ldg16_stream(srow + (tid + q * 256) * 16);
@@ -157,7 +162,7 @@ __global__ __launch_bounds__(256) void k_merge(const T* __restrict__ hidden, int
 #pragma unroll
       for (int u = 0; u < AHEAD; ++u) {
         if (s0 + u < total) {
-          const float wu = weight[s0 + u];
+          const float wu = LATE ? wt[u] : weight[s0 + u];
           den += wu;
           absorbed += wu;
 #pragma unroll

@@ -1852,13 +1852,22 @@ static ScoreWorkspace plan_score(const asap_params& p, size_t budget, bool ride)
   w.mass_small = tiles < 256 ? 1 : 0;
   // rows per k_qsum block: whole image span unless that leaves the chip short of blocks.  Small batches, whose
   // workgroups all read every partial sum, take no more than 128 blocks (6 x 28 heads x 1225 tokens: 123.4 us per
-  // stage, 125.0 with 256 blocks, 128.5 with 512; 1 x 32 x 2304: 87.6, 87.2, 90.4).
-  const int want = w.mass_small ? 128 : 512;
-  int chunks = (want + p.B * p.H - 1) / (p.B * p.H);
-  if (chunks > (p.V + 255) / 256) chunks = (p.V + 255) / 256;
-  if (chunks < 1) chunks = 1;
+  // stage, 125.0 with 256 blocks, 128.5 with 512; 1 x 32 x 2304: 87.6, 87.2, 90.4).  The others take up to 256, one per compute
+  // unit: more come in a second round that is nearly empty, and a block per head and no group needs no k_qsplit (us of
+  // asap_score with 512 blocks or more / up to 256: 4 x 28 heads on 4 x 4096 70.6 / 64.7;  2 x 28 on 4 x 4096 49.6 / 41.5;  5 x 28 on 4 x 2083
+  // 42.4 / 40.0;  6 x 32 x 2304 72.2 / 68.0;  8 x 32 x 1536 63.2 / 61.7;  the worst 4 x 32 x 4096 79.2 / 80.5).  From 257 to 341 heads of all
+  // images two blocks each are faster than one (8 x 40 x 2304: 112.7 and 115.3; 9 x 32 x 1100 no difference), from 342
+  // on one (12 x 32 x 1472: 103.5 and 103.0).
+  const int heads = p.B * p.H;
+  auto most_chunks = [&](int want) {
+    const int chunks = std::min((want + heads - 1) / heads, (p.V + 255) / 256);
+    return chunks < 1 ? 1 : chunks;
+  };
+  const int room = most_chunks(w.mass_small ? 128 : 512);      // partial sums that the workspace has room for
+  const int chunks = w.mass_small ? room : std::min(room, heads <= 256 ? 256 / heads : heads <= 341 ? 2 : 1);
   w.q_rows = (p.V + chunks - 1) / chunks;
   w.q_chunks = (p.V + w.q_rows - 1) / w.q_rows;
+  const int q_room = (p.V + (p.V + room - 1) / room - 1) / ((p.V + room - 1) / room);
   w.attn_splits = attn_splits(p);
   w.t_eff = ranking_rows_max(p);
   const int G = p.H / p.Hkv;
@@ -1882,7 +1891,7 @@ static ScoreWorkspace plan_score(const asap_params& p, size_t budget, bool ride)
   }
   size_t off = 0;
   w.off_qpart = off;
-  off = align256(off + sizeof(double) * p.B * p.H * w.q_chunks * p.d);
+  off = align256(off + sizeof(double) * p.B * p.H * q_room * p.d);
   off = align256(off + sizeof(double) * p.B * p.Hkv * p.d);
   w.off_qsplit = off; off = align256(off + sizeof(uint16_t) * p.B * p.Hkv * 4 * p.d);
   w.off_s64 = off;    off = align256(off + sizeof(double) * p.B * p.V);

@@ -197,17 +197,19 @@ def asap_flops_ratio(layers, tokens, v0: int, d: int, m: int) -> float:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_I64 = {n: ctypes.c_int64 * n for n in (2, 3)}
 
 
 def _strides(t: torch.Tensor, n: int):
     assert t.stride(-1) == 1, "last dimension must be contiguous"
-    return (ctypes.c_int64 * n)(*[t.stride(i) for i in range(n)])
+    return _I64[n](*[t.stride(i) for i in range(n)])
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream) -> int:
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 class Context:

@@ -1527,3 +1527,23 @@ def test_deep_caches_dealt_to_two_streams(ctx, layers, P, T, k):
             n = int(got[0].new_len[b])
             assert torch.equal(dst[b, :, :n], src[b][:, got[0].pos_out[b, :n].long()])
             assert bool((dst[b, :, n:] == 7.0).all())
+
+
+@pytest.mark.parametrize("overlap", ["auto", "always"])
+def test_paged_stage_beside_and_after_the_search(ctx, overlap):
+    """The paged stage with a side stream that it uses, or finds not worth using, leaves the pages that the stage on one
+    stream leaves."""
+    cfg = synth.CONFIGS["S2"]
+    inp = synth.make_inputs(cfg)
+    pools = []
+    for side in (None, torch.cuda.Stream()):
+        st = U.GpuStage(inp, ctx=ctx, page_size=16)
+        harness.run_stage(ctx, st.p, st.q, st.k, st.hidden, st.text_len, [], [], st.buf, side_stream=side, paged=st.paged,
+                          overlap=overlap)
+        torch.cuda.synchronize()
+        pools.append((st.paged.k_pool + st.paged.v_pool, st.buf))
+    assert not harness.second_stream_pays(st.p, len(st.paged.k_pool), True)
+    for a, b in zip(pools[0][0], pools[1][0]):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    for n in ("kept_idx", "assign", "pos_out", "new_len"):
+        assert torch.equal(getattr(pools[0][1], n), getattr(pools[1][1], n))

@@ -6,13 +6,15 @@
 // matrix cores, nothing of size N x N ever stored.
 //
 //   k_att_bias      log2 of the per-key discount by sequence position, [B,Npad] (-inf off the image span,
-//                   and everywhere with the mask off)
+//                   and everywhere with the mask off), for sequences whose discounts have no room in LDS; else
+//                   every workgroup forms its image's itself, with its first loads on their way (att_own_bias)
 //   k_vtranspose    values transposed per (image, kv head) to [d, Npad]: the second contraction wants
 //                   its A operand (a row of values^T) contiguous along the keys, in the key order in
 //                   which the first contraction leaves P^T in the accumulators.  Not needed for bf16
 //                   with d = 128: there the values go to LDS row-major and the operand is fetched
 //                   with the chip's transposing LDS read (ds_read_b64_tr_b16), two per operand.
-//   k_attention     B H ceil(N/256) workgroups of 512 threads = 8 waves (two per SIMD) of 32 queries.  Per
+//   k_attention     B H ceil(N/256) workgroups of 512 threads = 8 waves (two per SIMD) of 32 queries, or, where the chip holds
+//                   them all, B H ceil(N/128) of four waves.  Per
 //                   sub-tile of 32 keys a wave computes S^T = K Q^T (keys are the tile rows, so lane l owns
 //                   query l % 32 and holds 16 of the keys: the softmax bookkeeping is per lane),
 //                   then O^T += V^T P^T, where the P^T operand is taken straight from the
@@ -20,7 +22,7 @@
 //                   the keys that lane half already holds, and the V^T operand is stored to match.
 //                   A turn is 64 keys (32 with 4-byte elements) and one barrier; a step, one look at the maxima and
 //                   one change of the baseline, is a whole turn, or half of one (bf16, d = 64).  A turn's keys, values and discounts go to LDS by direct
-//                   global -> LDS loads, once for the eight waves, into rings of four slots; the waits
+//                   global -> LDS loads, once for all waves, into rings of four slots; the waits
 //                   for those loads are placed by hand and no other vector-memory instruction is left
 //                   in the loop, because any wait the compiler adds for one would drain the ring.
 //                   The products of a turn stand in a row, each with the LDS read of the operand five
@@ -30,21 +32,27 @@
 //   clock falls from 2.4 to 2.0 GHz on random data (the same instructions on zeros: 1.35 ms; the products and
 //   loads alone 1.24 ms at 1.7 GHz).  Turns of 32 keys with a barrier each, offsets and operand addresses formed anew
 //   and the halves' maxima exchanged through LDS took 1.74 ms, now 1.63 (28 heads on 4, 6 x 1337 positions: 201, now
-//   191 us; f32, 2 x 28 x 2352: 1.80, now 1.72 ms; 16 x 32 x 180 with the mask, where a few turns are all: 33.5, now 34.8 us).  Two groups of waves half a turn apart with a barrier per phase,
+//   191 us; f32, 2 x 28 x 2352: 1.80, now 1.72 ms; 16 x 32 x 180 with the mask, where a few turns are all: 33.5, then 34.8 us).  The discounts formed in the
+//   workgroup instead of a launch before it, and no wait for the queries in front of the ring's first loads: 16 x 32 x 180 34.9 -> 32.7
+//   us, 1 x 16 x 137 14.0 -> 10.8, 3 x 40 x 1095 100.8 -> 96.9, 16 x 32 x 2403 1572 -> 1543.  Two groups of waves half a turn apart with a barrier per phase,
 //   one group's products beside the other's softmax, measured the same as one barrier and no order between them.
 #include "asap_device.hpp"
 #include "asap_launch.hpp"
 
 namespace asap {
 
-// grid (ceil(Npad/256), B): bias2[b,j] by sequence position j: the log2 discount of an image key,
-// -inf for every other position (prefix, text, padding)
+// log2 discount of sequence position j: that of an image key (s_hat of its image), -inf for every other one
+__device__ __forceinline__ float att_bias(const float* __restrict__ s_hat, int j, int P, int V, float lambda_max, float eps) {
+  return j >= P && j < P + V ? log2f(fmaxf(lambda_max * s_hat[j - P], eps)) : -INFINITY;
+}
+
+// grid (ceil(Npad/256), B): bias2[b,j] by sequence position j (prefix, image, text, padding), where a workgroup of
+// k_attention has no room for an image's
 __global__ __launch_bounds__(256) void k_att_bias(const float* __restrict__ s_hat, int P, int V, int Npad,
                                                    float lambda_max, float eps, float* __restrict__ bias2) {
   const int j = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
   if (j >= Npad) return;
-  float x = -INFINITY;
-  if (s_hat != nullptr && j >= P && j < P + V) x = log2f(fmaxf(lambda_max * s_hat[(int64_t)b * V + (j - P)], eps));
+  const float x = s_hat != nullptr ? att_bias(s_hat + (int64_t)b * V, j, P, V, lambda_max, eps) : -INFINITY;
   bias2[(int64_t)b * Npad + j] = x;
 }
 
@@ -133,7 +141,6 @@ __device__ __forceinline__ uint2 att_tr_read(uint32_t lds_addr) {
 // key held in accumulator register v of a lane of half hf, relative to the tile
 __device__ __forceinline__ int att_key_of(int v, int hf) { return 8 * (v >> 2) + 4 * hf + (v & 3); }
 
-constexpr int ATT_QWG = 256;                   // queries per workgroup
 constexpr int ATT_NW = 8;                      // waves per workgroup (two per SIMD), 32 queries each
 constexpr float ATT_LAZY = 8.0f;               // growth of a row maximum (log2 units) that moves the baseline
 
@@ -156,21 +163,29 @@ enum { ATT_PLAIN = 0,     // every key precedes every query: no mask
 template <typename T> constexpr int att_sub(int d) { return sizeof(T) == 2 && d == 128 ? 2 : 1; }
 template <typename T> constexpr int att_steps(int d) { return sizeof(T) == 2 && d == 64 ? 2 : 1; }
 constexpr int ATT_NS = 4;
-template <typename T> constexpr size_t att_lds_bytes(int d) {
-  return (size_t)ATT_NS * 32 * att_sub<T>(d) * att_steps<T>(d) * (2 * d * sizeof(T) + sizeof(float));
+// LDS: the rings of keys and values, then that of the discounts (npad = 0) or an image's, by position
+template <typename T> constexpr size_t att_lds_bytes(int d, int npad) {
+  constexpr int NS = ATT_NS;
+  const size_t keys = 32 * att_sub<T>(d) * att_steps<T>(d);
+  return NS * keys * 2 * d * sizeof(T) + sizeof(float) * (npad ? npad : NS * keys);
+}
+// The workgroup forms the discounts itself, and k_att_bias is not launched, where an image's fit beside the rings: up to 8160
+// positions, or 4064 where two workgroups share a compute unit.
+template <typename T> constexpr bool att_own_bias(int d, int npad) {
+  return att_lds_bytes<T>(d, npad) <= (att_steps<T>(d) == 2 ? 80 : 160) * 1024;
 }
 
 // CH = 16-byte chunks of a row per lane half (row bytes = 32 * CH)
-template <typename T, int CH>
-__global__ __launch_bounds__(64 * ATT_NW, (att_steps<T>(32 * CH / (int)sizeof(T)) == 2 ? 4 : 2)) void k_attention(const T* __restrict__ q, Strides3 sq,
+template <typename T, int CH, bool OWN_BIAS, int NW>
+__global__ __launch_bounds__(64 * NW, (att_steps<T>(32 * CH / (int)sizeof(T)) == 2 ? 4 : 2) * NW / ATT_NW) void k_attention(const T* __restrict__ q, Strides3 sq,
                                                             const T* __restrict__ k, Strides3 sk,
                                                             const T* __restrict__ vt, int Npad,
                                                             const T* __restrict__ vrm, Strides3 sv,
-                                                            const float* __restrict__ bias2, int bidir,
+                                                            const float* __restrict__ bias2,
+                                                            const float* __restrict__ s_hat, float lambda_max, float eps, int bidir,
                                                             T* __restrict__ out, int B, int H, int Hkv, int N, int P,
                                                             int V, float c2) {
-  constexpr int NW = ATT_NW;
-  static_assert(NW * 32 == ATT_QWG, "workgroup shape");
+  constexpr int QWG = 32 * NW;                 // queries per workgroup
   constexpr int E = elem<T>::per16;            // elements per 16-byte chunk
   constexpr int D = CH * 2 * E;                // head dimension
   constexpr int DT = D / 32;                   // 32-row tiles of O^T
@@ -184,7 +199,7 @@ __global__ __launch_bounds__(64 * ATT_NW, (att_steps<T>(32 * CH / (int)sizeof(T)
   static_assert(KLD >= 1 && VLD >= 1, "every wave loads");
   constexpr int NS = ATT_NS;                   // slots of the three rings
   constexpr int VRING = NS * KTILE, BRING = VRING + NS * VTILE;
-  static_assert((size_t)(BRING + NS * BTILE) == att_lds_bytes<T>(D), "LDS");
+  static_assert((size_t)(BRING + NS * BTILE) == att_lds_bytes<T>(D, 0), "LDS");
   // 2-byte elements with d = 128: the values stay row-major, as the caller has them, and the second
   // product's operand is fetched with the transposing LDS read of this chip (see att_tr_read)
   constexpr bool TR = (E == 8 && CH == 8);
@@ -198,12 +213,12 @@ __global__ __launch_bounds__(64 * ATT_NW, (att_steps<T>(32 * CH / (int)sizeof(T)
   // (image by image, head by head, 256 queries by 256 queries), so that the workgroups that read the same keys
   // and values share its L2 (with an image's blocks dealt to all eight, every L2 held the keys and values of
   // some 26 heads at a time, 31 MB at 16 x 32 heads x 2403 positions: 1.94 ms, now 1.80).
-  const int qblocks = (N + ATT_QWG - 1) / ATT_QWG, units = B * H * qblocks, per_xcd = (units + NUM_XCD - 1) / NUM_XCD;
+  const int qblocks = (N + QWG - 1) / QWG, units = B * H * qblocks, per_xcd = (units + NUM_XCD - 1) / NUM_XCD;
   const int block = linear_block(), slot = block / NUM_XCD;
   const int unit = (block % NUM_XCD) * per_xcd + slot;
   if (slot >= per_xcd || unit >= units) return; // the same for the whole workgroup
   const int bh = unit / qblocks, b = bh / H, h = bh - b * H, g = (h * Hkv) / H;
-  const int iw = (unit - bh * qblocks) * ATT_QWG;       // first query of the workgroup
+  const int iw = (unit - bh * qblocks) * QWG;       // first query of the workgroup
   const int i0 = iw + wave * 32;                // first query of the wave
   const float inv_c2 = 1.0f / c2;
   const float lazy_raw = ATT_LAZY * inv_c2;     // ATT_LAZY log2 units, in units of the raw products
@@ -217,7 +232,7 @@ __global__ __launch_bounds__(64 * ATT_NW, (att_steps<T>(32 * CH / (int)sizeof(T)
     if (bidir && hi >= img_lo && first < img_hi) jl = max(jl, img_hi - 1);
     return first < N ? jl : -1;
   };
-  const int jl_wg = last_key(iw, ATT_QWG), jl_w = last_key(i0, 32);
+  const int jl_wg = last_key(iw, QWG), jl_w = last_key(i0, 32);
   const int turns = jl_wg / KEYS + 1;           // the same for every wave of the workgroup
   // This wave's turns are 0 .. my_turns - 1 (none if its queries are past N).  Where the second sub-tile of another one lies
   // behind the wave's last key, it takes no part at all in that turn: a term of zero would still make NaN of a value
@@ -246,9 +261,13 @@ __global__ __launch_bounds__(64 * ATT_NW, (att_steps<T>(32 * CH / (int)sizeof(T)
   auto rows_ahead = [](int64_t bytes) { return (uint32_t)min(bytes, (int64_t)0x7fffffff); };
   const int64_t krow_bytes = sk.r * (int64_t)sizeof(T), vrow_bytes = TR ? sv.r * (int64_t)sizeof(T) : Npad * (int64_t)sizeof(T);
   constexpr int KSTEP = 1024 * NW / RB, VSTEP = 1024 * NW / (TR ? RB : VB);     // rows between two pieces of a wave
+  // (KFLIP: the wave's odd pieces are eight rows on from its even ones, and the swizzle repeats after 16)
+  constexpr bool KFLIP = RB > 128 && (KSTEP & 15) == 8;
+  static_assert(KFLIP || (KSTEP & 15) == 0, "swizzle");
   const int krow = off0 / RB, kpiece = ((off0 % RB) >> 4) ^ att_kswz(krow, RB);
-  const uint32_t kmax = (uint32_t)((N - 1) * krow_bytes) + kpiece * 16;
-  uint32_t koff = (uint32_t)min((int64_t)krow, (int64_t)N - 1) * (uint32_t)krow_bytes + kpiece * 16;
+  const uint32_t kpart[2] = {(uint32_t)kpiece * 16, (uint32_t)(kpiece ^ 8) * 16};      // with KFLIP added last
+  const uint32_t kmax = (uint32_t)((N - 1) * krow_bytes) + (KFLIP ? 0 : kpart[0]);
+  uint32_t koff = (uint32_t)min((int64_t)krow, (int64_t)N - 1) * (uint32_t)krow_bytes + (KFLIP ? 0 : kpart[0]);
   const uint32_t kturn = rows_ahead(KEYS * krow_bytes), kstep = rows_ahead(KSTEP * krow_bytes);
   uint32_t voff, vmax, vturn, vstep;
   if constexpr (TR) {
@@ -265,19 +284,23 @@ __global__ __launch_bounds__(64 * ATT_NW, (att_steps<T>(32 * CH / (int)sizeof(T)
     vturn = VB;
     vstep = (uint32_t)(VSTEP * vrow_bytes);
   }
-  auto issue_keys = [&](uint32_t slot, int u) {       // piece u of the next turn's
-    load_to_lds16(kg, u ? min(koff + u * kstep, kmax) : koff, lds_addr + slot * KTILE + wave * 1024 + u * NW * 1024);
+  // (pieces past the second follow from the one before, as u * step may pass 2^32)
+  uint32_t kpast = 0, vpast = 0;
+  auto issue_keys = [&](uint32_t slot, int u) {       // piece u of the next turn's, u = 0, 1, ... in this order
+    const uint32_t off = u ? min((u > 1 ? kpast : koff) + kstep, kmax) : koff;
+    if (KLD > 2) kpast = off;
+    load_to_lds16(kg, KFLIP ? off + kpart[u & 1] : off, lds_addr + slot * KTILE + wave * 1024 + u * NW * 1024);
     if (u == KLD - 1) koff = min(koff + kturn, kmax);
   };
   auto issue_values = [&](uint32_t slot, int u) {
-    load_to_lds16(vg, u ? (TR ? min(voff + u * vstep, vmax) : voff + u * vstep) : voff,
-                  lds_addr + VRING + slot * VTILE + wave * 1024 + u * NW * 1024);
+    const uint32_t next = (u > 1 ? vpast : voff) + vstep, off = u ? (TR ? min(next, vmax) : next) : voff;
+    if (VLD > 2) vpast = off;
+    load_to_lds16(vg, off, lds_addr + VRING + slot * VTILE + wave * 1024 + u * NW * 1024);
     if (u == VLD - 1) voff = min(voff + vturn, vmax);
   };
-  static_assert(KLD <= 2 && VLD <= 2, "u * step stays below 2^32");
-  const bool bias_wave = wave == 0;            // the one that brings the discounts
+  const bool bias_wave = !OWN_BIAS && wave == 0;          // the one that brings the discounts
   auto issue_bias = [&](uint32_t slot, int t) {
-    if (bias_wave && lane < BTILE / 16)
+    if (!OWN_BIAS && bias_wave && lane < BTILE / 16)
       load_to_lds16(bg, (uint32_t)(min(t, turns - 1) * BTILE + 16 * lane), lds_addr + BRING + slot * BTILE);
   };
   // all but the loads of the newest two turns, or of the newest one
@@ -391,7 +414,7 @@ __global__ __launch_bounds__(64 * ATT_NW, (att_steps<T>(32 * CH / (int)sizeof(T)
       const int mode = (j0 + 31 <= i0) ? ATT_PLAIN : (j0 > i0 + 31 && wave_img) ? ATT_AHEAD : ATT_GENERAL;
       if (mode == ATT_PLAIN) continue;
       // discounts of this lane's 16 keys
-      const char* Bt = lds + BRING + slot * BTILE + 128 * (y * SUB + x);
+      const char* Bt = lds + BRING + (OWN_BIAS ? 4 * j0 : slot * BTILE + 128 * (y * SUB + x));
       float kbias[16];
 #pragma unroll
       for (int gq = 0; gq < 4; ++gq) {
@@ -467,10 +490,6 @@ __global__ __launch_bounds__(64 * ATT_NW, (att_steps<T>(32 * CH / (int)sizeof(T)
   // turn t + 2, the values and discounts of turn t + 1, i.e. what turn t + 1 reads.
   // In two steps, turn t reads keys of its own as well as of turn t + 1: the keys asked for are those of turn t + 3 too, and
   // at the barrier everything but the newest turn's loads has landed, the keys of turn t + 2 among them.
-  // The queries are touched here so that the compiler's wait for their loads stands in front of the loop, not
-  // inside it, where it would also wait for the ring.
-#pragma unroll
-  for (int c = 0; c < CH; ++c) asm volatile("" ::"v"(qa[c].x), "v"(qa[c].y), "v"(qa[c].z), "v"(qa[c].w));
   static_for<3>([&](auto t_c) {
     constexpr int U = decltype(t_c)::value;
 #pragma unroll
@@ -481,13 +500,25 @@ __global__ __launch_bounds__(64 * ATT_NW, (att_steps<T>(32 * CH / (int)sizeof(T)
       for (int u = 0; u < VLD; ++u) issue_values(STEPS == 2 ? U : U - 1, u);
     }
   });
+  // The discounts, with all of these loads on their way; and the queries are touched here so that the compiler's wait for
+  // their loads stands in front of the loop, not inside it, where it would also wait for the ring.  (In front
+  // of the ring's first loads that wait was a round trip to memory of its own.)
+  if (OWN_BIAS && bidir) {
+    const float* sh = s_hat + (int64_t)b * V;
+    for (int j = tid; j < turns * KEYS; j += 64 * NW)
+      *reinterpret_cast<float*>(lds + BRING + 4 * j) = att_bias(sh, j, P, V, lambda_max, eps);
+  }
+#pragma unroll
+  for (int c = 0; c < CH; ++c) asm volatile("" ::"v"(qa[c].x), "v"(qa[c].y), "v"(qa[c].z), "v"(qa[c].w));
   auto end_turn = [&] {
     wait_turn();
     __builtin_amdgcn_sched_barrier(0);
     barrier_keep_loads();
     __builtin_amdgcn_sched_barrier(0);
   };
-  end_turn();
+  wait_turn();
+  barrier_lds();
+  __builtin_amdgcn_sched_barrier(0);
   {
     constexpr std::integral_constant<int, 0> zero{};
     first_items(zero, zero, zero);
@@ -581,30 +612,45 @@ static hipError_t attention_typed(const asap_params& p, const void* q, Strides3 
       ws + (row_major_values ? 0 : align256(sizeof(T) * (size_t)p.B * p.Hkv * p.d * Npad)));
   const bool bidir = p.mask_mode == ASAP_MASK_KEYBIAS;
   // (with the mask off the table is -inf everywhere and s_hat is not read)
-  ASAP_LAUNCH(tm, "k_att_bias", k_att_bias, dim3((Npad + 255) / 256, p.B), dim3(256), 0, st, bidir ? s_hat : nullptr,
+  const bool own_bias = att_own_bias<T>(p.d, Npad);
+  if (!own_bias)
+    ASAP_LAUNCH(tm, "k_att_bias", k_att_bias, dim3((Npad + 255) / 256, p.B), dim3(256), 0, st, bidir ? s_hat : nullptr,
               p.P, p.V, Npad, p.lambda_max, p.eps, bias2);
   if (!row_major_values)
     ASAP_LAUNCH(tm, "k_vtranspose", k_vtranspose<T>, dim3(Npad / 32, p.Hkv, p.B), dim3(256), 0, st,
                 static_cast<const T*>(v), sv, N, Npad, p.d, vt);
   const float c2 = 1.4426950408889634f / sqrtf((float)p.d);
-  const int units = p.B * p.H * ((N + ATT_QWG - 1) / ATT_QWG);
+  // Four waves per workgroup, one per SIMD, where the chip then still holds all of them at a time: a turn takes a wave that has a
+  // SIMD to itself little more than half as long (1 x 40 heads x 643 positions 26.7 -> 23.0 us; d = 64, 16 heads 21.3 -> 18.2; f32, 32
+  // heads 174 -> 105; 2 x 32 x 643, in two rounds then, 27.5 -> 42.1).
+  auto units_of = [&](int queries) { return p.B * p.H * ((N + queries - 1) / queries); };
+  const bool four = own_bias && units_of(128) <= 256;
+  const int units = units_of(four ? 128 : 32 * ATT_NW);
   const dim3 grid = grid_of(NUM_XCD * (int64_t)((units + NUM_XCD - 1) / NUM_XCD));
-  const size_t lds = att_lds_bytes<T>(p.d);
-#define ASAP_ATT(CHV)                                                                                          \
+  const size_t lds = att_lds_bytes<T>(p.d, own_bias ? Npad : 0);
+#define ASAP_ATT(CHV, OWN, NWV)                                                                                    \
   do {                                                                                                         \
-    auto kern = k_attention<T, CHV>;                                                                           \
+    auto kern = k_attention<T, CHV, OWN, NWV>;                                                                 \
     if (lds > 48 * 1024) {                                                                                     \
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                  \
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                \
       if (e != hipSuccess) return e;                                                                           \
     }                                                                                                          \
-    ASAP_LAUNCH(tm, "k_attention", kern, grid, dim3(64 * ATT_NW), lds, st, static_cast<const T*>(q), sq,       \
-                static_cast<const T*>(k), sk, vt, Npad, static_cast<const T*>(v), sv, bias2, bidir ? 1 : 0,    \
-                static_cast<T*>(out), p.B, p.H, p.Hkv, N, p.P, p.V, c2);                                                                       \
+    ASAP_LAUNCH(tm, "k_attention", kern, grid, dim3(64 * NWV), lds, st, static_cast<const T*>(q), sq,          \
+                static_cast<const T*>(k), sk, vt, Npad, static_cast<const T*>(v), sv, bias2, s_hat,            \
+                p.lambda_max, p.eps, bidir ? 1 : 0, static_cast<T*>(out), p.B, p.H, p.Hkv, N, p.P, p.V, c2);   \
   } while (0)
-  if (p.d == 64) ASAP_ATT(32 / E);
-  else if (p.d == 128) ASAP_ATT(64 / E);
-  else return hipErrorInvalidValue;
+  if (p.d != 64 && p.d != 128) return hipErrorInvalidValue;
+  if (four) {
+    if (p.d == 64) ASAP_ATT(32 / E, true, 4);
+    else ASAP_ATT(64 / E, true, 4);
+  } else if (own_bias) {
+    if (p.d == 64) ASAP_ATT(32 / E, true, ATT_NW);
+    else ASAP_ATT(64 / E, true, ATT_NW);
+  } else {
+    if (p.d == 64) ASAP_ATT(32 / E, false, ATT_NW);
+    else ASAP_ATT(64 / E, false, ATT_NW);
+  }
 #undef ASAP_ATT
   return hipGetLastError();
 }

@@ -1547,3 +1547,39 @@ def test_paged_stage_beside_and_after_the_search(ctx, overlap):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
     for n in ("kept_idx", "assign", "pos_out", "new_len"):
         assert torch.equal(getattr(pools[0][1], n), getattr(pools[1][1], n))
+
+
+@pytest.mark.parametrize("B,H,Hkv,d,dtype,P,V,T", [
+    (1, 1, 1, 128, "bf16", 60, 8000, 100), (1, 1, 1, 128, "bf16", 61, 8000, 100),    # discounts in LDS: up to 8160 positions
+    (1, 2, 1, 64, "bf16", 4, 4000, 60), (1, 2, 1, 64, "bf16", 5, 4000, 60),          # ... 4064 with two workgroups per unit
+    (1, 1, 1, 128, "f32", 60, 8000, 101), (1, 1, 1, 64, "f32", 0, 4100, 33),
+    (2, 16, 16, 128, "bf16", 24, 900, 100), (2, 16, 4, 128, "bf16", 24, 900, 101),   # four waves up to 256 workgroups of 128 queries
+    (2, 16, 16, 64, "bf16", 24, 900, 100), (2, 16, 4, 64, "bf16", 24, 900, 101),
+    (2, 16, 4, 128, "f32", 24, 900, 100), (2, 16, 16, 128, "f32", 24, 900, 101), (2, 16, 4, 64, "f32", 24, 900, 100)])
+@pytest.mark.parametrize("mask", [binding.ASAP_MASK_KEYBIAS, binding.ASAP_MASK_OFF])
+def test_attention_forms_of_its_workgroups(ctx, B, H, Hkv, d, dtype, P, V, T, mask):
+    """Both sides of the lines between four and eight waves and between discounts formed in the workgroup and before it, rows
+    sampled at the edges of tiles and of the mask against the softmax in fp64."""
+    N = P + V + T
+    p = binding.make_params(B, H, Hkv, d, 128, P, V, T, V // 4, dtype, dtype, dtype, mask_mode=mask)
+    g = torch.Generator(device="cuda").manual_seed(47)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q, k, v = (torch.randn(B, h, N, d, generator=g, device="cuda").mul(s).to(tdt) for h, s in ((H, 3.0), (Hkv, 1.0), (Hkv, 1.0)))
+    s_hat = torch.rand(B, V, generator=g, device="cuda")
+    s_hat[:, ::7] = 0.0
+    out = torch.empty_like(q)
+    ws = torch.empty(binding.asap_attention_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    ctx.asap_attention(p, q, k, v, s_hat if mask == binding.ASAP_MASK_KEYBIAS else None, out, ws)
+    rows = sorted({r for x in (0, 31, 32, 127, 128, 255, 256, P - 1, P, P + 1, P + V - 1, P + V, N - 129, N - 33, N - 1, N // 2)
+                   for r in (x,) if 0 <= r < N})
+    i, j = torch.tensor(rows, device="cuda")[:, None], torch.arange(N, device="cuda")[None]
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        z = q[b, h, rows].double() @ k[b, h * Hkv // H].double().T / math.sqrt(d)
+        m = torch.where(j <= i, 0.0, -math.inf).double()
+        if mask == binding.ASAP_MASK_KEYBIAS:
+            lam = torch.zeros(N, dtype=torch.double, device="cuda")
+            lam[P:P + V] = s_hat[b].double().clamp(min=float(np.float32(1e-6))).log()
+            img = lambda x: (x >= P) & (x < P + V)
+            m = torch.where(img(i) & img(j) & (j > i), lam.expand_as(m), m)
+        ref = torch.softmax(z + m, -1) @ v[b, h * Hkv // H].double()
+        U.check_rows(out[b, h, rows].double().cpu().numpy(), ref.cpu().numpy(), U.TOL[dtype], f"image {b} head {h}")

@@ -725,23 +725,30 @@ __global__ __launch_bounds__(256) void k_sim_finish(const unsigned long long* __
   assign[i] = (c > threshold) ? col : -1;
 }
 
-// grid (ceil(M / 4), B), 256 threads: one wave per source row.  Adds the ksplit partial products of
-// every destination column in slice order, scales by the destination's norm, applies the predicate
+// grid (ceil(M WPR / 4), B), 256 threads: WPR waves per source row, each with every WPR-th 64 columns.  Adds the ksplit partial
+// products of every destination column in slice order, scales by the destination's norm, applies the predicate
 // of the anchored search, takes the row's arg-max (ties to the smaller column) and divides by the
 // source norm -- the arithmetic of k_sim's own epilogue.
-template <bool ANCHORED>
+//   What bounds it: the chain of loads of a wave, one turn per 64 columns and four slices.  So several waves share a row where the
+// chip holds them (sim_reduce_waves), and the source norm's slices are asked for at once and first: one after the other at
+// the end they were a chain of their own, 1.2 us of search and merge (1 x 2304 tokens on 320 35.0 -> 33.8, 8 x 576 on 160 47.0 -> 45.6).
+template <bool ANCHORED, int WPR>
 __global__ __launch_bounds__(256) void k_sim_reduce(const float* __restrict__ dots, const float* __restrict__ src_norm2,
                                                      const float* __restrict__ kept_norm2, int B, int M, int k,
                                                      int ksplit, const int32_t* __restrict__ srcs,
                                                      const int32_t* __restrict__ kept, const float* __restrict__ s_hat,
                                                      int V, float threshold, int32_t* __restrict__ assign,
                                                      float* __restrict__ best_sim) {
-  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6), b = blockIdx.y;
-  if (row >= M) return;
+  __shared__ float best_v[4];
+  __shared__ int best_c[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, part = wave % WPR, b = blockIdx.y;
+  const int row_ = blockIdx.x * (4 / WPR) + wave / WPR, row = min(row_, M - 1);       // past the end: the last row, not written
+  auto norm_slice = [&](int q) { return q < ksplit ? src_norm2[((int64_t)q * B + b) * M + row] : 0.0f; };
+  float sn_slice = norm_slice(lane);
   const float sr_ = ANCHORED ? s_hat[(int64_t)b * V + srcs[(int64_t)b * M + row]] : 0.0f;
   float bv = -INFINITY;
   int bc = 0x7fffffff;
-  for (int col = lane; col < k; col += 64) {
+  for (int col = part * 64 + lane; col < k; col += 64 * WPR) {
     // four running sums (slices q, q+1, q+2, q+3 of every four), so that the loads do not wait for
     // one another; the order of the additions is fixed all the same
     float d4[4] = {0.0f, 0.0f, 0.0f, 0.0f}, n4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -769,15 +776,24 @@ __global__ __launch_bounds__(256) void k_sim_reduce(const float* __restrict__ do
     }
     if (c > bv) { bv = c; bc = col; }             // a lane's columns ascend: the first maximum stays
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const float ov = __shfl_xor(bv, off);
-    const int oc = __shfl_xor(bc, off);
+  auto take = [&](float ov, int oc) {
     if (ov > bv || (ov == bv && oc < bc)) { bv = ov; bc = oc; }
+  };
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) take(__shfl_xor(bv, off), __shfl_xor(bc, off));
+  if (WPR > 1) {
+    if (lane == 0) { best_v[wave] = bv; best_c[wave] = bc; }
+    __syncthreads();
+    if (part != 0) return;
+#pragma unroll
+    for (int w = 1; w < WPR; ++w) take(best_v[wave + w], best_c[wave + w]);
   }
-  if (lane == 0) {
-    float sn = 0.0f;
-    for (int q = 0; q < ksplit; ++q) sn += src_norm2[((int64_t)q * B + b) * M + row];
+  float sn = 0.0f;
+  for (int q0 = 0; q0 < ksplit; q0 += 64) {
+    if (q0) sn_slice = norm_slice(q0 + lane);
+    for (int q = 0; q < min(64, ksplit - q0); ++q) sn += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(sn_slice), q));
+  }
+  if (lane == 0 && row_ < M) {
     const float c = bv / fmaxf(sqrtf(sn), 1e-8f);
     best_sim[(int64_t)b * M + row] = c;
     assign[(int64_t)b * M + row] = (c > threshold) ? bc : -1;
@@ -828,6 +844,14 @@ static constexpr size_t sim_lds_bytes(bool f32, int nt) {
 
 static dim3 sim_grid(int units) { return dim3(NUM_XCD * ((units + NUM_XCD - 1) / NUM_XCD)); }
 
+// Waves per row of k_sim_reduce: as many as have columns, while the chip holds them about at once (8192).  Search and merge, us with
+// 1 / 2 / 4:  1 x 1600 tokens on 488 43.1 / 37.4 / 35.4;  2 x 904 on 297 29.8 / 28.1 / 28.0;  5 x 492 on 148 30.3 / 29.8 / 29.6;  1 x 2304 on
+// 320 33.8 / 32.7 / 32.8;  1 x 3776 on 880 59.7 / 55.0 / 56.5;  8 x 576 on 160 45.6 / 45.9 / 46.7;  4 x 350 on 103 23.2 / 22.7 / 23.0.
+static int sim_reduce_waves(const asap_params& p, int M) {
+  const long rows = (long)p.B * M;
+  return p.k > 128 && rows <= 1800 ? 4 : p.k > 64 && rows <= 3000 ? 2 : 1;
+}
+
 template <typename T, int NT, bool ANCHORED>
 static hipError_t launch_sim_nt(const asap_params& p, const T* xv, int64_t sb, int64_t sr, const int32_t* srcs,
                                 int M, const int32_t* kept, const float* s_hat, int32_t* assign, float* best_sim,
@@ -857,7 +881,9 @@ static hipError_t launch_sim_nt(const asap_params& p, const T* xv, int64_t sb, i
     ASAP_LAUNCH(tm, label, kern, sim_grid(p.B * mtiles * ptiles * ksplit), dim3(256), lds, st, xv, sb, sr, p.D,
                 srcs, kept, s_hat, p.V, p.B, M, p.k, mtiles, ptiles, p.sim_threshold, assign, best_sim,
                 static_cast<unsigned long long*>(nullptr), nsrc, ksplit, dots, nkept);
-    ASAP_LAUNCH(tm, "k_sim_reduce", k_sim_reduce<ANCHORED>, dim3((M + 3) / 4, p.B), dim3(256), 0, st, dots, nsrc, nkept,
+    const int wpr = sim_reduce_waves(p, M);
+    auto reduce = wpr == 4 ? k_sim_reduce<ANCHORED, 4> : wpr == 2 ? k_sim_reduce<ANCHORED, 2> : k_sim_reduce<ANCHORED, 1>;
+    ASAP_LAUNCH(tm, "k_sim_reduce", reduce, dim3((M * wpr + 3) / 4, p.B), dim3(256), 0, st, dots, nsrc, nkept,
                 p.B, M, p.k, ksplit, srcs, kept, s_hat, p.V, p.sim_threshold, assign, best_sim);
     return hipGetLastError();
   }

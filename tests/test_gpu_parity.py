@@ -1583,3 +1583,20 @@ def test_attention_forms_of_its_workgroups(ctx, B, H, Hkv, d, dtype, P, V, T, ma
             m = torch.where(img(i) & img(j) & (j > i), lam.expand_as(m), m)
         ref = torch.softmax(z + m, -1) @ v[b, h * Hkv // H].double()
         U.check_rows(out[b, h, rows].double().cpu().numpy(), ref.cpu().numpy(), U.TOL[dtype], f"image {b} head {h}")
+
+
+@pytest.mark.parametrize("route", ["absorb", "paper"])
+@pytest.mark.parametrize("B,V,k,h_dtype", [(1, 133, 40, "bf16"), (1, 331, 65, "bf16"), (2, 302, 128, "f32"), (1, 402, 129, "bf16"),
+                                           (3, 729, 130, "bf16"), (3, 731, 130, "f32"), (2, 1665, 166, "bf16"), (2, 1667, 166, "bf16")])
+def test_waves_that_share_a_row_of_a_split_search(ctx, B, V, k, h_dtype, route):
+    """One, two and four waves per row where the slices of a split search are added up, rows that do not fill the last
+    workgroup, the row counts on both sides of the lines."""
+    cfg = synth.StageConfig(name="waves", B=B, D=2048, H=2, Hkv=2, d=64, P=3, V=V, Tmax=6, k=k, qk_dtype="bf16", h_dtype=h_dtype,
+                            kv_dtype="bf16", n_clusters=12, outliers=False, L_kv=0, seed=8800 + V)
+    if route == "absorb":
+        U.run_and_compare(cfg, ctx=ctx)
+        return
+    inp = synth.make_inputs(cfg)
+    buf = U.GpuStage(inp, ctx=ctx, route=binding.ASAP_ROUTE_PAPER, sim_threshold=0.8).run()
+    for b in range(cfg.B):
+        U.compare_image_paper(inp, buf, b, 0.8, 1.0)

@@ -938,7 +938,18 @@ __device__ __forceinline__ void final_row_stats(const AttnArgs& a, int b, int h,
     if (row_ok) {
       const float* ps = a.pstat + (((int64_t)b * a.H + h) * a.S * 2) * NR + first;
       float m = ps[tid], s = ps[NR + tid];
-      for (int wv = 1; wv < a.S; ++wv) merge_stat(m, s, ps[(wv * 2) * NR + tid], ps[(wv * 2 + 1) * NR + tid], a.c2);
+      for (int w0 = 1; w0 < a.S; w0 += 4) {     // four splits' loads in flight
+        float mw[4], sw[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float* pw = ps + min(w0 + u, a.S - 1) * 2 * NR + tid;
+          mw[u] = pw[0];
+          sw[u] = pw[NR];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (w0 + u < a.S) merge_stat(m, s, mw[u], sw[u], a.c2);
+      }
       float m2 = m * a.c2;                                           // log2 units from here on
       if (a.lse_extra != nullptr) {
         float l2 = a.lse_extra[((int64_t)b * a.H + h) * a.Tmax + row0 + tid] * 1.4426950408889634f;
@@ -1468,8 +1479,16 @@ __global__ __launch_bounds__(256) void k_rowstats_logits(AttnArgs a) {
   range.reduce(mlo, mhi);
   const double minv = 1.0 / (mhi - mlo + a.eps);
   const float* z = a.zlog + (((int64_t)b * a.H + h) * a.T_eff + t) * a.V;
+  // Eight keys of a thread in flight: a load after the other took most of the kernel (5 x 28 heads on 4 x 2083 tokens by the
+  // last row: stage 108.5 -> 105.1 us).
   float m = ATT_NEG;
-  for (int j = tid; j < a.V; j += 256) m = fmaxf(m, z[j]);
+  for (int j0 = tid; j0 < a.V; j0 += 8 * 256) {
+    float x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = z[min(j0 + 256 * u, a.V - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) m = fmaxf(m, x[u]);
+  }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
   if (lane == 0) red_m[wave] = m;
@@ -1477,7 +1496,20 @@ __global__ __launch_bounds__(256) void k_rowstats_logits(AttnArgs a) {
   m = fmaxf(fmaxf(red_m[0], red_m[1]), fmaxf(red_m[2], red_m[3]));
   const float offv = -m * a.c2;
   float s = 0.0f;
-  for (int j = tid; j < a.V; j += 256) s = fmaf(discount(a, b, j, mlo, minv), fast_exp2(fmaf(z[j], a.c2, offv)), s);
+  const double* s64 = a.s64 + (int64_t)b * a.V;
+  for (int j0 = tid; j0 < a.V; j0 += 8 * 256) {
+    float x[8];
+    double sj[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int j = min(j0 + 256 * u, a.V - 1);
+      x[u] = z[j];
+      sj[u] = a.mask_on ? s64[j] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (j0 + 256 * u < a.V) s = fmaf(discount_of(a, sj[u], mlo, minv), fast_exp2(fmaf(x[u], a.c2, offv)), s);
+  }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
   if (lane == 0) red_s[wave] = s;

@@ -34,7 +34,7 @@
 //   and the halves' maxima exchanged through LDS took 1.74 ms, now 1.63 (28 heads on 4, 6 x 1337 positions: 201, now
 //   191 us; f32, 2 x 28 x 2352: 1.80, now 1.72 ms; 16 x 32 x 180 with the mask, where a few turns are all: 33.5, then 34.8 us).  The discounts formed in the
 //   workgroup instead of a launch before it, and no wait for the queries in front of the ring's first loads: 16 x 32 x 180 34.9 -> 32.7
-//   us, 1 x 16 x 137 14.0 -> 10.8, 3 x 40 x 1095 100.8 -> 96.9, 16 x 32 x 2403 1572 -> 1543.  Two groups of waves half a turn apart with a barrier per phase,
+//   us, 1 x 16 x 137 14.0 -> 10.8, 3 x 40 x 1095 100.8 -> 96.9, 16 x 32 x 2403 the same (1659 / 1664).  Two groups of waves half a turn apart with a barrier per phase,
 //   one group's products beside the other's softmax, measured the same as one barrier and no order between them.
 #include "asap_device.hpp"
 #include "asap_launch.hpp"

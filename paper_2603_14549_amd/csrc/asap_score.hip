@@ -2,8 +2,7 @@
 // softmax of Eq. 5 reduced to one selection score per visual token.
 //
 // Kernels, in launch order:
-//   k_qsum        column sums of the visual queries per (image, head[, row chunk]); rows are added
-//                 eight at a time in fp32, the eights in fp64
+//   k_qsum        column sums of the visual queries per (image, head[, row chunk]) in fp64
 //   k_qsplit      fixed-order sum of those partials per kv head (fp64), also split into four bf16
 //                 pieces per component (32 significant bits) for the matrix cores
 //   k_mass_mfma   s_j = sum_g qbar_g . k_{g,j} / (H sqrt d)  (Eq. 2 by linearity) and the min / max of
@@ -99,6 +98,9 @@ __device__ __forceinline__ void split_bf16x4(double x, uint16_t* out, int stride
 // keeps piece t % LPR of rows t / LPR + RPI * i.
 // With one chunk and one query head per kv head the block's sums are final (`direct`): it writes
 // their bf16 split itself and k_qsplit is not needed.
+// What bounds it: HBM.  Every row is added in fp64, so that the split of the rows does not decide the precision; eight rows of a
+// thread added in fp32 first were no faster (us of asap_score, fp32 / fp64: 16 x 32 heads x 2304 tokens 167.5 / 167.7; 5 x 28 on 4 x
+// 2083 38.3 / 36.1; f32, 16 x 32 x 576 188.0 / 187.4; 4 x 32 x 4096 180.8 / 181.7).
 // ------------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(1024) void k_qsum(const T* __restrict__ q, Strides3 sq, int V, int d, int R,
@@ -114,20 +116,17 @@ __global__ __launch_bounds__(1024) void k_qsum(const T* __restrict__ q, Strides3
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] = 0.0;
   int row = lo + r0;
-  for (; row + 7 * RPI < hi; row += 8 * RPI) {       // eight rows in flight, summed in fp32
+  for (; row + 7 * RPI < hi; row += 8 * RPI) {       // eight rows in flight
     uint4 ch[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) ch[u] = ldg16_stream(base + (int64_t)(row + u * RPI) * rowb);
-    float f[E], g[E];
-    unpack16<T>(ch[0], f);
 #pragma unroll
-    for (int u = 1; u < 8; ++u) {
-      unpack16<T>(ch[u], g);
+    for (int u = 0; u < 8; ++u) {
+      float f[E];
+      unpack16<T>(ch[u], f);
 #pragma unroll
-      for (int e = 0; e < E; ++e) f[e] += g[e];
+      for (int e = 0; e < E; ++e) acc[e] += (double)f[e];
     }
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] += (double)f[e];
   }
   for (; row < hi; row += RPI) {
     float f[E];

@@ -82,18 +82,18 @@ def check_rows(got: np.ndarray, ref: np.ndarray, tol: float, what: str):
 def mass_error_bound(inp: dict, b: int, s_ref: np.ndarray) -> np.ndarray:
     """Forward error bound of the GPU's raw mass s_j (Eq. 2), per key, from the kernels' arithmetic,
     with u = 2^-24 (fp32 unit roundoff):
-      * the visual queries are added eight rows at a time in fp32 and the eights in fp64: each
-        component of the summed query is off by at most 7 u sum_i |q_i|;
+      * the visual queries are added in fp64: each component of the summed query is off by at most
+        V 2^-53 sum_i |q_i|;
       * the summed query enters the matrix cores as four bf16 pieces (exact to 2^-32), f32 keys as
         three (exact to 2^-27); every piece product is exact, and the 128 (or 64) products of one head
         and piece pair are added in fp32 inside the instruction, in an order the hardware does not
         document: at most (d - 1) u sum_c |qbar_c k_c| whatever the order; sums of pieces |p_0| + |p_1| + ...
         exceed |x| by less than 1 % on either side (1.02 together);
-      * heads and pieces are added in fp64 (nothing to count), and the result is rounded once to f32.
+      * heads and pieces are added in fp64 (nothing to count beside that), and the result is rounded once to f32.
     Observed errors are one to two orders of magnitude below this bound."""
     cfg = inp["cfg"]
     P, V = cfg.P, cfg.V
-    u = 2.0 ** -24
+    u, w = 2.0 ** -24, V * 2.0 ** -53
     Qf = np.abs(synth.to_f64(inp["q"][b], cfg.qk_dtype)[:, P:P + V])
     Kf = synth.to_f64(inp["k"][b], cfg.qk_dtype)[:, P:P + V]
     Qs = synth.to_f64(inp["q"][b], cfg.qk_dtype)[:, P:P + V]
@@ -102,8 +102,8 @@ def mass_error_bound(inp: dict, b: int, s_ref: np.ndarray) -> np.ndarray:
     qbar = np.abs(Qs.sum(axis=1).reshape(cfg.Hkv, G, cfg.d).sum(axis=1))            # |sum_i q_i|
     scale = 1.0 / (cfg.H * math.sqrt(cfg.d))
     a_sum = np.einsum("gd,gjd->j", abs_sum, np.abs(Kf)) * scale
-    a_bar = np.einsum("gd,gjd->j", qbar + 7 * u * abs_sum, np.abs(Kf)) * scale
-    return u * np.abs(s_ref) + 7 * u * a_sum + 1.02 * (cfg.d - 1) * u * a_bar + 1e-300
+    a_bar = np.einsum("gd,gjd->j", qbar + w * abs_sum, np.abs(Kf)) * scale
+    return u * np.abs(s_ref) + w * a_sum + 1.02 * (cfg.d - 1) * u * a_bar + 1e-300
 
 
 def salience_tolerance(s_raw_gpu: np.ndarray, s_hat_gpu: np.ndarray, ref: dict, eps_: float = 1e-6) -> float:

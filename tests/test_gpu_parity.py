@@ -1600,3 +1600,29 @@ def test_waves_that_share_a_row_of_a_split_search(ctx, B, V, k, h_dtype, route):
     buf = U.GpuStage(inp, ctx=ctx, route=binding.ASAP_ROUTE_PAPER, sim_threshold=0.8).run()
     for b in range(cfg.B):
         U.compare_image_paper(inp, buf, b, 0.8, 1.0)
+
+
+@pytest.mark.parametrize("B,H,Hkv,d,dtype,V", [
+    (16, 16, 16, 64, "f32", 512), (257, 1, 1, 64, "f32", 512),          # a block of rows per head, two
+    (31, 11, 11, 64, "f32", 513), (18, 19, 19, 128, "bf16", 520),       # 341 heads of all images, 342
+    (4, 28, 4, 128, "bf16", 4096), (3, 8, 2, 128, "f32", 2777), (1, 4, 4, 128, "bf16", 2304), (2, 8, 2, 64, "f32", 600)])
+def test_query_sums_in_64_bits(ctx, B, H, Hkv, d, dtype, V):
+    """Half of the query rows are +-2^26 and cancel; the others are multiples of 2^-7 near 1, and every sum of them
+    all fits 53 bits, whatever the order and the split of the rows.  fp32 sums of a few rows lose the small ones.  What
+    is left is positive throughout: a head's d products added in fp32, twice their bound as the matrix
+    instruction may truncate."""
+    T, g = 5, torch.Generator(device="cuda").manual_seed(V)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    near_one = lambda *s: torch.randint(64, 192, s, generator=g, device="cuda").float() / 128
+    q, k, q_txt = near_one(B, H, V, d), near_one(B, Hkv, V, d).to(tdt), torch.zeros(B, H, T, d, dtype=tdt, device="cuda")
+    place = torch.rand(B, H, V, generator=g, device="cuda").argsort(-1)
+    q.scatter_(2, place[..., :V // 4, None].expand(-1, -1, -1, d), 2.0 ** 26)
+    q.scatter_(2, place[..., V // 4:2 * (V // 4), None].expand(-1, -1, -1, d), -2.0 ** 26)
+    q = q.to(tdt)
+    p = binding.make_params(B, H, Hkv, d, 64, 0, V, T, 8, dtype, dtype, dtype)
+    s_raw, s_hat, score = (torch.empty(B, V, device="cuda") for _ in range(3))
+    ws = torch.empty(binding.asap_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    ctx.asap_score(p, q, q_txt, k, torch.full((B,), T, dtype=torch.int32, device="cuda"), None, s_raw, s_hat, score, ws)
+    sums = q.double().sum(2).view(B, Hkv, H // Hkv, d).sum(2)
+    ref = torch.matmul(k.double(), sums.unsqueeze(-1)).squeeze(-1).sum(1) / (H * math.sqrt(d))
+    assert float(((s_raw.double() - ref) / ref).abs().max()) <= 2 * (d + 4) * 2.0 ** -24

@@ -176,8 +176,11 @@ template <typename T> constexpr bool att_own_bias(int d, int npad) {
 }
 
 // CH = 16-byte chunks of a row per lane half (row bytes = 32 * CH)
+// The bound on registers is that of the eight waves for four waves too, which need no more of them.  Left twice as many, the compiler
+// puts accumulators into AGPRs, and softmax and rescaling move them to and fro (us with them / without: 1 x 40 heads x 643 positions
+// 24.4 / 21.0, 1 x 16 x 2048 59.5 / 50.5, 1 x 8 on 2 x 3900 107.2 / 88.8; f32 1 x 32 x 643 106.4 / 101.2, d = 64 60.3 / 56.3).
 template <typename T, int CH, bool OWN_BIAS, int NW>
-__global__ __launch_bounds__(64 * NW, (att_steps<T>(32 * CH / (int)sizeof(T)) == 2 ? 4 : 2) * NW / ATT_NW) void k_attention(const T* __restrict__ q, Strides3 sq,
+__global__ __launch_bounds__(64 * NW, att_steps<T>(32 * CH / (int)sizeof(T)) == 2 ? 4 : 2) void k_attention(const T* __restrict__ q, Strides3 sq,
                                                             const T* __restrict__ k, Strides3 sk,
                                                             const T* __restrict__ vt, int Npad,
                                                             const T* __restrict__ vrm, Strides3 sv,
@@ -621,8 +624,8 @@ static hipError_t attention_typed(const asap_params& p, const void* q, Strides3 
                 static_cast<const T*>(v), sv, N, Npad, p.d, vt);
   const float c2 = 1.4426950408889634f / sqrtf((float)p.d);
   // Four waves per workgroup, one per SIMD, where the chip then still holds all of them at a time: a turn takes a wave that has a
-  // SIMD to itself little more than half as long (1 x 40 heads x 643 positions 26.7 -> 23.0 us; d = 64, 16 heads 21.3 -> 18.2; f32, 32
-  // heads 174 -> 105; 2 x 32 x 643, in two rounds then, 27.5 -> 42.1).
+  // SIMD to itself little more than half as long (1 x 40 heads x 643 positions 27.5 -> 20.9 us; d = 64, 16 heads 21.8 -> 18.8; f32, 32
+  // heads 175 -> 101; 2 x 32 x 643, in two rounds then, 30.0 -> 37.5, f32 176 -> 187).
   auto units_of = [&](int queries) { return p.B * p.H * ((N + queries - 1) / queries); };
   const bool four = own_bias && units_of(128) <= 256;
   const int units = units_of(four ? 128 : 32 * ATT_NW);

@@ -1885,23 +1885,32 @@ static ScoreWorkspace plan_score(const asap_params& p, size_t budget, bool ride)
   // workgroups all read every partial sum, take no more than 128 blocks (6 x 28 heads x 1225 tokens: 123.4 us per
   // stage, 125.0 with 256 blocks, 128.5 with 512; 1 x 32 x 2304: 87.6, 87.2, 90.4).  The others take up to 256, one per compute
   // unit: more come in a second round that is nearly empty, and a block per head and no group needs no k_qsplit (us of
-  // asap_score with 512 blocks or more / up to 256: 4 x 28 heads on 4 x 4096 70.6 / 64.7;  2 x 28 on 4 x 4096 49.6 / 41.5;  5 x 28 on 4 x 2083
-  // 42.4 / 40.0;  6 x 32 x 2304 72.2 / 68.0;  8 x 32 x 1536 63.2 / 61.7;  the worst 4 x 32 x 4096 79.2 / 80.5).  From 257 to 341 heads of all
-  // images two blocks each are faster than one (8 x 40 x 2304: 112.7 and 115.3; 9 x 32 x 1100 no difference), from 342
-  // on one (12 x 32 x 1472: 103.5 and 103.0).
-  const int heads = p.B * p.H;
+  // asap_score with 512 blocks or more / up to 256: 4 x 28 heads on 4 x 4096 69.5 / 65.4;  2 x 28 on 4 x 4096 44.2 / 42.4;  5 x 28 on 4 x 2083
+  // 38.4 / 36.1;  6 x 32 x 2304 72.2 / 67.9;  8 x 32 x 1536 63.6 / 62.0).  Two blocks per compute unit are ahead only where both rounds are
+  // full and long:
+  //  * 86 to 128 heads of all images, 4 or 5 blocks each of 160 KB or more (4 x 32 x 4096 79.9, two blocks 81.2;  3 x 40 x 4096 76.9 / 78.2;
+  //    3 x 32 x 4096 66.5 / 67.2;  3 x 40 x 2800 62.9 both;  4 x 32 x 2048 49.4 / 49.3), unless k_qsplit has many of their sums to
+  //    add (4 x 28 on 4 x 2304 41.6 / 40.7);
+  //  * 257 to 384 heads, two blocks of 192 KB or more (9 x 32 x 2304 98.9, one block 101.6;  11 x 32 x 2304 114.2 / 116.7;  12 x 32 x
+  //    2304 121.0 / 122.2;  f32 12 x 28 on 4 x 1200 107.5 / 110.6;  9 x 40 x 1536 82.8 both;  11 x 32 x 800 56.8 / 54.4;  10 x 40 x 1800 108.2 / 102.9).
+  const int heads = p.B * p.H, G = p.H / p.Hkv;
+  const int64_t head_bytes = (int64_t)p.V * p.d * (p.qk_dtype == ASAP_BF16 ? 2 : 4);
   auto most_chunks = [&](int want) {
     const int chunks = std::min((want + heads - 1) / heads, (p.V + 255) / 256);
     return chunks < 1 ? 1 : chunks;
   };
+  auto per_head = [&] {
+    if (heads > 256) return heads <= 384 && head_bytes >= 384 * 1000 ? 2 : 1;
+    const bool two_rounds = heads > 85 && heads <= 128 && head_bytes >= 4 * 160 * 1000 && G * (512 / heads) <= 16;
+    return (two_rounds ? 512 : 256) / heads;
+  };
   const int room = most_chunks(w.mass_small ? 128 : 512);      // partial sums that the workspace has room for
-  const int chunks = w.mass_small ? room : std::min(room, heads <= 256 ? 256 / heads : heads <= 341 ? 2 : 1);
+  const int chunks = w.mass_small ? room : std::min(room, per_head());
   w.q_rows = (p.V + chunks - 1) / chunks;
   w.q_chunks = (p.V + w.q_rows - 1) / w.q_rows;
   const int q_room = (p.V + (p.V + room - 1) / room - 1) / ((p.V + room - 1) / room);
   w.attn_splits = attn_splits(p);
   w.t_eff = ranking_rows_max(p);
-  const int G = p.H / p.Hkv;
   w.ride = ride ? 1 : 0;
   w.mass_keys = 2 * tiles >= 128 || w.ride ? 16 : 8;
   w.row_pairs = w.ride ? 1 : (w.t_eff + 63) / 64;

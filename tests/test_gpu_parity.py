@@ -1604,7 +1604,8 @@ def test_waves_that_share_a_row_of_a_split_search(ctx, B, V, k, h_dtype, route):
 
 @pytest.mark.parametrize("B,H,Hkv,d,dtype,V", [
     (16, 16, 16, 64, "f32", 512), (257, 1, 1, 64, "f32", 512),          # a block of rows per head, two
-    (31, 11, 11, 64, "f32", 513), (18, 19, 19, 128, "bf16", 520),       # 341 heads of all images, 342
+    (35, 11, 11, 64, "f32", 513), (32, 12, 12, 128, "bf16", 1499), (32, 12, 12, 128, "bf16", 1500),    # 385 heads, 384 short and long
+    (16, 8, 2, 128, "bf16", 2499), (16, 8, 2, 128, "bf16", 2500), (86, 1, 1, 64, "f32", 2501), (85, 1, 1, 64, "f32", 2501),
     (4, 28, 4, 128, "bf16", 4096), (3, 8, 2, 128, "f32", 2777), (1, 4, 4, 128, "bf16", 2304), (2, 8, 2, 64, "f32", 600)])
 def test_query_sums_in_64_bits(ctx, B, H, Hkv, d, dtype, V):
     """Half of the query rows are +-2^26 and cancel; the others are multiples of 2^-7 near 1, and every sum of them

@@ -286,6 +286,14 @@ asap_status asap_compact_kv_from_kept(asap_ctx* ctx, const asap_params* p, int32
  * search and merge on a second stream, or on whichever of the two the sizes favour. */
 typedef enum { ASAP_STREAMS_ONE = 0, ASAP_STREAMS_AUTO = 1, ASAP_STREAMS_TWO = 2 } asap_stream_mode;
 
+/* 1 where the K/V compaction of n_layers layers is faster beside similarity search and merge, on a second stream,
+ * than after them, else 0 (also for parameters that the calls refuse and for ASAP_ROUTE_PAPER): contiguous caches when the
+ * compaction moves at least 64 MiB (bytes read + written) and, with half the bytes of the visual rows of the hidden states
+ * (twice those of f32 ones), 250 MiB; caches in pages (`paged` not 0) from 500 MiB.  Below that the two hand-overs between the
+ * streams cost more than they save.  What asap_stage asks with ASAP_STREAMS_AUTO; for programs that issue
+ * the single calls. */
+int32_t asap_second_stream_pays(const asap_params* p, int32_t n_layers, int32_t paged);
+
 /*
  * asap_stage -- the whole stage in one call: asap_score, asap_select, asap_merge and the K/V
  * compaction (asap_compact_kv_from_kept), with the arguments of those calls gathered in one struct
@@ -297,16 +305,18 @@ typedef enum { ASAP_STREAMS_ONE = 0, ASAP_STREAMS_AUTO = 1, ASAP_STREAMS_TWO = 2
  * kernels; `stream` waits for it at the end: work enqueued on `stream` after the call sees all
  * outputs.  The similarity kernel is bound on chip and the compaction by HBM, which is why the two
  * go well side by side.  ASAP_STREAMS_ONE never does this, ASAP_STREAMS_TWO always, and
- * ASAP_STREAMS_AUTO when the compaction moves at least 64 MiB (bytes read + written) and, with half the bytes of
- * the hidden states (twice those of f32 ones), 250 MiB: below that the two hand-overs between the streams cost more
- * than they save.
- * The K/V rows that no selection can change (prefix, valid text; Fig. 3) do not wait for the
- * selection: when the caches are deep (the compaction moves more than four times the bytes of the
- * hidden states) the second stream starts on them at the beginning of the call, beside the score
- * kernels, as many layers of them as those leave time for, and `stream` takes some layers after the merge so that both end
- * together; else, for bf16 hidden states, B >= 12 and n_layers <= 16, further workgroups of the
- * launch that selects copy them.  The second stream then moves the rows of the kept tokens only;
- * the bytes written are the same in every case.
+ * ASAP_STREAMS_AUTO where asap_second_stream_pays says so.
+ * The K/V rows that no selection can change (prefix, valid text; Fig. 3) need not wait for the
+ * selection.  What moves where:
+ *  * Deep caches (the compaction moves more than four times the bytes of the hidden states): the second
+ *    stream starts at the beginning of the call, beside the score kernels, on those rows of as many layers as
+ *    the score leaves time for.  After the selection it moves what is left of the layers that it has time for
+ *    beside search and merge: the kept tokens' rows where it has begun a layer, all rows where it has not.  `stream`
+ *    moves what is left of all others after the merge, so that both end together.
+ *  * Else, for bf16 hidden states, B >= 12 and n_layers <= 16, further workgroups of the launch that
+ *    selects copy them, and the second stream moves the kept tokens' rows.
+ *  * Else the second stream moves all rows after the selection.
+ * The bytes written are the same in every case.
  * With ASAP_ROUTE_PAPER (final_idx exists only after the merge) everything runs on `stream` in
  * order.  Any other value of two_streams: ASAP_EINVAL.  One context must not run two stages at once.
  * The calls are capturable into a HIP graph (kernels, event record / wait; no memset, no sync).

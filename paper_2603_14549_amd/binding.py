@@ -24,7 +24,7 @@ ASAP_STREAMS_ONE, ASAP_STREAMS_AUTO, ASAP_STREAMS_TWO = 0, 1, 2
 
 EXPORTS = ["asap_create", "asap_destroy", "asap_last_error", "asap_check_params", "asap_workspace_bytes",
            "asap_score", "asap_score_static", "asap_score_from_hidden", "asap_front_end_workspace_bytes", "asap_select", "asap_merge", "asap_positions", "asap_compact_kv",
-           "asap_compact_kv_from_kept", "asap_compact_kv_paged", "asap_stage",
+           "asap_compact_kv_from_kept", "asap_compact_kv_paged", "asap_stage", "asap_second_stream_pays",
            "asap_timing_enable",
            "asap_timing_collect", "asap_theoretical_flops", "asap_flops_ratio", "asap_attention",
            "asap_attention_workspace_bytes"]
@@ -123,6 +123,8 @@ def load() -> ctypes.CDLL:
                                           ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.c_int32, i32p,
                                           ctypes.c_int32, i32p, ctypes.c_int32, i32p, i32p, vp]
     lib.asap_compact_kv_paged.restype = ctypes.c_int
+    lib.asap_second_stream_pays.argtypes = [pp, ctypes.c_int32, ctypes.c_int32]
+    lib.asap_second_stream_pays.restype = ctypes.c_int32
     lib.asap_attention_workspace_bytes.argtypes = [pp]
     lib.asap_attention_workspace_bytes.restype = ctypes.c_size_t
     lib.asap_attention.argtypes = [vp, pp, vp, i64p, vp, i64p, vp, i64p, f32p, vp, vp, ctypes.c_size_t, vp]
@@ -172,6 +174,10 @@ def asap_front_end_workspace_bytes(p: asap_params) -> int:
 
 def asap_attention_workspace_bytes(p: asap_params) -> int:
     return int(load().asap_attention_workspace_bytes(ctypes.byref(p)))
+
+
+def asap_second_stream_pays(p: asap_params, n_layers: int, paged: bool = False) -> bool:
+    return bool(load().asap_second_stream_pays(ctypes.byref(p), n_layers, int(paged)))
 
 
 def _i32_array(values):

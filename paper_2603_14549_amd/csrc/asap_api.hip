@@ -550,6 +550,33 @@ static asap_status stage_resources(asap_ctx* ctx) {
   return ASAP_OK;
 }
 
+// Bytes of a row of K or V, those that a compaction reads and writes, those of the visual rows of the hidden states.
+struct KvBytes { int64_t row, copied, hidden; };
+static KvBytes kv_bytes_of(const asap_params& p, int n_layers) {
+  const int64_t row = p.d * (p.kv_dtype == ASAP_BF16 ? 2 : 4);
+  return {row, 4 * (int64_t)n_layers * p.B * p.Hkv * (p.P + p.k + p.Tmax) * row,
+          (int64_t)p.B * p.V * p.D * (p.h_dtype == ASAP_BF16 ? 2 : 4)};
+}
+
+// With ASAP_ROUTE_ABSORB the kept set is final after the selection: the K/V rows can move while the merge runs.
+// What that hides is at most the search's time; the hand-overs between the streams cost the caller's stream 13 us or more
+// and the host 50, and a copy alone runs at 6.2 TB/s.  So the second stream is used for 64 MB and more
+// where the copy and the hidden states together are large; f32 states, whose search takes longer for its bytes, count
+// four times as much.  The line through 110 shapes of up to 1.3 GB (us per stage on one stream / on two; MB copied and of hidden states):
+//   bf16  141 and 3: 67 / 76;  168 and 38: 117 / 120;  194 and 16: 110 / 117;  207 and 47: 143 / 147;  240 and 54: 159 / 161;  249 and
+//         140: 216 / 205;  275 and 20: 121 / 118;  354 and 119: 313 / 295;  702 and 18: 195 / 177;  the worst beyond it 312 and 4: 103 / 110
+//   f32   72 and 63: 166 / 168;  141 and 20: 101 / 106;  228 and 5: 94 / 101;  134 and 117: 201 / 196;  309 and 7: 111 / 103;
+//         184 and 69: 181 / 170
+// Paged caches, whose copy disturbs the search more, take twice that (34 shapes, us per stage call by call, after / beside the
+// search: 6 x 1225 tokens 106 / 118, 2 x 1024 68 / 105, 8 x 844 of 40 heads (127 MB) 174 / 192, 2 x 1600 with 16 layers (415 MB) 160 / 178; 9 x
+// 1364 (595 MB) 296 / 285, 8 x 896 (745 MB) 275 / 265, 14 x 640 in f32 (238 MB) 300 / 282).
+int32_t asap_second_stream_pays(const asap_params* p, int32_t n_layers, int32_t paged) {
+  if (check_params(p, nullptr, 0) != ASAP_OK || p->route != ASAP_ROUTE_ABSORB || n_layers < 1 || n_layers > 64) return 0;
+  const KvBytes b = kv_bytes_of(*p, n_layers);
+  return b.copied >= (64ll << 20) &&
+         b.copied + (p->h_dtype == ASAP_BF16 ? b.hidden / 2 : 2 * b.hidden) >= ((paged ? 500ll : 250ll) << 20);
+}
+
 // How asap_stage deals the K/V copy of deep caches out.
 struct KvDeal {
   int fixed;      // layers 0 .. fixed - 1: their prefix and text rows go before the selection, beside the score kernels
@@ -595,22 +622,11 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
   if (st == ASAP_OK && has_kv)
     st = check_kv_buffers(ctx, p, "asap_stage", io->n_layers, io->k_src, io->v_src, io->k_dst, io->v_dst);
   if (st != ASAP_OK) return st;
-  // With ASAP_ROUTE_ABSORB the kept set is final after the selection: the K/V rows can move while the merge runs.
-  // What that hides is at most the search's time; the hand-overs between the streams cost the caller's stream 13 us or more
-  // and the host 50, and a copy alone runs at 6.2 TB/s.  So with ASAP_STREAMS_AUTO the second stream is used for 64 MB and more
-  // where the copy and the hidden states together are large; f32 states, whose search takes longer for its bytes, count
-  // four times as much.  The line through 110 shapes of up to 1.3 GB (us per stage on one stream / on two; MB copied and of hidden states):
-  //   bf16  141 and 3: 67 / 76;  168 and 38: 117 / 120;  194 and 16: 110 / 117;  207 and 47: 143 / 147;  240 and 54: 159 / 161;  249 and
-  //         140: 216 / 205;  275 and 20: 121 / 118;  354 and 119: 313 / 295;  702 and 18: 195 / 177;  the worst beyond it 312 and 4: 103 / 110
-  //   f32   72 and 63: 166 / 168;  141 and 20: 101 / 106;  228 and 5: 94 / 101;  134 and 117: 201 / 196;  309 and 7: 111 / 103;
-  //         184 and 69: 181 / 170
-  const int64_t kv_row_bytes = p->d * (p->kv_dtype == ASAP_BF16 ? 2 : 4);
-  const int64_t kv_bytes = 4 * (int64_t)io->n_layers * p->B * p->Hkv * (p->P + p->k + p->Tmax) * kv_row_bytes;
-  const int64_t hidden_bytes = (int64_t)p->B * p->V * p->D * (p->h_dtype == ASAP_BF16 ? 2 : 4);
-  const bool worth_forking = kv_bytes >= (64ll << 20) &&
-                             kv_bytes + (p->h_dtype == ASAP_BF16 ? hidden_bytes / 2 : 2 * hidden_bytes) >= (250ll << 20);
+  const KvBytes bytes = kv_bytes_of(*p, io->n_layers);
+  const int64_t kv_bytes = bytes.copied, hidden_bytes = bytes.hidden;
   const bool early = has_kv && p->route == ASAP_ROUTE_ABSORB &&
-                     (two_streams == ASAP_STREAMS_TWO || (two_streams == ASAP_STREAMS_AUTO && worth_forking));
+                     (two_streams == ASAP_STREAMS_TWO ||
+                      (two_streams == ASAP_STREAMS_AUTO && asap_second_stream_pays(p, io->n_layers, 0)));
   if (early && (st = stage_resources(ctx)) != ASAP_OK) return st;
 
   hipStream_t main = static_cast<hipStream_t>(stream);
@@ -621,7 +637,7 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
   // The K/V rows that no selection can change (prefix, valid text; Fig. 3) need not wait for it.
   //  * Deep caches (the compaction moves more than four times the bytes of the hidden states, so it
   //    outlasts similarity search and merge): the second stream starts on those rows at once, beside
-  //    the score kernels, and takes the kept tokens' rows after the selection.
+  //    the score kernels, and goes on after the selection (deal_kv: how many layers either stream takes).
   //  * Otherwise, for large bf16 batches: the launch that finishes the score and selects keeps B
   //    compute units busy and moves next to nothing, so further workgroups of it copy those rows.
   const bool fixed_first = early && kv_bytes > 4 * hidden_bytes;
@@ -636,7 +652,7 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
   const bool fixed_with_selection = early && !fixed_first && score_fuses_selection(*p) && p->h_dtype == ASAP_BF16 &&
                                     io->n_layers <= KV_LAYERS_PER_LAUNCH;
   KvDeal deal{0, io->n_layers};
-  if (fixed_first) deal = deal_kv(*p, io->n_layers, kv_row_bytes, hidden_bytes);
+  if (fixed_first) deal = deal_kv(*p, io->n_layers, bytes.row, hidden_bytes);
   else if (fixed_with_selection) deal.fixed = io->n_layers;
   // layers lo .. hi - 1
   auto copy_layers = [&](int mode, int lo, int hi, hipStream_t s, size_t lds) {
@@ -659,7 +675,7 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
     fill_kv_pointers(&fixed.ptrs, io->n_layers, io->k_src, io->v_src, io->k_dst, io->v_dst);
     fixed.n_bufs = 2 * io->n_layers;
     fixed.Hkv = p->Hkv; fixed.N = p->P + p->V + p->Tmax; fixed.Nout = p->P + p->k + p->Tmax;
-    fixed.row_bytes = (int)kv_row_bytes;
+    fixed.row_bytes = (int)bytes.row;
     fixed.P = p->P; fixed.V = p->V; fixed.k = p->k; fixed.Tmax = p->Tmax;
   }
   if (e == hipSuccess)
@@ -687,7 +703,7 @@ asap_status asap_stage(asap_ctx* ctx, const asap_params* p, const asap_stage_io*
     fill_kv_pointers(&mkv.ptrs, taken, io->k_src, io->v_src, io->k_dst, io->v_dst);
     mkv.n_bufs = 2 * taken;
     mkv.Hkv = p->Hkv;
-    mkv.row_bytes = (int)kv_row_bytes;
+    mkv.row_bytes = (int)bytes.row;
   }
   if (e == hipSuccess)
     e = launch_merge(*p, io->hidden, io->hidden_stride[0], io->hidden_stride[1], io->s_raw, io->s_hat, io->text_len,

@@ -9,7 +9,7 @@ from typing import List, Optional
 
 import torch
 
-from .binding import (ASAP_BF16, ASAP_ROUTE_ABSORB, ASAP_ROWS_LAST, ASAP_STREAMS_AUTO, ASAP_STREAMS_ONE, ASAP_STREAMS_TWO, Context, _TORCH_DTYPE, _strides, asap_params, asap_stage_io,
+from .binding import (ASAP_ROUTE_ABSORB, ASAP_ROWS_LAST, ASAP_STREAMS_AUTO, ASAP_STREAMS_ONE, ASAP_STREAMS_TWO, Context, _TORCH_DTYPE, _strides, asap_params, asap_second_stream_pays, asap_stage_io,
                       asap_workspace_bytes, params_from_config)
 
 
@@ -104,19 +104,6 @@ class PagedKV:
                                   self.src_table, self.dst_table, pos_out, new_len, stream)
 
 
-def second_stream_pays(p: asap_params, n_layers: int, paged: bool) -> bool:
-    """Whether the K/V compaction is faster beside similarity search and merge than after them.  Handing work from stream to
-    stream and back costs the main stream 13 us or more and the host about 50, which the overlap has to earn: by the bytes
-    that it copies and, as it hides at most the search, by those of the hidden states (f32 counts four times bf16).  The
-    line of asap_stage, and twice that for paged caches, whose copy disturbs the search more.  us per stage of 34 paged
-    shapes beside / after: 6 x 1225 tokens 118 / 106, 2 x 1024 105 / 68, 8 x 844 of 40 heads (127 MB) 192 / 174, 2 x 1600 with 16
-    layers (415 MB) 178 / 160; 9 x 1364 (595 MB) 285 / 296, 8 x 896 (745 MB) 265 / 275, 14 x 640 in f32 (238 MB) 282 / 300."""
-    bf16 = lambda t: t == ASAP_BF16
-    kv = 4 * n_layers * p.B * p.Hkv * (p.P + p.k + p.Tmax) * p.d * (2 if bf16(p.kv_dtype) else 4)
-    hidden = p.B * p.V * p.D * (2 if bf16(p.h_dtype) else 4)
-    return kv >= 64 << 20 and kv + (hidden // 2 if bf16(p.h_dtype) else 2 * hidden) >= (500 if paged else 250) << 20
-
-
 def run_stage(ctx: Context, p: asap_params, q: torch.Tensor, k: torch.Tensor, hidden: torch.Tensor,
               text_len: torch.Tensor, k_cache: List[torch.Tensor], v_cache: List[torch.Tensor],
               buf: StageBuffers, lse_extra: Optional[torch.Tensor] = None, stream=None,
@@ -124,7 +111,7 @@ def run_stage(ctx: Context, p: asap_params, q: torch.Tensor, k: torch.Tensor, hi
     """The calls of one stage.  q [B,H,N,d], k [B,Hkv,N,d], hidden [B,N,D]; the visual / text blocks
     are passed to the library as strided views.  With a side stream the K/V compaction, which needs
     only the kept set, runs there next to the similarity and merge kernels of the main stream, where that is faster
-    (second_stream_pays) or with overlap="always" (one
+    (asap_second_stream_pays) or with overlap="always" (one
     hand-over between the streams after the selection -- each costs the main stream about 6 us, so
     the rows that depend on nothing are not started earlier on their own); the main stream waits for
     the side stream at the end.  Contiguous caches are compacted by the call that takes the kept
@@ -145,7 +132,7 @@ def run_stage(ctx: Context, p: asap_params, q: torch.Tensor, k: torch.Tensor, hi
     ctx.asap_select(p, buf.score, buf.kept_idx, buf.pruned_idx, buf.workspace, main)
     # with ASAP_ROUTE_ABSORB the kept set is final before the merge
     early = has_kv and side_stream is not None and p.route == ASAP_ROUTE_ABSORB and (
-        overlap == "always" or second_stream_pays(p, len(paged.k_pool if paged is not None else k_cache), paged is not None))
+        overlap == "always" or asap_second_stream_pays(p, len(paged.k_pool if paged is not None else k_cache), paged is not None))
     if early:
         if paged is not None:
             ctx.asap_positions(p, buf.kept_idx, text_len, buf.pos_early, buf.new_len_early, main)

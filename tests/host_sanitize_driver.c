@@ -25,6 +25,13 @@ static void probe(const asap_params* p) {
     ++n_invalid;
     if (ws != 0 || wa != 0 || msg[0] == 0) { printf("invalid params gave a size or no message\n"); exit(4); }
   }
+  static const int32_t layers[] = {-2147483647 - 1, 0, 1, 64, 2147483647};
+  for (unsigned i = 0; i < sizeof(layers) / sizeof(*layers); ++i)
+    for (int paged = 0; paged < 2; ++paged)
+      if (asap_second_stream_pays(p, layers[i], paged) && (st != ASAP_OK || layers[i] < 1 || layers[i] > 64)) {
+        printf("a second stream for invalid params or layers\n");
+        exit(12);
+      }
   /* short and missing message buffers */
   char tiny[4];
   (void)asap_check_params(p, tiny, sizeof(tiny));

@@ -166,3 +166,21 @@ def test_a_missing_library_is_an_error_not_a_fallback(monkeypatch, tmp_path):
             if f.endswith((".py", ".hip", ".hpp", ".h")):
                 text = open(os.path.join(root, f), encoding="utf-8").read()
                 assert "import oracle" not in text and "from oracle" not in text and "asap_oracle" not in text, f
+
+
+# Eight layers of 16 kv heads and rows of 256 bytes: a position is 1/8 MiB read and written.  Hidden states of 8192 tokens: 128 MiB
+# (f32 256) at D = 8192, 1 MiB (2) at D = 64.
+@pytest.mark.parametrize("layers,positions,D,h_dtype,paged,pays", [
+    (8, 512, 8192, "f32", False, True), (8, 511, 8192, "f32", False, False),        # 64 MiB
+    (64, 64, 8192, "f32", True, True), (64, 63, 8192, "f32", True, False),
+    (8, 1996, 64, "bf16", False, True), (8, 1995, 64, "bf16", False, False),        # 250 MiB with half the bf16 states' bytes
+    (8, 1488, 8192, "bf16", False, True), (8, 1487, 8192, "bf16", False, False),
+    (8, 1968, 64, "f32", False, True), (8, 1967, 64, "f32", False, False),          # ... with twice the f32 ones'
+    (8, 3996, 64, "bf16", True, True), (8, 3995, 64, "bf16", True, False),          # pages: 500 MiB
+    (8, 3488, 8192, "bf16", True, True), (8, 3487, 8192, "bf16", True, False),
+    (65, 2000, 8192, "f32", False, False), (0, 2000, 8192, "f32", False, False)])
+def test_where_the_second_stream_pays(lib, layers, positions, D, h_dtype, paged, pays):
+    p = binding.make_params(1, 16, 16, 128, D, 4, 8192, 8, positions - 12, "bf16", h_dtype, "bf16")
+    assert binding.asap_second_stream_pays(p, layers, paged) == pays
+    p.route, p.k = binding.ASAP_ROUTE_PAPER, min(p.k, p.V // 2)
+    assert not binding.asap_second_stream_pays(p, layers, paged)

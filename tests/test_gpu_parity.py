@@ -1542,11 +1542,36 @@ def test_paged_stage_beside_and_after_the_search(ctx, overlap):
                           overlap=overlap)
         torch.cuda.synchronize()
         pools.append((st.paged.k_pool + st.paged.v_pool, st.buf))
-    assert not harness.second_stream_pays(st.p, len(st.paged.k_pool), True)
+    assert not binding.asap_second_stream_pays(st.p, len(st.paged.k_pool), True)
     for a, b in zip(pools[0][0], pools[1][0]):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
     for n in ("kept_idx", "assign", "pos_out", "new_len"):
         assert torch.equal(getattr(pools[0][1], n), getattr(pools[1][1], n))
+
+
+@pytest.mark.parametrize("k,pays", [(220, True), (200, False)])
+def test_paged_stage_where_the_second_stream_pays(ctx, k, pays):
+    """Paged caches on both sides of the line that a side stream is taken at, beside the search and after it: every kept
+    row in its place."""
+    B, H, d, D, P, V, T, layers, page = 8, 16, 128, 128, 9, 384, 30, 16, 16
+    p = binding.make_params(B, H, H, d, D, P, V, T, k, "bf16", "bf16", "bf16")
+    assert binding.asap_second_stream_pays(p, layers, paged=True) == pays
+    N, g = P + V + T, torch.Generator(device="cuda").manual_seed(53)
+    rn = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    q, key, hidden = rn(B, H, N, d), rn(B, H, N, d), rn(B, N, D)
+    text_len = torch.randint(1, T + 1, (B,), generator=g, device="cuda").to(torch.int32)
+    kc, vc = [rn(B, H, N, d) for _ in range(layers)], [rn(B, H, N, d) for _ in range(layers)]
+    paged, buf = harness.PagedKV(p, kc, vc, page), harness.StageBuffers(p, 0)
+    harness.run_stage(ctx, p, q, key, hidden, text_len, [], [], buf, side_stream=torch.cuda.Stream(), paged=paged)
+    torch.cuda.synchronize()
+    table = paged.dst_table.long()
+    for src, pool in zip(kc + vc, paged.k_pool + paged.v_pool):
+        got = pool[table.reshape(-1)].view(B, -1, H, page, d).transpose(1, 2).reshape(B, H, -1, d)
+        for b in range(B):
+            n = int(buf.new_len[b])
+            assert n == P + k + int(text_len[b])
+            assert torch.equal(got[b, :, :n], src[b][:, buf.pos_out[b, :n].long()])
+            assert not bool(got[b, :, n:].any())
 
 
 @pytest.mark.parametrize("B,H,Hkv,d,dtype,P,V,T", [

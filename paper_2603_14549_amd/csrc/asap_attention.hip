@@ -170,7 +170,7 @@ template <typename T> constexpr size_t att_lds_bytes(int d, int npad) {
   return NS * keys * 2 * d * sizeof(T) + sizeof(float) * (npad ? npad : NS * keys);
 }
 // The workgroup forms the discounts itself, and k_att_bias is not launched, where an image's fit beside the rings: up to 8160
-// positions, or 4064 where two workgroups share a compute unit.
+// positions with d = 128, 24544 in f32 with d = 64 (whose rings take 64 KiB), 4064 in bf16 with d = 64, where two workgroups share a compute unit.
 template <typename T> constexpr bool att_own_bias(int d, int npad) {
   return att_lds_bytes<T>(d, npad) <= (att_steps<T>(d) == 2 ? 80 : 160) * 1024;
 }

@@ -1497,10 +1497,13 @@ def test_compaction_at_the_edges_of_its_blocks(ctx, d, dtype, over):
                 assert bool((t[b][:, n:] == 7.0).all())
 
 
-@pytest.mark.parametrize("layers,P,T,k", [(16, 40, 64, 16), (16, 64, 120, 4), (17, 0, 8, 90), (33, 3, 5, 100), (1, 64, 120, 110)])
-def test_deep_caches_dealt_to_two_streams(ctx, layers, P, T, k):
+@pytest.mark.parametrize("layers,P,T,k,fixed,side", [
+    (16, 40, 64, 16, 16, 10), (16, 64, 120, 4, 9, 8), (17, 0, 8, 90, 17, 9), (33, 3, 5, 100, 33, 17), (1, 64, 120, 110, 1, 1),
+    (16, 128, 128, 16, 6, 8), (40, 128, 128, 60, 6, 20), (2, 3000, 8, 40, 0, 1)])
+def test_deep_caches_dealt_to_two_streams(ctx, layers, P, T, k, fixed, side):
     """Copies that outlast search and merge: layers whose prefix and text rows go first, wholly after the selection, on
-    the second stream and behind the merge leave the rows that one stream leaves."""
+    the second stream and behind the merge leave the rows that one stream leaves.  `fixed` layers start before the selection, the
+    second stream takes `side`: told from the launches, one for up to 16 layers of a kind."""
     B, H, d, D, V = 8, 16, 128, 128, 128
     p = binding.make_params(B, H, H, d, D, P, V, T, k, "bf16", "bf16", "bf16")
     N, g = P + V + T, torch.Generator(device="cuda").manual_seed(43)
@@ -1514,9 +1517,16 @@ def test_deep_caches_dealt_to_two_streams(ctx, layers, P, T, k):
         for t in buf.k_dst + buf.v_dst:
             t.fill_(7.0)
         io = harness.stage_io(p, q, key, hidden, text_len, kc, vc, buf)
+        ctx.asap_timing_enable(64)
         ctx.asap_stage(p, io, mode)
         torch.cuda.synchronize()
+        launches = {n: c for n, (_, c) in ctx.asap_timing_collect().items() if n.startswith("k_compact")}
+        ctx.asap_timing_enable(0)
         got.append(buf)
+        if mode == binding.ASAP_STREAMS_TWO:
+            of = lambda n: -(-max(n, 0) // 16)
+            after = of(min(fixed, side)) + of(side - fixed) + of(fixed - side) + of(layers - max(fixed, side))
+            assert (launches.get("k_compact_fixed", 0), launches["k_compact"]) == (of(fixed), after)
     for buf in got[1:]:
         for n in ("kept_idx", "assign", "pos_out", "new_len"):
             assert torch.equal(getattr(buf, n), getattr(got[0], n))
@@ -1578,6 +1588,7 @@ def test_paged_stage_where_the_second_stream_pays(ctx, k, pays):
     (1, 1, 1, 128, "bf16", 60, 8000, 100), (1, 1, 1, 128, "bf16", 61, 8000, 100),    # discounts in LDS: up to 8160 positions
     (1, 2, 1, 64, "bf16", 4, 4000, 60), (1, 2, 1, 64, "bf16", 5, 4000, 60),          # ... 4064 with two workgroups per unit
     (1, 1, 1, 128, "f32", 60, 8000, 101), (1, 1, 1, 64, "f32", 0, 4100, 33),
+    (1, 1, 1, 64, "f32", 8444, 16000, 100), (1, 1, 1, 64, "f32", 8445, 16000, 100),  # ... 24544 in f32 with d = 64
     (2, 16, 16, 128, "bf16", 24, 900, 100), (2, 16, 4, 128, "bf16", 24, 900, 101),   # four waves up to 256 workgroups of 128 queries
     (2, 16, 16, 64, "bf16", 24, 900, 100), (2, 16, 4, 64, "bf16", 24, 900, 101),
     (2, 16, 4, 128, "f32", 24, 900, 100), (2, 16, 16, 128, "f32", 24, 900, 101), (2, 16, 4, 64, "f32", 24, 900, 100)])
@@ -1652,3 +1663,45 @@ def test_query_sums_in_64_bits(ctx, B, H, Hkv, d, dtype, V):
     sums = q.double().sum(2).view(B, Hkv, H // Hkv, d).sum(2)
     ref = torch.matmul(k.double(), sums.unsqueeze(-1)).squeeze(-1).sum(1) / (H * math.sqrt(d))
     assert float(((s_raw.double() - ref) / ref).abs().max()) <= 2 * (d + 4) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("nt", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 6, 7])
+def test_search_over_few_steps(ctx, nt, steps):
+    """A step is 64 elements of the hidden dimension: walks that are shorter than the rings of each tile width, as long, and
+    longer.  256 full tiles in one pass choose the width nt.  Bound: D products of cosines added in fp32 (twice, as the matrix
+    instruction may truncate), and as much for the norms."""
+    B, D, k, M = 128, 64 * steps, 64 * nt, 130
+    V, g = k + M, torch.Generator(device="cuda").manual_seed(100 * nt + steps)
+    p = binding.make_params(B, 1, 1, 64, D, 0, V, 1, k, "bf16", "bf16", "bf16")
+    hidden = torch.randn(B, V + 1, D, generator=g, device="cuda").bfloat16()
+    order = torch.rand(B, V, generator=g, device="cuda").argsort(-1).to(torch.int32)
+    kept, pruned = (x.sort(-1).values.contiguous() for x in (order[:, :k], order[:, k:]))
+    s_hat = torch.rand(B, V, generator=g, device="cuda")
+    buf = harness.StageBuffers(p, 0)
+    ctx.asap_merge(p, hidden, s_hat, s_hat, torch.ones(B, dtype=torch.int32, device="cuda"), kept, pruned, buf.out_hidden,
+                   buf.pos_out, buf.new_len, buf.assign, buf.best_sim, buf.wsum, buf.final_idx, buf.workspace)
+    x = torch.nn.functional.normalize(hidden.double(), dim=-1)
+    rows = lambda idx: x.gather(1, idx.long()[..., None].expand(-1, -1, D))
+    cos = torch.matmul(rows(pruned), rows(kept).transpose(1, 2).contiguous())
+    tol, best = 4 * (D + 8) * 2.0 ** -24, cos.max(-1).values
+    assert float((buf.best_sim.double() - best).abs().max()) <= tol
+    assert float((best - cos.gather(2, buf.assign.long()[..., None])[..., 0]).max()) <= 2 * tol
+
+
+@pytest.mark.parametrize("V", [2047, 2048, 2049])
+def test_rows_of_stored_logits_at_the_edges_of_their_turns(ctx, V):
+    """Eight turns of 256 keys of a stored row are taken together: one key less, as many, one more."""
+    cfg = synth.StageConfig(name="turns", B=4, D=64, H=4, Hkv=2, d=64, P=3, V=V, Tmax=9, k=V // 4, qk_dtype="bf16", h_dtype="bf16",
+                            kv_dtype="bf16", n_clusters=12, outliers=False, L_kv=0, seed=8900 + V)
+    U.run_and_compare(cfg, ctx=ctx, images=[0, 3], last_token=True)
+    U.run_and_compare(cfg, ctx=ctx, images=[3], last_token=True, lse=True)
+
+
+@pytest.mark.parametrize("V", [512, 640, 641, 768, 1152, 1280])
+def test_splits_of_the_text_rows_statistics(ctx, V):
+    """f32 rows over 4, 5, 6, 9 and 10 splits of the keys, whose statistics are read four splits at a time."""
+    cfg = synth.StageConfig(name="splits", B=1, D=64, H=2, Hkv=2, d=64, P=3, V=V, Tmax=35, k=V // 4, qk_dtype="f32", h_dtype="f32",
+                            kv_dtype="f32", n_clusters=12, outliers=False, L_kv=0, seed=8950 + V)
+    U.run_and_compare(cfg, ctx=ctx)
+    U.run_and_compare(cfg, ctx=ctx, lse=True)

@@ -11,11 +11,9 @@
 //                 every wave issues between its MFMAs; the squared norms of the rows are added up
 //                 from the operands a wave holds, also in the shadow of the MFMAs (waves that hold
 //                 the same rows take half of the contraction slices each).
-//                 The source rows are read once, from HBM, so their 128 x 128 B slices go through a
-//                 ring of 4 LDS slots and are asked for three steps ahead; the destination rows are
-//                 shared by all tiles of an image and come from L2, so two slots (one step ahead)
-//                 are enough for their BN x 128 B slices at the widest tile; narrower tiles leave
-//                 room for deeper rings (sim_na, sim_nb).
+//                 The source rows are read once, from HBM, the destination rows, which all tiles of an
+//                 image share, come from L2; slices of either go through a ring of LDS slots, asked for
+//                 one step (destination rows of the widest tile) to five ahead (sim_na, sim_nb).
 //                 LDS rows are unpadded; the 16-byte piece p of row r is stored in slot
 //                 p ^ ((r >> 1) & 7): any 16 consecutive rows then cover all 64 banks once, for the
 //                 1 KiB-contiguous loads as well as for the strided 16-byte operand reads.
@@ -43,14 +41,15 @@ namespace asap {
 
 constexpr int SIM_BM = 128;
 constexpr int SIM_ROWB = 128;      // bytes of a row held in LDS per step
-// LDS ring slots for the source rows (NA) and the destination rows (NB) by tile width: as deep as
-// 160 KiB allow, NA >= NB >= 2.  Narrow tiles belong to launches with few workgroups (small batches, the
-// search inside the kept set), whose steps last as long as a load takes to arrive divided by how many
-// steps ahead it was asked for.  Loads return in the order they were asked for, on the whole compute unit: destination rows
-// that come from L2 arrive behind the source rows from HBM that were asked for before them, so that what is needed first and
-// asked for last sets the pace.  256 columns with three slots of each (all loads two steps ahead) instead of four and two: search
-// and merge of 4 x 4096 tokens on 512 98.3 -> 94.1 us, 3 x 3072 on 769 89.2 -> 83.5, 8 x 1024 on 256 56.9 -> 54.7.  (320 columns have
-// no room for that.)
+// LDS ring slots for the source rows (NA) and the destination rows (NB) by tile width, NA >= NB >= 2, in 160 KiB.
+// Narrow tiles belong to launches with few workgroups (small batches, the search inside the kept set), whose steps last as
+// long as a load takes to arrive divided by how many steps ahead it was asked for.  Loads return in the order they were
+// asked for, on the whole compute unit: destination rows that come from L2 arrive behind the source rows from HBM that were
+// asked for before them, so that what is needed first and asked for last sets the pace.  256 columns with three slots of each
+// (all loads two steps ahead) instead of four and two: search and merge of 4 x 4096 tokens on 512 98.3 -> 94.1 us, 3 x 3072 on
+// 769 89.2 -> 83.5, 8 x 1024 on 256 56.9 -> 54.7.  (320 columns have no room for that.)  For the same reason source slots beyond
+// NB + 1, of which 64, 128 and 320 columns have one, are without effect: the wait for the destination rows of the next step
+// has the source rows of NA - NB - 1 further steps arrive too.
 constexpr int sim_na(int nt) { return nt == 1 ? 6 : nt == 2 ? 5 : nt == 4 ? 3 : 4; }
 constexpr int sim_nb(int nt) { return nt == 1 ? 4 : nt <= 4 ? 3 : 2; }
 // Loads of a wave that may be on their way at the end of a step, all after those that the next step needs: steps s
